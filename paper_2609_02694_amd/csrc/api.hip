@@ -80,7 +80,7 @@ struct rbe_ctx {
   double *epart = nullptr;   // energy partial sums
   double *nh_part = nullptr, *nh_scale = nullptr;  // thermostat: |v|^2 partials, pending velocity scaling
   int *err = nullptr;
-  double *qstats = nullptr;  // [sum q, sum |q|]
+  double *qstats = nullptr;  // [2 kQBlocks] per-block (sum q, sum |q|)
   unsigned long long *counters = nullptr;
   bool counting = false;
   Timer tm;
@@ -355,6 +355,11 @@ static int ctx_geometry(rbe_ctx *c, const rbe_params *p, int64_t n_max, std::str
   return RBE_OK;
 }
 
+// Blocks of the charge sums (each leaves one partial pair) and the largest
+// particle count that one block sums by itself.
+constexpr int kQBlocks = 1024;
+constexpr int64_t kQOneBlock = 8192;
+
 // ---------------------------------------------------------------------------
 // create / destroy
 // ---------------------------------------------------------------------------
@@ -436,7 +441,7 @@ extern "C" int rbe_create(rbe_ctx **out, const rbe_params *p, int64_t n_max, int
   c->nh_part = b.alloc<double>(nh_part_len());
   c->nh_scale = b.alloc<double>(1);
   c->err = b.alloc<int>(1);
-  c->qstats = b.alloc<double>(2);
+  c->qstats = b.alloc<double>(2 * kQBlocks);
   c->counters = b.alloc<unsigned long long>(12);
   if (p->ghost_width > 0) {
     // ghost capacity: the expected image count of a uniform fluid in the
@@ -664,48 +669,79 @@ extern "C" const char *rbe_last_error(const rbe_ctx *ctx) {
 // ---------------------------------------------------------------------------
 // charge checks (on the device: no call waits for them)
 // ---------------------------------------------------------------------------
-// stats[0] += sum q, stats[1] += sum |q| (one atomic per wave, in any order:
-// the sums only feed the neutrality test below); a non-finite charge raises
-// kErrNonFinite.
-__global__ void __launch_bounds__(256) k_qstats(int64_t n, const double *__restrict__ q, double *stats, int *err) {
-  double s = 0.0, a = 0.0;
-  bool bad = false;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const double v = q[i];
-    bad |= !isfinite(v);
-    s += v;
-    a += fabs(v);
-  }
+// Eq. 1 asks for a neutral system: |sum q| above 1e-10 sum |q| (and above
+// 1e-12) raises kErrNonNeutral.
+__device__ inline void flag_charge(double s, double a, int *err) {
+  if (isfinite(s) && isfinite(a) && fabs(s) > 1e-10 * fmax(a, 1e-300) && fabs(s) > 1e-12)
+    atomicOr(err, kErrNonNeutral);
+}
+
+// Sums of two values over a 256-thread block in a fixed order (thread 0).
+__device__ inline void block_sum2(double &s, double &a) {
+  __shared__ double lds[8];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     s += __shfl_xor(s, o, 64);
     a += __shfl_xor(a, o, 64);
   }
-  if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(err, kErrNonFinite);
+  const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) {
-    atomicAdd(&stats[0], s);
-    atomicAdd(&stats[1], a);
+    lds[w] = s;
+    lds[4 + w] = a;
+  }
+  __syncthreads();
+  s = (lds[0] + lds[1]) + (lds[2] + lds[3]);
+  a = (lds[4] + lds[5]) + (lds[6] + lds[7]);
+}
+
+// part[2 b], part[2 b + 1] = sum q, sum |q| over block b's share; a
+// non-finite charge raises kErrNonFinite. A lone block tests the sums at
+// once. Bound by its launch and by reading q: the sums go to a partial per
+// block because FP64 atomics of every wave on one pair of addresses
+// serialize (77 us at n = 200,000 and 102 us at 1,000,000 that way, 7 us and
+// 8 us for this kernel and the next).
+__global__ void __launch_bounds__(256) k_qstats(int64_t n, const double *__restrict__ q, double *__restrict__ part,
+                                                int *err) {
+  double s = 0.0, a = 0.0;
+  bool bad = false;
+#pragma unroll 4
+  for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const double v = q[i];
+    bad |= !isfinite(v);
+    s += v;
+    a += fabs(v);
+  }
+  if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(err, kErrNonFinite);
+  block_sum2(s, a);
+  if (threadIdx.x != 0) return;
+  if (gridDim.x == 1) {
+    flag_charge(s, a, err);
+  } else {
+    part[2 * blockIdx.x] = s;
+    part[2 * blockIdx.x + 1] = a;
   }
 }
 
-// Eq. 1 asks for a neutral system: |sum q| above 1e-10 sum |q| (and above
-// 1e-12) raises kErrNonNeutral.
-__global__ void k_qstatus(const double *__restrict__ stats, int *err) {
-  const double s = stats[0], a = stats[1];
-  if (isfinite(s) && isfinite(a) && fabs(s) > 1e-10 * fmax(a, 1e-300) && fabs(s) > 1e-12)
-    atomicOr(err, kErrNonNeutral);
+__global__ void __launch_bounds__(256) k_qstatus(int nb, const double *__restrict__ part, int *err) {
+  double s = 0.0, a = 0.0;
+#pragma unroll
+  for (int k = 0; k < kQBlocks / 256; ++k) {
+    const int b = threadIdx.x + 256 * k;
+    s += b < nb ? part[2 * b] : 0.0;
+    a += b < nb ? part[2 * b + 1] : 0.0;
+  }
+  block_sum2(s, a);
+  if (threadIdx.x == 0) flag_charge(s, a, err);
 }
 
 // Neutrality and finiteness of the charges, reported through the device flag
 // that rbe_sync_check reads (the counts that size the later launches are read
 // on the device too, so nothing here waits).
 static void launch_charge_check(rbe_ctx *c, int64_t n, const double *q, hipStream_t st) {
-  launch_fill_f64(c->qstats, 2, 0.0, st);
-  int64_t blocks = (n + 255) / 256;
-  if (blocks > 1024) blocks = 1024;
-  if (blocks < 1) blocks = 1;
+  int64_t blocks = n <= kQOneBlock ? 1 : (n + 1023) / 1024;
+  if (blocks > kQBlocks) blocks = kQBlocks;
   k_qstats<<<(unsigned)blocks, 256, 0, st>>>(n, q, c->qstats, c->err);
-  k_qstatus<<<1, 1, 0, st>>>(c->qstats, c->err);
+  if (blocks > 1) k_qstatus<<<1, 256, 0, st>>>((int)blocks, c->qstats, c->err);
 }
 
 // ---------------------------------------------------------------------------
@@ -1554,7 +1590,7 @@ extern "C" int rbe_forces_noalloc(const rbe_params *p, const rbe_state *s, const
   c.mean_part = cv.take<double>(3 * (int64_t)mean_blocks(n) + 3);
   c.mean = cv.take<double>(3);
   c.err = cv.take<int>(1);
-  c.qstats = cv.take<double>(2);
+  c.qstats = cv.take<double>(2 * kQBlocks);
   if (!cv.ok) return create_fail(RBE_ERANGE, "the problem does not fit the scratch array");
   hipStream_t st = (hipStream_t)stream;
   launch_fill_i32(c.err, 1, 0, st);  // the array keeps the previous call's flag
