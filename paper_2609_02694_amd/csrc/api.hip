@@ -300,6 +300,7 @@ static Grid make_grid(const rbe_params &p, const int nc[3]) {
   for (int d = 0; d < 3; ++d) {
     g.L[d] = p.L[d];
     g.inv_h[d] = (double)nc[d] / p.L[d];
+    g.h[d] = p.L[d] / nc[d];
     g.goff[d] = 0;
   }
   g.pnx = g.nx;
@@ -330,6 +331,7 @@ static int ctx_geometry(rbe_ctx *c, const rbe_params *p, int64_t n_max, std::str
   for (int d = 0; d < 3; ++d) {
     g.L[d] = p->L[d];
     g.inv_h[d] = (double)nc[d] / p->L[d];
+    g.h[d] = p->L[d] / nc[d];
     c->p.ncell[d] = nc[d];
     // ghost layers: enough cells to hold every image within ghost_width
     g.goff[d] = p->ghost_width > 0 ? (int)std::ceil(p->ghost_width * g.inv_h[d] * (1.0 + 1e-12)) : 0;
@@ -791,6 +793,10 @@ static int eval_sorted(rbe_ctx *c, int64_t n, const int32_t *m, const double *w,
         launch_pair(c->p.prec, PAIR_PART_COULOMB, pp, n, nq, c->srt, c->cell_start, c->inv_id, gb, fx, fy, fz,
                     part_cnt(PAIR_PART_CHARGED), st);
       }
+    } else if (!pp.rbl && pair_grouped(c->p.prec, n) && !c->counting && !c->tm.on) {
+      // one launch for both ranges (the counters and timings tell them apart)
+      launch_pair(c->p.prec, PAIR_PART_BOTH, pp, n, nq, c->srt, c->cell_start, c->inv_id, gb, fx, fy, fz,
+                  PairCounters{nullptr}, st);
     } else {
       {
         TScope ts(c, RBE_TK_PAIR_CHARGED, st);

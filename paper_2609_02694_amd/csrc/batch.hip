@@ -100,7 +100,7 @@ __device__ inline int block_scan_excl(int v, int *lds, int *total) {
 // Plain near-field sums of one particle (no random batch list, no ghosts),
 // one thread walking the stencil rows of its own cell in its replica.
 template <bool F32>
-__device__ inline void batch_pair(const BatchArgs &a, const RepDesc &R, int64_t i) {
+__device__ inline void batch_pair(const BatchArgs &a, const RepDesc &R, int64_t i, ForceAcc<F32> &acc) {
   const Grid &g = R.g;
   const PairParams &pp = a.pp;
   const double4 pi4 = a.xq[i];
@@ -108,14 +108,13 @@ __device__ inline void batch_pair(const BatchArgs &a, const RepDesc &R, int64_t 
   const int cx = cell_coord(xi, g.inv_h[0], g.nx);
   const int cy = cell_coord(yi, g.inv_h[1], g.ny);
   const int cz = cell_coord(zi, g.inv_h[2], g.nz);
-  ForceAcc<F32> acc;
-  auto visit_q = [&](int j, const double4 &pj, int, double shx, double shy, double shz) {
+  auto visit_q = [&](int j, const double4 &pj, double shx, double shy, double shz) {
     const double dx = (xi - pj.x) - shx, dy = (yi - pj.y) - shy, dz = (zi - pj.z) - shz;
     const double r2 = sq_dist(dx, dy, dz);
     if (r2 == 0.0 && j == (int)i) return;
     if (r2 <= pp.rq2) acc.template add_row<true>(pp, a.pf, r2, qi, pj.w, dx, dy, dz);
   };
-  auto visit_lj = [&](int j, const double4 &pj, int, double shx, double shy, double shz) {
+  auto visit_lj = [&](int j, const double4 &pj, double shx, double shy, double shz) {
     const double dx = (xi - pj.x) - shx, dy = (yi - pj.y) - shy, dz = (zi - pj.z) - shz;
     const double r2 = sq_dist(dx, dy, dz);
     if (r2 == 0.0 && j == (int)i) return;
@@ -123,21 +122,17 @@ __device__ inline void batch_pair(const BatchArgs &a, const RepDesc &R, int64_t 
   };
   // FP32C: a row's terms summed plainly, the row sum added with Kahan compensation
   auto row_end = [&]() { acc.flush_row(); };
-  const Reach rq{xi, yi, zi, pp.rq2}, rlj{xi, yi, zi, pp.rlj2};
+  auto walk = [&](int blk, const Sten &s, double r2, auto &&fn) {
+    for_stencil(g, a.cell_start, a.xq, blk, cx, cy, cz, s, xi, yi, zi, r2, fn, R.c0, row_end);
+  };
   if (qi != 0.0) {
-    if (pp.do_coul || pp.do_lj)
-      for_stencil<false>(g, a.cell_start, a.xq, a.sid, 0, cx, cy, cz, R.s_coul, rq, visit_q, R.c0, row_end);
-    if (pp.do_lj)
-      for_stencil<false>(g, a.cell_start, a.xq, a.sid, 1, cx, cy, cz, R.s_lj, rlj, visit_lj, R.c0, row_end);
+    if (pp.do_coul || pp.do_lj) walk(0, R.s_coul, pp.rq2, visit_q);
+    if (pp.do_lj) walk(1, R.s_lj, pp.rlj2, visit_lj);
   } else if (pp.do_lj) {
-    for_stencil<false>(g, a.cell_start, a.xq, a.sid, 0, cx, cy, cz, R.s_lj, rlj, visit_lj, R.c0, row_end);
-    for_stencil<false>(g, a.cell_start, a.xq, a.sid, 1, cx, cy, cz, R.s_lj, rlj, visit_lj, R.c0, row_end);
+    walk(0, R.s_lj, pp.rlj2, visit_lj);
+    walk(1, R.s_lj, pp.rlj2, visit_lj);
   }
-  a.ofx[i] = acc.get(0);
-  a.ofy[i] = acc.get(1);
-  a.ofz[i] = acc.get(2);
 }
-
 
 template <bool F32>
 __global__ void __launch_bounds__(kBatchThreads) k_batch_step(BatchArgs a) {
@@ -438,13 +433,50 @@ __global__ void __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per
 k_batch_near(BatchArgs a) {
   const int64_t i = blockIdx.x * (int64_t)kBatchThreads + threadIdx.x;
   if (i >= a.ntot) return;
-  if (a.pp.do_coul || a.pp.do_lj) {
-    batch_pair<F32>(a, a.reps[a.rep_of[i]], i);
-  } else {
-    a.ofx[i] = 0.0;
-    a.ofy[i] = 0.0;
-    a.ofz[i] = 0.0;
+  ForceAcc<F32> acc;
+  if (a.pp.do_coul || a.pp.do_lj) batch_pair<F32>(a, a.reps[a.rep_of[i]], i, acc);
+  a.ofx[i] = acc.get(0);
+  a.ofy[i] = acc.get(1);
+  a.ofz[i] = acc.get(2);
+}
+
+// The same for batches of too few particles to fill the chip with one thread
+// each: G lanes share a particle (pair_device.h, group walks).
+template <bool F32, int G>
+__global__ void __launch_bounds__(kBatchThreads) k_batch_near_group(BatchArgs a) {
+  __shared__ GroupRows<G> rows[kBatchThreads / G];
+  __shared__ GroupTerms<F32 ? G : 1> terms[kBatchThreads / G];
+  const int64_t per = (a.ntot + gridDim.x - 1) / gridDim.x;  // consecutive particles per block
+  const int64_t first = blockIdx.x * per, last = min(a.ntot, first + per);
+  for (int64_t i = first + threadIdx.x / G; i < last; i += kBatchThreads / G) {  // the lanes of a group together
+    const RepDesc &R = a.reps[a.rep_of[i]];
+    ForceAcc<F32> acc;
+    group_sums<F32, false, G>(a.pp, a.pf, R.g, R.s_coul, R.s_lj, a.cell_start + R.c0, a.xq, nullptr, nullptr, 0,
+                              (int)i, a.xq[i], false, rows[threadIdx.x / G], &terms[threadIdx.x / G].t[0], acc,
+                              [](bool, double) {});
+    const double f0 = acc.template total<G>(0), f1 = acc.template total<G>(1), f2 = acc.template total<G>(2);
+    if (threadIdx.x % G == 0) {
+      a.ofx[i] = f0;
+      a.ofy[i] = f1;
+      a.ofz[i] = f2;
+    }
   }
+}
+
+// Near-field kernel of a batch and its blocks. The group form up to these
+// sizes of the whole batch; a step of 8 to 128 replicas in us, thread form
+// against group form: FP64 20,000 particles 1190, 789; 150,000: 1604, 1311;
+// 300,000: 2016, 2003; 600,000: 2696, 3019. FP32C 20,000: 1154, 872; 150,000:
+// 1411, 1332; 300,000: 1733, 1929.
+constexpr int64_t kBatchGroupMost64 = 262144, kBatchGroupMost32 = 131072;
+using BatchKernel = void (*)(BatchArgs);
+static BatchKernel batch_near_kernel(int prec, int64_t ntot, unsigned *blocks) {
+  if (ntot <= (prec == RBE_FP32C ? kBatchGroupMost32 : kBatchGroupMost64)) {
+    *blocks = group_blocks(ntot, 32);
+    return prec == RBE_FP32C ? k_batch_near_group<true, 32> : k_batch_near_group<false, 32>;
+  }
+  *blocks = (unsigned)((ntot + kBatchThreads - 1) / kBatchThreads);
+  return prec == RBE_FP32C ? k_batch_near<true> : k_batch_near<false>;
 }
 
 int batch_grid_blocks(int prec, int device) {
@@ -465,31 +497,26 @@ void launch_batch_step(int prec, int blocks, const BatchArgs &a, hipStream_t st)
   BatchArgs a1 = a, a2 = a;
   a1.launch_part = 1;
   a2.launch_part = 2;
-  const unsigned near_blocks = (unsigned)((a.ntot + kBatchThreads - 1) / kBatchThreads);
-  if (prec == RBE_FP32C) {
-    k_batch_step<true><<<blocks, kBatchThreads, 0, st>>>(a1);
-    k_batch_near<true><<<near_blocks, kBatchThreads, 0, st>>>(a);
-    k_batch_step<true><<<blocks, kBatchThreads, 0, st>>>(a2);
-  } else {
-    k_batch_step<false><<<blocks, kBatchThreads, 0, st>>>(a1);
-    k_batch_near<false><<<near_blocks, kBatchThreads, 0, st>>>(a);
-    k_batch_step<false><<<blocks, kBatchThreads, 0, st>>>(a2);
-  }
+  unsigned near_blocks;
+  const BatchKernel near = batch_near_kernel(prec, a.ntot, &near_blocks);
+  const BatchKernel step = prec == RBE_FP32C ? k_batch_step<true> : k_batch_step<false>;
+  step<<<blocks, kBatchThreads, 0, st>>>(a1);
+  near<<<near_blocks, kBatchThreads, 0, st>>>(a);
+  step<<<blocks, kBatchThreads, 0, st>>>(a2);
 }
 
 int batch_scan_tiles(int64_t nkeys) { return (int)((nkeys + kScanTileB - 1) / kScanTileB); }
 
 hipError_t add_batch_node(hipGraph_t graph, hipGraphNode_t *node, const hipGraphNode_t *deps, int ndeps, int prec,
                           int blocks, BatchArgs *a) {
-  const bool f32 = prec == RBE_FP32C;
   BatchArgs parts[3] = {*a, *a, *a};
   parts[0].launch_part = 1;
   parts[2].launch_part = 2;
-  void *funcs[3] = {f32 ? reinterpret_cast<void *>(k_batch_step<true>) : reinterpret_cast<void *>(k_batch_step<false>),
-                    f32 ? reinterpret_cast<void *>(k_batch_near<true>) : reinterpret_cast<void *>(k_batch_near<false>),
-                    f32 ? reinterpret_cast<void *>(k_batch_step<true>) : reinterpret_cast<void *>(k_batch_step<false>)};
-  const unsigned grids[3] = {(unsigned)blocks, (unsigned)((a->ntot + kBatchThreads - 1) / kBatchThreads),
-                             (unsigned)blocks};
+  unsigned near_blocks;
+  const BatchKernel near = batch_near_kernel(prec, a->ntot, &near_blocks);
+  const BatchKernel step = prec == RBE_FP32C ? k_batch_step<true> : k_batch_step<false>;
+  void *funcs[3] = {reinterpret_cast<void *>(step), reinterpret_cast<void *>(near), reinterpret_cast<void *>(step)};
+  const unsigned grids[3] = {(unsigned)blocks, near_blocks, (unsigned)blocks};
   hipGraphNode_t prev = nullptr;
   for (int k = 0; k < 3; ++k) {
     hipKernelNodeParams kp{};

@@ -17,6 +17,8 @@
 namespace rbe {
 
 constexpr int kEnergyThreads = 256;
+constexpr int kEnergyGroup = 64;            // lanes per particle of the near field
+constexpr int64_t kEnergyNearBlocks = 16384;  // most blocks of the near field (each leaves one partial sum)
 constexpr int kEnergySqBlocks = 1024;  // grid of the q^2 / v^2 sums
 
 // Sum of v over the block; the result is valid in thread 0.
@@ -50,19 +52,18 @@ __global__ void __launch_bounds__(kEnergyThreads) k_energy_near(PairParams pp, d
                                                                 const int32_t *__restrict__ cell_start,
                                                                 double *__restrict__ part) {
   __shared__ double lds[kEnergyThreads / 64];
-  const int64_t i = blockIdx.x * (int64_t)kEnergyThreads + threadIdx.x;
+  constexpr int G = kEnergyGroup;
+  __shared__ GroupRows<G> rows[kEnergyThreads / G];
+  const int64_t per = (n + gridDim.x - 1) / gridDim.x;  // consecutive particles per block
+  const int64_t end = min(n, (blockIdx.x + 1) * per);
+  const Grid &g = pp.g;
+  const Block near_lj = pp.do_lj ? Block{pp.s_lj, pp.rlj2} : no_block();
   double uc = 0.0, ul = 0.0, wc = 0.0, wl = 0.0;
-  if (i < n) {
-    const Grid &g = pp.g;
+  for (int64_t i = blockIdx.x * per + threadIdx.x / G; i < end; i += kEnergyThreads / G) {
     const double4 pi4 = xq[i];
-    const double xi = pi4.x, yi = pi4.y, zi = pi4.z, qi = pi4.w;
-    const int cx = cell_coord(xi, g.inv_h[0], g.nx);
-    const int cy = cell_coord(yi, g.inv_h[1], g.ny);
-    const int cz = cell_coord(zi, g.inv_h[2], g.nz);
-    auto visit = [&](int j, const double4 &pj, int, double shx, double shy, double shz) {
-      const double dx = (xi - pj.x) - shx, dy = (yi - pj.y) - shy, dz = (zi - pj.z) - shz;
-      const double r2 = sq_dist(dx, dy, dz);
-      if (r2 == 0.0 && j == (int)i) return;
+    const double qi = pi4.w;
+    auto visit = [&](bool ok, int, int, int j, const double4 &pj, double, double, double, double r2) {
+      if (!ok || j == (int)i) return;
       if (pp.do_coul && r2 <= pp.rc2 && qi != 0.0 && pj.w != 0.0) {
         const double r = sqrt(r2);
         const double qq = pp.kc * qi * pj.w;
@@ -76,19 +77,13 @@ __global__ void __launch_bounds__(kEnergyThreads) k_energy_near(PairParams pp, d
         wl += 2.0 * s6 * s6 - s6;
       }
     };
-    const Reach rq{xi, yi, zi, pp.rq2}, rlj{xi, yi, zi, pp.rlj2};
-    if (qi != 0.0) {
-      for_stencil<false>(g, cell_start, xq, nullptr, 0, cx, cy, cz, pp.s_coul, rq, visit);
-      if (pp.do_lj) for_stencil<false>(g, cell_start, xq, nullptr, 1, cx, cy, cz, pp.s_lj, rlj, visit);
-    } else if (pp.do_lj) {
-      for_stencil<false>(g, cell_start, xq, nullptr, 0, cx, cy, cz, pp.s_lj, rlj, visit);
-      for_stencil<false>(g, cell_start, xq, nullptr, 1, cx, cy, cz, pp.s_lj, rlj, visit);
-    }
-    uc *= 0.5;
-    ul *= 0.5 * lj4;
-    wc *= 0.5;
-    wl *= 0.5 * pp.eps24;
+    group_walk<G, false>(g, cell_start, xq, nullptr, nullptr, 0, pi4, qi != 0.0 ? Block{pp.s_coul, pp.rq2} : near_lj,
+                         near_lj, rows[threadIdx.x / G], visit, [](int, int) {}, [](int) {});
   }
+  uc *= 0.5;
+  ul *= 0.5 * lj4;
+  wc *= 0.5;
+  wl *= 0.5 * pp.eps24;
   const double sc = block_sum(uc, lds);
   const double sl = block_sum(ul, lds);
   const double vc = block_sum(wc, lds);
@@ -167,17 +162,19 @@ __global__ void __launch_bounds__(kEnergyThreads) k_energy_final(EnergyFinal a) 
   }
 }
 
-int energy_part_len(int64_t n_max) {
-  const int64_t nb = (n_max + kEnergyThreads - 1) / kEnergyThreads;
-  return (int)(4 * nb + 2 * kEnergySqBlocks);
+static int64_t energy_near_blocks(int64_t n) {
+  const int64_t nb = (n * kEnergyGroup + kEnergyThreads - 1) / kEnergyThreads;
+  return nb < kEnergyNearBlocks ? nb : kEnergyNearBlocks;
 }
+
+int energy_part_len(int64_t n_max) { return (int)(4 * energy_near_blocks(n_max) + 2 * kEnergySqBlocks); }
 
 void launch_energy(const PairParams &pp, double lj4, int64_t n, const Sorted &s,
                    const int32_t *cell_start, bool near, const double *q, const double *vx, const double *vy,
                    const double *vz, double *part, EnergyFinal fin, hipStream_t st) {
   int64_t nb_near = 0;
   if (near && n > 0) {
-    nb_near = (n + kEnergyThreads - 1) / kEnergyThreads;
+    nb_near = energy_near_blocks(n);
     k_energy_near<<<(unsigned)nb_near, kEnergyThreads, 0, st>>>(pp, lj4, 2.0 * std::sqrt(pp.alpha / kPi), n, s.xq,
                                                                  cell_start, part);
   }

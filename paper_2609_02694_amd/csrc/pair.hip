@@ -31,6 +31,8 @@
 // Pair force on i: (kc q_i q_j G(r) + G_LJ(r)) d, d = r_i - r_j,
 //   G(r)    = erfc(sqrt(a) r)/r^3 + 2 sqrt(a) exp(-a r^2)/(sqrt(pi) r^2),
 //   G_LJ(r) = 24 eps (2 sigma^12/r^14 - sigma^6/r^8).
+#include <algorithm>
+
 #include "pair_device.h"
 
 namespace rbe {
@@ -124,14 +126,14 @@ __device__ inline ClusterI load_cluster_i(const PairCtx &c, int64_t first, int64
 }
 
 // Periodic or ghost-shell stencil walk of one particle (thread form).
-template <bool GHOST, bool WITH_ID, class Fn, class RowEnd>
-__device__ inline void stencil(const PairCtx &c, int blk, int cx, int cy, int cz, const Sten &s, const Reach &R,
-                               Fn &&fn, RowEnd &&row_end) {
+template <bool GHOST, class Fn, class RowEnd>
+__device__ inline void stencil(const PairCtx &c, int blk, int cx, int cy, int cz, const Sten &s, const double4 &p,
+                               double r2, Fn &&fn, RowEnd &&row_end) {
   if (GHOST)
-    for_stencil_ghost<WITH_ID>(c.pp.g, c.cell_start, c.xq, c.ids, c.gcell_start, c.gxq, c.gid, (int)c.n, blk, cx, cy,
-                               cz, s, R, fn, row_end);
+    for_stencil_ghost(c.pp.g, c.cell_start, c.xq, c.gcell_start, c.gxq, (int)c.n, blk, cx, cy, cz, s, p.x, p.y, p.z,
+                      r2, fn, row_end);
   else
-    for_stencil<WITH_ID>(c.pp.g, c.cell_start, c.xq, c.ids, blk, cx, cy, cz, s, R, fn, 0, row_end);
+    for_stencil(c.pp.g, c.cell_start, c.xq, blk, cx, cy, cz, s, p.x, p.y, p.z, r2, fn, 0, row_end);
 }
 
 // Plain cutoff sums, one thread per particle i walking its own stencil (on
@@ -149,6 +151,8 @@ template <bool F32, bool COUNT, int MODE, bool GHOST>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(F32 ? (MODE ? 5 : 6) : (MODE ? 3 : 7))))
 k_pair_plain(PairCtx c) {
   static_assert(MODE >= 0 && MODE <= 2, "mode");
+  const int64_t nq = *c.nq_ptr;
+  if (group_lanes(F32, MODE, MODE ? nq : c.n - nq) > 1) return;  // too few particles: k_pair_group
   int64_t first, end;
   if (!part_block(c, blockDim.x, &first, &end)) return;
   const int64_t i = first + threadIdx.x;
@@ -163,7 +167,7 @@ k_pair_plain(PairCtx c) {
   ForceAcc<F32> acc;
   unsigned long long n_coul = 0, n_lj = 0, n_tested = 0;
   // Coulomb + LJ against charged j (block 0 of a charged i)
-  auto visit_q = [&](int j, const double4 &pj, int, double shx, double shy, double shz) {
+  auto visit_q = [&](int j, const double4 &pj, double shx, double shy, double shz) {
     const double dx = (xi - pj.x) - shx, dy = (yi - pj.y) - shy, dz = (zi - pj.z) - shz;
     const double r2 = sq_dist(dx, dy, dz);
     if (COUNT) ++n_tested;
@@ -177,7 +181,7 @@ k_pair_plain(PairCtx c) {
     }
   };
   // LJ only (every other species pairing)
-  auto visit_lj = [&](int j, const double4 &pj, int, double shx, double shy, double shz) {
+  auto visit_lj = [&](int j, const double4 &pj, double shx, double shy, double shz) {
     const double dx = (xi - pj.x) - shx, dy = (yi - pj.y) - shy, dz = (zi - pj.z) - shz;
     const double r2 = sq_dist(dx, dy, dz);
     if (COUNT) ++n_tested;
@@ -188,25 +192,69 @@ k_pair_plain(PairCtx c) {
     }
   };
   auto row_end = [&]() { acc.flush_row(); };
-  const Reach rq{xi, yi, zi, pp.rq2}, rlj{xi, yi, zi, pp.rlj2};
   if (MODE == 2) {
     // pp.do_lj is off for this launch: visit_q adds the screened Coulomb term only
-    const Reach rc{xi, yi, zi, pp.rc2};
-    stencil<GHOST, false>(c, 0, cx, cy, cz, pp.s_coul, rc, visit_q, row_end);
+    stencil<GHOST>(c, 0, cx, cy, cz, pp.s_coul, pi4, pp.rc2, visit_q, row_end);
     c.fx[i] += acc.get(0);
     c.fy[i] += acc.get(1);
     c.fz[i] += acc.get(2);
   } else {
     if (MODE == 1) {
-      stencil<GHOST, false>(c, 0, cx, cy, cz, pp.s_coul, rq, visit_q, row_end);
-      if (pp.do_lj) stencil<GHOST, false>(c, 1, cx, cy, cz, pp.s_lj, rlj, visit_lj, row_end);
+      stencil<GHOST>(c, 0, cx, cy, cz, pp.s_coul, pi4, pp.rq2, visit_q, row_end);
+      if (pp.do_lj) stencil<GHOST>(c, 1, cx, cy, cz, pp.s_lj, pi4, pp.rlj2, visit_lj, row_end);
     } else if (pp.do_lj) {
-      stencil<GHOST, false>(c, 0, cx, cy, cz, pp.s_lj, rlj, visit_lj, row_end);
-      stencil<GHOST, false>(c, 1, cx, cy, cz, pp.s_lj, rlj, visit_lj, row_end);
+      stencil<GHOST>(c, 0, cx, cy, cz, pp.s_lj, pi4, pp.rlj2, visit_lj, row_end);
+      stencil<GHOST>(c, 1, cx, cy, cz, pp.s_lj, pi4, pp.rlj2, visit_lj, row_end);
     }
     c.fx[i] = acc.get(0);
     c.fy[i] = acc.get(1);
     c.fz[i] = acc.get(2);
+  }
+  flush_counts<COUNT>(c, n_coul, n_lj, n_tested, 0);
+}
+
+// Plain cutoff sums of particles too few to fill the chip with one thread
+// each: G lanes share one (pair_device.h, group walks). c.charged: 1 the
+// charged range, 0 the neutral one, 2 both; coulomb: the charged range's
+// screened Coulomb terms only, added to f. Small launches are bound by the
+// latency of a particle's chain of loads, large ones by the issue of the pair
+// terms (about half the lanes hold a pair inside the cutoff): 2,000 ions out
+// to r = 8 in FP64 13 us (422 us as one thread each), 50,000 147 us (357).
+template <bool F32, bool COUNT, bool GHOST, int G>
+__global__ void __launch_bounds__(256) k_pair_group(PairCtx c, int coulomb) {
+  __shared__ GroupRows<G> rows[256 / G];
+  __shared__ GroupTerms<F32 ? G : 1> terms[256 / G];
+  const int64_t nq = *c.nq_ptr;
+  const int64_t a = c.charged ? 0 : nq, end = c.charged == 1 ? nq : c.n;
+  if (group_lanes(F32, c.charged, end - a) == 1) return;  // enough particles: k_pair_plain
+  const int64_t per = (end - a + gridDim.x - 1) / gridDim.x;  // consecutive particles per block
+  const int64_t first = a + blockIdx.x * per, last = min(end, first + per);
+  const PairParams &pp = c.pp;
+  unsigned long long n_coul = 0, n_lj = 0, n_tested = 0;
+  for (int64_t i = first + threadIdx.x / G; i < last; i += 256 / G) {  // the lanes of a group together
+    const double4 pi4 = c.xq[i];
+    ForceAcc<F32> acc;
+    group_sums<F32, GHOST, G>(
+        pp, c.pf, pp.g, pp.s_coul, pp.s_lj, c.cell_start, c.xq, c.gcell_start, c.gxq, (int)c.n, (int)i, pi4,
+        coulomb != 0, rows[threadIdx.x / G], &terms[threadIdx.x / G].t[0], acc, [&](bool coul, double r2) {
+          if (COUNT) {
+            ++n_tested;
+            n_coul += (coul && pp.do_coul && r2 <= pp.rc2);
+            n_lj += (!coulomb && pp.do_lj && r2 <= pp.rlj2);
+          }
+        });
+    const double f0 = acc.template total<G>(0), f1 = acc.template total<G>(1), f2 = acc.template total<G>(2);
+    if (threadIdx.x % G == 0) {
+      if (coulomb) {
+        c.fx[i] += f0;
+        c.fy[i] += f1;
+        c.fz[i] += f2;
+      } else {
+        c.fx[i] = f0;
+        c.fy[i] = f1;
+        c.fz[i] = f2;
+      }
+    }
   }
   flush_counts<COUNT>(c, n_coul, n_lj, n_tested, 0);
 }
@@ -363,16 +411,27 @@ PairF32 make_pair_f32(const PairParams &pp) {
   return pf;
 }
 
-// Thread form: 256 particles per block. Cluster form: one wave of kCI
-// particles per block. Grids cover all n particles (the part's range is read
-// on the device; surplus blocks exit at once).
-template <class K>
-static void launch_threads(K kernel, PairCtx c, hipStream_t st) {
-  kernel<<<(unsigned)((c.n + 255) / 256), 256, 0, st>>>(c);
-}
+// Cluster form: one wave of kCI particles per block. Grids cover all n
+// particles (the part's range is read on the device; surplus blocks exit at
+// once).
 template <class K>
 static void launch_clusters(K kernel, PairCtx c, hipStream_t st) {
   kernel<<<(unsigned)((c.n + kCI - 1) / kCI), 64, 0, st>>>(c);
+}
+
+// Plain sums of a part (c.charged): one thread per particle, or a group of
+// lanes when the part is small. Whether a part of a large system is small is
+// known on the device only, so both kernels are launched then and one of them
+// exits at once (about 3 us beside a walk of hundreds).
+template <bool F32, bool COUNT, int MODE, bool GHOST>
+static void launch_plain(PairCtx c, hipStream_t st) {
+  const int lanes = group_lanes(F32, MODE, c.n);
+  const int64_t most = std::min(c.n, group_most(F32, MODE));
+  if (lanes == 64)
+    k_pair_group<F32, COUNT, GHOST, 64><<<group_blocks(most, 64), 256, 0, st>>>(c, MODE == 2);
+  else
+    k_pair_group<F32, COUNT, GHOST, 32><<<group_blocks(most, 32), 256, 0, st>>>(c, MODE == 2);
+  if (lanes == 1) k_pair_plain<F32, COUNT, MODE, GHOST><<<(unsigned)((c.n + 255) / 256), 256, 0, st>>>(c);
 }
 
 // Charged particles occupy [0, nq) of the sorted order, neutral ones [nq, n).
@@ -380,7 +439,8 @@ static void launch_clusters(K kernel, PairCtx c, hipStream_t st) {
 // neutral ones too when r_lj > r_core (their LJ terms then reach the shell),
 // else their sums are plain (every LJ term lies in the core).
 // part: PAIR_PART_CHARGED, PAIR_PART_SHELL (nothing left to do: the shell is
-// fused into the charged part) or PAIR_PART_NEUTRAL.
+// fused into the charged part), PAIR_PART_NEUTRAL, PAIR_PART_COULOMB or
+// PAIR_PART_BOTH.
 template <bool F32, bool COUNT, bool GHOST>
 static void launch_part(PairCtx c, int part, hipStream_t st) {
   const PairParams pp = c.pp;
@@ -388,17 +448,22 @@ static void launch_part(PairCtx c, int part, hipStream_t st) {
     c.charged = 1;
     if (pp.rbl && pp.shell_charged) launch_clusters(k_pair_rbl<F32, COUNT, GHOST, true>, c, st);
     else if (pp.rbl) launch_clusters(k_pair_rbl<F32, COUNT, GHOST, false>, c, st);
-    else launch_threads(k_pair_plain<F32, COUNT, 1, GHOST>, c, st);
+    else launch_plain<F32, COUNT, 1, GHOST>(c, st);
   } else if (part == PAIR_PART_COULOMB) {
     c.charged = 1;
     c.pp.do_lj = 0;
-    launch_threads(k_pair_plain<F32, COUNT, 2, GHOST>, c, st);
+    launch_plain<F32, COUNT, 2, GHOST>(c, st);
   } else if (part == PAIR_PART_NEUTRAL) {
     c.charged = 0;
     if (pp.rbl && pp.rlj2 > pp.rcore2 && pp.do_lj) launch_clusters(k_pair_rbl<F32, COUNT, GHOST, false>, c, st);
-    else launch_threads(k_pair_plain<F32, COUNT, 0, GHOST>, c, st);
+    else launch_plain<F32, COUNT, 0, GHOST>(c, st);
+  } else if (part == PAIR_PART_BOTH) {
+    c.charged = 2;
+    launch_plain<F32, COUNT, 0, GHOST>(c, st);
   }
 }
+
+bool pair_grouped(int prec, int64_t n) { return group_lanes(prec == RBE_FP32C, false, n) > 1; }
 
 template <bool GHOST>
 static void launch_prec(int prec, PairCtx c, int part, hipStream_t st) {

@@ -217,120 +217,124 @@ __device__ inline double min_image(double a, double L) {
   return a - L * rint(a / L);
 }
 
-// Calls fn(jofs + j, p_j, id_j, shx, shy, shz) for the records j0..j1-1 of xq
-// (and ids when WITH_ID, else id_j = 0); jofs separates the index ranges of
-// natives (0) and ghosts (n). Four fixed slots: slot k holds record
-// j + k and is reloaded with j + k + 4 right after use, so each load has
-// three candidates of work to complete behind it. The lookahead reads up to
-// kScanPad - 1 records past j1: every array scanned here is allocated with
-// kScanPad records of padding, so those loads stay inside the allocation
-// (their values are never used), and the addresses are plain increments.
-template <bool WITH_ID, class Fn>
-__device__ inline void scan_range(const double4 *__restrict__ xq, const int32_t *__restrict__ ids, int j0, int j1,
-                                  double shx, double shy, double shz, Fn &&fn, int jofs = 0) {
+// Calls fn(jofs + j, p_j, shx, shy, shz) for the records j0..j1-1 of xq;
+// jofs separates the index ranges of natives (0) and ghosts (n). Four fixed
+// slots: slot k holds record j + k and is reloaded with j + k + 4 right after
+// use, so each load has three candidates of work to complete behind it. The
+// lookahead reads up to kScanPad - 1 records past j1: every array scanned
+// here is allocated with kScanPad records of padding, so those loads stay
+// inside the allocation (their values are never used), and the addresses are
+// plain increments.
+template <class Fn>
+__device__ inline void scan_range(const double4 *__restrict__ xq, int j0, int j1, double shx, double shy, double shz,
+                                  Fn &&fn, int jofs = 0) {
   if (j0 >= j1) return;
   const double4 *p = xq + j0;
-  const int32_t *q = WITH_ID ? ids + j0 : ids;
   double4 r0 = p[0], r1 = p[1], r2 = p[2], r3 = p[3];
-  int d0 = 0, d1 = 0, d2 = 0, d3 = 0;
-  if (WITH_ID) {
-    d0 = q[0];
-    d1 = q[1];
-    d2 = q[2];
-    d3 = q[3];
-  }
+  j0 += jofs;
+  j1 += jofs;
 #pragma unroll 1
   for (int j = j0; j < j1; j += 4) {
-    fn(jofs + j, r0, d0, shx, shy, shz);
+    fn(j, r0, shx, shy, shz);
     r0 = p[4];
-    if (WITH_ID) d0 = q[4];
-    if (j + 1 < j1) fn(jofs + j + 1, r1, d1, shx, shy, shz);
+    if (j + 1 < j1) fn(j + 1, r1, shx, shy, shz);
     r1 = p[5];
-    if (WITH_ID) d1 = q[5];
-    if (j + 2 < j1) fn(jofs + j + 2, r2, d2, shx, shy, shz);
+    if (j + 2 < j1) fn(j + 2, r2, shx, shy, shz);
     r2 = p[6];
-    if (WITH_ID) d2 = q[6];
-    if (j + 3 < j1) fn(jofs + j + 3, r3, d3, shx, shy, shz);
+    if (j + 3 < j1) fn(j + 3, r3, shx, shy, shz);
     r3 = p[7];
-    if (WITH_ID) d3 = q[7];
     p += 4;
-    if (WITH_ID) q += 4;
   }
 }
 
-// Walking particle of a thread-form traversal: position and the squared
-// reach of the walk. Each stencil row is trimmed to the x-cells the reach
-// sphere can touch: the gap g from (y, z) to the row's y/z cell slabs bounds
-// the x extent by sqrt(r^2 - g^2), and rows with g > r are skipped. The
-// gaps are shrunk and the extent grown by kTrimMargin, which covers the
-// rounding of the binning (a particle binned to cell c lies within a few ulp
-// of [c h, (c + 1) h]); every pair is still classified exactly afterwards.
-struct Reach {
-  double x, y, z, r2;
+// Rows of a walk: each stencil row is trimmed to the x-cells the reach sphere
+// can touch. The gap g from (y, z) to the row's y/z cell slabs bounds the x
+// extent by sqrt(r^2 - g^2), and rows with g > r are skipped. All of it in
+// FP32, in the frame of the particle's own cell (coordinates of the size of
+// the reach, whatever the box): the squared reach is enlarged by 2^-18 and
+// the gaps and the extent by 2^-18 of the reach and the largest cell edge,
+// tens of times the rounding of these few operations and of the binning, so
+// no cell inside the reach is left out; every pair is classified exactly
+// afterwards. (In FP64, with its square root, the set-up of a row cost as
+// many issue cycles as several candidates.)
+struct RowFrame {
+  float ux, uy, uz;        // offset of the particle in its cell
+  float hy, hz, inv_hx;
+  float r2, margin;
+  __device__ inline RowFrame(const Grid &g, double x, double y, double z, int cx, int cy, int cz, double reach2) {
+    ux = (float)(x - (double)cx * g.h[0]);
+    uy = (float)(y - (double)cy * g.h[1]);
+    uz = (float)(z - (double)cz * g.h[2]);
+    hy = (float)g.h[1];
+    hz = (float)g.h[2];
+    inv_hx = (float)g.inv_h[0];
+    r2 = (float)reach2 * (1.0f + 0x1p-18f);
+    margin = 0x1p-18f * (__builtin_amdgcn_sqrtf(r2) + fmaxf((float)g.h[0], fmaxf(hy, hz)));
+  }
+  // Distance from an offset u to the slab of the cell o cells away, less the margin, at least 0.
+  __device__ inline float gap(float u, int o, float h) const {
+    const float lo = (float)o * h;
+    return fmaxf(fmaxf(lo - u, u - (lo + h)) - margin, 0.0f);
+  }
+  // x-cell offsets [*a, *b] (within [-s, s]) of a row at gaps whose squares sum to g2; false if out of reach.
+  __device__ inline bool range(float g2, int s, int *a, int *b) const {
+    const float rem = r2 - g2;
+    if (rem < 0.0f) return false;
+    const float ext = __builtin_amdgcn_sqrtf(rem) + margin;
+    *a = max(-s, (int)floorf((ux - ext) * inv_hx));
+    *b = min(s, (int)floorf((ux + ext) * inv_hx));
+    return *a <= *b;
+  }
 };
-constexpr double kTrimMargin = 1e-9;
-// Distance from p to the cell slab [c h, (c + 1) h] (unwrapped cell index c),
-// minus the margin, at least 0.
-__device__ inline double slab_gap(double p, int c, double h) {
-#pragma clang fp contract(off)
-  const double lo = (double)c * h, hi = lo + h;
-  const double d = lo - p > 0.0 ? lo - p : (p - hi > 0.0 ? p - hi : 0.0);
-  return d > kTrimMargin ? d - kTrimMargin : 0.0;
-}
-// x-cell range [*xa, *xb] (unwrapped, inside [cx - s, cx + s]) of a row at
-// y/z gaps gy, gz; false if the row is out of reach.
-__device__ inline bool row_range(const Grid &g, const Reach &R, double gy, double gz, int cx, int s, int *xa,
-                                 int *xb) {
-#pragma clang fp contract(off)
-  const double rem = R.r2 - (gy * gy + gz * gz);
-  if (rem < 0.0) return false;
-  const double ext = sqrt(rem) + kTrimMargin;
-  const int lo = (int)floor((R.x - ext) * g.inv_h[0]);
-  const int hi = (int)floor((R.x + ext) * g.inv_h[0]);
-  *xa = max(cx - s, lo);
-  *xb = min(cx + s, hi);
-  return *xa <= *xb;
+
+// Cell in [0, n) of an unwrapped cell index a in [-n, 2 n), and the boxes it
+// lies off. (A cutoff is at most half the box, so a stencil radius is at most
+// n and the neighbours of a cell of the grid lie in that range.)
+__device__ inline int wrap_cell(int a, int n, int *q) {
+  *q = a < 0 ? -1 : (a >= n ? 1 : 0);
+  return a - *q * n;
 }
 
-// Periodic traversal: every particle j of species block `blk` in the
-// (2 s.x + 1)(2 s.y + 1)(2 s.z + 1) cells around (cx, cy, cz) that the reach
-// of R can touch;
-// (shx, shy, shz) is the image shift of j (its image lies at r_j + shift).
+// Periodic traversal: every particle j of species block `blk` (keys cell_base
+// + blk C + cell) in the (2 s.x + 1)(2 s.y + 1)(2 s.z + 1) cells around
+// (cx, cy, cz), the cell of (x, y, z), that the squared reach r2 can touch,
+// each met once per periodic image; (shx, shy, shz) is the image shift of j
+// (its image lies at r_j + shift).
 // row_end() is called after each stencil row (the FP32C accumulators close a
 // row's plain partial sum there).
 struct NoRowEnd {
   __device__ inline void operator()() const {}
 };
-template <bool WITH_ID, class Fn, class RowEnd = NoRowEnd>
+template <class Fn, class RowEnd = NoRowEnd>
 __device__ inline void for_stencil(const Grid &g, const int32_t *__restrict__ cell_start,
-                                   const double4 *__restrict__ xq, const int32_t *__restrict__ ids, int blk, int cx,
-                                   int cy, int cz, const Sten &s, const Reach &R, Fn &&fn, int64_t cell_base = 0,
+                                   const double4 *__restrict__ xq, int blk, int cx, int cy, int cz, const Sten &s,
+                                   double x, double y, double z, double r2, Fn &&fn, int64_t cell_base = 0,
                                    RowEnd row_end = RowEnd()) {
-  const int64_t base = cell_base + (int64_t)blk * g.ncell;
-  const double hy = g.L[1] / g.ny, hz = g.L[2] / g.nz;
+  const int32_t *cs = cell_start + cell_base + (int64_t)blk * g.ncell;
+  const RowFrame F(g, x, y, z, cx, cy, cz, r2);
   for (int oz = -s.z; oz <= s.z; ++oz) {
-    const int az = cz + oz;
-    const double gz = slab_gap(R.z, az, hz);
-    if (gz * gz > R.r2) continue;
-    const int qz = floor_div(az, g.nz);
-    const int wz = az - qz * g.nz;
+    const float gz = F.gap(F.uz, oz, F.hz);
+    if (gz * gz > F.r2) continue;
+    int qz;
+    const int wz = wrap_cell(cz + oz, g.nz, &qz);
     const double shz = (double)qz * g.L[2];
     for (int oy = -s.y; oy <= s.y; ++oy) {
-      const int ay = cy + oy;
+      const float gy = F.gap(F.uy, oy, F.hy);
       int a, a_end;
-      if (!row_range(g, R, slab_gap(R.y, ay, hy), gz, cx, s.x, &a, &a_end)) continue;
-      const int qy = floor_div(ay, g.ny);
-      const int wy = ay - qy * g.ny;
+      if (!F.range(fmaf(gy, gy, gz * gz), s.x, &a, &a_end)) continue;
+      a += cx;
+      a_end += cx;
+      int qy;
+      const int wy = wrap_cell(cy + oy, g.ny, &qy);
       const double shy = (double)qy * g.L[1];
-      const int64_t row = base + (int64_t)(wz * g.ny + wy) * g.nx;
-      while (a <= a_end) {
-        const int qx = floor_div(a, g.nx);
+      const int32_t *row = cs + (wz * g.ny + wy) * g.nx;
+      do {
+        int qx;
+        const int wa = wrap_cell(a, g.nx, &qx);
         const int b = min(a_end, (qx + 1) * g.nx - 1);
-        const int j0 = cell_start[row + (a - qx * g.nx)];
-        const int j1 = cell_start[row + (b - qx * g.nx) + 1];
-        scan_range<WITH_ID>(xq, ids, j0, j1, (double)qx * g.L[0], shy, shz, fn);
+        scan_range(xq, row[wa], row[b - qx * g.nx + 1], (double)qx * g.L[0], shy, shz, fn);
         a = b + 1;
-      }
+      } while (a <= a_end);
       row_end();
     }
   }
@@ -338,44 +342,241 @@ __device__ inline void for_stencil(const Grid &g, const int32_t *__restrict__ ce
 
 // Ghost-shell traversal (no periodic images): the natives of the stencil
 // rows that lie inside the native grid, then the ghosts of the same rows of
-// the padded grid, each row trimmed to the reach of R. (cx, cy, cz) is a
-// native cell. Ghosts reach fn with indices offset by nnat.
-template <bool WITH_ID, class Fn, class RowEnd = NoRowEnd>
+// the padded grid, each row trimmed to the reach. (cx, cy, cz) is a native
+// cell. Ghosts reach fn with indices offset by nnat.
+template <class Fn, class RowEnd = NoRowEnd>
 __device__ inline void for_stencil_ghost(const Grid &g, const int32_t *__restrict__ cell_start,
-                                         const double4 *__restrict__ xq, const int32_t *__restrict__ ids,
+                                         const double4 *__restrict__ xq,
                                          const int32_t *__restrict__ gcell_start, const double4 *__restrict__ gxq,
-                                         const int32_t *__restrict__ gid, int nnat, int blk, int cx, int cy,
-                                         int cz, const Sten &s, const Reach &R, Fn &&fn,
-                                         RowEnd row_end = RowEnd()) {
-  const int base = blk * g.ncell;
-  const int pbase = blk * g.pncell;
-  const double hy = g.L[1] / g.ny, hz = g.L[2] / g.nz;
+                                         int nnat, int blk, int cx, int cy, int cz, const Sten &s, double px,
+                                         double py, double pz, double r2, Fn &&fn, RowEnd row_end = RowEnd()) {
+  const int32_t *cs = cell_start + (int64_t)blk * g.ncell;
+  const int32_t *gs = gcell_start + (int64_t)blk * g.pncell;
+  const RowFrame F(g, px, py, pz, cx, cy, cz, r2);
   for (int oz = -s.z; oz <= s.z; ++oz) {
+    const float gz = F.gap(F.uz, oz, F.hz);
+    if (gz * gz > F.r2) continue;
     const int z = cz + oz;
-    const double gz = slab_gap(R.z, z, hz);
-    if (gz * gz > R.r2) continue;
     for (int oy = -s.y; oy <= s.y; ++oy) {
-      const int y = cy + oy;
+      const float gy = F.gap(F.uy, oy, F.hy);
       int xa, xb;
-      if (!row_range(g, R, slab_gap(R.y, y, hy), gz, cx, s.x, &xa, &xb)) continue;
+      if (!F.range(fmaf(gy, gy, gz * gz), s.x, &xa, &xb)) continue;
+      xa += cx;
+      xb += cx;
+      const int y = cy + oy;
       const bool inner = z >= 0 && z < g.nz && y >= 0 && y < g.ny;
       if (inner) {
         const int na = max(xa, 0), nb = min(xb, g.nx - 1);
         if (na <= nb) {
-          const int row = base + (z * g.ny + y) * g.nx;
-          scan_range<WITH_ID>(xq, ids, cell_start[row + na], cell_start[row + nb + 1], 0.0, 0.0, 0.0, fn);
+          const int32_t *row = cs + (z * g.ny + y) * g.nx;
+          scan_range(xq, row[na], row[nb + 1], 0.0, 0.0, 0.0, fn);
         }
       }
       // the padded cells over the native grid hold no ghosts: a row range
       // inside it has none to scan
       if (!inner || xa < 0 || xb >= g.nx) {
-        const int prow = pbase + ((z + g.goff[2]) * g.pny + (y + g.goff[1])) * g.pnx + g.goff[0];
-        scan_range<WITH_ID>(gxq, gid, gcell_start[prow + xa], gcell_start[prow + xb + 1], 0.0, 0.0, 0.0, fn, nnat);
+        const int32_t *prow = gs + ((z + g.goff[2]) * g.pny + (y + g.goff[1])) * g.pnx + g.goff[0];
+        scan_range(gxq, prow[xa], prow[xb + 1], 0.0, 0.0, 0.0, fn, nnat);
       }
       row_end();
     }
   }
 }
+
+// ---------------------------------------------------------------------------
+// Group walks: G consecutive lanes per particle
+// ---------------------------------------------------------------------------
+// Sum over the G lanes of a group (fixed order; the lanes of a group together).
+template <int G>
+__device__ inline double group_sum(double v) {
+#pragma unroll
+  for (int o = 1; o < G; o <<= 1) v += __shfl_xor(v, o, G);
+  return v;
+}
+// The lanes of this lane's group for which v holds, as bits 0..G-1.
+template <int G>
+__device__ inline uint64_t group_ballot(bool v) {
+  const uint64_t b = __ballot(v);
+  if (G == 64) return b;
+  return (b >> (threadIdx.x & 63 & ~(G - 1))) & ((1ull << (G & 63)) - 1ull);
+}
+
+// Particles of one species block to meet: its stencil and squared reach.
+struct Block {
+  Sten s;
+  double r2;
+  __device__ inline int rows() const { return s.y < 0 ? 0 : (2 * s.y + 1) * (2 * s.z + 1); }
+};
+__device__ inline Block no_block() { return Block{Sten{0, -1, 0}, 0.0}; }
+
+// Candidates listed at a time, and the group's table of listed rows in LDS:
+// the first record of a row less its place in the list, its image shifts and
+// species block, and one bit per candidate that starts a row.
+template <int G>
+constexpr int kGroupList = 8 * G;
+template <int G>
+struct GroupRows {
+  int base[G], code[G];
+  uint32_t starts[kGroupList<G> / 32];
+};
+
+// The signed 10-bit field of v that starts at bit `at`.
+__device__ inline int bits10(int v, int at) { return (int)((uint32_t)v << (22 - at)) >> 22; }
+// Orders the LDS accesses of a wave's lanes before and after it (a wave's LDS
+// operations execute in order; this holds the compiler to it).
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A group's walk of its particle's stencil rows (block A's, then block B's,
+// each z-major), G rows at a time, one to a lane. The rows' candidates are
+// put end to end by a prefix sum of their counts, and the lanes then take G
+// consecutive ones each trip, whatever rows they come from: a lane finds its
+// row by counting the start bits up to its own place. So all lanes stay busy
+// however short or uneven the rows are, and the walk's length is that of the
+// particle's whole neighbourhood divided by G, not of its longest row.
+// visit(ok, k, blk, j, p_j, dx, dy, dz, r^2) is called by the whole group; k
+// is the place in the listed chunk of kGroupList<G> (ok false: nothing there).
+// listed(first, len) follows each chunk: this lane's row holds the places
+// [first, first + len) of it (len may be 0). rows_end(k) follows each round of
+// G rows, of which the last may hold fewer (k).
+// GHOST: no periodic images, but the ghost arrays (indexed from nnat on).
+template <int G, bool GHOST, class Visit, class Listed, class RowsEnd>
+__device__ inline void group_walk(const Grid &g, const int32_t *__restrict__ cell_start,
+                                  const double4 *__restrict__ xq, const int32_t *__restrict__ gcell_start,
+                                  const double4 *__restrict__ gxq, int nnat, const double4 &pi, const Block &A,
+                                  const Block &B, GroupRows<G> &T, Visit &&visit, Listed &&listed,
+                                  RowsEnd &&rows_end) {
+  constexpr int CH = kGroupList<G>;
+  const int sub = threadIdx.x & (G - 1);
+  const int cx = cell_coord(pi.x, g.inv_h[0], g.nx), cy = cell_coord(pi.y, g.inv_h[1], g.ny),
+            cz = cell_coord(pi.z, g.inv_h[2], g.nz);
+  const int ra = A.rows(), rows = ra + B.rows();
+  for (int r0 = 0; r0 < rows; r0 += G) {
+    // this lane's row: its unwrapped x-cells [a, a_end], none if out of reach
+    int row = r0 + sub, a = 1, a_end = 0, y = 0, z = 0, blk = 0;
+    if (row < rows) {
+      blk = row >= ra;
+      const Sten s = blk ? B.s : A.s;
+      if (blk) row -= ra;
+      const RowFrame F(g, pi.x, pi.y, pi.z, cx, cy, cz, blk ? B.r2 : A.r2);
+      const int ny = 2 * s.y + 1;
+      int oz = (int)(((float)row + 0.5f) / (float)ny);  // row / ny: the quotient is at least 0.5/ny off an integer
+      const int oy = row - oz * ny - s.y;
+      oz -= s.z;
+      const float gz = F.gap(F.uz, oz, F.hz), gy = F.gap(F.uy, oy, F.hy);
+      if (F.range(fmaf(gy, gy, gz * gz), s.x, &a, &a_end)) {
+        a += cx;
+        a_end += cx;
+      } else {
+        a = 1;
+        a_end = 0;
+      }
+      y = cy + oy;
+      z = cz + oz;
+    }
+    // a row's records lie in one piece, or in several: the pieces of a row that
+    // crosses the box edge, the natives and the ghosts of one at the edge
+    bool more = a <= a_end;
+    for (int pass = 0; group_ballot<G>(more); ++pass) {
+      int j0 = 0, len = 0, code = 0;
+      if (more) {
+        if (GHOST) {
+          if (pass == 0) {
+            const bool inner = z >= 0 && z < g.nz && y >= 0 && y < g.ny;
+            const int na = max(a, 0), nb = min(a_end, g.nx - 1);
+            if (inner && na <= nb) {
+              const int32_t *t = cell_start + (int64_t)blk * g.ncell + (z * g.ny + y) * g.nx;
+              j0 = t[na];
+              len = t[nb + 1] - j0;
+            }
+            // the padded cells over the native grid hold no ghosts
+            more = !inner || a < 0 || a_end >= g.nx;
+          } else {
+            const int32_t *t = gcell_start + (int64_t)blk * g.pncell +
+                               ((z + g.goff[2]) * g.pny + (y + g.goff[1])) * g.pnx + g.goff[0];
+            j0 = t[a];
+            len = t[a_end + 1] - j0;
+            more = false;
+          }
+        } else {
+          int qx, qy, qz;
+          const int wz = wrap_cell(z, g.nz, &qz), wy = wrap_cell(y, g.ny, &qy);
+          const int32_t *t = cell_start + (int64_t)blk * g.ncell + (wz * g.ny + wy) * g.nx;
+          const int wa = wrap_cell(a, g.nx, &qx);
+          const int b = min(a_end, (qx + 1) * g.nx - 1);
+          j0 = t[wa];
+          len = t[b - qx * g.nx + 1] - j0;
+          a = b + 1;
+          more = a <= a_end;
+          code = ((qx & 1023) << 20) | ((qy & 1023) << 10) | (qz & 1023);
+        }
+      }
+      int end = len;  // inclusive prefix sum over the group
+#pragma unroll
+      for (int o = 1; o < G; o <<= 1) {
+        const int t = __shfl_up(end, o, G);
+        if (sub >= o) end += t;
+      }
+      const int start = end - len, total = __shfl(end, G - 1, G);
+      if (total == 0) {
+        listed(0, 0);
+        continue;
+      }
+      const uint64_t some = group_ballot<G>(len > 0);
+      const bool shifted = !GHOST && group_ballot<G>(code != 0) != 0;
+      if (len > 0) {
+        const int rank = __popcll(some & ((1ull << sub) - 1ull));
+        T.base[rank] = j0 - start;
+        T.code[rank] = code << 1 | blk;
+      }
+      for (int c0 = 0; c0 < total; c0 += CH) {
+        if (sub < CH / 32) T.starts[sub] = 0;
+        wave_sync();
+        if (len > 0 && start >= c0 && start < c0 + CH)
+          atomicOr(&T.starts[(start - c0) >> 5], 1u << ((start - c0) & 31));
+        wave_sync();
+        int seen = c0 ? __popcll(group_ballot<G>(len > 0 && start < c0)) : 0;
+        const int cnt = min(CH, total - c0);
+        for (int k0 = 0; k0 < cnt; k0 += G) {
+          uint64_t bits;
+          if (G == 64) bits = (uint64_t)T.starts[k0 >> 5] | ((uint64_t)T.starts[(k0 >> 5) + 1] << 32);
+          else bits = (T.starts[k0 >> 5] >> (k0 & 31)) & (uint32_t)((1ull << (G & 63)) - 1ull);
+          const bool ok = k0 + sub < cnt;
+          // rows started up to and including this place; past the end any row serves
+          const int r = ok ? seen + __popcll(bits & ((2ull << sub) - 1ull)) - 1 : 0;
+          seen += __popcll(bits);
+          const int j = T.base[r] + (ok ? c0 + k0 + sub : 0);
+          const int cd = T.code[r];
+          const double4 p = GHOST && pass ? gxq[j] : xq[j];
+          double dx = pi.x - p.x, dy = pi.y - p.y, dz = pi.z - p.z;
+          if (shifted) {
+            dx -= (double)(bits10(cd, 21)) * g.L[0];
+            dy -= (double)(bits10(cd, 11)) * g.L[1];
+            dz -= (double)(bits10(cd, 1)) * g.L[2];
+          }
+          visit(ok, k0 + sub, cd & 1, GHOST && pass ? nnat + j : j, p, dx, dy, dz, sq_dist(dx, dy, dz));
+        }
+        wave_sync();
+        const int first = max(start - c0, 0);
+        listed(first, max(0, min(end - c0, cnt) - first));
+        wave_sync();
+      }
+    }
+    rows_end(min(G, rows - r0));
+  }
+}
+
+// Ordered sums of the FP32C form in a group walk: the terms of a chunk are
+// left in LDS by the lanes that evaluated them, each row's are then added in
+// order by the lane of that row, and the rows' sums by every lane (flush_rows):
+// the same bits as one thread walking the rows one after another.
+template <int G>
+struct GroupTerms {
+  float4 t[kGroupList<G>];  // pair scalar and displacement
+};
 
 // Accumulator of the per-particle force in the two precision forms.
 // add<true> evaluates Coulomb + LJ, add<false> LJ only (j neutral); TABLE
@@ -394,6 +595,11 @@ struct ForceAcc<false> {
     v[2] = fma(sc, dz, v[2]);
   }
   __device__ inline double get(int k) const { return v[k]; }
+  // the sum over the lanes of a group
+  template <int G>
+  __device__ inline double total(int k) const {
+    return group_sum<G>(v[k]);
+  }
   // the thread-form walks: same as add (FP64 sums need no row partials)
   template <bool COUL, bool TABLE = false>
   __device__ inline void add_row(const PairParams &pp, const PairF32 &pf, double r2, double qi, double qj, double dx,
@@ -422,6 +628,27 @@ struct ForceAcc<true> {
       p[c] = 0.f;
     }
   }
+  // a row's terms of one chunk of a group walk, in order
+  __device__ inline void add_terms(const float4 *t, int n) {
+#pragma unroll 4
+    for (int u = 0; u < n; ++u) {
+      const float4 v = t[u];
+      p[0] = fmaf(v.x, v.y, p[0]);
+      p[1] = fmaf(v.x, v.z, p[1]);
+      p[2] = fmaf(v.x, v.w, p[2]);
+    }
+  }
+  // the sums of the group's rows, in order (every lane holds the total)
+  template <int G>
+  __device__ inline void flush_rows(int rows) {
+    for (int r = 0; r < rows; ++r)
+      for (int c = 0; c < 3; ++c) k.add(c, __shfl(p[c], r, G));
+    for (int c = 0; c < 3; ++c) p[c] = 0.f;
+  }
+  template <int G>
+  __device__ inline double total(int c) const {
+    return k.get(c);
+  }
   template <bool COUL, bool TABLE = false>
   __device__ inline void add(const PairParams &pp, const PairF32 &pf, double r2, double qi, double qj, double dx,
                              double dy, double dz) {
@@ -432,6 +659,69 @@ struct ForceAcc<true> {
   }
   __device__ inline double get(int c) const { return k.get(c); }
 };
+
+// Lanes per particle of the plain sums of `count` particles: 64 or 32 (group
+// walk), or 1 (thread form). One thread each leaves the chip nearly idle below
+// a few hundred thousand particles: its time is then that of one particle's
+// walk. Measured on one MI355X, thread form against 64 and 32 lanes, in us:
+// charged FP64 (r = 6, 8): 1,000 particles 393, 11, 22; 25,000: 410, 86, 88;
+// 100,000: 536, 312, 295; 200,000: 860, 581, 518; 800,000: 2084, 2211, 1945
+// (10 % charged, 80,000: 294, 224, 187 and ten times that many 1280, -, 1850:
+// hence the line). Neutral FP64 (LJ only): 45,000: 77, 77, 54; 100,000: 82,
+// 151, 98. FP32C: 25,000: 283, 91, 81; 100,000: 318, 322, 265; 80,000 of a
+// sparse kind: 150, 239, 160.
+__host__ __device__ inline int64_t group_most(bool f32, bool charged) { return !f32 && charged ? 262144 : 65536; }
+__host__ __device__ inline int group_lanes(bool f32, bool charged, int64_t count) {
+  return count <= 8192 ? 64 : count <= group_most(f32, charged) ? 32 : 1;
+}
+// Blocks of a group launch over up to `most` particles (each block takes a
+// run of consecutive ones; enough for several waves per SIMD, and few enough
+// that a launch whose part turns out empty or large ends in about 4 us).
+inline unsigned group_blocks(int64_t most, int lanes) {
+  const int64_t nb = (most * lanes + 255) / 256;
+  return (unsigned)(nb < 4096 ? nb : 4096);
+}
+
+// Plain sums of particle i by its group: charged i against the charged block
+// out to max(r_coul, r_lj) and the neutral block out to r_lj, neutral i
+// against both out to r_lj; coulomb: the screened Coulomb terms alone.
+// tested(coul, r^2) is called for every candidate but i.
+template <bool F32, bool GHOST, int G, class Tested>
+__device__ inline void group_sums(const PairParams &pp, const PairF32 &pf, const Grid &g, const Sten &s_coul,
+                                  const Sten &s_lj, const int32_t *__restrict__ cell_start,
+                                  const double4 *__restrict__ xq, const int32_t *__restrict__ gcell_start,
+                                  const double4 *__restrict__ gxq, int nnat, int i, const double4 &pi, bool coulomb,
+                                  GroupRows<G> &rows, float4 *terms, ForceAcc<F32> &acc, Tested &&tested) {
+  const double qi = pi.w;
+  const bool charged = qi != 0.0;
+  const Block near_lj = pp.do_lj ? Block{s_lj, pp.rlj2} : no_block();
+  const Block A = coulomb ? Block{s_coul, pp.rc2}
+                  : !charged ? near_lj
+                  : pp.do_coul || pp.do_lj ? Block{s_coul, pp.rq2}
+                                           : no_block();
+  const Block B = coulomb ? no_block() : near_lj;
+  group_walk<G, GHOST>(
+      g, cell_start, xq, gcell_start, gxq, nnat, pi, A, B, rows,
+      [&](bool ok, int k, int blk, int j, const double4 &pj, double dx, double dy, double dz, double r2) {
+        const bool coul = charged && blk == 0;  // every other pairing: LJ only
+        const bool in = ok & (j != i) & (r2 <= (coul ? A.r2 : pp.rlj2));
+        if (ok & (j != i)) tested(coul, r2);
+        if constexpr (F32) {
+          float sc = 0.f;
+          if (in) sc = coul ? pair_scalar_f32(pp, pf, r2, (float)(qi * pj.w)) : pair_scalar_lj_f32(pp, pf, r2);
+          terms[k] = in ? make_float4(sc, (float)dx, (float)dy, (float)dz) : make_float4(0.f, 0.f, 0.f, 0.f);
+        } else if (in) {
+          if (coul) acc.template add<true>(pp, pf, r2, qi, pj.w, dx, dy, dz);
+          else acc.template add<false>(pp, pf, r2, qi, pj.w, dx, dy, dz);
+        }
+      },
+      [&](int first, int len) {
+        if constexpr (F32) acc.add_terms(terms + first, len);
+      },
+      [&](int n) {
+        if constexpr (F32) acc.template flush_rows<G>(n);
+      });
+}
 
 }  // namespace rbe
 

@@ -73,6 +73,7 @@ struct Grid {
   int ncell;          // nx * ny * nz (keys run over 2 * ncell: charged, then neutral)
   double L[3];        // box
   double inv_h[3];    // n_d / L_d (cell scale used by the binning key)
+  double h[3];        // cell edges L_d / n_d
   // ghost shell (ghost_width > 0): the padded grid extends the native grid by
   // goff[d] cells on both sides; cell c of the native grid is padded cell
   // c + goff[d]. Zero layers without a ghost shell.
