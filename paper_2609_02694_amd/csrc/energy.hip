@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(kEnergyThreads) k_energy_near(PairParams pp, d
       }
     };
     group_walk<G, false>(g, cell_start, xq, nullptr, nullptr, 0, pi4, qi != 0.0 ? Block{pp.s_coul, pp.rq2} : near_lj,
-                         near_lj, rows[threadIdx.x / G], visit, [](int, int) {}, [](int) {});
+                         near_lj, rows[threadIdx.x / G], visit, [](int, int) {}, [](uint64_t) {});
   }
   uc *= 0.5;
   ul *= 0.5 * lj4;

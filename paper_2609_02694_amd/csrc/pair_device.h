@@ -440,8 +440,8 @@ __device__ inline void wave_sync() {
 // visit(ok, k, blk, j, p_j, dx, dy, dz, r^2) is called by the whole group; k
 // is the place in the listed chunk of kGroupList<G> (ok false: nothing there).
 // listed(first, len) follows each chunk: this lane's row holds the places
-// [first, first + len) of it (len may be 0). rows_end(k) follows each round of
-// G rows, of which the last may hold fewer (k).
+// [first, first + len) of it (len may be 0). rows_end(reached) follows each
+// round of G rows: the lanes whose rows the particle's reach touches.
 // GHOST: no periodic images, but the ghost arrays (indexed from nnat on).
 template <int G, bool GHOST, class Visit, class Listed, class RowsEnd>
 __device__ inline void group_walk(const Grid &g, const int32_t *__restrict__ cell_start,
@@ -480,6 +480,7 @@ __device__ inline void group_walk(const Grid &g, const int32_t *__restrict__ cel
     // a row's records lie in one piece, or in several: the pieces of a row that
     // crosses the box edge, the natives and the ghosts of one at the edge
     bool more = a <= a_end;
+    const uint64_t reached = group_ballot<G>(more);
     for (int pass = 0; group_ballot<G>(more); ++pass) {
       int j0 = 0, len = 0, code = 0;
       if (more) {
@@ -565,7 +566,7 @@ __device__ inline void group_walk(const Grid &g, const int32_t *__restrict__ cel
         wave_sync();
       }
     }
-    rows_end(min(G, rows - r0));
+    rows_end(reached);
   }
 }
 
@@ -638,11 +639,11 @@ struct ForceAcc<true> {
       p[2] = fmaf(v.x, v.w, p[2]);
     }
   }
-  // the sums of the group's rows, in order (every lane holds the total)
+  // the sums of the group's rows in `rows` (bits), in order (every lane holds the total)
   template <int G>
-  __device__ inline void flush_rows(int rows) {
-    for (int r = 0; r < rows; ++r)
-      for (int c = 0; c < 3; ++c) k.add(c, __shfl(p[c], r, G));
+  __device__ inline void flush_rows(uint64_t rows) {
+    for (; rows; rows &= rows - 1)
+      for (int c = 0; c < 3; ++c) k.add(c, __shfl(p[c], __ffsll((long long)rows) - 1, G));
     for (int c = 0; c < 3; ++c) p[c] = 0.f;
   }
   template <int G>
@@ -718,8 +719,8 @@ __device__ inline void group_sums(const PairParams &pp, const PairF32 &pf, const
       [&](int first, int len) {
         if constexpr (F32) acc.add_terms(terms + first, len);
       },
-      [&](int n) {
-        if constexpr (F32) acc.template flush_rows<G>(n);
+      [&](uint64_t reached) {
+        if constexpr (F32) acc.template flush_rows<G>(reached);
       });
 }
 
