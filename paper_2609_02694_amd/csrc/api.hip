@@ -409,6 +409,8 @@ extern "C" int rbe_create(rbe_ctx **out, const rbe_params *p, int64_t n_max, int
   c->srt.xq = b.alloc<double4>(n_max + kScanPad);
   c->srt.sq = b.alloc<double4>(n_max);
   c->srt.id = b.alloc<int32_t>(n_max + kScanPad);
+  if (p->prec == RBE_FP64) c->srt.pk = b.alloc<uint2>(n_max + kScanPad);
+  c->srt.pk_scale = pack_scale(std::fmax(p->r_coul, p->r_lj));
   for (int s = 0; s < 2; ++s) {
     WorkSet &w = c->ws[s];
     w.x = b.alloc<double>(n_max);
@@ -459,6 +461,7 @@ extern "C" int rbe_create(rbe_ctx **out, const rbe_params *p, int64_t n_max, int
     const int64_t pkeys = 2 * (int64_t)g.pncell;
     gb.xq = b.alloc<double4>(cap + kScanPad);
     gb.id = b.alloc<int32_t>(cap + kScanPad);
+    if (p->prec == RBE_FP64) gb.pk = b.alloc<uint2>(cap + kScanPad);
     gb.cell_start = b.alloc<int32_t>(pkeys + 1);
     gb.cell_count = b.alloc<int32_t>(pkeys);
     gb.cell_scan_tmp = b.alloc<int32_t>(scan_tiles(pkeys));
@@ -605,6 +608,8 @@ extern "C" int rbe_create_batch(rbe_ctx **out, int32_t n_sys, const rbe_params *
   c->srt.xq = b.alloc<double4>(n + kScanPad);
   c->srt.sq = b.alloc<double4>(n);
   c->srt.id = b.alloc<int32_t>(n + kScanPad);
+  if (c->p.prec == RBE_FP64) c->srt.pk = b.alloc<uint2>(n + kScanPad);
+  c->srt.pk_scale = pack_scale(std::fmax(c->p.r_coul, c->p.r_lj));
   c->perm = b.alloc<int32_t>(n);
   c->cell_start = b.alloc<int32_t>(B.nkeys + 1);
   c->cdf_dev = b.alloc<double>((int64_t)cdf_all.size());
@@ -952,6 +957,10 @@ static BatchArgs batch_args(rbe_ctx *c, int mode) {
   a.xq = c->srt.xq;
   a.sq = c->srt.sq;
   a.sid = c->srt.id;
+  a.pk = c->srt.pk;
+  a.pk_scale = c->srt.pk_scale;
+  a.t2_q = pack_reach2(std::sqrt(c->pp.rq2), a.pk_scale);
+  a.t2_lj = pack_reach2(std::sqrt(c->pp.rlj2), a.pk_scale);
   a.key = B.key;
   a.slot = B.slot;
   a.tmp = B.tmp;
@@ -1262,9 +1271,7 @@ extern "C" int rbe_energy(rbe_ctx *c, const rbe_state *s, const int32_t *m, cons
 // With inv (random batch list), also the id -> slot map: inv[id] = k for ids
 // inside [0, n) (the ids were validated by the call's first evaluation).
 __global__ void __launch_bounds__(256) k_reorder_pack(int64_t n, const int32_t *__restrict__ perm, StateArrays in,
-                                                      StateArrays out, Grid g, double4 *__restrict__ xq,
-                                                      double4 *__restrict__ sq, int32_t *__restrict__ ids,
-                                                      int32_t *__restrict__ inv) {
+                                                      StateArrays out, Grid g, Sorted s, int32_t *__restrict__ inv) {
   const int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (k >= n) return;
   const int j = perm[k];
@@ -1279,9 +1286,10 @@ __global__ void __launch_bounds__(256) k_reorder_pack(int64_t n, const int32_t *
   out.vz[k] = in.vz[j];
   out.q[k] = q;
   out.id[k] = id;
-  xq[k] = make_double4(x, y, z, q);
-  if (q != 0.0) sq[k] = make_double4(x / g.L[0], y / g.L[1], z / g.L[2], q);
-  ids[k] = id;
+  s.xq[k] = make_double4(x, y, z, q);
+  if (q != 0.0) s.sq[k] = make_double4(x / g.L[0], y / g.L[1], z / g.L[2], q);
+  s.id[k] = id;
+  if (s.pk) s.pk[k] = pack_position(x, y, z, s.pk_scale);
 }
 
 extern "C" int rbe_step(rbe_ctx *c, rbe_state *s, int32_t nsteps, uint64_t first_eval, void *stream) {
@@ -1354,7 +1362,7 @@ extern "C" int rbe_step(rbe_ctx *c, rbe_state *s, int32_t nsteps, uint64_t first
       // of the random batch list (the first step's evaluation validates ids)
       int32_t *inv = (k > 0 && c->pp.rbl && near) ? c->inv_id : nullptr;
       k_reorder_pack<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(n, c->perm, A->arrays(), B->arrays(), c->g,
-                                                                   c->srt.xq, c->srt.sq, c->srt.id, inv);
+                                                                   c->srt, inv);
     }
     const int64_t P = c->p.P;
     // a fixed table (rbe_set_modes) sits in slot 0 and is never redrawn

@@ -97,43 +97,6 @@ __device__ inline int block_scan_excl(int v, int *lds, int *total) {
   return off + incl - v;
 }
 
-// Plain near-field sums of one particle (no random batch list, no ghosts),
-// one thread walking the stencil rows of its own cell in its replica.
-template <bool F32>
-__device__ inline void batch_pair(const BatchArgs &a, const RepDesc &R, int64_t i, ForceAcc<F32> &acc) {
-  const Grid &g = R.g;
-  const PairParams &pp = a.pp;
-  const double4 pi4 = a.xq[i];
-  const double xi = pi4.x, yi = pi4.y, zi = pi4.z, qi = pi4.w;
-  const int cx = cell_coord(xi, g.inv_h[0], g.nx);
-  const int cy = cell_coord(yi, g.inv_h[1], g.ny);
-  const int cz = cell_coord(zi, g.inv_h[2], g.nz);
-  auto visit_q = [&](int j, const double4 &pj, double shx, double shy, double shz) {
-    const double dx = (xi - pj.x) - shx, dy = (yi - pj.y) - shy, dz = (zi - pj.z) - shz;
-    const double r2 = sq_dist(dx, dy, dz);
-    if (r2 == 0.0 && j == (int)i) return;
-    if (r2 <= pp.rq2) acc.template add_row<true>(pp, a.pf, r2, qi, pj.w, dx, dy, dz);
-  };
-  auto visit_lj = [&](int j, const double4 &pj, double shx, double shy, double shz) {
-    const double dx = (xi - pj.x) - shx, dy = (yi - pj.y) - shy, dz = (zi - pj.z) - shz;
-    const double r2 = sq_dist(dx, dy, dz);
-    if (r2 == 0.0 && j == (int)i) return;
-    if (r2 <= pp.rlj2) acc.template add_row<false>(pp, a.pf, r2, qi, pj.w, dx, dy, dz);
-  };
-  // FP32C: a row's terms summed plainly, the row sum added with Kahan compensation
-  auto row_end = [&]() { acc.flush_row(); };
-  auto walk = [&](int blk, const Sten &s, double r2, auto &&fn) {
-    for_stencil(g, a.cell_start, a.xq, blk, cx, cy, cz, s, xi, yi, zi, r2, fn, R.c0, row_end);
-  };
-  if (qi != 0.0) {
-    if (pp.do_coul || pp.do_lj) walk(0, R.s_coul, pp.rq2, visit_q);
-    if (pp.do_lj) walk(1, R.s_lj, pp.rlj2, visit_lj);
-  } else if (pp.do_lj) {
-    walk(0, R.s_lj, pp.rlj2, visit_lj);
-    walk(1, R.s_lj, pp.rlj2, visit_lj);
-  }
-}
-
 template <bool F32>
 __global__ void __launch_bounds__(kBatchThreads) k_batch_step(BatchArgs a) {
   __shared__ int lds[kBatchThreads / 64];
@@ -281,6 +244,7 @@ __global__ void __launch_bounds__(kBatchThreads) k_batch_step(BatchArgs a) {
       a.xq[k] = make_double4(x, y, z, q);
       if (q != 0.0) a.sq[k] = make_double4(x / R.g.L[0], y / R.g.L[1], z / R.g.L[2], q);
       a.sid[k] = id;
+      if (a.pk) a.pk[k] = pack_position(x, y, z, a.pk_scale);
     }
     grid_barrier(a.bar, a.err);
     return;
@@ -425,16 +389,94 @@ __global__ void __launch_bounds__(kBatchThreads) k_batch_step(BatchArgs a) {
 
 // The near field of every particle of the batch, between the two launches of
 // the step kernel: a plain launch, so that its occupancy is not bound to the
-// persistent kernel's registers. Four waves per SIMD in FP32C (no spills;
-// five, with 13 VGPRs spilled, ran no faster), three in FP64 (16 VGPRs
-// spilled, 11.0 against 12.1 ms per 256-replica step at two).
-template <bool F32>
-__global__ void __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(F32 ? 4 : 3)))
-k_batch_near(BatchArgs a) {
+// persistent kernel's registers.
+// FP32C: one thread per particle walking the stencil rows of its own cell in
+// its replica. Four waves per SIMD (no spills; five, with 13 VGPRs spilled,
+// ran no faster).
+__global__ void __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(4))) k_batch_near(BatchArgs a) {
   const int64_t i = blockIdx.x * (int64_t)kBatchThreads + threadIdx.x;
   if (i >= a.ntot) return;
-  ForceAcc<F32> acc;
-  if (a.pp.do_coul || a.pp.do_lj) batch_pair<F32>(a, a.reps[a.rep_of[i]], i, acc);
+  const RepDesc &R = a.reps[a.rep_of[i]];
+  const Grid &g = R.g;
+  const PairParams &pp = a.pp;
+  const double4 pi4 = a.xq[i];
+  const double xi = pi4.x, yi = pi4.y, zi = pi4.z, qi = pi4.w;
+  const int cx = cell_coord(xi, g.inv_h[0], g.nx);
+  const int cy = cell_coord(yi, g.inv_h[1], g.ny);
+  const int cz = cell_coord(zi, g.inv_h[2], g.nz);
+  ForceAcc<true> acc;
+  auto visit_q = [&](int j, const double4 &pj, double shx, double shy, double shz) {
+    const double dx = (xi - pj.x) - shx, dy = (yi - pj.y) - shy, dz = (zi - pj.z) - shz;
+    const double r2 = sq_dist(dx, dy, dz);
+    if (r2 == 0.0 && j == (int)i) return;
+    if (r2 <= pp.rq2) acc.template add_row<true>(pp, a.pf, r2, qi, pj.w, dx, dy, dz);
+  };
+  auto visit_lj = [&](int j, const double4 &pj, double shx, double shy, double shz) {
+    const double dx = (xi - pj.x) - shx, dy = (yi - pj.y) - shy, dz = (zi - pj.z) - shz;
+    const double r2 = sq_dist(dx, dy, dz);
+    if (r2 == 0.0 && j == (int)i) return;
+    if (r2 <= pp.rlj2) acc.template add_row<false>(pp, a.pf, r2, qi, pj.w, dx, dy, dz);
+  };
+  // a row's terms summed plainly, the row sum added with Kahan compensation
+  auto row_end = [&]() { acc.flush_row(); };
+  auto walk = [&](int blk, const Sten &s, double r2, auto &&fn) {
+    for_stencil(g, a.cell_start, a.xq, blk, cx, cy, cz, s, xi, yi, zi, r2, fn, R.c0, row_end);
+  };
+  if (qi != 0.0) {
+    if (pp.do_coul || pp.do_lj) walk(0, R.s_coul, pp.rq2, visit_q);
+    if (pp.do_lj) walk(1, R.s_lj, pp.rlj2, visit_lj);
+  } else if (pp.do_lj) {
+    walk(0, R.s_lj, pp.rlj2, visit_lj);
+    walk(1, R.s_lj, pp.rlj2, visit_lj);
+  }
+  a.ofx[i] = acc.get(0);
+  a.ofy[i] = acc.get(1);
+  a.ofz[i] = acc.get(2);
+}
+
+// FP64: one lane per particle, candidates filtered on packed positions
+// (pair_device.h, queue walks).
+__global__ void __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(4)))
+k_batch_near_queue(BatchArgs a) {
+  static_assert(kBatchThreads == kQueueThreads, "queue layout");
+  __shared__ uint32_t queue[kQueueCap * kQueueThreads];
+  const int64_t i = blockIdx.x * (int64_t)kBatchThreads + threadIdx.x;
+  const bool active = i < a.ntot;  // the whole wave takes part
+  const int64_t ia = active ? i : a.ntot - 1;
+  const RepDesc &R = a.reps[a.rep_of[ia]];
+  const PairParams &pp = a.pp;
+  const double4 pi = a.xq[ia];
+  const bool charged = pi.w != 0.0;
+  ForceAcc<false> acc;
+  HitQueue Q(queue);
+  const bool coded = a.ntot <= (1ll << kIndexBits);
+  auto one = [&](uint32_t e) {
+    const uint32_t code = coded ? e >> kIndexBits : Q.now;
+    const int j = (int)(coded ? e & ((1u << kIndexBits) - 1u) : e);
+    const double4 pj = a.xq[j];
+    double dx = pi.x - pj.x, dy = pi.y - pj.y, dz = pi.z - pj.z;
+    if (wave_count(code != kNoShift)) {
+      dx -= code_shift(code, 0) * R.g.L[0];
+      dy -= code_shift(code, 1) * R.g.L[1];
+      dz -= code_shift(code, 2) * R.g.L[2];
+    }
+    const double r2 = sq_dist(dx, dy, dz);
+    const bool coul = charged && pj.w != 0.0;
+    if ((r2 <= (coul ? pp.rq2 : pp.rlj2)) & (j != (int)i)) {
+      if (coul) acc.template add<true, true>(pp, a.pf, r2, pi.w, pj.w, dx, dy, dz);
+      else acc.template add<false>(pp, a.pf, r2, pi.w, pj.w, dx, dy, dz);
+    }
+  };
+  auto drain = [&](bool all) { drain_queue(Q, all, one); };
+  const bool far = charged && (pp.do_coul || pp.do_lj);
+  const bool some = far || pp.do_lj;
+  const int32_t *cs = a.cell_start + R.c0;
+  queue_walk<false>(R.g, cs, a.pk, nullptr, nullptr, 0, active && some, pi, far ? R.s_coul : R.s_lj,
+                    far ? pp.rq2 : pp.rlj2, far ? a.t2_q : a.t2_lj, a.pk_scale, coded, Q, [](int) {}, drain);
+  queue_walk<false>(R.g, cs + R.g.ncell, a.pk, nullptr, nullptr, 0, active && pp.do_lj, pi, R.s_lj, pp.rlj2, a.t2_lj,
+                    a.pk_scale, coded, Q, [](int) {}, drain);
+  drain(true);
+  if (!active) return;
   a.ofx[i] = acc.get(0);
   a.ofy[i] = acc.get(1);
   a.ofz[i] = acc.get(2);
@@ -476,7 +518,7 @@ static BatchKernel batch_near_kernel(int prec, int64_t ntot, unsigned *blocks) {
     return prec == RBE_FP32C ? k_batch_near_group<true, 32> : k_batch_near_group<false, 32>;
   }
   *blocks = (unsigned)((ntot + kBatchThreads - 1) / kBatchThreads);
-  return prec == RBE_FP32C ? k_batch_near<true> : k_batch_near<false>;
+  return prec == RBE_FP32C ? k_batch_near : k_batch_near_queue;
 }
 
 int batch_grid_blocks(int prec, int device) {

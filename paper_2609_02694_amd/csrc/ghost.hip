@@ -53,8 +53,8 @@ __global__ void __launch_bounds__(256) k_ghost_cell_counts(Grid g, const int32_t
 __global__ void __launch_bounds__(256) k_ghost_fill(Grid g, int64_t cap, const int32_t *__restrict__ cell_start,
                                                     const double4 *__restrict__ xq, const int32_t *__restrict__ ids,
                                                     int32_t *__restrict__ gstart, double4 *__restrict__ gxq,
-                                                    int32_t *__restrict__ gid, int32_t *__restrict__ gcount,
-                                                    int *err) {
+                                                    int32_t *__restrict__ gid, uint2 *__restrict__ gpk,
+                                                    double pk_scale, int32_t *__restrict__ gcount, int *err) {
   const int64_t key = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int64_t nkeys = 2 * (int64_t)g.pncell;
   if (key > nkeys) return;
@@ -76,6 +76,7 @@ __global__ void __launch_bounds__(256) k_ghost_fill(Grid g, int64_t cap, const i
       const double4 r = xq[j];
       gxq[d] = make_double4(r.x + sx, r.y + sy, r.z + sz, r.w);
       gid[d] = ids[j];
+      if (gpk) gpk[d] = pack_position(r.x + sx, r.y + sy, r.z + sz, pk_scale);
     }
   }
   gstart[key] = (int32_t)(d0 < cap ? d0 : cap);
@@ -89,7 +90,7 @@ void launch_build_ghosts(const Grid &g, int64_t n, const int32_t *cell_start, co
   k_ghost_cell_counts<<<blocks, 256, 0, st>>>(g, cell_start, gb.cell_count);
   launch_exclusive_scan(gb.cell_count, nkeys, gb.cell_start, gb.cell_scan_tmp, st);
   k_ghost_fill<<<(unsigned)((nkeys + 1 + 255) / 256), 256, 0, st>>>(g, gb.cap, cell_start, s.xq, s.id, gb.cell_start,
-                                                                    gb.xq, gb.id, gb.count, err);
+                                                                    gb.xq, gb.id, gb.pk, s.pk_scale, gb.count, err);
 }
 
 }  // namespace rbe

@@ -9,22 +9,22 @@ __global__ void __launch_bounds__(256) k_gather_sorted(int64_t n, const int32_t 
                                                        const double *__restrict__ x, const double *__restrict__ y,
                                                        const double *__restrict__ z, const double *__restrict__ q,
                                                        const int32_t *__restrict__ id, Grid g,
-                                                       double4 *__restrict__ xq, double4 *__restrict__ sq,
-                                                       int32_t *__restrict__ ids) {
+                                                       Sorted s) {
   const int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (k >= n) return;
   const int j = perm[k];
   const double wx = wrap_coord(x[j], g.L[0]), wy = wrap_coord(y[j], g.L[1]), wz = wrap_coord(z[j], g.L[2]);
   const double qq = q[j];
-  xq[k] = make_double4(wx, wy, wz, qq);
-  if (qq != 0.0) sq[k] = make_double4(wx / g.L[0], wy / g.L[1], wz / g.L[2], qq);
-  if (id) ids[k] = id[j];
+  s.xq[k] = make_double4(wx, wy, wz, qq);
+  if (qq != 0.0) s.sq[k] = make_double4(wx / g.L[0], wy / g.L[1], wz / g.L[2], qq);
+  if (id) s.id[k] = id[j];
+  if (s.pk) s.pk[k] = pack_position(wx, wy, wz, s.pk_scale);
 }
 
 void launch_gather_sorted(int64_t n, const int32_t *perm, const double *x, const double *y, const double *z,
                           const double *q, const int32_t *id, const Grid &g, Sorted s, hipStream_t st) {
   if (n <= 0) return;
-  k_gather_sorted<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(n, perm, x, y, z, q, id, g, s.xq, s.sq, s.id);
+  k_gather_sorted<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(n, perm, x, y, z, q, id, g, s);
 }
 
 // inv must hold -1 everywhere on entry. Ids outside [0, n) and repeated ids

@@ -33,11 +33,34 @@ void launch_bin_place(const BinBuffers &b, const Grid &g, int64_t n, int32_t *ce
 //   xq[i] = (x, y, z, q) wrapped coordinates (near field)
 //   sq[i] = (x/L_x, y/L_y, z/L_z, q) fractional coordinates (Fourier part,
 //           only the charged range [0, nq) is used)
+//   pk[i] = packed 16-bit positions (pack_position), the candidates of the
+//           FP64 queue walks; nullptr in FP32C and in the scratch-only form,
+//           whose sizes take other walks.
 struct Sorted {
   double4 *xq;
   double4 *sq;
   int32_t *id;
+  uint2 *pk;
+  double pk_scale;
 };
+
+// Positions on a 16-bit grid per axis, modulo its period: x | y << 16, z.
+// `scale` is 1 / period, the period four times the largest reach, so that a
+// difference of two packed coordinates (mod 2^16, signed) is that of the
+// positions in grid units to within one unit whenever the positions are less
+// than half a period apart, and whatever the box. Farther pairs alias, at
+// worst to a candidate that the exact test then rejects.
+__host__ __device__ inline double pack_scale(double reach) { return 0.25 / reach; }
+__device__ inline uint2 pack_position(double x, double y, double z, double scale) {
+  auto one = [&](double v) { return (uint32_t)(__builtin_amdgcn_fract(v * scale) * 65536.0) & 0xFFFFu; };
+  return make_uint2(one(x) | (one(y) << 16), one(z));
+}
+// Squared reach in grid units that no pair inside r exceeds: each coordinate
+// difference is off by less than one unit, the distance by less than sqrt 3.
+__host__ __device__ inline uint32_t pack_reach2(double r, double scale) {
+  const double g = r * scale * 65536.0 + 1.75;
+  return (uint32_t)(g * g) + 1u;
+}
 // Gather the caller's arrays through perm into the packed sorted records
 // (id may be nullptr: then s.id is left as it is).
 void launch_gather_sorted(int64_t n, const int32_t *perm, const double *x, const double *y, const double *z,
@@ -55,6 +78,7 @@ struct GhostBuffers {
   int64_t cap;             // ghost capacity
   double4 *xq;             // [cap + kScanPad] ghost records in padded cell order
   int32_t *id;             // [cap + kScanPad] ids of their natives
+  uint2 *pk;               // [cap + kScanPad] packed positions (FP64)
   int32_t *cell_start;     // [2 * pncell + 1] first ghost of every padded key (clamped to cap)
   int32_t *cell_count;     // [2 * pncell]
   int32_t *cell_scan_tmp;  // [scan_tiles(2 * pncell)]
@@ -315,6 +339,9 @@ struct BatchArgs {
   int32_t *oid;
   double *cfx, *cfy, *cfz;  // force-only mode: output in the caller's order
   double4 *xq, *sq;
+  uint2 *pk;                // packed positions (FP64; nullptr in FP32C)
+  double pk_scale;
+  uint32_t t2_q, t2_lj;     // squared reaches in their units
   int32_t *sid;
   int32_t *key, *slot, *tmp, *perm, *count, *cell_start, *tile_sum;
   const double *cdf;

@@ -32,6 +32,7 @@
 //   G(r)    = erfc(sqrt(a) r)/r^3 + 2 sqrt(a) exp(-a r^2)/(sqrt(pi) r^2),
 //   G_LJ(r) = 24 eps (2 sigma^12/r^14 - sigma^6/r^8).
 #include <algorithm>
+#include <type_traits>
 
 #include "pair_device.h"
 
@@ -55,6 +56,11 @@ struct PairCtx {
   const double4 *__restrict__ gxq;
   const int32_t *__restrict__ gid;
   const int32_t *__restrict__ gcell_start;
+  // packed positions of both, and the squared reaches in their units (FP64)
+  const uint2 *__restrict__ pk;
+  const uint2 *__restrict__ gpk;
+  double pk_scale;
+  uint32_t t2_q, t2_lj;  // max(r_coul, r_lj), r_lj
 };
 
 // Cluster walk of one species block for a row group.
@@ -143,13 +149,15 @@ __device__ inline void stencil(const PairCtx &c, int blk, int cx, int cy, int cz
 // (charged block out to max(r_coul, r_lj), neutral block out to r_lj); MODE
 // 2: charged i, screened Coulomb terms only (charged block out to r_coul),
 // added to f, which holds the LJ terms of the tile pass.
-// Occupancy asked of the compiler: FP32 forms five (charged) or six
-// (neutral) waves per SIMD, the most without spills once a row's partial
-// sums are held; FP64 forms three or seven (measured best; the FP64 charged
-// form spills at four).
-template <bool F32, bool COUNT, int MODE, bool GHOST>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(F32 ? (MODE ? 5 : 6) : (MODE ? 3 : 7))))
+// The FP32C form: its pair terms are cheap beside a queue entry's fetch, so
+// it evaluates each candidate where it finds it (6M ions 6.4 ms, as a queue
+// walk 7.4; the FP64 form 12.3 and 9.8).
+// Occupancy asked of the compiler: five (charged) or six (neutral) waves per
+// SIMD, the most without spills once a row's partial sums are held.
+template <bool COUNT, int MODE, bool GHOST>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE ? 5 : 6)))
 k_pair_plain(PairCtx c) {
+  constexpr bool F32 = true;
   static_assert(MODE >= 0 && MODE <= 2, "mode");
   const int64_t nq = *c.nq_ptr;
   if (group_lanes(F32, MODE, MODE ? nq : c.n - nq) > 1) return;  // too few particles: k_pair_group
@@ -213,6 +221,75 @@ k_pair_plain(PairCtx c) {
   flush_counts<COUNT>(c, n_coul, n_lj, n_tested, 0);
 }
 
+// The FP64 form, one lane per particle (pair_device.h, queue walks), MODE 0
+// and 1 as above. Bound by the issue of the FP64 pair terms and by the gather
+// of the queued records. Against one thread evaluating each candidate as it
+// meets it, 6M particles: ions 12.3 -> 9.8 ms, half-charged fluid 6.6 -> 5.5
+// and (neutral part) 1.20 -> 1.05 ms, 10 % charged with ghosts 1.02 -> 0.86
+// and 2.32 -> 1.97 ms.
+template <bool COUNT, int MODE, bool GHOST>
+__global__ void __launch_bounds__(kQueueThreads) __attribute__((amdgpu_waves_per_eu(4))) k_pair_queue(PairCtx c) {
+  constexpr bool F32 = false;
+  static_assert(MODE == 0 || MODE == 1, "mode");
+  __shared__ uint32_t queue[kQueueCap * kQueueThreads];
+  const int64_t nq = *c.nq_ptr;
+  if (group_lanes(F32, MODE, MODE ? nq : c.n - nq) > 1) return;  // too few particles: k_pair_group
+  int64_t first, end;
+  if (!part_block(c, blockDim.x, &first, &end)) return;
+  const int64_t i = first + threadIdx.x;
+  const bool active = i < end;  // the whole wave takes part
+  const PairParams &pp = c.pp;
+  const Grid &g = pp.g;
+  const double4 pi = c.xq[active ? i : end - 1];
+  ForceAcc<F32> acc;
+  unsigned long long n_coul = 0, n_lj = 0, n_tested = 0;
+  HitQueue Q(queue);
+  const bool coded = c.n <= (1ll << kIndexBits);
+  // an entry: the record, its exact classification, the pair term (COUL:
+  // Coulomb and LJ; else LJ only)
+  auto one = [&](uint32_t e, auto coul) {
+    constexpr bool COUL = decltype(coul)::value;
+    const uint32_t code = GHOST ? kNoShift : coded ? e >> kIndexBits : Q.now;
+    const int j = (int)(GHOST || !coded ? e : e & ((1u << kIndexBits) - 1u));
+    const double4 pj = GHOST && j >= c.n ? c.gxq[j - c.n] : c.xq[j];
+    double dx = pi.x - pj.x, dy = pi.y - pj.y, dz = pi.z - pj.z;
+    if (!GHOST && wave_count(code != kNoShift)) {
+      dx -= code_shift(code, 0) * g.L[0];
+      dy -= code_shift(code, 1) * g.L[1];
+      dz -= code_shift(code, 2) * g.L[2];
+    }
+    const double r2 = sq_dist(dx, dy, dz);
+    if ((r2 <= (COUL ? pp.rq2 : pp.rlj2)) & (j != (int)i)) {  // ghosts are indexed from n on
+      acc.template add<COUL, true>(pp, c.pf, r2, pi.w, pj.w, dx, dy, dz);
+      if (COUNT) {
+        n_coul += (COUL && pp.do_coul && r2 <= pp.rc2);
+        n_lj += (pp.do_lj && r2 <= pp.rlj2);
+      }
+    }
+  };
+  auto tested = [&](int len) {
+    if (COUNT) n_tested += len;
+  };
+  auto walk = [&](auto coul, int blk, const Sten &s, double r2, uint32_t t2) {
+    auto drain = [&](bool all) { drain_queue(Q, all, [&](uint32_t e) { one(e, coul); }); };
+    queue_walk<GHOST>(g, c.cell_start + (int64_t)blk * g.ncell, c.pk,
+                      GHOST ? c.gcell_start + (int64_t)blk * g.pncell : nullptr, c.gpk, (int)c.n, active, pi, s, r2,
+                      t2, c.pk_scale, coded, Q, tested, drain);
+    drain(true);
+  };
+  constexpr std::true_type coul_lj{};
+  constexpr std::false_type lj_only{};
+  if (MODE == 1) walk(coul_lj, 0, pp.s_coul, pp.rq2, c.t2_q);
+  else if (pp.do_lj) walk(lj_only, 0, pp.s_lj, pp.rlj2, c.t2_lj);
+  if (pp.do_lj) walk(lj_only, 1, pp.s_lj, pp.rlj2, c.t2_lj);
+  if (active) {
+    c.fx[i] = acc.get(0);
+    c.fy[i] = acc.get(1);
+    c.fz[i] = acc.get(2);
+  }
+  flush_counts<COUNT>(c, n_coul, n_lj, n_tested, 0);
+}
+
 // Plain cutoff sums of particles too few to fill the chip with one thread
 // each: G lanes share one (pair_device.h, group walks). c.charged: 1 the
 // charged range, 0 the neutral one, 2 both; coulomb: the charged range's
@@ -226,7 +303,7 @@ __global__ void __launch_bounds__(256) k_pair_group(PairCtx c, int coulomb) {
   __shared__ GroupTerms<F32 ? G : 1> terms[256 / G];
   const int64_t nq = *c.nq_ptr;
   const int64_t a = c.charged ? 0 : nq, end = c.charged == 1 ? nq : c.n;
-  if (group_lanes(F32, c.charged, end - a) == 1) return;  // enough particles: k_pair_plain
+  if (group_lanes(F32, c.charged, end - a) == 1) return;  // enough particles: k_pair_plain or k_pair_queue
   const int64_t per = (end - a + gridDim.x - 1) / gridDim.x;  // consecutive particles per block
   const int64_t first = a + blockIdx.x * per, last = min(end, first + per);
   const PairParams &pp = c.pp;
@@ -431,7 +508,10 @@ static void launch_plain(PairCtx c, hipStream_t st) {
     k_pair_group<F32, COUNT, GHOST, 64><<<group_blocks(most, 64), 256, 0, st>>>(c, MODE == 2);
   else
     k_pair_group<F32, COUNT, GHOST, 32><<<group_blocks(most, 32), 256, 0, st>>>(c, MODE == 2);
-  if (lanes == 1) k_pair_plain<F32, COUNT, MODE, GHOST><<<(unsigned)((c.n + 255) / 256), 256, 0, st>>>(c);
+  if (lanes > 1) return;
+  const unsigned blocks = (unsigned)((c.n + 255) / 256);
+  if constexpr (F32) k_pair_plain<COUNT, MODE, GHOST><<<blocks, 256, 0, st>>>(c);
+  else k_pair_queue<COUNT, MODE, GHOST><<<blocks, kQueueThreads, 0, st>>>(c);
 }
 
 // Charged particles occupy [0, nq) of the sorted order, neutral ones [nq, n).
@@ -452,7 +532,7 @@ static void launch_part(PairCtx c, int part, hipStream_t st) {
   } else if (part == PAIR_PART_COULOMB) {
     c.charged = 1;
     c.pp.do_lj = 0;
-    launch_plain<F32, COUNT, 2, GHOST>(c, st);
+    if constexpr (F32) launch_plain<F32, COUNT, 2, GHOST>(c, st);  // the tile pass is FP32C
   } else if (part == PAIR_PART_NEUTRAL) {
     c.charged = 0;
     if (pp.rbl && pp.rlj2 > pp.rcore2 && pp.do_lj) launch_clusters(k_pair_rbl<F32, COUNT, GHOST, false>, c, st);
@@ -497,6 +577,11 @@ void launch_pair(int prec, int part, const PairParams &pp, int64_t n, const int3
   c.gxq = gb ? gb->xq : nullptr;
   c.gid = gb ? gb->id : nullptr;
   c.gcell_start = gb ? gb->cell_start : nullptr;
+  c.pk = s.pk;
+  c.gpk = gb ? gb->pk : nullptr;
+  c.pk_scale = s.pk_scale;
+  c.t2_q = pack_reach2(std::sqrt(pp.rq2), s.pk_scale);
+  c.t2_lj = pack_reach2(std::sqrt(pp.rlj2), s.pk_scale);
   if (gb) launch_prec<true>(prec, c, part, st);
   else launch_prec<false>(prec, c, part, st);
 }

@@ -661,6 +661,187 @@ struct ForceAcc<true> {
   __device__ inline double get(int c) const { return k.get(c); }
 };
 
+// ---------------------------------------------------------------------------
+// Queue walks: one lane per particle, candidates filtered on packed positions
+// ---------------------------------------------------------------------------
+// A thread-form walk that tests its candidates in two steps. The first reads
+// 8 packed bytes per candidate (pack_position) and compares integer distances
+// with a reach no pair inside the cutoff exceeds; the candidates that pass go
+// to the lane's queue in LDS. The second takes a queue entry per lane, loads
+// its FP64 record, classifies it exactly and evaluates it. What this buys: a
+// lane's load of a 32-byte record keeps the CU's 64 bytes per clock return
+// path busy for half a clock, so four SIMDs testing FP64 records wait on it
+// (128 SIMD cycles per candidate and wave) whatever the arithmetic costs, and
+// a pair term evaluated as soon as any lane holds a pair runs with a quarter
+// to half of the lanes. The filter needs a quarter of the bytes and six
+// integer instructions; the queues let the pair terms run with nearly all
+// lanes, however the pairs are spread over the rows.
+constexpr int kQueueCap = 32;       // entries per lane (a ring)
+constexpr int kQueueThreads = 256;  // block size: entry e of a lane at [e * kQueueThreads]
+constexpr int kCodeBits = 6;        // image shifts of an entry, two bits per axis
+constexpr int kIndexBits = 32 - kCodeBits;
+
+// A lane's ring of entries: byte offsets into the block's queue (slot e of
+// lane t at 4 (e kQueueThreads + t)), so that a push is a store and a step of
+// the offset.
+struct HitQueue {
+  char *lds;  // the block's queue
+  uint32_t head, tail;
+  uint32_t now = 0;  // image code of the piece being scanned
+  static constexpr uint32_t kStep = 4 * kQueueThreads, kMask = kQueueCap * kStep - 1;
+  __device__ inline HitQueue(uint32_t *queue) : lds((char *)queue), head(4 * threadIdx.x), tail(head) {}
+  __device__ inline uint32_t pending() const { return (tail - head) & kMask; }  // in bytes: entries times kStep
+  __device__ inline bool nearly_full() const { return pending() > (kQueueCap - 5) * kStep; }
+  __device__ inline void push(uint32_t e) {
+    *(uint32_t *)(lds + tail) = e;
+    tail = (tail + kStep) & kMask;
+  }
+  __device__ inline uint32_t pop() {
+    const uint32_t e = *(uint32_t *)(lds + head);
+    head = (head + kStep) & kMask;
+    return e;
+  }
+};
+// Squared distance of two packed positions in grid units (each difference a
+// signed 16-bit integer), at most 2^31 - 1. The clamp is there for far pairs;
+// it also takes the three-operand form of the dot product, which needs no
+// register cleared first.
+__device__ inline uint32_t packed_dist2(uint32_t axy, uint32_t az, uint32_t bxy, uint32_t bz) {
+  typedef short s2 __attribute__((ext_vector_type(2)));
+  const s2 dxy = __builtin_bit_cast(s2, axy) - __builtin_bit_cast(s2, bxy);
+  const s2 dz = __builtin_bit_cast(s2, az) - __builtin_bit_cast(s2, bz);
+  return (uint32_t)__builtin_amdgcn_sdot2(dz, dz, __builtin_amdgcn_sdot2(dxy, dxy, 0, true), true);
+}
+// Shift of one axis (boxes) from a code's two bits.
+__device__ inline double code_shift(uint32_t code, int axis) { return (double)((int)((code >> (2 * axis)) & 3u) - 1); }
+constexpr uint32_t kNoShift = 0x15u;  // 1 on every axis
+
+// Lanes of the wave for which v holds, as a scalar.
+__device__ inline int wave_count(bool v) { return __builtin_amdgcn_readfirstlane(__popcll(__ballot(v))); }
+// Largest v over the wave, as a scalar.
+__device__ inline int wave_max(int v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
+  return __builtin_amdgcn_readfirstlane(v);
+}
+
+// One species block of a queue walk, by the whole wave (lanes with active
+// false take part without candidates): the rows of stencil s out to the
+// squared reach r2 around pi, whose candidates within the integer squared
+// reach t2 are queued. drain(all) empties the queues of the wave, all of them
+// or only as far as it pays; it is called when a queue might overflow, and
+// (`coded` false: entries have no room for the image code) with all = true at
+// the end of every piece of a row, whose code is then the queue's `now`.
+// gs, gpk: the ghost arrays (GHOST), entries indexed from nnat on.
+template <bool GHOST, class Tested, class Drain>
+__device__ inline void queue_walk(const Grid &g, const int32_t *__restrict__ cs, const uint2 *__restrict__ pk,
+                                  const int32_t *__restrict__ gs, const uint2 *__restrict__ gpk, int nnat,
+                                  bool active, const double4 &pi, const Sten &s, double r2, uint32_t t2,
+                                  double scale, bool coded, HitQueue &Q, Tested &&tested, Drain &&drain) {
+  typedef uint32_t quad __attribute__((ext_vector_type(4), aligned(8)));  // two packed records
+  const int cx = cell_coord(pi.x, g.inv_h[0], g.nx), cy = cell_coord(pi.y, g.inv_h[1], g.ny),
+            cz = cell_coord(pi.z, g.inv_h[2], g.nz);
+  const RowFrame F(g, pi.x, pi.y, pi.z, cx, cy, cz, r2);
+  const uint2 home = pack_position(pi.x, pi.y, pi.z, scale);
+  const int my = wave_max(active ? s.y : 0), mz = wave_max(active ? s.z : 0);
+  for (int oz = -mz; oz <= mz; ++oz) {
+    const float gz = F.gap(F.uz, oz, F.hz);
+    if (wave_count(active && gz * gz <= F.r2) == 0) continue;
+    for (int oy = -my; oy <= my; ++oy) {
+      const float gy = F.gap(F.uy, oy, F.hy);
+      int a = 1, a_end = 0;
+      const bool in = active && abs(oz) <= s.z && abs(oy) <= s.y && F.range(fmaf(gy, gy, gz * gz), s.x, &a, &a_end);
+      if (wave_count(in) == 0) continue;
+      const int y = cy + oy, z = cz + oz;
+      a += cx;
+      a_end += cx;
+      bool more = in;
+      for (int pass = 0;; ++pass) {
+        int j0 = 0, len = 0;
+        const uint2 *rec = pk;
+        uint2 own = home;
+        uint32_t code = GHOST ? 0u : kNoShift;
+        if (more) {
+          if (GHOST) {
+            const bool inner = z >= 0 && z < g.nz && y >= 0 && y < g.ny;
+            if (pass == 0) {
+              const int na = max(a, 0), nb = min(a_end, g.nx - 1);
+              if (inner && na <= nb) {
+                const int32_t *t = cs + (z * g.ny + y) * g.nx;
+                j0 = t[na];
+                len = t[nb + 1] - j0;
+              }
+              more = !inner || a < 0 || a_end >= g.nx;  // the padded cells over the native grid hold no ghosts
+            } else {
+              const int32_t *t = gs + ((z + g.goff[2]) * g.pny + (y + g.goff[1])) * g.pnx + g.goff[0];
+              j0 = t[a];
+              len = t[a_end + 1] - j0;
+              more = false;
+            }
+          } else {
+            int qx, qy, qz;
+            const int wz = wrap_cell(z, g.nz, &qz), wy = wrap_cell(y, g.ny, &qy);
+            const int32_t *t = cs + (wz * g.ny + wy) * g.nx;
+            const int wa = wrap_cell(a, g.nx, &qx);
+            const int b = min(a_end, (qx + 1) * g.nx - 1);
+            j0 = t[wa];
+            len = t[b - qx * g.nx + 1] - j0;
+            a = b + 1;
+            more = a <= a_end;
+            code = (uint32_t)(qx + 1) | (uint32_t)(qy + 1) << 2 | (uint32_t)(qz + 1) << 4;
+          }
+        }
+        if (GHOST) {
+          if (pass) rec = gpk;
+        } else if (wave_count(code != kNoShift)) {
+          own = pack_position(pi.x - code_shift(code, 0) * g.L[0], pi.y - code_shift(code, 1) * g.L[1],
+                              pi.z - code_shift(code, 2) * g.L[2], scale);
+        }
+        tested(len);
+        Q.now = code;
+        const uint32_t tag = GHOST ? (pass ? (uint32_t)nnat : 0u) : (coded ? code << kIndexBits : 0u);
+        rec += j0;
+        quad n0{}, n1{};
+        if (len > 0) {
+          n0 = *(const quad *)rec;
+          n1 = *(const quad *)(rec + 2);
+        }
+        for (int k = 0, going = wave_count(k < len); going; k += 4) {
+          if (k < len) {
+            // four candidates, the next four requested before them (up to 7
+            // records past the end are read: padding)
+            const uint32_t xy[4] = {n0.x, n0.z, n1.x, n1.z}, zz[4] = {n0.y, n0.w, n1.y, n1.w};
+            n0 = *(const quad *)(rec + k + 4);
+            n1 = *(const quad *)(rec + k + 6);
+            const uint32_t e = (uint32_t)(j0 + k) + tag;
+            const int rest = len - k;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              if ((packed_dist2(own.x, own.y, xy[u], zz[u]) <= t2) & (rest > u)) Q.push(e + u);
+            }
+          }
+          going = wave_count(k + 4 < len);
+          const bool piece = !GHOST && !coded && going == 0;  // its code is not in the entries
+          if (piece || wave_count(Q.nearly_full())) drain(piece);
+        }
+        if (wave_count(more) == 0) break;
+      }
+    }
+  }
+}
+
+// The steps of a drain: one(e) for an entry of every lane that has one, until
+// all queues are empty (all), or until none is close to overflowing and fewer
+// than three quarters of the lanes would take part.
+template <class One>
+__device__ inline void drain_queue(HitQueue &Q, bool all, One &&one) {
+  for (;;) {
+    const bool any = Q.pending() != 0;
+    if (wave_count(any) < (all || wave_count(Q.nearly_full()) ? 1 : 48)) return;
+    if (any) one(Q.pop());
+  }
+}
+
 // Lanes per particle of the plain sums of `count` particles: 64 or 32 (group
 // walk), or 1 (thread form). One thread each leaves the chip nearly idle below
 // a few hundred thousand particles: its time is then that of one particle's
