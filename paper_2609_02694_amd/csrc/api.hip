@@ -91,22 +91,15 @@ struct rbe_ctx {
     std::vector<RepDesc> reps;  // host copy (the nq and chunk fields live on the device only)
     std::vector<int64_t> off;   // [nrep + 1]
     int64_t ntot = 0, nkeys = 0;
-    int ntiles = 0, blocks = 0;
     int64_t part_chunks = 0;    // chunk capacity of the partial array
     RepDesc *reps_dev = nullptr;
-    int32_t *rep_of = nullptr, *key = nullptr, *slot = nullptr, *tmp = nullptr, *count = nullptr;
-    int32_t *tile_sum = nullptr, *nq = nullptr;
+    int32_t *rep_of = nullptr, *nq = nullptr;
     int64_t *off_dev = nullptr;
     double *qs = nullptr, *wk = nullptr;
     GatherMode *modes = nullptr;
     double2 *part = nullptr;
-    unsigned *bar = nullptr;
-    uint64_t *eval = nullptr;
-    int *rho_items = nullptr;  // device: structure-factor items of this call
-    int *bad_rep = nullptr;    // device: first replica that failed the charge checks (-1: none)
-    BatchArgs node_args[2]{};  // arguments of the two graph nodes
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
+    int *rho_chunks = nullptr;  // device: structure-factor chunks of this call
+    int *bad_rep = nullptr;     // device: first replica that failed the charge checks (-1: none)
   } bt;
   bool batched() const { return bt.nrep > 0; }
 
@@ -488,9 +481,6 @@ extern "C" int rbe_create(rbe_ctx **out, const rbe_params *p, int64_t n_max, int
   return RBE_OK;
 }
 
-// Structure-factor chunk length of the batched form (particles per wave item).
-constexpr int kBatchChunk = 128;
-
 static bool same_shared_physics(const rbe_params &a, const rbe_params &b) {
   auto t = [](int v) { return v == 0 ? RBE_TERM_ALL : v; };
   return a.alpha == b.alpha && a.r_coul == b.r_coul && a.r_lj == b.r_lj && a.r_core == b.r_core &&
@@ -585,7 +575,6 @@ extern "C" int rbe_create_batch(rbe_ctx **out, int32_t n_sys, const rbe_params *
     return create_fail(RBE_EINVAL, "cell grids too large");
   }
   B.nkeys = key0;
-  B.ntiles = batch_scan_tiles(key0);
   B.part_chunks = chunks;
   const int64_t n = B.ntot;
   const int P = c->p.P;
@@ -607,7 +596,6 @@ extern "C" int rbe_create_batch(rbe_ctx **out, int32_t n_sys, const rbe_params *
   }
   c->srt.xq = b.alloc<double4>(n + kScanPad);
   c->srt.sq = b.alloc<double4>(n);
-  c->srt.id = b.alloc<int32_t>(n + kScanPad);
   if (c->p.prec == RBE_FP64) c->srt.pk = b.alloc<uint2>(n + kScanPad);
   c->srt.pk_scale = pack_scale(std::fmax(c->p.r_coul, c->p.r_lj));
   c->perm = b.alloc<int32_t>(n);
@@ -615,11 +603,12 @@ extern "C" int rbe_create_batch(rbe_ctx **out, int32_t n_sys, const rbe_params *
   c->cdf_dev = b.alloc<double>((int64_t)cdf_all.size());
   c->err = b.alloc<int>(1);
   c->counters = b.alloc<unsigned long long>(12);
-  B.key = b.alloc<int32_t>(n);
-  B.slot = b.alloc<int32_t>(n);
-  B.tmp = b.alloc<int32_t>(n);
-  B.count = b.alloc<int32_t>(B.nkeys);
-  B.tile_sum = b.alloc<int32_t>(B.ntiles);
+  c->bb.key = b.alloc<int32_t>(n);
+  c->bb.slot = b.alloc<int32_t>(n);
+  c->bb.tmp = b.alloc<int32_t>(n);
+  c->bb.count = b.alloc<int32_t>(B.nkeys);
+  c->bb.scan_tmp = b.alloc<int32_t>(scan_tiles(B.nkeys));
+  c->fb.turn_tab = b.alloc<double2>(kTurnTableEntries);
   B.rep_of = b.alloc<int32_t>(n);
   B.reps_dev = b.alloc<RepDesc>(n_sys);
   B.off_dev = b.alloc<int64_t>(n_sys + 1);
@@ -628,9 +617,7 @@ extern "C" int rbe_create_batch(rbe_ctx **out, int32_t n_sys, const rbe_params *
   B.modes = b.alloc<GatherMode>((int64_t)n_sys * P);
   B.wk = b.alloc<double>((int64_t)n_sys * P);
   B.part = b.alloc<double2>(chunks * P);
-  B.bar = b.alloc<unsigned>(2);
-  B.eval = b.alloc<uint64_t>(1);
-  B.rho_items = b.alloc<int>(1);
+  B.rho_chunks = b.alloc<int>(1);
   B.bad_rep = b.alloc<int>(1);
   if (!b.ok) {
     b.release();
@@ -640,13 +627,14 @@ extern "C" int rbe_create_batch(rbe_ctx **out, int32_t n_sys, const rbe_params *
   std::vector<int32_t> rep_of(n);
   for (int32_t r = 0; r < n_sys; ++r)
     for (int64_t i = offset[r]; i < offset[r + 1]; ++i) rep_of[i] = r;
-  B.blocks = batch_grid_blocks(c->p.prec, device);
+  double2 turn_host[kTurnTableEntries];
+  fill_turn_table(turn_host, kTurnTableEntries);
   if (hipMemcpy(c->cdf_dev, cdf_all.data(), sizeof(double) * cdf_all.size(), hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(B.rep_of, rep_of.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(B.off_dev, offset, sizeof(int64_t) * (n_sys + 1), hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(B.reps_dev, B.reps.data(), sizeof(RepDesc) * n_sys, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemset(B.count, 0, sizeof(int32_t) * B.nkeys) != hipSuccess ||
-      hipMemset(B.bar, 0, 2 * sizeof(unsigned)) != hipSuccess || hipMemset(c->err, 0, sizeof(int)) != hipSuccess ||
+      hipMemcpy(c->fb.turn_tab, turn_host, sizeof turn_host, hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemset(c->err, 0, sizeof(int)) != hipSuccess ||
       hipMemset(c->counters, 0, 12 * sizeof(unsigned long long)) != hipSuccess ||
       hipDeviceSynchronize() != hipSuccess) {
     b.release();
@@ -661,8 +649,6 @@ extern "C" void rbe_destroy(rbe_ctx *ctx) {
   if (!ctx) return;
   (void)hipSetDevice(ctx->device);
   (void)hipDeviceSynchronize();
-  if (ctx->bt.exec) (void)hipGraphExecDestroy(ctx->bt.exec);
-  if (ctx->bt.graph) (void)hipGraphDestroy(ctx->bt.graph);
   ctx->buf.release();
   for (auto &e : ctx->tm.ev) (void)hipEventDestroy(e);
   delete ctx;
@@ -933,7 +919,7 @@ extern "C" int rbe_sample_k(const rbe_params *p, uint64_t eval, int32_t *m, doub
 static void batch_prepare(rbe_ctx *c, const double *q, hipStream_t st) {
   auto &B = c->bt;
   launch_qstats_rep(B.nrep, B.off_dev, q, B.nq, B.qs, st);
-  launch_batch_layout(B.nrep, B.nq, B.qs, c->p.P, kBatchChunk, B.reps_dev, B.rho_items, B.bad_rep, c->err, st);
+  launch_batch_layout(B.nrep, B.nq, B.qs, B.reps_dev, B.rho_chunks, B.bad_rep, c->err, st);
 }
 
 // Launch arguments shared by both modes; the caller sets the state arrays.
@@ -945,10 +931,10 @@ static BatchArgs batch_args(rbe_ctx *c, int mode) {
   a.rep_of = B.rep_of;
   a.ntot = B.ntot;
   a.nkeys = B.nkeys;
-  a.ntiles = B.ntiles;
   a.P = c->p.P;
   a.mode = mode;
-  a.rho_items = B.rho_items;
+  a.rho_chunks = B.rho_chunks;
+  a.chunk_cap = B.part_chunks;
   a.do_far = (c->p.terms & RBE_TERM_FOURIER) != 0;
   a.pp = c->pp;
   a.pf = make_pair_f32(a.pp);
@@ -956,25 +942,19 @@ static BatchArgs batch_args(rbe_ctx *c, int mode) {
   a.dt = c->p.dt;
   a.xq = c->srt.xq;
   a.sq = c->srt.sq;
-  a.sid = c->srt.id;
   a.pk = c->srt.pk;
   a.pk_scale = c->srt.pk_scale;
   a.t2_q = pack_reach2(std::sqrt(c->pp.rq2), a.pk_scale);
   a.t2_lj = pack_reach2(std::sqrt(c->pp.rlj2), a.pk_scale);
-  a.key = B.key;
-  a.slot = B.slot;
-  a.tmp = B.tmp;
+  a.bin = c->bb;
   a.perm = c->perm;
-  a.count = B.count;
   a.cell_start = c->cell_start;
-  a.tile_sum = B.tile_sum;
+  a.turn_tab = c->fb.turn_tab;
   a.cdf = c->cdf_dev;
   a.modes = B.modes;
   a.wk = B.wk;
   a.part = B.part;
   a.err = c->err;
-  a.bar = B.bar;
-  a.eval = B.eval;
   return a;
 }
 
@@ -1005,38 +985,12 @@ static BatchArgs batch_step_args(rbe_ctx *c, const WorkSet &in, const WorkSet &o
   return a;
 }
 
-// Start of a batched call: eval, barrier and histogram start from known values.
-static int batch_begin(rbe_ctx *c, uint64_t eval, hipStream_t st) {
-  auto &B = c->bt;
-  launch_set_u64(B.eval, eval, st);
-  launch_fill_i32((int32_t *)B.bar, 2, 0, st);
-  launch_fill_i32(B.count, B.nkeys, 0, st);
-  return RBE_OK;
-}
-
-// Two-step graph (ws[0] -> ws[1] -> ws[0]), instantiated on the first call
-// with two or more steps (the layout it depends on is read on the device).
-static int batch_graph(rbe_ctx *c) {
-  auto &B = c->bt;
-  if (B.exec) return RBE_OK;
-  B.node_args[0] = batch_step_args(c, c->ws[0], c->ws[1]);
-  B.node_args[1] = batch_step_args(c, c->ws[1], c->ws[0]);
-  HIP_TRY(c, hipGraphCreate(&B.graph, 0));
-  hipGraphNode_t n0 = nullptr, n1 = nullptr;
-  HIP_TRY(c, add_batch_node(B.graph, &n0, nullptr, 0, c->p.prec, B.blocks, &B.node_args[0]));
-  HIP_TRY(c, add_batch_node(B.graph, &n1, &n0, 1, c->p.prec, B.blocks, &B.node_args[1]));
-  HIP_TRY(c, hipGraphInstantiate(&B.exec, B.graph, nullptr, nullptr, 0));
-  return RBE_OK;
-}
-
 static int batch_forces(rbe_ctx *c, const rbe_state *s, const int32_t *m, const double *w, uint64_t eval,
                         double *rho_out, hipStream_t st) {
   auto &B = c->bt;
   if (m || w || rho_out) return c->fail(RBE_EINVAL, "a batched context draws its own modes: m, w, rho_out must be NULL");
   if (s->n != B.ntot) return c->fail(RBE_ERANGE, "n = %lld, the batch holds %lld", (long long)s->n, (long long)B.ntot);
   batch_prepare(c, s->q, st);
-  const int rc = batch_begin(c, eval, st);
-  if (rc != RBE_OK) return rc;
   BatchArgs a = batch_args(c, 1);
   a.ix = s->x;
   a.iy = s->y;
@@ -1044,11 +998,6 @@ static int batch_forces(rbe_ctx *c, const rbe_state *s, const int32_t *m, const 
   a.iq = s->q;
   a.iid = s->id;
   const WorkSet &o = c->ws[1];
-  a.ox = o.x;
-  a.oy = o.y;
-  a.oz = o.z;
-  a.oq = o.q;
-  a.oid = o.id;
   a.ofx = o.fx;
   a.ofy = o.fy;
   a.ofz = o.fz;
@@ -1057,7 +1006,7 @@ static int batch_forces(rbe_ctx *c, const rbe_state *s, const int32_t *m, const 
   a.cfz = s->fz;
   {
     TScope ts(c, RBE_TK_BATCH, st);
-    launch_batch_step(c->p.prec, B.blocks, a, st);
+    launch_batch_step(c->p.prec, a, eval, st);
   }
   HIP_TRY(c, hipGetLastError());
   return RBE_OK;
@@ -1073,46 +1022,29 @@ static int copy_state(rbe_ctx *c, const double *const src[10], const int32_t *si
 
 // Batched steps without copying the state: the first step reads the caller's
 // arrays and reorders into ws[0], the steps between alternate between the
-// working sets (pairs of them through the two-step graph), and the last step
-// reorders into the caller's arrays. A single step copies the state into
-// ws[0] first.
+// working sets, and the last step reorders into the caller's arrays. A single
+// step copies the state into ws[0] first.
 static int batch_step(rbe_ctx *c, rbe_state *s, int32_t nsteps, uint64_t first_eval, hipStream_t st) {
   auto &B = c->bt;
   if (s->n != B.ntot) return c->fail(RBE_ERANGE, "n = %lld, the batch holds %lld", (long long)s->n, (long long)B.ntot);
   batch_prepare(c, s->q, st);
   const int64_t n = s->n;
   WorkSet S{s->x, s->y, s->z, s->vx, s->vy, s->vz, s->q, s->fx, s->fy, s->fz, s->id};
-  int rc = batch_begin(c, first_eval, st);
-  if (rc != RBE_OK) return rc;
-  auto direct = [&](const WorkSet &in, const WorkSet &out) {
-    BatchArgs a = batch_step_args(c, in, out);
-    TScope ts(c, RBE_TK_BATCH, st);
-    launch_batch_step(c->p.prec, B.blocks, a, st);
-  };
+  const WorkSet *in = &S;
   if (nsteps == 1) {
     WorkSet &A = c->ws[0];
     const double *src[10] = {s->x, s->y, s->z, s->vx, s->vy, s->vz, s->fx, s->fy, s->fz, s->q};
     double *dst[10] = {A.x, A.y, A.z, A.vx, A.vy, A.vz, A.fx, A.fy, A.fz, A.q};
-    rc = copy_state(c, src, s->id, dst, A.id, n, st);
+    const int rc = copy_state(c, src, s->id, dst, A.id, n, st);
     if (rc != RBE_OK) return rc;
-    direct(A, S);
-  } else {
-    direct(S, c->ws[0]);
-    const int32_t middle = nsteps - 2;
-    if (middle >= 2) {
-      rc = batch_graph(c);
-      if (rc != RBE_OK) return rc;
-      for (int32_t k = 0; k + 1 < middle; k += 2) {
-        TScope ts(c, RBE_TK_BATCH, st, 2);
-        HIP_TRY(c, hipGraphLaunch(B.exec, st));
-      }
-    }
-    const WorkSet *cur = &c->ws[0];
-    if (middle & 1) {
-      direct(c->ws[0], c->ws[1]);
-      cur = &c->ws[1];
-    }
-    direct(*cur, S);
+    in = &A;
+  }
+  for (int32_t k = 0; k < nsteps; ++k) {
+    const WorkSet *out = k == nsteps - 1 ? &S : &c->ws[k % 2];
+    const BatchArgs a = batch_step_args(c, *in, *out);
+    TScope ts(c, RBE_TK_BATCH, st);
+    launch_batch_step(c->p.prec, a, first_eval + (uint64_t)k, st);
+    in = out;
   }
   HIP_TRY(c, hipGetLastError());
   return RBE_OK;
@@ -1418,7 +1350,6 @@ extern "C" int rbe_sync_check(rbe_ctx *c, void *stream) {
   if (flag & kErrBadId) return c->fail(RBE_ERANGE, "a particle id lies outside [0, n)");
   if (flag & kErrSampler) return c->fail(RBE_EINVAL, "mode sampler rejected every attempt");
   if (flag & kErrGhostOverflow) return c->fail(RBE_ERANGE, "the ghost shell exceeded its capacity");
-  if (flag & kErrBarrier) return c->fail(RBE_EDEVICE, "a grid barrier of the batched step timed out");
   if (flag & kErrNonNeutral) return c->fail(RBE_ENONNEUTRAL, "the charges do not sum to zero (Eq. 1)%s", who);
   if (flag & kErrTileOverflow)
     return c->fail(RBE_ERANGE, "a cell row of the near-field tiles exceeded the LDS staging (density far above the mean)");

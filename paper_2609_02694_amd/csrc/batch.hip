@@ -1,32 +1,27 @@
 // Batched form: many independent systems ("replicas") of uneven size advanced
-// together, three launches per velocity-Verlet step.
+// together.
 //
 // All replicas live in concatenated arrays; replica r owns particles
 // [p0, p0 + n) and binning keys [c0, c0 + 2 C_r) (its charged cells, then its
-// neutral cells). A persistent kernel runs the step for every replica, phase
-// by phase, with a grid-wide barrier between phases, in two launches: P0-P6,
-// then P7-P9. Between them a plain kernel sums the near field of every
-// particle, with the occupancy of its own register count:
+// neutral cells), so one counting sort, one launch per pass, serves every
+// replica:
 //
-//   P0  half-kick + drift + wrap; binning keys + histogram; mode sample of
-//       every replica (Eq. 9)
-//   P1  scan: tile sums of the concatenated histogram
-//   P2  scan: one block scans the tile sums
-//   P3  scan: cell starts (one exclusive scan serves every replica, because
-//       replica r's keys and particles both follow those of replicas < r)
-//   P4  provisional scatter (atomic slots)
-//   P5  stable placement (each bucket's entries in increasing input order)
-//   P6  reorder of the state and packing of the sorted records
-//   --  near field of every particle (k_batch_near)
-//   P7  structure-factor partials (chunk x mode)
-//   P8  structure factors: fixed-order sum of the chunk partials per mode
-//   P9  Fourier gather + second half-kick
+//   half-kick + drift + wrap, binning keys + histogram, and the mode samples
+//     of every replica (Eq. 9)                              k_batch_drift
+//   scan, scatter and stable placement of the keys          bin.hip
+//   reorder of the state, packing of the sorted records     k_batch_reorder
+//   near field of every particle                            k_batch_near*
+//   structure-factor partials (chunk x mode)                k_batch_rho
+//   structure factors: fixed-order sums of the partials     k_batch_rho_final
+//   Fourier gather + second half-kick                       k_batch_gather
 //
-// The grid is sized to the kernel's resident capacity, so every block is
-// resident and the barrier cannot wait on a block that never starts; the
-// barrier's wait is still bounded in time and reports an error instead of
-// hanging. Data written inside the kernel is read only through vector loads
-// after an agent-scope fence.
+// Plain launches: a launch boundary costs 2-4 us here, while a barrier across
+// the resident blocks of one persistent kernel cost about 40 us (every block's
+// arrival is an atomic on one address, seen from eight L2s), and each pass
+// then has the registers, and so the waves per SIMD, of its own code. The
+// passes other than the near field took 715 us of a step of 24 replicas
+// (150,000 particles, FP64) and 2,150 us of one of 256 (3.4M, FP32C) as two
+// persistent launches, 100 and 580 us as these.
 #include "fourier_device.h"
 #include "pair_device.h"
 #include "sampler_device.h"
@@ -34,362 +29,100 @@
 namespace rbe {
 
 constexpr int kBatchThreads = 256;
-constexpr int kScanTileB = kBatchThreads * 8;
-constexpr uint64_t kBarrierTimeoutTicks = 200000000ull;  // 2 s at the 100 MHz wall clock
 
-// Grid-wide barrier. A wait longer than the time limit flags kErrBarrier;
-// once that flag is up no block waits again, so a launch whose blocks were
-// not all resident still ends (with its result reported as failed).
-// Every wave waits until its own stores have reached the L2 (s_waitcnt 0)
-// before the block barrier; one wave per block then releases the block's
-// stores at agent scope with its arrival (the L2 write-back covers them all)
-// and, after the wait, acquires the other blocks' (invalidating the caches
-// every wave of the block reads through). Fences in every wave would repeat
-// the write-back and the invalidation per wave.
-__device__ inline void grid_barrier(unsigned *bar, int *err) {
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    // the arrival releases the block's stores (and acquires the earlier
-    // arrivals' for the last one); the generation read before it needs no
-    // ordering of its own
-    const unsigned gen = __hip_atomic_load(&bar[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned arrived = __hip_atomic_fetch_add(&bar[0], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1;
-    if (arrived == gridDim.x) {
-      __hip_atomic_store(&bar[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_fetch_add(&bar[1], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      const uint64_t t0 = wall_clock64();
-      // relaxed polls (an acquire would invalidate the caches on every poll);
-      // the fence after the wait acquires
-      while (__hip_atomic_load(&bar[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gen) {
-        if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kErrBarrier) break;
-        __builtin_amdgcn_s_sleep(4);
-        if (wall_clock64() - t0 > kBarrierTimeoutTicks) {
-          atomicOr(err, kErrBarrier);
-          break;
-        }
-      }
+// ---------------------------------------------------------------------------
+// drift, keys and mode samples
+// ---------------------------------------------------------------------------
+// Blocks [0, nb): one thread per particle. mode 0: v += h f, x <- wrap(x + dt
+// v) in place; both modes: the binning key of the (wrapped) position, its run
+// slot and the histogram (cleared before). Blocks from nb on: one thread per
+// (replica, mode) of evaluation `eval`.
+__global__ void __launch_bounds__(kBatchThreads) k_batch_drift(BatchArgs a, uint64_t eval, unsigned nb) {
+  if (blockIdx.x >= nb) {
+    const int64_t it = (blockIdx.x - nb) * (int64_t)kBatchThreads + threadIdx.x;
+    if (it >= (int64_t)a.nrep * a.P) return;
+    const int r = (int)(it / a.P), l = (int)(it % a.P);
+    const RepDesc &R = a.reps[r];
+    const uint64_t ek = stream_out(R.seed ^ kTagModes, eval);
+    int mv[3];
+    if (!draw_mode(R.mt, a.cdf + R.cdf_off, ek, l, mv)) {
+      atomicOr(a.err, kErrSampler);
+      mv[0] = 1;
+      mv[1] = 0;
+      mv[2] = 0;
     }
-    __threadfence();
-  }
-  __syncthreads();
-}
-
-__device__ inline int block_scan_excl(int v, int *lds, int *total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int incl = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += t;
-  }
-  if (lane == 63) lds[wave] = incl;
-  __syncthreads();
-  int off = 0, tot = 0;
-  for (int w = 0; w < kBatchThreads / 64; ++w) {
-    const int s = lds[w];
-    if (w < wave) off += s;
-    tot += s;
-  }
-  __syncthreads();
-  *total = tot;
-  return off + incl - v;
-}
-
-template <bool F32>
-__global__ void __launch_bounds__(kBatchThreads) k_batch_step(BatchArgs a) {
-  __shared__ int lds[kBatchThreads / 64];
-  const int tid = threadIdx.x;
-  const int64_t gtid = xcd_block(blockIdx.x, gridDim.x) * kBatchThreads + tid;
-  const int64_t gstride = (int64_t)gridDim.x * kBatchThreads;
-  const int lane = tid & 63;
-  const int64_t gwave = xcd_block(blockIdx.x, gridDim.x) * (kBatchThreads / 64) + (tid >> 6);
-  const int64_t nwaves = (int64_t)gridDim.x * (kBatchThreads / 64);
-  const int P = a.P;
-  const bool do_far = a.do_far != 0;
-  const uint64_t eval = *((volatile uint64_t *)a.eval);
-
-  if (a.launch_part == 1) {
-    // ---- P0: drift, keys + histogram, mode sample ----------------------------
-    // wave-uniform trip count (every lane takes part in the slot vote)
-    for (int64_t i = gtid; i - lane < a.ntot; i += gstride) {
-      const bool active = i < a.ntot;
-      int k = -1 - lane;  // lanes past the end: a key no other lane has
-      if (active) {
-        const RepDesc &R = a.reps[a.rep_of[i]];
-        double x = a.ix[i], y = a.iy[i], z = a.iz[i];
-        if (a.mode == 0) {
-          const double u = a.ivx[i] + a.h * a.ifx[i], v = a.ivy[i] + a.h * a.ify[i], w = a.ivz[i] + a.h * a.ifz[i];
-          a.ivx[i] = u;
-          a.ivy[i] = v;
-          a.ivz[i] = w;
-          x = wrap_coord(x + a.dt * u, R.g.L[0]);
-          y = wrap_coord(y + a.dt * v, R.g.L[1]);
-          z = wrap_coord(z + a.dt * w, R.g.L[2]);
-          a.ix[i] = x;
-          a.iy[i] = y;
-          a.iz[i] = z;
-          if (!isfinite(u) || !isfinite(v) || !isfinite(w)) atomicOr(a.err, kErrNonFinite);
-        } else {
-          x = wrap_coord(x, R.g.L[0]);
-          y = wrap_coord(y, R.g.L[1]);
-          z = wrap_coord(z, R.g.L[2]);
-        }
-        const int cx = cell_coord(x, R.g.inv_h[0], R.g.nx);
-        const int cy = cell_coord(y, R.g.inv_h[1], R.g.ny);
-        const int cz = cell_coord(z, R.g.inv_h[2], R.g.nz);
-        k = (int)(R.c0 + (a.iq[i] == 0.0 ? R.g.ncell : 0) + (cz * R.g.ny + cy) * R.g.nx + cx);
-        a.key[i] = k;
-      }
-      const int sl = run_slot(k, active, a.count);
-      if (active) a.slot[i] = sl;
-    }
-    if (P > 0) {
-      for (int64_t it = gtid; it < (int64_t)a.nrep * P; it += gstride) {
-        const int r = (int)(it / P), l = (int)(it % P);
-        const RepDesc &R = a.reps[r];
-        const uint64_t ek = stream_out(R.seed ^ kTagModes, eval);
-        int mv[3];
-        if (!draw_mode(R.mt, a.cdf + R.cdf_off, ek, l, mv)) {
-          atomicOr(a.err, kErrSampler);
-          mv[0] = 1;
-          mv[1] = 0;
-          mv[2] = 0;
-        }
-        GatherMode gm;
-        gm.mx = (double)mv[0];
-        gm.my = (double)mv[1];
-        gm.mz = (double)mv[2];
-        gm.a = 0.0;
-        gm.b = 0.0;
-        gather_floats(gm);
-        a.modes[it] = gm;
-        a.wk[it] = mode_weight(R.mt, P, mv[0], mv[1], mv[2]);
-      }
-    }
-    grid_barrier(a.bar, a.err);
-
-    // ---- P1: tile sums -------------------------------------------------------
-    for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
-      const int64_t base = (int64_t)t * kScanTileB + (int64_t)tid * 8;
-      int s = 0;
-      for (int k = 0; k < 8; ++k)
-        if (base + k < a.nkeys) s += a.count[base + k];
-      int tot;
-      block_scan_excl(s, lds, &tot);
-      if (tid == 0) a.tile_sum[t] = tot;
-    }
-    grid_barrier(a.bar, a.err);
-
-    // ---- P2: scan of the tile sums (one block) --------------------------------
-    if (blockIdx.x == 0) {
-      int carry = 0;
-      for (int b = 0; b < a.ntiles; b += kBatchThreads) {
-        const int t = b + tid;
-        const int v = t < a.ntiles ? a.tile_sum[t] : 0;
-        int tot;
-        const int ex = block_scan_excl(v, lds, &tot);
-        if (t < a.ntiles) a.tile_sum[t] = carry + ex;
-        carry += tot;
-      }
-      if (tid == 0) a.cell_start[a.nkeys] = carry;
-    }
-    grid_barrier(a.bar, a.err);
-
-    // ---- P3: cell starts -------------------------------------------------------
-    for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
-      const int64_t base = (int64_t)t * kScanTileB + (int64_t)tid * 8;
-      int v[8];
-      int s = 0;
-      for (int k = 0; k < 8; ++k) {
-        v[k] = base + k < a.nkeys ? a.count[base + k] : 0;
-        s += v[k];
-      }
-      int tot;
-      int run = a.tile_sum[t] + block_scan_excl(s, lds, &tot);
-      for (int k = 0; k < 8; ++k) {
-        if (base + k < a.nkeys) a.cell_start[base + k] = run;
-        run += v[k];
-      }
-    }
-    grid_barrier(a.bar, a.err);
-
-    // ---- P4: provisional scatter -----------------------------------------------
-    for (int64_t i = gtid; i < a.ntot; i += gstride) a.tmp[a.cell_start[a.key[i]] + a.slot[i]] = (int32_t)i;
-    grid_barrier(a.bar, a.err);
-
-    // ---- P5: stable placement; clear the histogram for the next step -----------
-    for (int64_t k = gtid; k < a.nkeys; k += gstride) place_bucket(a.cell_start[k], a.cell_start[k + 1], a.tmp, a.perm);
-    for (int64_t k = gtid; k < a.nkeys; k += gstride) a.count[k] = 0;
-    grid_barrier(a.bar, a.err);
-
-    // ---- P6: reorder + pack ------------------------------------------------------
-    for (int64_t k = gtid; k < a.ntot; k += gstride) {
-      const int j = a.perm[k];
-      const RepDesc &R = a.reps[a.rep_of[k]];
-      const double x = wrap_coord(a.ix[j], R.g.L[0]), y = wrap_coord(a.iy[j], R.g.L[1]),
-                   z = wrap_coord(a.iz[j], R.g.L[2]), q = a.iq[j];
-      const int32_t id = a.iid[j];
-      a.ox[k] = x;
-      a.oy[k] = y;
-      a.oz[k] = z;
-      a.oq[k] = q;
-      a.oid[k] = id;
-      if (a.mode == 0) {
-        a.ovx[k] = a.ivx[j];
-        a.ovy[k] = a.ivy[j];
-        a.ovz[k] = a.ivz[j];
-      }
-      a.xq[k] = make_double4(x, y, z, q);
-      if (q != 0.0) a.sq[k] = make_double4(x / R.g.L[0], y / R.g.L[1], z / R.g.L[2], q);
-      a.sid[k] = id;
-      if (a.pk) a.pk[k] = pack_position(x, y, z, a.pk_scale);
-    }
-    grid_barrier(a.bar, a.err);
+    GatherMode gm;
+    gm.mx = (double)mv[0];
+    gm.my = (double)mv[1];
+    gm.mz = (double)mv[2];
+    gm.a = 0.0;
+    gm.b = 0.0;
+    gather_floats(gm);
+    a.modes[it] = gm;
+    a.wk[it] = mode_weight(R.mt, a.P, mv[0], mv[1], mv[2]);
     return;
   }
-
-
-  // ---- P7: structure-factor partials (the near field ran in k_batch_near) --------
-  if (P > 0 && do_far) {
-    const int groups = (P + 63) / 64;
-    const int64_t rho_items = *a.rho_items;
-    for (int64_t it = gwave; it < rho_items; it += nwaves) {
-      // replica of this item: last r with rho_item_off <= it
-      int lo = 0, hi = a.nrep - 1;
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (a.reps[mid].rho_item_off <= it) lo = mid;
-        else hi = mid - 1;
-      }
-      const RepDesc &R = a.reps[lo];
-      const int local = (int)(it - R.rho_item_off);
-      const int chunk = local / groups, grp = local % groups;
-      const int l = grp * 64 + lane;
-      const bool active = l < P;
-      const GatherMode gm = a.modes[(int64_t)lo * P + (active ? l : 0)];
-      const int64_t j0 = R.p0 + (int64_t)chunk * R.chunk_len;
-      const int64_t j1 = min(R.p0 + (int64_t)R.nq, j0 + R.chunk_len);
-      double2 out;
-      if (F32) {
-        float re = 0.f, rc = 0.f, im = 0.f, ic = 0.f;
-#pragma unroll 4
-        for (int64_t j = j0; j < j1; ++j) {
-          const double4 s = a.sq[j];
-          const float t = turn_f32(gm.mx, gm.my, gm.mz, s.x, s.y, s.z);
-          const float q = (float)s.w;
-          kahan_fma(re, rc, q, __builtin_amdgcn_cosf(t));
-          kahan_fma(im, ic, q, __builtin_amdgcn_sinf(t));
-        }
-        out = make_double2((double)re - (double)rc, (double)im - (double)ic);
-      } else {
-        double re = 0.0, im = 0.0;
-#pragma unroll 4
-        for (int64_t j = j0; j < j1; ++j) {
-          const double4 s = a.sq[j];
-          const double t = turn_fraction(gm.mx, gm.my, gm.mz, s.x, s.y, s.z);
-          double sn, cs;
-          sincos_turn_f64(t, &sn, &cs);
-          re = fma(s.w, cs, re);
-          im = fma(s.w, sn, im);
-        }
-        out = make_double2(re, im);
-      }
-      if (active) a.part[(int64_t)(R.chunk_off + chunk) * P + l] = out;
-    }
-  }
-  grid_barrier(a.bar, a.err);
-
-  // ---- P8: structure factors and gather coefficients --------------------------
-  if (P > 0 && do_far) {
-    for (int64_t it = gwave; it < (int64_t)a.nrep * P; it += nwaves) {
-      const int r = (int)(it / P), l = (int)(it % P);
-      const RepDesc &R = a.reps[r];
-      double re = 0.0, im = 0.0;
-      for (int c = lane; c < R.nchunks; c += 64) {
-        const double2 v = a.part[(int64_t)(R.chunk_off + c) * P + l];
-        re += v.x;
-        im += v.y;
-      }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        re += __shfl_xor(re, o, 64);
-        im += __shfl_xor(im, o, 64);
-      }
-      if (lane == 0) {
-        const double w = a.pp.kc * a.wk[it];
-        a.modes[it].a = w * im;
-        a.modes[it].b = w * re;
-        a.modes[it].af = (float)(w * im);
-        a.modes[it].bf = (float)(w * re);
-      }
-    }
-  }
-  grid_barrier(a.bar, a.err);
-
-  // ---- P9: Fourier gather + second half-kick -----------------------------------
-  for (int64_t i = gtid; i < a.ntot; i += gstride) {
-    const int r = a.rep_of[i];
-    const RepDesc &R = a.reps[r];
-    double fx = a.ofx[i], fy = a.ofy[i], fz = a.ofz[i];
-    if (P > 0 && do_far && i < R.p0 + R.nq) {
-      const double4 s = a.sq[i];
-      const GatherMode *md = a.modes + (int64_t)r * P;
-      if (F32) {
-        float gx = 0.f, gy = 0.f, gz = 0.f, ex = 0.f, ey = 0.f, ez = 0.f;
-#pragma unroll 4
-        for (int l = 0; l < P; ++l) {
-          const GatherMode gm = md[l];
-          const float t = turn_f32(gm.mx, gm.my, gm.mz, s.x, s.y, s.z);
-          const float g = fmaf(gm.af, __builtin_amdgcn_cosf(t), -gm.bf * __builtin_amdgcn_sinf(t));
-          kahan_fma(gx, ex, g, gm.mxf);
-          kahan_fma(gy, ey, g, gm.myf);
-          kahan_fma(gz, ez, g, gm.mzf);
-        }
-        fx -= s.w * (kTwoPi / R.g.L[0]) * ((double)gx - (double)ex);
-        fy -= s.w * (kTwoPi / R.g.L[1]) * ((double)gy - (double)ey);
-        fz -= s.w * (kTwoPi / R.g.L[2]) * ((double)gz - (double)ez);
-      } else {
-        double gx = 0.0, gy = 0.0, gz = 0.0;
-#pragma unroll 4
-        for (int l = 0; l < P; ++l) {
-          const GatherMode gm = md[l];
-          const double t = turn_fraction(gm.mx, gm.my, gm.mz, s.x, s.y, s.z);
-          double sn, cs;
-          sincos_turn_f64(t, &sn, &cs);
-          const double g = gm.a * cs - gm.b * sn;
-          gx = fma(g, gm.mx, gx);
-          gy = fma(g, gm.my, gy);
-          gz = fma(g, gm.mz, gz);
-        }
-        fx -= s.w * (kTwoPi / R.g.L[0]) * gx;
-        fy -= s.w * (kTwoPi / R.g.L[1]) * gy;
-        fz -= s.w * (kTwoPi / R.g.L[2]) * gz;
-      }
-    }
-    a.ofx[i] = fx;
-    a.ofy[i] = fy;
-    a.ofz[i] = fz;
+  const int64_t i = blockIdx.x * (int64_t)kBatchThreads + threadIdx.x;
+  const bool active = i < a.ntot;
+  int k = -1 - (int)(threadIdx.x & 63);  // lanes past the end: a key no other lane has
+  if (active) {
+    const RepDesc &R = a.reps[a.rep_of[i]];
+    double x = a.ix[i], y = a.iy[i], z = a.iz[i];
     if (a.mode == 0) {
-      const double u = a.ovx[i] + a.h * fx, v = a.ovy[i] + a.h * fy, w = a.ovz[i] + a.h * fz;
-      a.ovx[i] = u;
-      a.ovy[i] = v;
-      a.ovz[i] = w;
+      const double u = a.ivx[i] + a.h * a.ifx[i], v = a.ivy[i] + a.h * a.ify[i], w = a.ivz[i] + a.h * a.ifz[i];
+      a.ivx[i] = u;
+      a.ivy[i] = v;
+      a.ivz[i] = w;
+      x = wrap_coord(x + a.dt * u, R.g.L[0]);
+      y = wrap_coord(y + a.dt * v, R.g.L[1]);
+      z = wrap_coord(z + a.dt * w, R.g.L[2]);
+      a.ix[i] = x;
+      a.iy[i] = y;
+      a.iz[i] = z;
       if (!isfinite(u) || !isfinite(v) || !isfinite(w)) atomicOr(a.err, kErrNonFinite);
     } else {
-      const int j = a.perm[i];
-      a.cfx[j] = fx;
-      a.cfy[j] = fy;
-      a.cfz[j] = fz;
+      x = wrap_coord(x, R.g.L[0]);
+      y = wrap_coord(y, R.g.L[1]);
+      z = wrap_coord(z, R.g.L[2]);
     }
+    const int cx = cell_coord(x, R.g.inv_h[0], R.g.nx);
+    const int cy = cell_coord(y, R.g.inv_h[1], R.g.ny);
+    const int cz = cell_coord(z, R.g.inv_h[2], R.g.nz);
+    k = (int)(R.c0 + (a.iq[i] == 0.0 ? R.g.ncell : 0) + (cz * R.g.ny + cy) * R.g.nx + cx);
+    a.bin.key[i] = k;
   }
-  if (a.mode == 0 && gtid == 0) *((volatile uint64_t *)a.eval) = eval + 1;
+  const int sl = run_slot(k, active, a.bin.count);  // every lane of the wave takes part in the vote
+  if (active) a.bin.slot[i] = sl;
 }
 
-// The near field of every particle of the batch, between the two launches of
-// the step kernel: a plain launch, so that its occupancy is not bound to the
-// persistent kernel's registers.
+// ---------------------------------------------------------------------------
+// reorder + pack
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(kBatchThreads) k_batch_reorder(BatchArgs a) {
+  const int64_t k = blockIdx.x * (int64_t)kBatchThreads + threadIdx.x;
+  if (k >= a.ntot) return;
+  const int j = a.perm[k];
+  const RepDesc &R = a.reps[a.rep_of[k]];
+  const double x = wrap_coord(a.ix[j], R.g.L[0]), y = wrap_coord(a.iy[j], R.g.L[1]),
+               z = wrap_coord(a.iz[j], R.g.L[2]), q = a.iq[j];
+  if (a.mode == 0) {
+    a.ox[k] = x;
+    a.oy[k] = y;
+    a.oz[k] = z;
+    a.oq[k] = q;
+    a.oid[k] = a.iid[j];
+    a.ovx[k] = a.ivx[j];
+    a.ovy[k] = a.ivy[j];
+    a.ovz[k] = a.ivz[j];
+  }
+  a.xq[k] = make_double4(x, y, z, q);
+  if (q != 0.0) a.sq[k] = make_double4(x / R.g.L[0], y / R.g.L[1], z / R.g.L[2], q);
+  if (a.pk) a.pk[k] = pack_position(x, y, z, a.pk_scale);
+}
+
+// ---------------------------------------------------------------------------
+// near field
+// ---------------------------------------------------------------------------
 // FP32C: one thread per particle walking the stencil rows of its own cell in
 // its replica. Four waves per SIMD (no spills; five, with 13 VGPRs spilled,
 // ran no faster).
@@ -521,73 +254,234 @@ static BatchKernel batch_near_kernel(int prec, int64_t ntot, unsigned *blocks) {
   return prec == RBE_FP32C ? k_batch_near : k_batch_near_queue;
 }
 
-int batch_grid_blocks(int prec, int device) {
-  int per_cu = 0, cus = 0;
-  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
-  if (prec == RBE_FP32C)
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(k_batch_step<true>),
-                                                 kBatchThreads, 0);
-  else
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(k_batch_step<false>),
-                                                 kBatchThreads, 0);
-  if (per_cu < 1) per_cu = 1;
-  if (cus < 1) cus = 1;
-  return per_cu * cus;
+// ---------------------------------------------------------------------------
+// structure factors
+// ---------------------------------------------------------------------------
+// A block takes `sub` consecutive chunks (of all replicas' chunks) and every
+// mode of theirs, one lane per (chunk, mode): with P = 100 two chunks keep 200
+// of 256 lanes busy where whole waves of modes would keep 100 of 128. The
+// chunks' records are staged in LDS; a lane sums its chunk's terms in order.
+constexpr int kBatchSubMax = 4;
+template <bool F32>
+__global__ void __launch_bounds__(kBatchThreads) k_batch_rho(BatchArgs a, const RepDesc *__restrict__ reps,
+                                                             const double4 *__restrict__ sq,
+                                                             const GatherMode *__restrict__ modes,
+                                                             const double2 *__restrict__ turn_tab, int sub) {
+  static_assert(kBatchThreads == kTurnTable, "one table entry per thread");
+  __shared__ double4 rec[kBatchSubMax * kBatchChunk];
+  __shared__ double2 tab[F32 ? 1 : kTurnTable];
+  __shared__ int srep[kBatchSubMax], scnt[kBatchSubMax];
+  __shared__ int64_t sfirst[kBatchSubMax];
+  const int tid = threadIdx.x, P = a.P;
+  const int chunks = *a.rho_chunks, c0 = blockIdx.x * sub;
+  if (c0 >= chunks) return;  // uniform over the block
+  if (!F32) tab[tid] = turn_tab[tid];
+  if (tid < sub) {
+    // replica of the chunk: the last r with chunk_off <= c
+    const int c = c0 + tid;
+    int lo = 0, hi = a.nrep - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (reps[mid].chunk_off <= c) lo = mid;
+      else hi = mid - 1;
+    }
+    const int first = (c - reps[lo].chunk_off) * kBatchChunk;
+    srep[tid] = lo;
+    scnt[tid] = c < chunks ? min(reps[lo].nq - first, kBatchChunk) : 0;
+    sfirst[tid] = reps[lo].p0 + first;
+  }
+  __syncthreads();
+  for (int u = tid; u < sub * kBatchChunk; u += kBatchThreads) {
+    const int s = u / kBatchChunk, v = u % kBatchChunk;
+    if (v < scnt[s]) rec[u] = sq[sfirst[s] + v];
+  }
+  __syncthreads();
+  for (int it = tid; it < sub * P; it += kBatchThreads) {
+    const int s = it / P, l = it % P;
+    const int cnt = scnt[s];
+    if (cnt <= 0) continue;
+    const GatherMode &gm = modes[(int64_t)srep[s] * P + l];
+    const double mx = gm.mx, my = gm.my, mz = gm.mz;
+    const double4 *p = rec + s * kBatchChunk;
+    double2 out;
+    if (F32) {
+      float re = 0.f, rc = 0.f, im = 0.f, ic = 0.f;
+#pragma unroll 4
+      for (int j = 0; j < cnt; ++j) {
+        const double4 v = p[j];
+        const float t = turn_f32(mx, my, mz, v.x, v.y, v.z);
+        const float q = (float)v.w;
+        kahan_fma(re, rc, q, __builtin_amdgcn_cosf(t));
+        kahan_fma(im, ic, q, __builtin_amdgcn_sinf(t));
+      }
+      out = make_double2((double)re - (double)rc, (double)im - (double)ic);
+    } else {
+      double re = 0.0, im = 0.0;
+#pragma unroll 4
+      for (int j = 0; j < cnt; ++j) {
+        const double4 v = p[j];
+        double sn, cs;
+        sincos_turn_tab_f64(turn_fraction(mx, my, mz, v.x, v.y, v.z), tab, &sn, &cs);
+        re = fma(v.w, cs, re);
+        im = fma(v.w, sn, im);
+      }
+      out = make_double2(re, im);
+    }
+    a.part[(int64_t)(c0 + s) * P + l] = out;
+  }
 }
 
-void launch_batch_step(int prec, int blocks, const BatchArgs &a, hipStream_t st) {
-  BatchArgs a1 = a, a2 = a;
-  a1.launch_part = 1;
-  a2.launch_part = 2;
+// One wave per (replica, mode): the chunk partials in a fixed order, and the
+// gather coefficients.
+__global__ void __launch_bounds__(kBatchThreads) k_batch_rho_final(BatchArgs a) {
+  const int64_t it = (blockIdx.x * (int64_t)kBatchThreads + threadIdx.x) >> 6;
+  if (it >= (int64_t)a.nrep * a.P) return;
+  const int lane = threadIdx.x & 63, P = a.P;
+  const int r = (int)(it / P), l = (int)(it % P);
+  const RepDesc &R = a.reps[r];
+  double re = 0.0, im = 0.0;
+  for (int c = lane; c < R.nchunks; c += 64) {
+    const double2 v = a.part[(int64_t)(R.chunk_off + c) * P + l];
+    re += v.x;
+    im += v.y;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    re += __shfl_xor(re, o, 64);
+    im += __shfl_xor(im, o, 64);
+  }
+  if (lane == 0) {
+    const double w = a.pp.kc * a.wk[it];
+    GatherMode &gm = a.modes[it];
+    gm.a = w * im;
+    gm.b = w * re;
+    gm.af = (float)(w * im);
+    gm.bf = (float)(w * re);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Fourier gather + second half-kick
+// ---------------------------------------------------------------------------
+// Sum over the modes md of one particle at s: (g_x, g_y, g_z) of F^F = -q (2
+// pi / L) g.
+template <bool F32>
+__device__ inline void batch_gather_sum(const GatherMode *__restrict__ md, int P, const double4 &s,
+                                        const double2 *tab, double g[3]) {
+  if (F32) {
+    float gx = 0.f, gy = 0.f, gz = 0.f, ex = 0.f, ey = 0.f, ez = 0.f;
+#pragma unroll 4
+    for (int l = 0; l < P; ++l) {
+      const GatherMode gm = md[l];
+      const float t = turn_f32(gm.mx, gm.my, gm.mz, s.x, s.y, s.z);
+      const float h = fmaf(gm.af, __builtin_amdgcn_cosf(t), -gm.bf * __builtin_amdgcn_sinf(t));
+      kahan_fma(gx, ex, h, gm.mxf);
+      kahan_fma(gy, ey, h, gm.myf);
+      kahan_fma(gz, ez, h, gm.mzf);
+    }
+    g[0] = (double)gx - (double)ex;
+    g[1] = (double)gy - (double)ey;
+    g[2] = (double)gz - (double)ez;
+  } else {
+    double gx = 0.0, gy = 0.0, gz = 0.0;
+#pragma unroll 4
+    for (int l = 0; l < P; ++l) {
+      const GatherMode gm = md[l];
+      double sn, cs;
+      sincos_turn_tab_f64(turn_fraction(gm.mx, gm.my, gm.mz, s.x, s.y, s.z), tab, &sn, &cs);
+      const double h = gm.a * cs - gm.b * sn;
+      gx = fma(h, gm.mx, gx);
+      gy = fma(h, gm.my, gy);
+      gz = fma(h, gm.mz, gz);
+    }
+    g[0] = gx;
+    g[1] = gy;
+    g[2] = gz;
+  }
+}
+
+template <bool F32>
+__global__ void __launch_bounds__(kBatchThreads) k_batch_gather(BatchArgs a, const GatherMode *__restrict__ modes,
+                                                                const double2 *__restrict__ turn_tab) {
+  __shared__ double2 tab[F32 ? 1 : kTurnTable];
+  if (!F32) {
+    tab[threadIdx.x] = turn_tab[threadIdx.x];
+    __syncthreads();
+  }
+  const int64_t i = blockIdx.x * (int64_t)kBatchThreads + threadIdx.x;
+  if (i >= a.ntot) return;
+  const int r = a.rep_of[i];
+  const RepDesc &R = a.reps[r];
+  double fx = a.ofx[i], fy = a.ofy[i], fz = a.ofz[i];
+  if (a.do_far && i < R.p0 + R.nq) {
+    const double4 s = a.sq[i];
+    double g[3];
+    // a wave inside one replica reads its modes as scalars
+    const int r0 = __builtin_amdgcn_readfirstlane(r);
+    if (__all(r == r0)) batch_gather_sum<F32>(modes + (int64_t)r0 * a.P, a.P, s, tab, g);
+    else batch_gather_sum<F32>(modes + (int64_t)r * a.P, a.P, s, tab, g);
+    fx -= s.w * (kTwoPi / R.g.L[0]) * g[0];
+    fy -= s.w * (kTwoPi / R.g.L[1]) * g[1];
+    fz -= s.w * (kTwoPi / R.g.L[2]) * g[2];
+  }
+  if (a.mode == 0) {
+    a.ofx[i] = fx;
+    a.ofy[i] = fy;
+    a.ofz[i] = fz;
+    const double u = a.ovx[i] + a.h * fx, v = a.ovy[i] + a.h * fy, w = a.ovz[i] + a.h * fz;
+    a.ovx[i] = u;
+    a.ovy[i] = v;
+    a.ovz[i] = w;
+    if (!isfinite(u) || !isfinite(v) || !isfinite(w)) atomicOr(a.err, kErrNonFinite);
+  } else {
+    const int j = a.perm[i];
+    a.cfx[j] = fx;
+    a.cfy[j] = fy;
+    a.cfz[j] = fz;
+  }
+}
+
+void launch_batch_step(int prec, const BatchArgs &a, uint64_t eval, hipStream_t st) {
+  const unsigned nb = (unsigned)((a.ntot + kBatchThreads - 1) / kBatchThreads);
+  const int64_t nm = (int64_t)a.nrep * a.P;
+  const unsigned mb = a.do_far ? (unsigned)((nm + kBatchThreads - 1) / kBatchThreads) : 0u;
+  const bool f32 = prec == RBE_FP32C;
+  launch_fill_i32(a.bin.count, a.nkeys, 0, st);
+  k_batch_drift<<<nb + mb, kBatchThreads, 0, st>>>(a, eval, nb);
+  Grid keys{};
+  keys.ncell = (int)(a.nkeys / 2);  // every replica has 2 C_r keys
+  launch_bin_place(a.bin, keys, a.ntot, a.cell_start, a.perm, st);
+  k_batch_reorder<<<nb, kBatchThreads, 0, st>>>(a);
   unsigned near_blocks;
   const BatchKernel near = batch_near_kernel(prec, a.ntot, &near_blocks);
-  const BatchKernel step = prec == RBE_FP32C ? k_batch_step<true> : k_batch_step<false>;
-  step<<<blocks, kBatchThreads, 0, st>>>(a1);
   near<<<near_blocks, kBatchThreads, 0, st>>>(a);
-  step<<<blocks, kBatchThreads, 0, st>>>(a2);
-}
-
-int batch_scan_tiles(int64_t nkeys) { return (int)((nkeys + kScanTileB - 1) / kScanTileB); }
-
-hipError_t add_batch_node(hipGraph_t graph, hipGraphNode_t *node, const hipGraphNode_t *deps, int ndeps, int prec,
-                          int blocks, BatchArgs *a) {
-  BatchArgs parts[3] = {*a, *a, *a};
-  parts[0].launch_part = 1;
-  parts[2].launch_part = 2;
-  unsigned near_blocks;
-  const BatchKernel near = batch_near_kernel(prec, a->ntot, &near_blocks);
-  const BatchKernel step = prec == RBE_FP32C ? k_batch_step<true> : k_batch_step<false>;
-  void *funcs[3] = {reinterpret_cast<void *>(step), reinterpret_cast<void *>(near), reinterpret_cast<void *>(step)};
-  const unsigned grids[3] = {(unsigned)blocks, near_blocks, (unsigned)blocks};
-  hipGraphNode_t prev = nullptr;
-  for (int k = 0; k < 3; ++k) {
-    hipKernelNodeParams kp{};
-    kp.func = funcs[k];
-    kp.gridDim = dim3(grids[k]);
-    kp.blockDim = dim3(kBatchThreads);
-    kp.sharedMemBytes = 0;
-    void *args[] = {&parts[k]};
-    kp.kernelParams = args;
-    kp.extra = nullptr;
-    // the node copies the arguments
-    const hipGraphNode_t dep = prev;
-    const hipError_t e = k == 0 ? hipGraphAddKernelNode(&prev, graph, deps, (size_t)ndeps, &kp)
-                                : hipGraphAddKernelNode(&prev, graph, &dep, 1, &kp);
-    if (e != hipSuccess) return e;
+  if (a.do_far) {
+    int sub = a.P < kBatchThreads ? kBatchThreads / a.P : 1;
+    if (sub > kBatchSubMax) sub = kBatchSubMax;
+    const unsigned rb = (unsigned)((a.chunk_cap + sub - 1) / sub);
+    if (f32) k_batch_rho<true><<<rb, kBatchThreads, 0, st>>>(a, a.reps, a.sq, a.modes, a.turn_tab, sub);
+    else k_batch_rho<false><<<rb, kBatchThreads, 0, st>>>(a, a.reps, a.sq, a.modes, a.turn_tab, sub);
+    k_batch_rho_final<<<(unsigned)((nm * 64 + kBatchThreads - 1) / kBatchThreads), kBatchThreads, 0, st>>>(a);
   }
-  *node = prev;
-  return hipSuccess;
+  if (f32) k_batch_gather<true><<<nb, kBatchThreads, 0, st>>>(a, a.modes, a.turn_tab);
+  else k_batch_gather<false><<<nb, kBatchThreads, 0, st>>>(a, a.modes, a.turn_tab);
 }
 
-__global__ void __launch_bounds__(256) k_qstats_rep(const int64_t *__restrict__ off, const double *__restrict__ q,
-                                                    int32_t *__restrict__ nq, double *__restrict__ qs) {
-  __shared__ int lc[4];
-  __shared__ double ls[4], la[4];
+// ---------------------------------------------------------------------------
+// per-replica charge checks and layout
+// ---------------------------------------------------------------------------
+constexpr int kQstatThreads = 1024;
+__global__ void __launch_bounds__(kQstatThreads) k_qstats_rep(const int64_t *__restrict__ off,
+                                                              const double *__restrict__ q, int32_t *__restrict__ nq,
+                                                              double *__restrict__ qs) {
+  __shared__ int lc[kQstatThreads / 64];
+  __shared__ double ls[kQstatThreads / 64], la[kQstatThreads / 64];
   const int r = blockIdx.x;
   const int64_t lo = off[r], hi = off[r + 1];
   int c = 0;
   double s = 0.0, a = 0.0;
-  for (int64_t i = lo + threadIdx.x; i < hi; i += 256) {
+#pragma unroll 4
+  for (int64_t i = lo + threadIdx.x; i < hi; i += kQstatThreads) {
     const double v = q[i];
     c += v != 0.0;
     s += v;
@@ -607,59 +501,80 @@ __global__ void __launch_bounds__(256) k_qstats_rep(const int64_t *__restrict__ 
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    nq[r] = lc[0] + lc[1] + lc[2] + lc[3];
-    qs[2 * r] = (ls[0] + ls[1]) + (ls[2] + ls[3]);
-    qs[2 * r + 1] = (la[0] + la[1]) + (la[2] + la[3]);
+    c = 0;
+    s = a = 0.0;
+    for (int k = 0; k < kQstatThreads / 64; ++k) {
+      c += lc[k];
+      s += ls[k];
+      a += la[k];
+    }
+    nq[r] = c;
+    qs[2 * r] = s;
+    qs[2 * r + 1] = a;
   }
 }
 
 void launch_qstats_rep(int nrep, const int64_t *off, const double *q, int32_t *nq, double *qs, hipStream_t st) {
-  k_qstats_rep<<<nrep, 256, 0, st>>>(off, q, nq, qs);
+  k_qstats_rep<<<nrep, kQstatThreads, 0, st>>>(off, q, nq, qs);
 }
 
 // Per-replica checks of Eq. 1 (flags kErrNonNeutral / kErrNonFinite) and the
 // structure-factor layout of this call from the device counts: replica r's
-// charged particles in chunks of chunk_len, its chunk partials at chunk_off,
-// its (chunk, 64-mode group) items at rho_item_off; *rho_items receives the
-// total, *bad_rep the first replica that failed a check (-1: none). One
-// thread: the replica count is small.
-__global__ void k_batch_layout(int nrep, const int32_t *__restrict__ nq, const double *__restrict__ qs, int groups,
-                               int chunk_len, RepDesc *__restrict__ reps, int *__restrict__ rho_items,
-                               int *__restrict__ bad_rep, int *err) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int chunk_off = 0;
-  int64_t items = 0;
-  int flags = 0, bad = -1;
-  for (int r = 0; r < nrep; ++r) {
-    const double sq = qs[2 * r], sa = qs[2 * r + 1];
-    int f = 0;
-    if (!isfinite(sq) || !isfinite(sa)) f = kErrNonFinite;
-    else if (fabs(sq) > 1e-10 * fmax(sa, 1e-300) && fabs(sq) > 1e-12) f = kErrNonNeutral;
-    if (f && bad < 0) bad = r;
-    flags |= f;
-    RepDesc &d = reps[r];
-    d.nq = nq[r];
-    d.chunk_len = chunk_len;
-    d.nchunks = (d.nq + chunk_len - 1) / chunk_len;
-    d.chunk_off = chunk_off;
-    d.rho_item_off = (int)items;
-    chunk_off += d.nchunks;
-    items += (int64_t)d.nchunks * groups;
+// charged particles in chunks of kBatchChunk, its chunk partials at chunk_off;
+// *rho_chunks receives the total, *bad_rep the first replica that failed a
+// check (-1: none). One block, 256 replicas at a time.
+__global__ void __launch_bounds__(256) k_batch_layout(int nrep, const int32_t *__restrict__ nq,
+                                                      const double *__restrict__ qs, RepDesc *__restrict__ reps,
+                                                      int *__restrict__ rho_chunks, int *__restrict__ bad_rep,
+                                                      int *err) {
+  __shared__ int wsum[4], bad;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (threadIdx.x == 0) bad = 0x7FFFFFFF;
+  int carry = 0;
+  for (int b = 0; b < nrep; b += 256) {
+    const int r = b + threadIdx.x;
+    int chunks = 0, f = 0;
+    if (r < nrep) {
+      const double sq = qs[2 * r], sa = qs[2 * r + 1];
+      if (!isfinite(sq) || !isfinite(sa)) f = kErrNonFinite;
+      else if (fabs(sq) > 1e-10 * fmax(sa, 1e-300) && fabs(sq) > 1e-12) f = kErrNonNeutral;
+      chunks = (nq[r] + kBatchChunk - 1) / kBatchChunk;
+    }
+    int incl = chunks;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += t;
+    }
+    __syncthreads();  // wsum of the previous round is read
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    int off = carry;
+    for (int w = 0; w < 4; ++w) {
+      if (w < wave) off += wsum[w];
+      carry += wsum[w];
+    }
+    if (r < nrep) {
+      RepDesc &d = reps[r];
+      d.nq = nq[r];
+      d.nchunks = chunks;
+      d.chunk_off = off + incl - chunks;
+      if (f) {
+        atomicOr(err, f);
+        atomicMin(&bad, r);
+      }
+    }
   }
-  *rho_items = (int)items;
-  *bad_rep = bad;
-  if (flags) atomicOr(err, flags);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    *rho_chunks = carry;
+    *bad_rep = bad == 0x7FFFFFFF ? -1 : bad;
+  }
 }
 
-void launch_batch_layout(int nrep, const int32_t *nq, const double *qs, int P, int chunk_len, RepDesc *reps,
-                         int *rho_items, int *bad_rep, int *err, hipStream_t st) {
-  k_batch_layout<<<1, 64, 0, st>>>(nrep, nq, qs, (P + 63) / 64, chunk_len, reps, rho_items, bad_rep, err);
+void launch_batch_layout(int nrep, const int32_t *nq, const double *qs, RepDesc *reps, int *rho_chunks, int *bad_rep,
+                         int *err, hipStream_t st) {
+  k_batch_layout<<<1, 256, 0, st>>>(nrep, nq, qs, reps, rho_chunks, bad_rep, err);
 }
-
-__global__ void k_set_u64(uint64_t *p, uint64_t v) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *p = v;
-}
-
-void launch_set_u64(uint64_t *p, uint64_t v, hipStream_t st) { k_set_u64<<<1, 64, 0, st>>>(p, v); }
 
 }  // namespace rbe

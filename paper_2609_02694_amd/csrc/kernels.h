@@ -300,7 +300,7 @@ struct StateArrays {
 };
 
 // ---------------------------------------------------------------------------
-// batched form (many replicas, one persistent launch per step)
+// batched form (many replicas, one launch per pass over all of them)
 // ---------------------------------------------------------------------------
 struct RepDesc {
   Grid g;
@@ -311,11 +311,11 @@ struct RepDesc {
   int cdf_off;
   uint64_t seed;
   int nq;              // charged particles (the first nq of the replica's sorted range)
-  int chunk_len;       // structure-factor chunk length
-  int nchunks;         // chunks of this replica
-  int chunk_off;       // first chunk of this replica in the partial array
-  int rho_item_off;    // first structure-factor item of this replica
+  int nchunks;         // structure-factor chunks of this replica
+  int chunk_off;       // its first chunk in the partial array
 };
+// Structure-factor chunk length of the batched form (charged particles per partial sum).
+constexpr int kBatchChunk = 128;
 
 struct BatchArgs {
   int nrep;
@@ -323,11 +323,10 @@ struct BatchArgs {
   const int32_t *rep_of;  // replica of every particle slot
   int64_t ntot;
   int64_t nkeys;
-  int ntiles;
   int P;
   int mode;               // 0: step, 1: force evaluation only
-  int launch_part;        // launch of the step: 1 phases P0-P6, 2 phases P7-P9 (set by the launchers)
-  const int *rho_items;   // total structure-factor items (chunk x 64-mode group), on the device
+  const int *rho_chunks;  // structure-factor chunks of all replicas, on the device
+  int64_t chunk_cap;      // their bound (every particle charged)
   int do_far;             // Fourier part on
   PairParams pp;          // physics shared by all replicas (grid fields unused)
   PairF32 pf;
@@ -342,35 +341,26 @@ struct BatchArgs {
   uint2 *pk;                // packed positions (FP64; nullptr in FP32C)
   double pk_scale;
   uint32_t t2_q, t2_lj;     // squared reaches in their units
-  int32_t *sid;
-  int32_t *key, *slot, *tmp, *perm, *count, *cell_start, *tile_sum;
+  BinBuffers bin;
+  int32_t *perm, *cell_start;
+  const double2 *turn_tab;  // FP64 turn table
   const double *cdf;
   GatherMode *modes;      // [nrep * P]
   double *wk;             // [nrep * P] mode weights
   double2 *part;          // [total chunks * P]
   int *err;
-  unsigned *bar;          // [2] arrival count, generation
-  uint64_t *eval;         // evaluation index of the step (advanced by the kernel)
 };
 
-// Resident capacity of the step kernel (blocks), the launch, and the scan tiling.
-int batch_grid_blocks(int prec, int device);
-void launch_batch_step(int prec, int blocks, const BatchArgs &a, hipStream_t st);
-int batch_scan_tiles(int64_t nkeys);
-// Adds one step to `graph`: the first part of the step kernel, the near-field
-// kernel and the second part, chained; *node is the last (the nodes copy *a).
-hipError_t add_batch_node(hipGraph_t graph, hipGraphNode_t *node, const hipGraphNode_t *deps, int ndeps, int prec,
-                          int blocks, BatchArgs *a);
+// One step (mode 0) or force evaluation (mode 1) of every replica.
+void launch_batch_step(int prec, const BatchArgs &a, uint64_t eval, hipStream_t st);
 // Per-replica charge statistics: nq[r] charged count, qs[2r] = sum q, qs[2r+1] = sum |q|.
 void launch_qstats_rep(int nrep, const int64_t *off, const double *q, int32_t *nq, double *qs, hipStream_t st);
 // Checks of Eq. 1 per replica (device error flags) and the structure-factor
-// layout of every replica from the device counts (writes the nq, chunk and
-// item fields of reps[] on the device, the item total and the first replica
-// that failed a check, -1 if none).
-void launch_batch_layout(int nrep, const int32_t *nq, const double *qs, int P, int chunk_len, RepDesc *reps,
-                         int *rho_items, int *bad_rep, int *err, hipStream_t st);
-// *p = v on the stream (a kernel, so graph capture records no memset node).
-void launch_set_u64(uint64_t *p, uint64_t v, hipStream_t st);
+// layout of every replica from the device counts (writes the nq and chunk
+// fields of reps[] on the device, the chunk total and the first replica that
+// failed a check, -1 if none).
+void launch_batch_layout(int nrep, const int32_t *nq, const double *qs, RepDesc *reps, int *rho_chunks, int *bad_rep,
+                         int *err, hipStream_t st);
 
 // Error of a call without a context: the message rbe_last_error(NULL)
 // returns, and the status code passed through.
