@@ -403,7 +403,7 @@ extern "C" int rbe_create(rbe_ctx **out, const rbe_params *p, int64_t n_max, int
   c->srt.sq = b.alloc<double4>(n_max);
   c->srt.id = b.alloc<int32_t>(n_max + kScanPad);
   if (p->prec == RBE_FP64) c->srt.pk = b.alloc<uint2>(n_max + kScanPad);
-  c->srt.pk_scale = pack_scale(std::fmax(p->r_coul, p->r_lj));
+  c->srt.pk_scale = pack_scale(std::fmax(p->r_coul, p->r_lj), std::fmax(g.h[0], std::fmax(g.h[1], g.h[2])));
   for (int s = 0; s < 2; ++s) {
     WorkSet &w = c->ws[s];
     w.x = b.alloc<double>(n_max);
@@ -537,6 +537,7 @@ extern "C" int rbe_create_batch(rbe_ctx **out, int32_t n_sys, const rbe_params *
   c->n_max = B.ntot;
   std::vector<double> cdf_all;
   int64_t key0 = 0, chunks = 0;
+  double edge = 0.0;  // largest cell edge
   B.reps.resize(n_sys);
   for (int32_t r = 0; r < n_sys; ++r) {
     rbe_params pr = params[r];
@@ -550,6 +551,7 @@ extern "C" int rbe_create_batch(rbe_ctx **out, int32_t n_sys, const rbe_params *
     RepDesc &d = B.reps[r];
     d = RepDesc{};
     d.g = make_grid(pr, nc);
+    for (int k = 0; k < 3; ++k) edge = std::fmax(edge, d.g.h[k]);
     PairParams pr_pp;
     make_pair_params(pr, d.g, &pr_pp);
     d.s_coul = pr_pp.s_coul;
@@ -597,7 +599,7 @@ extern "C" int rbe_create_batch(rbe_ctx **out, int32_t n_sys, const rbe_params *
   c->srt.xq = b.alloc<double4>(n + kScanPad);
   c->srt.sq = b.alloc<double4>(n);
   if (c->p.prec == RBE_FP64) c->srt.pk = b.alloc<uint2>(n + kScanPad);
-  c->srt.pk_scale = pack_scale(std::fmax(c->p.r_coul, c->p.r_lj));
+  c->srt.pk_scale = pack_scale(std::fmax(c->p.r_coul, c->p.r_lj), edge);
   c->perm = b.alloc<int32_t>(n);
   c->cell_start = b.alloc<int32_t>(B.nkeys + 1);
   c->cdf_dev = b.alloc<double>((int64_t)cdf_all.size());
@@ -1523,6 +1525,8 @@ extern "C" int rbe_forces_noalloc(const rbe_params *p, const rbe_state *s, const
   c.srt.xq = cv.take<double4>(n + kScanPad);
   c.srt.sq = cv.take<double4>(n);
   c.srt.id = cv.take<int32_t>(n + kScanPad);
+  if (p->prec == RBE_FP64) c.srt.pk = cv.take<uint2>(n + kScanPad);
+  c.srt.pk_scale = pack_scale(std::fmax(p->r_coul, p->r_lj), std::fmax(c.g.h[0], std::fmax(c.g.h[1], c.g.h[2])));
   c.ws[1].fx = cv.take<double>(n);
   c.ws[1].fy = cv.take<double>(n);
   c.ws[1].fz = cv.take<double>(n);

@@ -34,8 +34,7 @@ void launch_bin_place(const BinBuffers &b, const Grid &g, int64_t n, int32_t *ce
 //   sq[i] = (x/L_x, y/L_y, z/L_z, q) fractional coordinates (Fourier part,
 //           only the charged range [0, nq) is used)
 //   pk[i] = packed 16-bit positions (pack_position), the candidates of the
-//           FP64 queue walks; nullptr in FP32C and in the scratch-only form,
-//           whose sizes take other walks.
+//           FP64 queue walks and batch lists; nullptr in FP32C.
 struct Sorted {
   double4 *xq;
   double4 *sq;
@@ -45,12 +44,16 @@ struct Sorted {
 };
 
 // Positions on a 16-bit grid per axis, modulo its period: x | y << 16, z.
-// `scale` is 1 / period, the period four times the largest reach, so that a
-// difference of two packed coordinates (mod 2^16, signed) is that of the
-// positions in grid units to within one unit whenever the positions are less
-// than half a period apart, and whatever the box. Farther pairs alias, at
-// worst to a candidate that the exact test then rejects.
-__host__ __device__ inline double pack_scale(double reach) { return 0.25 / reach; }
+// `scale` is 1 / period. A difference of two packed coordinates (mod 2^16,
+// signed) is that of the positions in grid units to within one unit whenever
+// the positions are less than half a period apart, whatever the box; farther
+// ones alias. The period is four times the largest reach, and at least so long
+// that a candidate of a trimmed row (at most the reach and one cell edge away
+// along an axis) never aliases to within the reach.
+__host__ __device__ inline double pack_scale(double reach, double edge) {
+  const double period = 2.02 * (reach + edge);
+  return 1.0 / (period > 4.0 * reach ? period : 4.0 * reach);
+}
 __device__ inline uint2 pack_position(double x, double y, double z, double scale) {
   auto one = [&](double v) { return (uint32_t)(__builtin_amdgcn_fract(v * scale) * 65536.0) & 0xFFFFu; };
   return make_uint2(one(x) | (one(y) << 16), one(z));
@@ -60,6 +63,11 @@ __device__ inline uint2 pack_position(double x, double y, double z, double scale
 __host__ __device__ inline uint32_t pack_reach2(double r, double scale) {
   const double g = r * scale * 65536.0 + 1.75;
   return (uint32_t)(g * g) + 1u;
+}
+// Squared grid distance below which every pair is inside r.
+__host__ __device__ inline uint32_t pack_inside2(double r, double scale) {
+  const double g = r * scale * 65536.0 - 1.75;
+  return g > 0.0 ? (uint32_t)(g * g) : 0u;
 }
 // Gather the caller's arrays through perm into the packed sorted records
 // (id may be nullptr: then s.id is left as it is).

@@ -61,6 +61,9 @@ struct PairCtx {
   const uint2 *__restrict__ gpk;
   double pk_scale;
   uint32_t t2_q, t2_lj;  // max(r_coul, r_lj), r_lj
+  // random batch list: no pair outside r_coul up to t2_out, every one inside
+  // it below t2_in; no pair inside r_core above t2_core
+  uint32_t t2_out, t2_in, t2_core;
 };
 
 // Cluster walk of one species block for a row group.
@@ -477,6 +480,231 @@ __global__ void __launch_bounds__(64, 5) k_pair_rbl(PairCtx c) {
   flush_counts<COUNT>(c, n_coul, n_lj, n_tested, I.b == 0 && I.valid ? (unsigned long long)m : 0ull);
 }
 
+// Random batch list, FP64 group form: G lanes per particle (pair_device.h,
+// group walks). The candidates are read as packed positions and ids, 12 bytes
+// each, and classified by integer distances: sure shell members are counted
+// and keyed without their FP64 record; those in the core, or within the grid's
+// rounding of either radius, go to a list that is classified exactly and
+// evaluated G at a time. Counts, places and the batch selection are ballots,
+// so nothing is atomic: the batch is the keys below a threshold that is moved
+// until exactly `need` lie below it.
+// Bound by issue: the key hash and the ballots' bookkeeping, about 80
+// instructions a trip; the cluster form spends 35 per candidate on a stencil
+// that holds 4.3 candidates per shell member, the trimmed rows about 2. What
+// it gains is the lanes: 20,000 electrolyte 250 -> 73 us, 1M 1.40 -> 1.35 ms.
+template <int G>
+struct RblLists {
+  uint2 near[kGroupList<G> + G];  // records to classify exactly: index, row code (sign bit: ghost)
+  uint32_t key[kShellCap];        // shell keys below the threshold
+  uint32_t sel[RBE_MAX_SHELL_BATCH];
+};
+template <bool COUNT, bool GHOST, bool QSHELL, int G>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_pair_rbl_group(PairCtx c) {
+  __shared__ GroupRows<G> rows_lds[256 / G];
+  __shared__ RblLists<G> lists[256 / G];
+  const int64_t nq = *c.nq_ptr;
+  const int64_t a = c.charged ? 0 : nq, end = c.charged ? nq : c.n;
+  const int64_t per = (end - a + gridDim.x - 1) / gridDim.x;  // consecutive particles per block
+  const int64_t first = a + xcd_block(blockIdx.x, gridDim.x) * per, last = min(end, first + per);
+  const int sub = threadIdx.x & (G - 1);
+  GroupRows<G> &rows = rows_lds[threadIdx.x / G];
+  RblLists<G> &Ls = lists[threadIdx.x / G];
+  const PairParams &pp = c.pp;
+  const Grid &g = pp.g;
+  const int p = pp.p_shell;
+  unsigned long long n_coul = 0, n_lj = 0, n_tested = 0, n_shell = 0;
+  for (int64_t i = first + threadIdx.x / G; i < last; i += 256 / G) {  // the lanes of a group together
+    const double4 pi = c.xq[i];
+    const ShellKey sk = shell_key_of(pp.shell_key, c.ids[i]);
+    const uint2 home = pack_position(pi.x, pi.y, pi.z, c.pk_scale);
+    ForceAcc<false> acc;
+    uint64_t T = QSHELL ? shell_first_threshold(pp, *c.nq_ptr) : pp.shell_T0, lo = 0, hi = 1ull << 32;
+    int m = 0, got = 0, need = 0;  // the same in all lanes of the group
+    struct Cand {
+      uint2 pk;
+      int id;
+    };
+    // keys of the lanes with `in` that lie below T join the list
+    auto collect = [&](bool in, uint32_t key) {
+      const bool take = in & (key <= (uint32_t)(T - 1));  // 0 < T <= 2^32
+      const uint64_t who = group_ballot<G>(take);
+      const int at = got + bits_below<G>(who);
+      if (take & (at < kShellCap)) Ls.key[at] = key;
+      got += __popcll(who);
+    };
+    // with a charged-only shell the neutral block matters inside the core only
+    // (r_lj <= r_core)
+    const Block A{pp.s_coul, pp.rc2};
+    const Block B = QSHELL ? Block{pp.s_core, fmax(pp.rcore2, pp.rlj2)} : A;
+    for (int round = 0; round < 40; ++round) {
+      // round 0 sums the core, counts the shell and collects its keys; the
+      // rounds after it (the list missed [need, kShellCap]; rare) collect only
+      int nn = 0;
+      got = 0;
+      auto classify = [&](int from, int cnt) {
+        wave_sync();
+        bool shell = false;
+        uint32_t key = 0;
+        if (sub < cnt) {
+          const uint2 e = Ls.near[from + sub];
+          const bool ghost = GHOST && (int)e.y < 0;
+          const int j = (int)e.x, code = (int)(e.y & 0x7FFFFFFFu);
+          const double4 pj = ghost ? c.gxq[j] : c.xq[j];
+          double dx = pi.x - pj.x, dy = pi.y - pj.y, dz = pi.z - pj.z;
+          if (!GHOST && code > 1) {
+            dx -= row_shift(code, 0) * g.L[0];
+            dy -= row_shift(code, 1) * g.L[1];
+            dz -= row_shift(code, 2) * g.L[2];
+          }
+          const double r2 = sq_dist(dx, dy, dz);
+          const bool live = ghost || j != (int)i;
+          if (live && r2 <= pp.rcore2) {
+            if (round == 0) {
+              acc.template add<true, true>(pp, c.pf, r2, pi.w, pj.w, dx, dy, dz);
+              if (COUNT) {
+                n_coul += (pp.do_coul && pi.w != 0.0 && pj.w != 0.0);
+                n_lj += (pp.do_lj && r2 <= pp.rlj2);
+              }
+            }
+          } else if (live && r2 <= pp.rc2 && (!QSHELL || pj.w != 0.0)) {
+            shell = true;
+            key = shell_rank(sk, ghost ? c.gid[j] : c.ids[j]);
+          }
+        }
+        if (round == 0) m += __popcll(group_ballot<G>(shell));
+        collect(shell, key);
+        wave_sync();
+      };
+      group_list<G, GHOST, 2>(
+          g, c.cell_start, c.gcell_start, pi, A, B, rows,
+          [&](int j, bool ghost) {
+            return Cand{ghost ? c.gpk[j] : c.pk[j], ghost ? c.gid[j] : c.ids[j]};
+          },
+          [&](bool ok, int, int j, int code, bool ghost, bool shifted, const Cand &f) {
+            uint2 own = home;
+            if (shifted && code > 1)
+              own = pack_position(pi.x - row_shift(code, 0) * g.L[0], pi.y - row_shift(code, 1) * g.L[1],
+                                  pi.z - row_shift(code, 2) * g.L[2], c.pk_scale);
+            const uint32_t d2 = packed_dist2(own.x, own.y, f.pk.x, f.pk.y);
+            if (COUNT) n_tested += ok && round == 0;
+            const bool in = ok & (d2 <= c.t2_out);
+            const bool sure = in & (d2 > c.t2_core) & (d2 < c.t2_in);
+            // (QSHELL: a neutral record beyond the core is no shell member)
+            const bool shell = sure & (!QSHELL | ((code & 1) == 0));
+            const uint64_t who = group_ballot<G>(in & !sure);
+            if (who) {
+              if (in & !sure)
+                Ls.near[nn + bits_below<G>(who)] = make_uint2((uint32_t)j, (uint32_t)code | (ghost ? 0x80000000u : 0u));
+              nn += __popcll(who);
+            }
+            if (round == 0) m += __popcll(group_ballot<G>(shell));
+            collect(shell, shell_rank(sk, f.id));
+          },
+          [&](int, int) {
+            // whole batches of the chunk's records; the rest joins the next chunk's
+            int done = 0;
+            for (; nn - done >= G; done += G) classify(done, G);
+            if (done) {
+              const uint2 rest = Ls.near[done + sub];
+              nn -= done;
+              wave_sync();
+              if (sub < nn) Ls.near[sub] = rest;
+              wave_sync();
+            }
+          },
+          [](uint64_t) {});
+      classify(0, nn);
+      if (round == 0) need = min(m, p);
+      if (need == 0 || (got >= need && got <= kShellCap)) break;
+      // bisection on T (distinct keys end it within 33 rounds; the bound only
+      // guards against duplicate ids, which the inverse id map reports)
+      if (got < need) lo = T;
+      else hi = T;
+      T = m <= kShellCap ? 1ull << 32 : lo + (hi - lo) / 2;
+    }
+    // the `need` smallest of the keys: those below X
+    got = min(got, kShellCap);
+    const int nb = min(need, got);  // = need unless ids repeat
+    constexpr int KL = kShellCap / G;  // keys per lane
+    wave_sync();
+    uint32_t mine[KL];
+    bool held[KL];
+#pragma unroll
+    for (int u = 0; u < KL; ++u) {
+      held[u] = sub + G * u < got;
+      mine[u] = held[u] ? Ls.key[sub + G * u] : 0u;
+    }
+    auto count_below = [&](uint64_t X) {
+      int n = 0;
+#pragma unroll
+      for (int u = 0; u < KL; ++u) n += __popcll(group_ballot<G>(held[u] && (uint64_t)mine[u] < X));
+      return n;
+    };
+    // `need` of them lie below X: found by interpolation (the keys are uniform
+    // below T), with every other step a bisection so that it ends in any case
+    uint64_t X = T;
+    if (got > nb) {
+      uint64_t xl = 0, xh = T;
+      int nl = 0, nh = got;
+      for (int k = 0; k < 66 && xh - xl > 1; ++k) {
+        const uint64_t w = xh - xl;
+        X = xl + ((k & 1) ? w / 2 : (uint64_t)((float)w * ((float)(nb - nl) / (float)(nh - nl))));
+        if (X <= xl) X = xl + 1;
+        if (X >= xh) X = xh - 1;
+        const int n = count_below(X);
+        if (n == nb) break;
+        if (n < nb) {
+          xl = X;
+          nl = n;
+        } else {
+          xh = X;
+          nh = n;
+        }
+        X = xh;
+      }
+    }
+    int at = 0;
+#pragma unroll
+    for (int u = 0; u < KL; ++u) {
+      const bool in = held[u] && (uint64_t)mine[u] < X;
+      const uint64_t who = group_ballot<G>(in);
+      const int k = at + bits_below<G>(who);
+      if (in && k < nb) Ls.sel[k] = mine[u];
+      at += __popcll(who);
+    }
+    wave_sync();
+    ForceAcc<false> sh;
+    for (int r = sub; r < nb; r += G) {
+      const int32_t idj = shell_id_of(sk, Ls.sel[r]);
+      if ((uint32_t)idj >= (uint32_t)c.n) continue;  // bad ids (flagged by the inverse map)
+      const int j = c.inv_id[idj];
+      if ((uint32_t)j >= (uint32_t)c.n) continue;
+      const double4 pj = c.xq[j];
+      const double dx = min_image(pi.x - pj.x, g.L[0]);
+      const double dy = min_image(pi.y - pj.y, g.L[1]);
+      const double dz = min_image(pi.z - pj.z, g.L[2]);
+      const double r2 = sq_dist(dx, dy, dz);
+      sh.template add<true, true>(pp, c.pf, r2, pi.w, pj.w, dx, dy, dz);
+      if (COUNT) {
+        n_coul += (pp.do_coul && pi.w != 0.0 && pj.w != 0.0);
+        n_lj += (pp.do_lj && r2 <= pp.rlj2);
+      }
+    }
+    // f = core + (#S_i / |B_i|) shell
+    const double scale = nb > 0 ? (double)m / (double)nb : 0.0;
+    const double f0 = group_sum<G>(fma(scale, sh.get(0), acc.get(0))),
+                 f1 = group_sum<G>(fma(scale, sh.get(1), acc.get(1))),
+                 f2 = group_sum<G>(fma(scale, sh.get(2), acc.get(2)));
+    if (sub == 0) {
+      c.fx[i] = f0;
+      c.fy[i] = f1;
+      c.fz[i] = f2;
+    }
+    if (sub == 0) n_shell += (unsigned long long)m;
+  }
+  flush_counts<COUNT>(c, n_coul, n_lj, n_tested, n_shell);
+}
+
 PairF32 make_pair_f32(const PairParams &pp) {
   PairF32 pf;
   pf.sqrt_alpha = (float)pp.sqrt_alpha;
@@ -488,12 +716,24 @@ PairF32 make_pair_f32(const PairParams &pp) {
   return pf;
 }
 
-// Cluster form: one wave of kCI particles per block. Grids cover all n
-// particles (the part's range is read on the device; surplus blocks exit at
-// once).
-template <class K>
-static void launch_clusters(K kernel, PairCtx c, hipStream_t st) {
-  kernel<<<(unsigned)((c.n + kCI - 1) / kCI), 64, 0, st>>>(c);
+// Random batch list of a part. FP32C: the cluster form, whose lanes add their
+// terms in its own order. FP64: the group form, 64 lanes per particle, or 32
+// where the mean shell would leave most of 64 without a candidate, up to the
+// size from which the cluster form's waves fill the chip (group / cluster):
+// wide shells 200,000 electrolyte 319 / 453 us, 1M 1.35 / 1.39 ms, 2M 2.62 /
+// 2.49; narrow ones 20,000 LJ electrolyte 32 / 43 us, 50,000 78 / 72, 200,000
+// 236 / 186.
+constexpr double kRblWide = 48.0;  // particles within r_coul of one, on average
+constexpr int64_t kRblGroupWide = 1 << 20, kRblGroupNarrow = 32768;
+template <bool F32, bool COUNT, bool GHOST, bool QSHELL>
+static void launch_rbl(PairCtx c, hipStream_t st) {
+  const Grid &g = c.pp.g;
+  const double r = std::sqrt(c.pp.rc2);
+  const bool wide = (double)c.n / (g.L[0] * g.L[1] * g.L[2]) * (4.0 / 3.0) * kPi * r * r * r >= kRblWide;
+  if (F32 || c.n > (wide ? kRblGroupWide : kRblGroupNarrow))
+    k_pair_rbl<F32, COUNT, GHOST, QSHELL><<<(unsigned)((c.n + kCI - 1) / kCI), 64, 0, st>>>(c);
+  else if (wide) k_pair_rbl_group<COUNT, GHOST, QSHELL, 64><<<group_blocks(c.n, 64), 256, 0, st>>>(c);
+  else k_pair_rbl_group<COUNT, GHOST, QSHELL, 32><<<group_blocks(c.n, 32), 256, 0, st>>>(c);
 }
 
 // Plain sums of a part (c.charged): one thread per particle, or a group of
@@ -526,8 +766,8 @@ static void launch_part(PairCtx c, int part, hipStream_t st) {
   const PairParams pp = c.pp;
   if (part == PAIR_PART_CHARGED) {
     c.charged = 1;
-    if (pp.rbl && pp.shell_charged) launch_clusters(k_pair_rbl<F32, COUNT, GHOST, true>, c, st);
-    else if (pp.rbl) launch_clusters(k_pair_rbl<F32, COUNT, GHOST, false>, c, st);
+    if (pp.rbl && pp.shell_charged) launch_rbl<F32, COUNT, GHOST, true>(c, st);
+    else if (pp.rbl) launch_rbl<F32, COUNT, GHOST, false>(c, st);
     else launch_plain<F32, COUNT, 1, GHOST>(c, st);
   } else if (part == PAIR_PART_COULOMB) {
     c.charged = 1;
@@ -535,7 +775,7 @@ static void launch_part(PairCtx c, int part, hipStream_t st) {
     if constexpr (F32) launch_plain<F32, COUNT, 2, GHOST>(c, st);  // the tile pass is FP32C
   } else if (part == PAIR_PART_NEUTRAL) {
     c.charged = 0;
-    if (pp.rbl && pp.rlj2 > pp.rcore2 && pp.do_lj) launch_clusters(k_pair_rbl<F32, COUNT, GHOST, false>, c, st);
+    if (pp.rbl && pp.rlj2 > pp.rcore2 && pp.do_lj) launch_rbl<F32, COUNT, GHOST, false>(c, st);
     else launch_plain<F32, COUNT, 0, GHOST>(c, st);
   } else if (part == PAIR_PART_BOTH) {
     c.charged = 2;
@@ -582,6 +822,9 @@ void launch_pair(int prec, int part, const PairParams &pp, int64_t n, const int3
   c.pk_scale = s.pk_scale;
   c.t2_q = pack_reach2(std::sqrt(pp.rq2), s.pk_scale);
   c.t2_lj = pack_reach2(std::sqrt(pp.rlj2), s.pk_scale);
+  c.t2_out = pack_reach2(std::sqrt(pp.rc2), s.pk_scale);
+  c.t2_in = pack_inside2(std::sqrt(pp.rc2), s.pk_scale);
+  c.t2_core = pack_reach2(std::sqrt(std::max(pp.rcore2, 0.0)), s.pk_scale);
   if (gb) launch_prec<true>(prec, c, part, st);
   else launch_prec<false>(prec, c, part, st);
 }

@@ -396,9 +396,16 @@ __device__ inline double group_sum(double v) {
 // The lanes of this lane's group for which v holds, as bits 0..G-1.
 template <int G>
 __device__ inline uint64_t group_ballot(bool v) {
-  const uint64_t b = __ballot(v);
+  const uint64_t b = __builtin_amdgcn_ballot_w64(v);
   if (G == 64) return b;
   return (b >> (threadIdx.x & 63 & ~(G - 1))) & ((1ull << (G & 63)) - 1ull);
+}
+
+// Bits of `who` (a group ballot) below this lane's place in its group.
+template <int G>
+__device__ inline int bits_below(uint64_t who) {
+  if (G == 64) return __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0));
+  return __popc((uint32_t)who & ((1u << (threadIdx.x & (G - 1))) - 1u));
 }
 
 // Particles of one species block to meet: its stencil and squared reach.
@@ -411,13 +418,13 @@ __device__ inline Block no_block() { return Block{Sten{0, -1, 0}, 0.0}; }
 
 // Candidates listed at a time, and the group's table of listed rows in LDS:
 // the first record of a row less its place in the list, its image shifts and
-// species block, and one bit per candidate that starts a row.
+// species block, and one bit per place, set if a row starts at the place after.
 template <int G>
 constexpr int kGroupList = 8 * G;
 template <int G>
 struct GroupRows {
   int base[G], code[G];
-  uint32_t starts[kGroupList<G> / 32];
+  alignas(8) uint32_t starts[kGroupList<G> / 32];
 };
 
 // The signed 10-bit field of v that starts at bit `at`.
@@ -437,18 +444,22 @@ __device__ inline void wave_sync() {
 // row by counting the start bits up to its own place. So all lanes stay busy
 // however short or uneven the rows are, and the walk's length is that of the
 // particle's whole neighbourhood divided by G, not of its longest row.
-// visit(ok, k, blk, j, p_j, dx, dy, dz, r^2) is called by the whole group; k
-// is the place in the listed chunk of kGroupList<G> (ok false: nothing there).
+// The whole group calls fetch(j, ghost) for record j of the natives or of the
+// ghosts (ghost: the same for all), for AHEAD (1 or 2) trips at a time so that
+// their loads are in flight together, then visit(ok, k, j, code, ghost,
+// shifted, fetched) for each: the row's code has its species block in bit 0, then its image
+// shifts (row_shift; shifted: some row of the piece has one); k is the place in
+// the listed chunk of kGroupList<G> (ok false: nothing there, and j the last
+// record listed).
 // listed(first, len) follows each chunk: this lane's row holds the places
 // [first, first + len) of it (len may be 0). rows_end(reached) follows each
 // round of G rows: the lanes whose rows the particle's reach touches.
-// GHOST: no periodic images, but the ghost arrays (indexed from nnat on).
-template <int G, bool GHOST, class Visit, class Listed, class RowsEnd>
-__device__ inline void group_walk(const Grid &g, const int32_t *__restrict__ cell_start,
-                                  const double4 *__restrict__ xq, const int32_t *__restrict__ gcell_start,
-                                  const double4 *__restrict__ gxq, int nnat, const double4 &pi, const Block &A,
-                                  const Block &B, GroupRows<G> &T, Visit &&visit, Listed &&listed,
-                                  RowsEnd &&rows_end) {
+// GHOST: no periodic images, but the ghost arrays.
+template <int G, bool GHOST, int AHEAD, class Fetch, class Visit, class Listed, class RowsEnd>
+__device__ inline void group_list(const Grid &g, const int32_t *__restrict__ cell_start,
+                                  const int32_t *__restrict__ gcell_start, const double4 &pi, const Block &A,
+                                  const Block &B, GroupRows<G> &T, Fetch &&fetch, Visit &&visit,
+                                  Listed &&listed, RowsEnd &&rows_end) {
   constexpr int CH = kGroupList<G>;
   const int sub = threadIdx.x & (G - 1);
   const int cx = cell_coord(pi.x, g.inv_h[0], g.nx), cy = cell_coord(pi.y, g.inv_h[1], g.ny),
@@ -529,36 +540,48 @@ __device__ inline void group_walk(const Grid &g, const int32_t *__restrict__ cel
       const uint64_t some = group_ballot<G>(len > 0);
       const bool shifted = !GHOST && group_ballot<G>(code != 0) != 0;
       if (len > 0) {
-        const int rank = __popcll(some & ((1ull << sub) - 1ull));
+        const int rank = bits_below<G>(some);
         T.base[rank] = j0 - start;
         T.code[rank] = code << 1 | blk;
       }
       for (int c0 = 0; c0 < total; c0 += CH) {
         if (sub < CH / 32) T.starts[sub] = 0;
         wave_sync();
-        if (len > 0 && start >= c0 && start < c0 + CH)
-          atomicOr(&T.starts[(start - c0) >> 5], 1u << ((start - c0) & 31));
+        if (len > 0 && start > c0 && start <= c0 + CH)
+          atomicOr(&T.starts[(start - 1 - c0) >> 5], 1u << ((start - 1 - c0) & 31));
         wave_sync();
-        int seen = c0 ? __popcll(group_ballot<G>(len > 0 && start < c0)) : 0;
+        // the row of the chunk's first place; a trip's row adds the starts before its place
+        int row0 = __popcll(group_ballot<G>(len > 0 && start <= c0)) - 1;
         const int cnt = min(CH, total - c0);
-        for (int k0 = 0; k0 < cnt; k0 += G) {
+        struct Place {
+          int k, j, code;
+          bool ok;
+        };
+        auto place = [&](int k0) {
           uint64_t bits;
-          if (G == 64) bits = (uint64_t)T.starts[k0 >> 5] | ((uint64_t)T.starts[(k0 >> 5) + 1] << 32);
+          if (G == 64) bits = *(const uint64_t *)&T.starts[k0 >> 5];
           else bits = (T.starts[k0 >> 5] >> (k0 & 31)) & (uint32_t)((1ull << (G & 63)) - 1ull);
-          const bool ok = k0 + sub < cnt;
-          // rows started up to and including this place; past the end any row serves
-          const int r = ok ? seen + __popcll(bits & ((2ull << sub) - 1ull)) - 1 : 0;
-          seen += __popcll(bits);
-          const int j = T.base[r] + (ok ? c0 + k0 + sub : 0);
-          const int cd = T.code[r];
-          const double4 p = GHOST && pass ? gxq[j] : xq[j];
-          double dx = pi.x - p.x, dy = pi.y - p.y, dz = pi.z - p.z;
-          if (shifted) {
-            dx -= (double)(bits10(cd, 21)) * g.L[0];
-            dy -= (double)(bits10(cd, 11)) * g.L[1];
-            dz -= (double)(bits10(cd, 1)) * g.L[2];
+          Place q;
+          q.k = k0 + sub;
+          q.ok = q.k < cnt;
+          const int r = row0 + bits_below<G>(bits);
+          row0 += __popcll(bits);
+          q.j = T.base[r] + c0 + min(q.k, cnt - 1);
+          q.code = T.code[r];
+          return q;
+        };
+        for (int k0 = 0; k0 < cnt; k0 += AHEAD * G) {
+          const bool ghost = GHOST && pass;
+          const Place a0 = place(k0);
+          const auto f0 = fetch(a0.j, ghost);
+          if (AHEAD == 2 && k0 + G < cnt) {
+            const Place a1 = place(k0 + G);
+            const auto f1 = fetch(a1.j, ghost);
+            visit(a0.ok, a0.k, a0.j, a0.code, ghost, shifted, f0);
+            visit(a1.ok, a1.k, a1.j, a1.code, ghost, shifted, f1);
+          } else {
+            visit(a0.ok, a0.k, a0.j, a0.code, ghost, shifted, f0);
           }
-          visit(ok, k0 + sub, cd & 1, GHOST && pass ? nnat + j : j, p, dx, dy, dz, sq_dist(dx, dy, dz));
         }
         wave_sync();
         const int first = max(start - c0, 0);
@@ -568,6 +591,31 @@ __device__ inline void group_walk(const Grid &g, const int32_t *__restrict__ cel
     }
     rows_end(reached);
   }
+}
+
+// Image shift (boxes) of a listed row's code along an axis.
+__device__ inline double row_shift(int code, int axis) { return (double)bits10(code, 21 - 10 * axis); }
+
+// The walk on FP64 records: visit(ok, k, blk, j, p_j, dx, dy, dz, r^2), ghosts
+// indexed from nnat on.
+template <int G, bool GHOST, class Visit, class Listed, class RowsEnd>
+__device__ inline void group_walk(const Grid &g, const int32_t *__restrict__ cell_start,
+                                  const double4 *__restrict__ xq, const int32_t *__restrict__ gcell_start,
+                                  const double4 *__restrict__ gxq, int nnat, const double4 &pi, const Block &A,
+                                  const Block &B, GroupRows<G> &T, Visit &&visit, Listed &&listed,
+                                  RowsEnd &&rows_end) {
+  group_list<G, GHOST, 1>(
+      g, cell_start, gcell_start, pi, A, B, T, [&](int j, bool ghost) { return ghost ? gxq[j] : xq[j]; },
+      [&](bool ok, int k, int j, int code, bool ghost, bool shifted, const double4 &p) {
+        double dx = pi.x - p.x, dy = pi.y - p.y, dz = pi.z - p.z;
+        if (shifted) {
+          dx -= row_shift(code, 0) * g.L[0];
+          dy -= row_shift(code, 1) * g.L[1];
+          dz -= row_shift(code, 2) * g.L[2];
+        }
+        visit(ok, k, code & 1, ghost ? nnat + j : j, p, dx, dy, dz, sq_dist(dx, dy, dz));
+      },
+      listed, rows_end);
 }
 
 // Ordered sums of the FP32C form in a group walk: the terms of a chunk are
@@ -717,7 +765,9 @@ __device__ inline double code_shift(uint32_t code, int axis) { return (double)((
 constexpr uint32_t kNoShift = 0x15u;  // 1 on every axis
 
 // Lanes of the wave for which v holds, as a scalar.
-__device__ inline int wave_count(bool v) { return __builtin_amdgcn_readfirstlane(__popcll(__ballot(v))); }
+__device__ inline int wave_count(bool v) {
+  return __builtin_amdgcn_readfirstlane(__popcll(__builtin_amdgcn_ballot_w64(v)));
+}
 // Largest v over the wave, as a scalar.
 __device__ inline int wave_max(int v) {
 #pragma unroll
