@@ -301,7 +301,8 @@ __global__ void __launch_bounds__(kBatchThreads) k_batch_rho(BatchArgs a, const 
     const int cnt = scnt[s];
     if (cnt <= 0) continue;
     const GatherMode &gm = modes[(int64_t)srep[s] * P + l];
-    const double mx = gm.mx, my = gm.my, mz = gm.mz;
+    const double unit = F32 ? 1.0 : kTurnTable;
+    const double mx = unit * gm.mx, my = unit * gm.my, mz = unit * gm.mz;
     const double4 *p = rec + s * kBatchChunk;
     double2 out;
     if (F32) {
@@ -321,7 +322,7 @@ __global__ void __launch_bounds__(kBatchThreads) k_batch_rho(BatchArgs a, const 
       for (int j = 0; j < cnt; ++j) {
         const double4 v = p[j];
         double sn, cs;
-        sincos_turn_tab_f64(turn_fraction(mx, my, mz, v.x, v.y, v.z), tab, &sn, &cs);
+        sincos_phase_f64(phase_dot(mx, my, mz, v.x, v.y, v.z), tab, &sn, &cs);
         re = fma(v.w, cs, re);
         im = fma(v.w, sn, im);
       }
@@ -383,12 +384,13 @@ __device__ inline void batch_gather_sum(const GatherMode *__restrict__ md, int P
     g[1] = (double)gy - (double)ey;
     g[2] = (double)gz - (double)ez;
   } else {
+    const double sx = kTurnTable * s.x, sy = kTurnTable * s.y, sz = kTurnTable * s.z;
     double gx = 0.0, gy = 0.0, gz = 0.0;
 #pragma unroll 4
     for (int l = 0; l < P; ++l) {
       const GatherMode gm = md[l];
       double sn, cs;
-      sincos_turn_tab_f64(turn_fraction(gm.mx, gm.my, gm.mz, s.x, s.y, s.z), tab, &sn, &cs);
+      sincos_phase_f64(phase_dot(gm.mx, gm.my, gm.mz, sx, sy, sz), tab, &sn, &cs);
       const double h = gm.a * cs - gm.b * sn;
       gx = fma(h, gm.mx, gx);
       gy = fma(h, gm.my, gy);

@@ -4,9 +4,9 @@
 // (kc the Coulomb prefactor, 1 in reduced units).
 //
 // Phase: k_l . r_j = 2 pi t with t = m_l . s_j (s = r/L, the fractional
-// coordinate). Whole turns are removed in FP64 (t - rint(t), exact for the
-// fraction) before the sine and cosine, so the trigonometric argument is a
-// fraction of a turn in [-1/2, 1/2] whatever the box size.
+// coordinate). Whole turns are removed in FP64 (exactly) before the sine and
+// cosine, so the trigonometric argument is a fraction of a turn whatever the
+// box size.
 //
 // Structure factor: thread = mode, particles walked in a wave-uniform loop
 // (scalar loads of the packed (s, q) records), one partial sum per particle
@@ -89,9 +89,9 @@ __global__ void __launch_bounds__(kModesPerBlock) k_rho_partial_f64(const int32_
   const int l = l0 + (active ? mi : 0);
   double mx = 0.0, my = 0.0, mz = 0.0;
   if (a > 0) {
-    mx = mkd[l];
-    my = mkd[P + l];
-    mz = mkd[2 * P + l];
+    mx = kTurnTable * mkd[l];
+    my = kTurnTable * mkd[P + l];
+    mz = kTurnTable * mkd[2 * P + l];
   }
   double re = 0.0, im = 0.0;
   for (int64_t b = j0; b < j1; b += kModesPerBlock) {
@@ -103,9 +103,8 @@ __global__ void __launch_bounds__(kModesPerBlock) k_rho_partial_f64(const int32_
 #pragma unroll 4
     for (int u = ph; u < cnt; u += rep) {
       const double4 r = rec[u];
-      const double t = turn_fraction(mx, my, mz, r.x, r.y, r.z);
       double sn, cs;
-      sincos_turn_tab_f64(t, tab, &sn, &cs);
+      sincos_phase_f64(phase_dot(mx, my, mz, r.x, r.y, r.z), tab, &sn, &cs);
       re = fma(r.w, cs, re);
       im = fma(r.w, sn, im);
     }
@@ -291,14 +290,14 @@ __global__ void __launch_bounds__(kTurnTable) k_gather_f64(const int32_t *__rest
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= nq) return;
   const double4 s = sq[i];
+  const double sx = kTurnTable * s.x, sy = kTurnTable * s.y, sz = kTurnTable * s.z;
   double gx = 0.0, gy = 0.0, gz = 0.0;
   const int lb = blockIdx.y * M, le = min(P, lb + M);
 #pragma unroll 4
   for (int l = lb; l < le; ++l) {
     const GatherMode gm = modes[l];
-    const double t = turn_fraction(gm.mx, gm.my, gm.mz, s.x, s.y, s.z);
     double sn, cs;
-    sincos_turn_tab_f64(t, tab, &sn, &cs);
+    sincos_phase_f64(phase_dot(gm.mx, gm.my, gm.mz, sx, sy, sz), tab, &sn, &cs);
     const double g = gm.a * cs - gm.b * sn;  // w Im(exp(-i theta) rho)
     gx = fma(g, gm.mx, gx);
     gy = fma(g, gm.my, gy);
