@@ -75,6 +75,7 @@ struct rbe_ctx {
   int32_t *m_dev = nullptr;  // [kSampleSteps][3][P] mode samples (rbe_step draws them ahead)
   double *w_dev = nullptr;   // [kSampleSteps][P]
   double *mkd_dev = nullptr; // [kSampleSteps][3][P] the same modes as doubles
+  ModeRuns runs{}, call_runs{};  // segments of the fixed table, and of a call's (cap = 0: none)
   bool fixed_modes = false;  // rbe_set_modes: slot 0 of m_dev/w_dev/mkd_dev is the caller's table
   double *mean_part = nullptr, *mean = nullptr;
   double *epart = nullptr;   // energy partial sums
@@ -429,6 +430,27 @@ extern "C" int rbe_create(rbe_ctx **out, const rbe_params *p, int64_t n_max, int
   c->fb.rho = b.alloc<double>(2 * P);
   c->fb.modes = b.alloc<GatherMode>(P);
   c->fb.turn_tab = b.alloc<double2>(kTurnTableEntries);
+  if (p->prec == RBE_FP64 && P >= kRunMinModes) {
+    // segments of the caller's table: the fixed one (rbe_set_modes) and that
+    // of a call, which share the partial sums; without the memory for them the
+    // kernels that take any mode serve such tables
+    Buf rb;
+    for (ModeRuns *R : {&c->runs, &c->call_runs}) {
+      R->cap = P / 4;
+      R->first = rb.alloc<int32_t>(R->cap + 1);
+      R->heads = rb.alloc<int32_t>((P + kRunsThreads - 1) / kRunsThreads);
+      R->count = rb.alloc<int32_t>(1);
+      R->rec = rb.alloc<double>((int64_t)R->cap * kRunRec);
+    }
+    c->runs.part = c->call_runs.part = rb.alloc<double2>(run_part_len(P / 4));
+    if (rb.ok) {
+      b.ptrs.insert(b.ptrs.end(), rb.ptrs.begin(), rb.ptrs.end());
+    } else {
+      rb.release();
+      (void)hipGetLastError();
+      c->runs = c->call_runs = ModeRuns{};
+    }
+  }
   c->m_dev = b.alloc<int32_t>((int64_t)kSampleSteps * 3 * P);
   c->w_dev = b.alloc<double>((int64_t)kSampleSteps * P);
   c->mkd_dev = b.alloc<double>((int64_t)kSampleSteps * 3 * P);
@@ -819,6 +841,12 @@ static int eval_sorted(rbe_ctx *c, int64_t n, const int32_t *m, const double *w,
   }
   if (terms & RBE_TERM_FOURIER) {
     FourierBuffers fb = c->fb;
+    if (c->fixed_modes && (mkd_pre || !m)) {
+      fb.runs = c->runs;
+    } else if (m && !mkd_pre && c->call_runs.cap) {
+      fb.runs = c->call_runs;
+      launch_mode_runs(P, m, fb.runs, st);
+    }
     if (mkd_pre) {
       fb.mkd = const_cast<double *>(mkd_pre);  // drawn ahead with the modes
     } else if (!m && c->fixed_modes) {
@@ -840,7 +868,7 @@ static int eval_sorted(rbe_ctx *c, int64_t n, const int32_t *m, const double *w,
     }
     {
       TScope ts(c, RBE_TK_RHO_FINAL, st);
-      launch_rho_final(nq, P, fb, w, c->p.coulomb_k, rho_out, st);
+      launch_rho_final(nq, n, P, fb, w, c->p.coulomb_k, rho_out, st);
     }
     {
       TScope ts(c, RBE_TK_GATHER, st);
@@ -1107,6 +1135,7 @@ extern "C" int rbe_set_modes(rbe_ctx *c, const int32_t *m, const double *w, void
   HIP_TRY(c, hipMemcpyAsync(c->m_dev, m, sizeof(int32_t) * 3 * P, hipMemcpyDeviceToDevice, st));
   HIP_TRY(c, hipMemcpyAsync(c->w_dev, w, sizeof(double) * P, hipMemcpyDeviceToDevice, st));
   launch_modes_to_double((int)P, c->m_dev, c->mkd_dev, st);
+  if (c->runs.cap) launch_mode_runs((int)P, c->m_dev, c->runs, st);
   HIP_TRY(c, hipGetLastError());
   c->fixed_modes = true;
   return RBE_OK;
@@ -1182,8 +1211,15 @@ extern "C" int rbe_energy(rbe_ctx *c, const rbe_state *s, const int32_t *m, cons
     launch_modes_to_double(P, m, c->fb.mkd, st);
     // structure factors always in FP64 here, whatever the context's precision
     const int32_t *nq = c->cell_start + c->g.ncell;
-    launch_rho_partial(RBE_FP64, nq, n, P, c->srt.sq, c->fb, st);
-    launch_rho_final(nq, P, c->fb, w, c->p.coulomb_k, rho_out, st);
+    FourierBuffers fb = c->fb;
+    if (m != c->m_dev) {
+      fb.runs = c->call_runs;
+      if (fb.runs.cap) launch_mode_runs(P, m, fb.runs, st);
+    } else if (c->fixed_modes) {
+      fb.runs = c->runs;
+    }
+    launch_rho_partial(RBE_FP64, nq, n, P, c->srt.sq, fb, st);
+    launch_rho_final(nq, n, P, fb, w, c->p.coulomb_k, rho_out, st);
     fin.w = w;
     fin.rho = c->fb.rho;
     fin.mkd = c->fb.mkd;

@@ -67,7 +67,9 @@ __global__ void __launch_bounds__(kModesPerBlock) k_rho_partial_f64(const int32_
                                                                      const double4 *__restrict__ sq,
                                                                      const double *__restrict__ mkd,
                                                                      const double2 *__restrict__ turn_tab,
-                                                                     double2 *__restrict__ part) {
+                                                                     double2 *__restrict__ part,
+                                                                     const int32_t *__restrict__ run_count) {
+  if (run_count && *run_count > 0) return;  // the segments' kernel has the table
   static_assert(kModesPerBlock == kTurnTable, "one table entry per thread");
   __shared__ double2 tab[kTurnTable];
   __shared__ double4 rec[kModesPerBlock];  // the chunk's records, staged a round at a time
@@ -201,6 +203,25 @@ __global__ void __launch_bounds__(kModesPerBlock) k_rho_partial_f32c(const int32
 // rho_l = sum over chunks (fixed order: thread-strided FP64 sums, a fixed
 // butterfly in each wave, then the waves in index order). Also forms the
 // gather coefficients of each mode.
+__device__ inline void put_rho(int l, int P, double re, double im, const double *__restrict__ mkd,
+                               const double *__restrict__ w, double kc, double *__restrict__ rho,
+                               GatherMode *__restrict__ modes, double *__restrict__ rho_out) {
+  rho[l] = re;
+  rho[P + l] = im;
+  if (rho_out) {
+    rho_out[l] = re;
+    rho_out[P + l] = im;
+  }
+  GatherMode gm;
+  gm.mx = mkd[l];
+  gm.my = mkd[P + l];
+  gm.mz = mkd[2 * P + l];
+  const double wl = kc * w[l];
+  gm.a = wl * im;
+  gm.b = wl * re;
+  gather_floats(gm);
+  modes[l] = gm;
+}
 constexpr int kRhoFinalThreads = 256;
 __global__ void __launch_bounds__(kRhoFinalThreads) k_rho_final(const int32_t *__restrict__ nq_ptr, int nchunk_max, int P,
                                                                 const double2 *__restrict__ part,
@@ -208,7 +229,9 @@ __global__ void __launch_bounds__(kRhoFinalThreads) k_rho_final(const int32_t *_
                                                                 const double *__restrict__ w, double kc,
                                                                 double *__restrict__ rho,
                                                                 GatherMode *__restrict__ modes,
-                                                                double *__restrict__ rho_out) {
+                                                                double *__restrict__ rho_out,
+                                                                const int32_t *__restrict__ run_count) {
+  if (run_count && *run_count > 0) return;
   __shared__ double2 wsum[kRhoFinalThreads / 64];
   int nchunks;
   (void)rho_layout(*nq_ptr, P, nchunk_max, &nchunks);
@@ -235,38 +258,289 @@ __global__ void __launch_bounds__(kRhoFinalThreads) k_rho_final(const int32_t *_
       re += wsum[k].x;
       im += wsum[k].y;
     }
+    put_rho(l, P, re, im, mkd, w, kc, rho, modes, rho_out);
+  }
+}
+
+// The same sums, in the same order, with a thread per mode where at most
+// kRhoFlat chunks are possible (many modes of few particles: an Ewald lattice):
+// a block per mode spends its time on being launched, 92,000 modes of 6 chunks
+// 98 us, now 7.6.
+constexpr int kRhoFlat = 16;
+__global__ void __launch_bounds__(256) k_rho_final_flat(const int32_t *__restrict__ nq_ptr, int nchunk_max, int P,
+                                                        const double2 *__restrict__ part,
+                                                        const double *__restrict__ mkd, const double *__restrict__ w,
+                                                        double kc, double *__restrict__ rho,
+                                                        GatherMode *__restrict__ modes, double *__restrict__ rho_out,
+                                                        const int32_t *__restrict__ run_count) {
+  if (run_count && *run_count > 0) return;
+  const int l = blockIdx.x * 256 + threadIdx.x;
+  if (l >= P) return;
+  int nchunks;
+  (void)rho_layout(*nq_ptr, P, nchunk_max, &nchunks);
+  double2 v[kRhoFlat];
+#pragma unroll
+  for (int c = 0; c < kRhoFlat; ++c) v[c] = c < nchunks ? part[(int64_t)c * P + l] : make_double2(0.0, 0.0);
+#pragma unroll
+  for (int o = kRhoFlat / 2; o > 0; o >>= 1) {
+#pragma unroll
+    for (int c = 0; c < o; ++c) {
+      v[c].x += v[c + o].x;
+      v[c].y += v[c + o].y;
+    }
+  }
+  put_rho(l, P, v[0].x, v[0].y, mkd, w, kc, rho, modes, rho_out);
+}
+
+
+// ---------------------------------------------------------------------------
+// tables with columns: segments of modes (kernels.h, ModeRuns)
+// ---------------------------------------------------------------------------
+// A segment starts at mode l unless l - 1 is its predecessor in m_z and the
+// boundary of two segments does not lie between them.
+__device__ inline int run_place(int mz) {
+  const int r = mz % kRunLen;
+  return r < 0 ? r + kRunLen : r;
+}
+__device__ inline bool run_head(int P, const int32_t *__restrict__ m, int l) {
+  if (l >= P) return false;
+  if (l == 0 || m[l] != m[l - 1] || m[P + l] != m[P + l - 1]) return true;
+  return (int64_t)m[2 * P + l] != (int64_t)m[2 * P + l - 1] + 1 || run_place(m[2 * P + l]) == 0;
+}
+// Segments that start in each block's kRunsThreads modes; then, with the sums
+// over the blocks before, their records.
+__global__ void __launch_bounds__(kRunsThreads) k_run_heads(int P, const int32_t *__restrict__ m, ModeRuns R) {
+  const int c = __syncthreads_count(run_head(P, m, blockIdx.x * kRunsThreads + threadIdx.x));
+  if (threadIdx.x == 0) R.heads[blockIdx.x] = c;
+}
+__global__ void __launch_bounds__(kRunsThreads) k_run_segments(int P, const int32_t *__restrict__ m, ModeRuns R) {
+  __shared__ int wsum[kRunsThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l = blockIdx.x * kRunsThreads + tid;
+  const bool head = run_head(P, m, l);
+  const uint64_t heads = __builtin_amdgcn_ballot_w64(head);
+  if (lane == 0) wsum[wave] = __popcll(heads);
+  __syncthreads();
+  int at = 0, total = 0;
+  for (int b = 0; b < (int)gridDim.x; ++b) {
+    if (b < (int)blockIdx.x) at += R.heads[b];
+    total += R.heads[b];
+  }
+  for (int k = 0; k < wave; ++k) at += wsum[k];
+  at += __popcll(heads & ((1ull << lane) - 1ull));
+  const bool fits = total <= R.cap;
+  if (head && fits) {
+    const int mz = m[2 * P + l];
+    R.first[at] = l;
+    double *r = R.rec + (int64_t)at * kRunRec;
+    r[0] = (double)m[l];
+    r[1] = (double)m[P + l];
+    r[2] = (double)mz + (kRunHalf - run_place(mz));
+    r[3] = (double)run_place(mz);
+  }
+  if (l == 0) {
+    if (fits) R.first[total] = P;
+    *R.count = fits ? total : 0;
+  }
+}
+
+void launch_mode_runs(int P, const int32_t *m, const ModeRuns &runs, hipStream_t st) {
+  const unsigned nb = (unsigned)((P + kRunsThreads - 1) / kRunsThreads);
+  k_run_heads<<<nb, kRunsThreads, 0, st>>>(P, m, runs);
+  k_run_segments<<<nb, kRunsThreads, 0, st>>>(P, m, runs);
+}
+
+// Blocks of kRunBlockSegs segments times chunks of particles: as many chunks
+// as kRunBlocks holds, of at least 16 particles.
+__device__ inline int run_chunks(int64_t nq, int nsb, int *len) {
+  const int64_t most = max(1, kRunBlocks / nsb);
+  const int64_t nc = min(most, max((int64_t)1, (nq + 15) / 16));
+  *len = (int)((nq + nc - 1) / nc);
+  return (int)nc;
+}
+static int run_grid(int cap) { return std::max(kRunBlocks, (cap + kRunBlockSegs - 1) / kRunBlockSegs); }
+
+// exp(2 pi i u s_z), u = 1..kRunHalf, of a particle: (cos, sin) of a power.
+__device__ inline double2 run_power(int u, double sz, const double2 *tab) {
+  double2 z;
+  sincos_phase_f64((double)u * (kTurnTable * sz), tab, &z.y, &z.x);
+  return z;
+}
+
+// Partial sums of the segments: a lane has two of them, the block's records
+// and powers are staged in LDS (half of a wave's time at one segment a lane
+// would go to reading them). Of a pair of modes u off the centre only the four
+// real products with the power are summed; the modes' sums are their sums and
+// differences, formed once at the end: 2 FP64 operations a mode and particle
+// and 18 a segment for its centre, 4.1 where the general kernel has 19.
+// Bound by FP64 issue and the LDS reads alike: 4,000 ions and the 92,000 modes
+// of their Ewald lattice 82 us, 320 by the general kernel. Twice the blocks
+// (more chunks) save 5 us here and cost 7 in the final sums.
+__global__ void __launch_bounds__(kRunBlockSegs / 2) __attribute__((amdgpu_waves_per_eu(4)))
+k_rho_runs(const int32_t *__restrict__ nq_ptr, const int32_t *__restrict__ count, const double *__restrict__ seg,
+           const double4 *__restrict__ sq, const double2 *__restrict__ turn_tab, double2 *__restrict__ part) {
+  constexpr int T = kRunBlockSegs / 2, kStage = T / 2;
+  static_assert(T == kTurnTable && kRunHalf == 4, "one table entry per thread, two threads a record");
+  __shared__ double2 tab[kTurnTable];
+  __shared__ double4 rec[kStage];
+  __shared__ double2 pow[kStage][kRunHalf];
+  const int nseg = *count;
+  if (nseg <= 0) return;  // uniform over the grid
+  const int nsb = (nseg + kRunBlockSegs - 1) / kRunBlockSegs;
+  const int64_t nq = *nq_ptr;
+  int len;
+  const int nc = run_chunks(nq, nsb, &len);
+  const int chunk = blockIdx.x / nsb, sb = blockIdx.x % nsb;
+  if (chunk >= nc) return;  // uniform over the block
+  const int tid = threadIdx.x;
+  tab[tid] = turn_tab[tid];
+  double mx[2], my[2], mz[2], c0[2], s0[2], cc[2][kRunHalf], ss[2][kRunHalf], sc[2][kRunHalf], cs[2][kRunHalf];
+#pragma unroll
+  for (int v = 0; v < 2; ++v) {
+    const int sg = min(sb * kRunBlockSegs + v * T + tid, nseg - 1);
+    const double *r = seg + (int64_t)sg * kRunRec;
+    mx[v] = kTurnTable * r[0];
+    my[v] = kTurnTable * r[1];
+    mz[v] = kTurnTable * r[2];
+    c0[v] = s0[v] = 0.0;
+#pragma unroll
+    for (int u = 0; u < kRunHalf; ++u) cc[v][u] = ss[v][u] = sc[v][u] = cs[v][u] = 0.0;
+  }
+  const int64_t j0 = (int64_t)chunk * len, j1 = min(nq, j0 + len);
+  for (int64_t b = j0; b < j1; b += kStage) {
+    const int cnt = (int)min((int64_t)kStage, j1 - b);
+    __syncthreads();  // the table is written; the previous round is no longer read
+    if ((tid >> 1) < cnt) {
+      const double4 r = sq[b + (tid >> 1)];
+      const int u = (tid & 1) * 2;
+      if (u == 0) rec[tid >> 1] = r;
+      pow[tid >> 1][u] = run_power(u + 1, r.z, tab);
+      pow[tid >> 1][u + 1] = run_power(u + 2, r.z, tab);
+    }
+    __syncthreads();
+    for (int k = 0; k < cnt; ++k) {
+      const double4 r = rec[k];
+      double2 z[kRunHalf];
+#pragma unroll
+      for (int u = 0; u < kRunHalf; ++u) z[u] = pow[k][u];
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        double sn, c;
+        sincos_phase_f64(phase_dot(mx[v], my[v], mz[v], r.x, r.y, r.z), tab, &sn, &c);
+        const double qc = r.w * c, qs = r.w * sn;
+        c0[v] += qc;
+        s0[v] += qs;
+#pragma unroll
+        for (int u = 0; u < kRunHalf; ++u) {
+          cc[v][u] = fma(qc, z[u].x, cc[v][u]);
+          ss[v][u] = fma(qs, z[u].y, ss[v][u]);
+          sc[v][u] = fma(qs, z[u].x, sc[v][u]);
+          cs[v][u] = fma(qc, z[u].y, cs[v][u]);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 2; ++v) {
+    const int sg = sb * kRunBlockSegs + v * T + tid;
+    if (sg >= nseg) continue;
+    double2 *out = part + (int64_t)chunk * kRunLen * nseg + sg;
+    out[0] = make_double2(c0[v], s0[v]);
+#pragma unroll
+    for (int u = 0; u < kRunHalf; ++u) {
+      out[(int64_t)(2 * u + 1) * nseg] = make_double2(cc[v][u], ss[v][u]);
+      out[(int64_t)(2 * u + 2) * nseg] = make_double2(sc[v][u], cs[v][u]);
+    }
+  }
+}
+
+// One thread per segment and its centre (k = 0) or pair (k = u): the chunks'
+// sums in order, the structure factors of the modes that exist, and the
+// segment's gather coefficients (zero for the modes it lacks).
+__global__ void __launch_bounds__(256) k_rho_runs_final(const int32_t *__restrict__ nq_ptr, int P,
+                                                        const int32_t *__restrict__ count,
+                                                        const int32_t *__restrict__ first,
+                                                        const double2 *__restrict__ part,
+                                                        const double *__restrict__ w, double kc,
+                                                        double *__restrict__ seg, double *__restrict__ rho,
+                                                        double *__restrict__ rho_out) {
+  const int nseg = *count;
+  const int64_t it = blockIdx.x * (int64_t)256 + threadIdx.x;
+  if (it >= (int64_t)nseg * (kRunHalf + 1)) return;
+  const int u = (int)(it / nseg), sg = (int)(it % nseg);
+  int len;
+  const int nc = run_chunks(*nq_ptr, (nseg + kRunBlockSegs - 1) / kRunBlockSegs, &len);
+  double *r = seg + (int64_t)sg * kRunRec;
+  const int off = (int)r[3];  // the segment's first mode is at this place of its kRunLen
+  const int f = first[sg], cnt = first[sg + 1] - f;
+  double2 A = make_double2(0.0, 0.0), B = A;
+  const int ka = u ? 2 * u - 1 : 0;
+  const double2 *pa = part + (int64_t)ka * nseg + sg;
+#pragma unroll 4
+  for (int c = 0; c < nc; ++c) {
+    const double2 va = pa[(int64_t)c * kRunLen * nseg];
+    A.x += va.x;
+    A.y += va.y;
+    if (u) {
+      const double2 vb = pa[((int64_t)c * kRunLen + 1) * nseg];
+      B.x += vb.x;
+      B.y += vb.y;
+    }
+  }
+  // structure factor of the segment's mode at place k, and its coefficients
+  auto put = [&](int k, double re, double im) {
+    if (k < off || k >= off + cnt) return make_double2(0.0, 0.0);
+    const int l = f + k - off;
     rho[l] = re;
     rho[P + l] = im;
     if (rho_out) {
       rho_out[l] = re;
       rho_out[P + l] = im;
     }
-    GatherMode gm;
-    gm.mx = mkd[l];
-    gm.my = mkd[P + l];
-    gm.mz = mkd[2 * P + l];
     const double wl = kc * w[l];
-    gm.a = wl * im;
-    gm.b = wl * re;
-    gather_floats(gm);
-    modes[l] = gm;
+    return make_double2(wl * im, wl * re);
+  };
+  if (u == 0) {
+    const double2 g = put(kRunHalf, A.x, A.y);
+    r[4] = g.x;
+    r[5] = g.y;
+  } else {
+    const double2 g = put(kRunHalf + u, A.x - A.y, B.x + B.y), h = put(kRunHalf - u, A.x + A.y, B.x - B.y);
+    r += 8 + 4 * (u - 1);
+    r[0] = g.x + h.x;
+    r[1] = g.y - h.y;
+    r[2] = g.x - h.x;
+    r[3] = g.y + h.y;
   }
 }
 
 void launch_rho_partial(int prec, const int32_t *nq, int64_t nq_max, int P, const double4 *sq,
                         const FourierBuffers &fb, hipStream_t st) {
+  const ModeRuns &R = fb.runs;
+  if (R.cap)
+    k_rho_runs<<<(unsigned)run_grid(R.cap), kRunBlockSegs / 2, 0, st>>>(nq, R.count, R.rec, sq, fb.turn_tab, R.part);
   const int nchunks = rho_max_chunks(nq_max, P, fb.nchunk_max);
   dim3 grid((unsigned)nchunks, (unsigned)((P + kModesPerBlock - 1) / kModesPerBlock));
   if (prec == RBE_FP32C)
     k_rho_partial_f32c<<<grid, kModesPerBlock, 0, st>>>(nq, P, fb.nchunk_max, sq, fb.mkd, fb.part);
   else
-    k_rho_partial_f64<<<grid, kModesPerBlock, 0, st>>>(nq, P, fb.nchunk_max, sq, fb.mkd, fb.turn_tab, fb.part);
+    k_rho_partial_f64<<<grid, kModesPerBlock, 0, st>>>(nq, P, fb.nchunk_max, sq, fb.mkd, fb.turn_tab, fb.part,
+                                                         R.cap ? R.count : nullptr);
 }
 
-void launch_rho_final(const int32_t *nq, int P, const FourierBuffers &fb, const double *w, double kc,
+void launch_rho_final(const int32_t *nq, int64_t nq_max, int P, const FourierBuffers &fb, const double *w, double kc,
                       double *rho_out, hipStream_t st) {
-  k_rho_final<<<P, kRhoFinalThreads, 0, st>>>(nq, fb.nchunk_max, P, fb.part, fb.mkd, w, kc, fb.rho, fb.modes,
-                                              rho_out);
+  const ModeRuns &R = fb.runs;
+  if (R.cap)
+    k_rho_runs_final<<<(unsigned)((R.cap * (int64_t)(kRunHalf + 1) + 255) / 256), 256, 0, st>>>(
+        nq, P, R.count, R.first, R.part, w, kc, R.rec, fb.rho, rho_out);
+  const int32_t *rc = R.cap ? R.count : nullptr;
+  if (rho_max_chunks(nq_max, P, fb.nchunk_max) <= kRhoFlat)
+    k_rho_final_flat<<<(P + 255) / 256, 256, 0, st>>>(nq, fb.nchunk_max, P, fb.part, fb.mkd, w, kc, fb.rho, fb.modes,
+                                                      rho_out, rc);
+  else
+    k_rho_final<<<P, kRhoFinalThreads, 0, st>>>(nq, fb.nchunk_max, P, fb.part, fb.mkd, w, kc, fb.rho, fb.modes,
+                                                rho_out, rc);
 }
 
 // ---------------------------------------------------------------------------
@@ -281,7 +555,9 @@ __global__ void __launch_bounds__(kTurnTable) k_gather_f64(const int32_t *__rest
                                                            const double2 *__restrict__ turn_tab, double kx,
                                                            double ky, double kz, double *__restrict__ fx,
                                                            double *__restrict__ fy, double *__restrict__ fz,
-                                                           double4 *__restrict__ gpart, int64_t stride) {
+                                                           double4 *__restrict__ gpart, int64_t stride,
+                                                           const int32_t *__restrict__ run_count) {
+  if (run_count && *run_count > 0) return;
   __shared__ double2 tab[kTurnTable];
   const int64_t nq = *nq_ptr;
   if ((int64_t)blockIdx.x * blockDim.x >= nq) return;  // uniform over the block
@@ -311,6 +587,103 @@ __global__ void __launch_bounds__(kTurnTable) k_gather_f64(const int32_t *__rest
   fx[i] -= q * kx * gx;
   fy[i] -= q * ky * gy;
   fz[i] -= q * kz * gz;
+}
+
+// The same sums over segments: with A_u = a_u + i b_u and Z = exp(2 pi i
+// s_z), the segment's sum of g is Re(e S), S = sum_u A_u Z^u, and that of u g
+// is Re(e W), W = sum_u u A_u Z^u, e the centre's exp(i k . r). The powers are
+// the particle's own, the pairs' coefficients come added and subtracted: 4
+// FP64 operations a mode and 25 a segment, 6.8 a mode where the general kernel
+// has 22. Two particles a lane, so that a segment's scalar loads (three cache
+// lines, waited for in full) serve 128 particles; the four waves of a block
+// take a quarter of the group's segments each, and their sums are added in
+// order. Bound by FP64 issue: 4,000 ions, 92,000 modes 122 us, 199 with one
+// particle a lane, 440 by the general kernel.
+constexpr int kRunGather = 128;  // particles per block
+__global__ void __launch_bounds__(256) k_gather_runs(const int32_t *__restrict__ nq_ptr,
+                                                     const int32_t *__restrict__ count,
+                                                     const double *__restrict__ seg, const double4 *__restrict__ sq,
+                                                     const double2 *__restrict__ turn_tab, double kx, double ky,
+                                                     double kz, double *__restrict__ fx, double *__restrict__ fy,
+                                                     double *__restrict__ fz, double4 *__restrict__ gpart,
+                                                     int64_t stride) {
+  static_assert(kTurnTable == 256, "one table entry per thread");
+  __shared__ double2 tab[kTurnTable];
+  __shared__ double sums[4][3][kRunGather];
+  const int64_t nq = *nq_ptr, i0 = blockIdx.x * (int64_t)kRunGather;
+  const int nseg = *count;
+  if (nseg <= 0 || i0 >= nq) return;  // uniform over the block
+  tab[threadIdx.x] = turn_tab[threadIdx.x];
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double s[2][3], gx[2], gy[2], gz[2];
+  double2 z[2][kRunHalf], uz[2][kRunHalf];
+#pragma unroll
+  for (int v = 0; v < 2; ++v) {
+    const double4 r = sq[min(i0 + 64 * v + lane, nq - 1)];
+    s[v][0] = kTurnTable * r.x;
+    s[v][1] = kTurnTable * r.y;
+    s[v][2] = kTurnTable * r.z;
+#pragma unroll
+    for (int u = 0; u < kRunHalf; ++u) {
+      z[v][u] = run_power(u + 1, r.z, tab);
+      uz[v][u] = make_double2((u + 1) * z[v][u].x, (u + 1) * z[v][u].y);
+    }
+    gx[v] = gy[v] = gz[v] = 0.0;
+  }
+  const int parts = 4 * gridDim.y, M = (nseg + parts - 1) / parts;
+  const int lb = (blockIdx.y * 4 + wave) * M, le = min(nseg, lb + M);
+  for (int l = lb; l < le; ++l) {
+    struct Rec {
+      double v[kRunRec];
+    };
+    const Rec r = ((const Rec *)seg)[l];
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      double sn, cs;
+      sincos_phase_f64(phase_dot(r.v[0], r.v[1], r.v[2], s[v][0], s[v][1], s[v][2]), tab, &sn, &cs);
+      double sr = r.v[4], si = r.v[5], wr = 0.0, wi = 0.0;
+#pragma unroll
+      for (int u = 0; u < kRunHalf; ++u) {
+        const double pa = r.v[8 + 4 * u], mb = r.v[9 + 4 * u], ma = r.v[10 + 4 * u], pb = r.v[11 + 4 * u];
+        sr = fma(pa, z[v][u].x, sr);
+        sr = fma(-mb, z[v][u].y, sr);
+        si = fma(ma, z[v][u].y, si);
+        si = fma(pb, z[v][u].x, si);
+        wr = fma(ma, uz[v][u].x, wr);
+        wr = fma(-pb, uz[v][u].y, wr);
+        wi = fma(pa, uz[v][u].y, wi);
+        wi = fma(mb, uz[v][u].x, wi);
+      }
+      const double g = fma(sr, cs, -(si * sn));
+      gx[v] = fma(g, r.v[0], gx[v]);
+      gy[v] = fma(g, r.v[1], gy[v]);
+      gz[v] = fma(g, r.v[2], gz[v]);
+      gz[v] = fma(wr, cs, gz[v]);
+      gz[v] = fma(-wi, sn, gz[v]);
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 2; ++v) {
+    sums[wave][0][64 * v + lane] = gx[v];
+    sums[wave][1][64 * v + lane] = gy[v];
+    sums[wave][2][64 * v + lane] = gz[v];
+  }
+  __syncthreads();
+  const int64_t i = i0 + threadIdx.x;
+  if (threadIdx.x >= kRunGather || i >= nq) return;
+  double g[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+    g[d] = ((sums[0][d][threadIdx.x] + sums[1][d][threadIdx.x]) + sums[2][d][threadIdx.x]) + sums[3][d][threadIdx.x];
+  if (gpart) {
+    gpart[blockIdx.y * stride + i] = make_double4(g[0], g[1], g[2], 0.0);
+    return;
+  }
+  const double q = sq[i].w;
+  fx[i] -= q * kx * g[0];
+  fy[i] -= q * ky * g[1];
+  fz[i] -= q * kz * g[2];
 }
 
 // Two charged particles per thread (i and i + 256 of the block's 512); every
@@ -389,14 +762,18 @@ __global__ void __launch_bounds__(kGatherThreads) k_gather_f32c(const int32_t *_
 
 // The groups' sums of each charged particle added in group order (FP64),
 // then applied like the single-group gather.
-__global__ void __launch_bounds__(256) k_gather_reduce(const int32_t *__restrict__ nq_ptr, int G, int64_t stride,
+__global__ void __launch_bounds__(256) k_gather_reduce(const int32_t *__restrict__ nq_ptr, int groups,
+                                                       int run_groups, const int32_t *__restrict__ run_count,
+                                                       int64_t stride,
                                                        const double4 *__restrict__ gpart,
                                                        const double4 *__restrict__ sq, double kx, double ky,
                                                        double kz, double *__restrict__ fx, double *__restrict__ fy,
                                                        double *__restrict__ fz) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= *nq_ptr) return;
+  const int G = run_count && *run_count > 0 ? run_groups : groups;
   double gx = 0.0, gy = 0.0, gz = 0.0;
+#pragma unroll 4
   for (int g = 0; g < G; ++g) {
     const double4 v = gpart[g * stride + i];
     gx += v.x;
@@ -435,13 +812,22 @@ void launch_fourier_gather(int prec, const int32_t *nq, int64_t nq_max, int P, c
   double4 *gp = G > 1 ? fb.gpart : nullptr;
   const int64_t stride = (int64_t)blocks * 256;
   const dim3 grid(blocks, (unsigned)G);
+  // segments: groups for about 1024 blocks, if the particles alone are fewer
+  const ModeRuns &R = fb.runs;
+  const int32_t *rc = R.cap ? R.count : nullptr;
+  const int64_t rb = (nq_max + kRunGather - 1) / kRunGather;
+  const int64_t rg = gp ? std::max<int64_t>(1, std::min(1024 / rb, kGatherPartMax / stride)) : 1;
   if (prec == RBE_FP32C)
     k_gather_f32c<<<dim3((unsigned)((nq_max + kGatherPerBlock - 1) / kGatherPerBlock), (unsigned)G), kGatherThreads,
                     0, st>>>(nq, P, M, sq, fb.modes, kx, ky, kz, fx, fy, fz, gp, stride);
-  else
+  else {
+    if (R.cap)
+      k_gather_runs<<<dim3((unsigned)rb, (unsigned)rg), 256, 0, st>>>(nq, R.count, R.rec, sq, fb.turn_tab, kx, ky, kz,
+                                                                      fx, fy, fz, gp, stride);
     k_gather_f64<<<grid, kTurnTable, 0, st>>>(nq, P, M, sq, fb.modes, fb.turn_tab, kx, ky, kz, fx, fy, fz, gp,
-                                              stride);
-  if (G > 1) k_gather_reduce<<<blocks, 256, 0, st>>>(nq, G, stride, gp, sq, kx, ky, kz, fx, fy, fz);
+                                              stride, rc);
+  }
+  if (G > 1) k_gather_reduce<<<blocks, 256, 0, st>>>(nq, G, (int)rg, rc, stride, gp, sq, kx, ky, kz, fx, fy, fz);
 }
 
 }  // namespace rbe

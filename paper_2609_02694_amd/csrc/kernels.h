@@ -181,7 +181,33 @@ struct GatherMode {
   double a, b;                      // w Im rho, w Re rho
   float af, bf, mxf, myf, mzf, pad; // FP32 copies for the FP32C gather
 };
+// A mode table of the caller's cut into segments of at most kRunLen modes of
+// one (m_x, m_y) whose m_z follow on one another within [kRunLen a, kRunLen a +
+// kRunLen) (the columns of an Ewald lattice), for the FP64 kernels: a
+// particle's exp(i k . r) of a whole segment is that of its centre times powers
+// of exp(2 pi i s_z), which serve every segment.
+constexpr int kRunHalf = 4, kRunLen = 2 * kRunHalf + 1;
+// Segment record: centre mode m (3), place of the first mode, gather coefficients of the centre (a,
+// b), 0, 0, and of each pair of modes u off the centre a+ + a-, b+ - b-,
+// a+ - a-, b+ + b-.
+constexpr int kRunRec = 8 + 4 * kRunHalf;
+// Blocks of the segments' partial sums, 512 segments each.
+constexpr int kRunBlocks = 512, kRunBlockSegs = 512;
+// Tables shorter than this are left to the kernels that take any mode: cutting
+// one costs two launches a call, and is in vain for a random sample; lattices
+// have more modes than this unless the box is a few cutoffs wide.
+constexpr int kRunMinModes = 4096;
+constexpr int kRunsThreads = 1024;  // modes per block of the cutting
+struct ModeRuns {
+  int32_t *first;   // [cap + 1] first mode of a segment (the last entry: P)
+  int32_t *heads;   // [RBE_MAX_P / kRunsThreads] segments per block of modes
+  int32_t *count;   // segments, 0: the table has none long enough
+  double *rec;      // [cap][kRunRec]
+  double2 *part;    // [chunk][kRunLen][count] partial sums
+  int cap;          // P / 4: fewer than 4 modes a segment gain nothing; 0: no buffers
+};
 struct FourierBuffers {
+  ModeRuns runs;         // cap = 0: not for this evaluation
   double *mkd;           // [3][P] mode vectors as doubles
   double2 *part;         // [nchunk_max][P] partial structure factors
   double *rho;           // [2 * P] Re | Im
@@ -223,13 +249,19 @@ inline int rho_max_chunks(int64_t nq_max, int P, int nchunk_max) {
   return m < 1 ? 1 : (int)m;
 }
 void launch_modes_to_double(int P, const int32_t *m, double *mkd, hipStream_t st);
+// Cuts the table m into segments (runs.first, runs.count, the centres).
+void launch_mode_runs(int P, const int32_t *m, const ModeRuns &runs, hipStream_t st);
+inline int64_t run_part_len(int cap) {
+  const int64_t segs = std::max<int64_t>((int64_t)kRunBlocks * kRunBlockSegs, cap + kRunBlockSegs);
+  return segs * kRunLen;
+}
 // The charged count nq is read on the device (*nq, the first neutral cell
 // start); nq_max bounds it (sizes the grids).
 void launch_rho_partial(int prec, const int32_t *nq, int64_t nq_max, int P, const double4 *sq,
                         const FourierBuffers &fb, hipStream_t st);
 // The gather coefficients take the weights times kc (the Coulomb prefactor
 // scales the Fourier force like every other Coulomb term).
-void launch_rho_final(const int32_t *nq, int P, const FourierBuffers &fb, const double *w, double kc,
+void launch_rho_final(const int32_t *nq, int64_t nq_max, int P, const FourierBuffers &fb, const double *w, double kc,
                       double *rho_out, hipStream_t st);
 void launch_fourier_gather(int prec, const int32_t *nq, int64_t nq_max, int P, const double4 *sq,
                            const FourierBuffers &fb, const Grid &g, double *fx, double *fy, double *fz,
