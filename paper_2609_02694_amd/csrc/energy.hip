@@ -17,7 +17,19 @@
 namespace rbe {
 
 constexpr int kEnergyThreads = 256;
-constexpr int kEnergyGroup = 64;            // lanes per particle of the near field
+// Lanes per particle of the near field: 64 or 32 (group walk), or one (queue
+// walk), which needs the packed positions of an FP64 context and is the faster
+// form from the size at which its waves fill the chip, sooner where the cutoff
+// sphere is nearly empty. A whole call in us with 64, 32 and one: electrolyte
+// 4,000 particles 82, 87, 455; 20,000: 131, 119, 459; 130,000: 386, 351, 446;
+// 260,000: 653, 575, 508; LJ electrolyte (21 particles in the sphere) 20,000:
+// 107, 90, 123; 65,000: 220, 164, 134.
+constexpr int64_t kEnergyWide = 196608, kEnergyNarrow = 40960;
+static int energy_lanes(const PairParams &pp, int64_t n, bool packed) {
+  const double r = std::sqrt(pp.rq2);
+  const double mean = (double)n / (pp.g.L[0] * pp.g.L[1] * pp.g.L[2]) * (4.0 / 3.0) * kPi * r * r * r;
+  return n <= 4096 ? 64 : !packed || n <= (mean < 48.0 ? kEnergyNarrow : kEnergyWide) ? 32 : 1;
+}
 constexpr int64_t kEnergyNearBlocks = 16384;  // most blocks of the near field (each leaves one partial sum)
 constexpr int kEnergySqBlocks = 1024;  // grid of the q^2 / v^2 sums
 
@@ -47,53 +59,107 @@ __device__ inline double block_sum(double v, double *lds) {
 // block out to r_lj; neutral i walk both blocks out to r_lj.
 // part[4 b + 0..3] = Coulomb energy, LJ energy, Coulomb virial, LJ virial of
 // block b.
-__global__ void __launch_bounds__(kEnergyThreads) k_energy_near(PairParams pp, double lj4, double two_sqrt_a_pi,
-                                                                int64_t n, const double4 *__restrict__ xq,
-                                                                const int32_t *__restrict__ cell_start,
-                                                                double *__restrict__ part) {
-  __shared__ double lds[kEnergyThreads / 64];
-  constexpr int G = kEnergyGroup;
-  __shared__ GroupRows<G> rows[kEnergyThreads / G];
-  const int64_t per = (n + gridDim.x - 1) / gridDim.x;  // consecutive particles per block
-  const int64_t end = min(n, (blockIdx.x + 1) * per);
-  const Grid &g = pp.g;
-  const Block near_lj = pp.do_lj ? Block{pp.s_lj, pp.rlj2} : no_block();
+struct EnergyNear {
+  PairParams pp;
+  double lj4, two_sqrt_a_pi;
+  int64_t n;
+  const double4 *__restrict__ xq;
+  const uint2 *__restrict__ pk;
+  double pk_scale;
+  uint32_t t2_q, t2_lj;  // squared reaches in packed units
+  const int32_t *__restrict__ cell_start;
+  double *__restrict__ part;
+};
+// A thread's share of the four sums.
+struct EnergySums {
   double uc = 0.0, ul = 0.0, wc = 0.0, wl = 0.0;
+  __device__ inline void add(const EnergyNear &a, double qi, double qj, double r2) {
+    const PairParams &pp = a.pp;
+    if (pp.do_coul && r2 <= pp.rc2 && qi != 0.0 && qj != 0.0) {
+      const double r = sqrt(r2);
+      const double qq = pp.kc * qi * qj;
+      const double er = erfc(pp.sqrt_alpha * r) / r;
+      uc += qq * er;
+      wc += qq * (er + a.two_sqrt_a_pi * exp(-pp.alpha * r2));
+    }
+    if (pp.do_lj && r2 <= pp.rlj2) {
+      const double s2 = pp.sig2 / r2, s6 = s2 * s2 * s2;
+      ul += s6 * s6 - s6;
+      wl += 2.0 * s6 * s6 - s6;
+    }
+  }
+  __device__ inline void put(const EnergyNear &a, double *lds) {
+    const double sc = block_sum(0.5 * uc, lds), sl = block_sum(0.5 * a.lj4 * ul, lds);
+    const double vc = block_sum(0.5 * wc, lds), vl = block_sum(0.5 * a.pp.eps24 * wl, lds);
+    if (threadIdx.x == 0) ((double4 *)a.part)[blockIdx.x] = make_double4(sc, sl, vc, vl);
+  }
+};
+
+template <int G>
+__global__ void __launch_bounds__(kEnergyThreads) k_energy_near(EnergyNear a) {
+  __shared__ double lds[kEnergyThreads / 64];
+  __shared__ GroupRows<G> rows[kEnergyThreads / G];
+  const int64_t per = (a.n + gridDim.x - 1) / gridDim.x;  // consecutive particles per block
+  const int64_t end = min(a.n, (blockIdx.x + 1) * per);
+  const PairParams &pp = a.pp;
+  const Block near_lj = pp.do_lj ? Block{pp.s_lj, pp.rlj2} : no_block();
+  EnergySums sums;
   for (int64_t i = blockIdx.x * per + threadIdx.x / G; i < end; i += kEnergyThreads / G) {
-    const double4 pi4 = xq[i];
-    const double qi = pi4.w;
-    auto visit = [&](bool ok, int, int, int j, const double4 &pj, double, double, double, double r2) {
-      if (!ok || j == (int)i) return;
-      if (pp.do_coul && r2 <= pp.rc2 && qi != 0.0 && pj.w != 0.0) {
-        const double r = sqrt(r2);
-        const double qq = pp.kc * qi * pj.w;
-        const double er = erfc(pp.sqrt_alpha * r) / r;
-        uc += qq * er;
-        wc += qq * (er + two_sqrt_a_pi * exp(-pp.alpha * r2));
+    const double4 pi = a.xq[i];
+    group_walk<G, false>(
+        pp.g, a.cell_start, a.xq, nullptr, nullptr, 0, pi, pi.w != 0.0 ? Block{pp.s_coul, pp.rq2} : near_lj, near_lj,
+        rows[threadIdx.x / G],
+        [&](bool ok, int, int, int j, const double4 &pj, double, double, double, double r2) {
+          if (ok && j != (int)i) sums.add(a, pi.w, pj.w, r2);
+        },
+        [](int, int) {}, [](uint64_t) {});
+  }
+  sums.put(a, lds);
+}
+
+// The same with one lane per particle, the candidates filtered on packed
+// positions and the terms of those that pass evaluated from the lanes' queues
+// (pair_device.h, queue walks): the error function runs with three quarters of
+// the lanes or more instead of the half whose candidate is inside the cutoff,
+// and the walk's set-up is a lane's, not a wave's. 1M ions 3.78 -> 3.00 ms a
+// call, 1M LJ electrolyte 1.26 -> 0.72.
+__global__ void __launch_bounds__(kEnergyThreads) __attribute__((amdgpu_waves_per_eu(3)))
+k_energy_near_queue(EnergyNear a) {
+  static_assert(kEnergyThreads == kQueueThreads, "queue layout");
+  __shared__ double lds[kEnergyThreads / 64];
+  __shared__ uint32_t queue[kQueueCap * kQueueThreads];
+  const PairParams &pp = a.pp;
+  const Grid &g = pp.g;
+  const bool coded = a.n <= (1ll << kIndexBits);
+  const int64_t tiles = (a.n + kEnergyThreads - 1) / kEnergyThreads;  // of consecutive particles
+  EnergySums sums;
+  for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+    const int64_t i = t * kEnergyThreads + threadIdx.x;
+    const bool active = i < a.n;  // the whole wave takes part
+    const double4 pi = a.xq[active ? i : a.n - 1];
+    HitQueue Q(queue);
+    auto one = [&](uint32_t e) {
+      const uint32_t code = coded ? e >> kIndexBits : Q.now;
+      const int j = (int)(coded ? e & ((1u << kIndexBits) - 1u) : e);
+      const double4 pj = a.xq[j];
+      double dx = pi.x - pj.x, dy = pi.y - pj.y, dz = pi.z - pj.z;
+      if (wave_count(code != kNoShift)) {
+        dx -= code_shift(code, 0) * g.L[0];
+        dy -= code_shift(code, 1) * g.L[1];
+        dz -= code_shift(code, 2) * g.L[2];
       }
-      if (pp.do_lj && r2 <= pp.rlj2) {
-        const double s2 = pp.sig2 / r2, s6 = s2 * s2 * s2;
-        ul += s6 * s6 - s6;
-        wl += 2.0 * s6 * s6 - s6;
-      }
+      if (j != (int)i) sums.add(a, pi.w, pj.w, sq_dist(dx, dy, dz));
     };
-    group_walk<G, false>(g, cell_start, xq, nullptr, nullptr, 0, pi4, qi != 0.0 ? Block{pp.s_coul, pp.rq2} : near_lj,
-                         near_lj, rows[threadIdx.x / G], visit, [](int, int) {}, [](uint64_t) {});
+    auto drain = [&](bool all) { drain_queue(Q, all, one); };
+    const bool charged = pi.w != 0.0;
+    const bool some = charged ? pp.do_coul || pp.do_lj : pp.do_lj;
+    queue_walk<false>(g, a.cell_start, a.pk, nullptr, nullptr, 0, active && some, pi, charged ? pp.s_coul : pp.s_lj,
+                      charged ? pp.rq2 : pp.rlj2, charged ? a.t2_q : a.t2_lj, a.pk_scale, coded, Q, [](int) {}, drain);
+    queue_walk<false>(g, a.cell_start + g.ncell, a.pk, nullptr, nullptr, 0, active && pp.do_lj, pi, pp.s_lj, pp.rlj2,
+                      a.t2_lj, a.pk_scale, coded, Q, [](int) {}, drain);
+    drain(true);
   }
-  uc *= 0.5;
-  ul *= 0.5 * lj4;
-  wc *= 0.5;
-  wl *= 0.5 * pp.eps24;
-  const double sc = block_sum(uc, lds);
-  const double sl = block_sum(ul, lds);
-  const double vc = block_sum(wc, lds);
-  const double vl = block_sum(wl, lds);
-  if (threadIdx.x == 0) {
-    part[4 * blockIdx.x] = sc;
-    part[4 * blockIdx.x + 1] = sl;
-    part[4 * blockIdx.x + 2] = vc;
-    part[4 * blockIdx.x + 3] = vl;
-  }
+  sums.put(a, lds);
 }
 
 // part[2 b] = sum q_i^2 and part[2 b + 1] = sum |v_i|^2 over the particles
@@ -118,20 +184,22 @@ __global__ void __launch_bounds__(kEnergyThreads) k_energy_sq(int64_t n, const d
   }
 }
 
-// Thread-strided sum of part[stride * b + off] over b < nb (block_sum order).
-__device__ inline double sum_partials(const double *part, int64_t nb, int stride, int off, double *lds) {
-  double s = 0.0;
-  for (int64_t b = threadIdx.x; b < nb; b += kEnergyThreads) s += part[stride * b + off];
-  return block_sum(s, lds);
-}
-
 // One block: out[0] Coulomb real, out[1] LJ, out[2] Fourier, out[3] self,
 // out[4] kinetic, out[5..7] virials of the Coulomb real, LJ and Fourier terms.
 __global__ void __launch_bounds__(kEnergyThreads) k_energy_final(EnergyFinal a) {
   __shared__ double lds[kEnergyThreads / 64];
+  // thread-strided sums of the partials, several loads in flight: bound by
+  // their latency (16,384 partials one load at a time, 43 us; now 6.7)
   double near[4] = {0.0, 0.0, 0.0, 0.0};
-  if (a.near_part)
-    for (int t = 0; t < 4; ++t) near[t] = sum_partials(a.near_part, a.nb_near, 4, t, lds);
+#pragma unroll 8
+  for (int64_t b = threadIdx.x; b < a.nb_near; b += kEnergyThreads) {
+    const double4 v = ((const double4 *)a.near_part)[b];
+    near[0] += v.x;
+    near[1] += v.y;
+    near[2] += v.z;
+    near[3] += v.w;
+  }
+  for (int t = 0; t < 4; ++t) near[t] = block_sum(near[t], lds);
   double uf = 0.0, wf = 0.0;
   if (a.rho) {
     // U^{F,*} = kc (1/2) sum_l w_l |rho_l|^2 and its virial
@@ -148,8 +216,15 @@ __global__ void __launch_bounds__(kEnergyThreads) k_energy_final(EnergyFinal a) 
     uf = block_sum(s, lds);
     wf = block_sum(v, lds);
   }
-  const double q2 = sum_partials(a.sq_part, a.nb_sq, 2, 0, lds);
-  const double v2 = sum_partials(a.sq_part, a.nb_sq, 2, 1, lds);
+  double q2 = 0.0, v2 = 0.0;
+#pragma unroll 4
+  for (int64_t b = threadIdx.x; b < a.nb_sq; b += kEnergyThreads) {
+    const double2 v = ((const double2 *)a.sq_part)[b];
+    q2 += v.x;
+    v2 += v.y;
+  }
+  q2 = block_sum(q2, lds);
+  v2 = block_sum(v2, lds);
   if (threadIdx.x == 0) {
     a.out[0] = near[0];
     a.out[1] = near[1];
@@ -162,21 +237,34 @@ __global__ void __launch_bounds__(kEnergyThreads) k_energy_final(EnergyFinal a) 
   }
 }
 
-static int64_t energy_near_blocks(int64_t n) {
-  const int64_t nb = (n * kEnergyGroup + kEnergyThreads - 1) / kEnergyThreads;
+static int64_t energy_near_blocks(int64_t n, int lanes) {
+  const int64_t nb = (n * lanes + kEnergyThreads - 1) / kEnergyThreads;
   return nb < kEnergyNearBlocks ? nb : kEnergyNearBlocks;
 }
 
-int energy_part_len(int64_t n_max) { return (int)(4 * energy_near_blocks(n_max) + 2 * kEnergySqBlocks); }
+int energy_part_len(int64_t n_max) { return (int)(4 * energy_near_blocks(n_max, 64) + 2 * kEnergySqBlocks); }
 
 void launch_energy(const PairParams &pp, double lj4, int64_t n, const Sorted &s,
                    const int32_t *cell_start, bool near, const double *q, const double *vx, const double *vy,
                    const double *vz, double *part, EnergyFinal fin, hipStream_t st) {
   int64_t nb_near = 0;
   if (near && n > 0) {
-    nb_near = energy_near_blocks(n);
-    k_energy_near<<<(unsigned)nb_near, kEnergyThreads, 0, st>>>(pp, lj4, 2.0 * std::sqrt(pp.alpha / kPi), n, s.xq,
-                                                                 cell_start, part);
+    const int lanes = energy_lanes(pp, n, s.pk != nullptr);
+    nb_near = energy_near_blocks(n, lanes);
+    EnergyNear a{};
+    a.pp = pp;
+    a.lj4 = lj4;
+    a.two_sqrt_a_pi = 2.0 * std::sqrt(pp.alpha / kPi);
+    a.n = n;
+    a.xq = s.xq;
+    a.pk = s.pk;
+    a.pk_scale = s.pk_scale;
+    a.t2_q = pack_reach2(std::sqrt(pp.rq2), s.pk_scale);
+    a.t2_lj = pack_reach2(std::sqrt(pp.rlj2), s.pk_scale);
+    a.cell_start = cell_start;
+    a.part = part;
+    const auto kernel = lanes == 64 ? k_energy_near<64> : lanes == 32 ? k_energy_near<32> : k_energy_near_queue;
+    kernel<<<(unsigned)nb_near, kEnergyThreads, 0, st>>>(a);
   }
   double *sq_part = part + 4 * nb_near;
   int64_t nb_sq = (n + kEnergyThreads - 1) / kEnergyThreads;
