@@ -1036,7 +1036,7 @@ static int batch_forces(rbe_ctx *c, const rbe_state *s, const int32_t *m, const 
   a.cfz = s->fz;
   {
     TScope ts(c, RBE_TK_BATCH, st);
-    launch_batch_step(c->p.prec, a, eval, st);
+    launch_batch_step(c->p.prec, a, eval, true, st);
   }
   HIP_TRY(c, hipGetLastError());
   return RBE_OK;
@@ -1073,7 +1073,7 @@ static int batch_step(rbe_ctx *c, rbe_state *s, int32_t nsteps, uint64_t first_e
     const WorkSet *out = k == nsteps - 1 ? &S : &c->ws[k % 2];
     const BatchArgs a = batch_step_args(c, *in, *out);
     TScope ts(c, RBE_TK_BATCH, st);
-    launch_batch_step(c->p.prec, a, first_eval + (uint64_t)k, st);
+    launch_batch_step(c->p.prec, a, first_eval + (uint64_t)k, k == 0, st);
     in = out;
   }
   HIP_TRY(c, hipGetLastError());
@@ -1313,8 +1313,9 @@ extern "C" int rbe_step(rbe_ctx *c, rbe_state *s, int32_t nsteps, uint64_t first
       // the drift also writes the binning keys and run slots of the new
       // positions (the keys pass of the counting sort, fused)
       TScope ts(c, RBE_TK_KICK_DRIFT, st);
-      launch_bin_clear(c->bb, c->g, st);
-      const BinKeyOut bk{A->q, c->bb.key, c->bb.slot, c->bb.count};
+      const int64_t nkeys = 2 * (int64_t)c->g.ncell;
+      if (k == 0) launch_bin_clear(c->bb, nkeys, n, st);
+      const BinKeyOut bk = bin_keys_out(c->bb, nkeys, n, A->q);
       if (k == 0 || nvt)
         launch_kick_drift(n, h, c->p.dt, c->g, nvt ? c->nh_scale : nullptr, A->fx, A->fy, A->fz, A->vx, A->vy, A->vz,
                           A->x, A->y, A->z, c->err, bk, st);
@@ -1324,7 +1325,7 @@ extern "C" int rbe_step(rbe_ctx *c, rbe_state *s, int32_t nsteps, uint64_t first
     }
     {
       TScope ts(c, RBE_TK_BIN, st);
-      launch_bin_place(c->bb, c->g, n, c->cell_start, c->perm, st);
+      launch_bin_place(c->bb, 2 * (int64_t)c->g.ncell, n, c->cell_start, c->perm, st);
     }
     {
       TScope ts(c, RBE_TK_REORDER, st);

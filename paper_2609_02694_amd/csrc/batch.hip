@@ -35,9 +35,10 @@ constexpr int kBatchThreads = 256;
 // ---------------------------------------------------------------------------
 // Blocks [0, nb): one thread per particle. mode 0: v += h f, x <- wrap(x + dt
 // v) in place; both modes: the binning key of the (wrapped) position, its run
-// slot and the histogram (cleared before). Blocks from nb on: one thread per
-// (replica, mode) of evaluation `eval`.
-__global__ void __launch_bounds__(kBatchThreads) k_batch_drift(BatchArgs a, uint64_t eval, unsigned nb) {
+// slot and the histogram (count, cleared before; nullptr: the key alone).
+// Blocks from nb on: one thread per (replica, mode) of evaluation `eval`.
+__global__ void __launch_bounds__(kBatchThreads) k_batch_drift(BatchArgs a, uint64_t eval, unsigned nb,
+                                                               int32_t *count) {
   if (blockIdx.x >= nb) {
     const int64_t it = (blockIdx.x - nb) * (int64_t)kBatchThreads + threadIdx.x;
     if (it >= (int64_t)a.nrep * a.P) return;
@@ -91,7 +92,8 @@ __global__ void __launch_bounds__(kBatchThreads) k_batch_drift(BatchArgs a, uint
     k = (int)(R.c0 + (a.iq[i] == 0.0 ? R.g.ncell : 0) + (cz * R.g.ny + cy) * R.g.nx + cx);
     a.bin.key[i] = k;
   }
-  const int sl = run_slot(k, active, a.bin.count);  // every lane of the wave takes part in the vote
+  if (!count) return;
+  const int sl = run_slot(k, active, count);  // every lane of the wave takes part in the vote
   if (active) a.bin.slot[i] = sl;
 }
 
@@ -443,16 +445,15 @@ __global__ void __launch_bounds__(kBatchThreads) k_batch_gather(BatchArgs a, con
   }
 }
 
-void launch_batch_step(int prec, const BatchArgs &a, uint64_t eval, hipStream_t st) {
+void launch_batch_step(int prec, const BatchArgs &a, uint64_t eval, bool first, hipStream_t st) {
   const unsigned nb = (unsigned)((a.ntot + kBatchThreads - 1) / kBatchThreads);
   const int64_t nm = (int64_t)a.nrep * a.P;
   const unsigned mb = a.do_far ? (unsigned)((nm + kBatchThreads - 1) / kBatchThreads) : 0u;
   const bool f32 = prec == RBE_FP32C;
-  launch_fill_i32(a.bin.count, a.nkeys, 0, st);
-  k_batch_drift<<<nb + mb, kBatchThreads, 0, st>>>(a, eval, nb);
-  Grid keys{};
-  keys.ncell = (int)(a.nkeys / 2);  // every replica has 2 C_r keys
-  launch_bin_place(a.bin, keys, a.ntot, a.cell_start, a.perm, st);
+  if (first) launch_bin_clear(a.bin, a.nkeys, a.ntot, st);
+  k_batch_drift<<<nb + mb, kBatchThreads, 0, st>>>(a, eval, nb,
+                                                   bin_keys_out(a.bin, a.nkeys, a.ntot, nullptr).count);
+  launch_bin_place(a.bin, a.nkeys, a.ntot, a.cell_start, a.perm, st);
   k_batch_reorder<<<nb, kBatchThreads, 0, st>>>(a);
   unsigned near_blocks;
   const BatchKernel near = batch_near_kernel(prec, a.ntot, &near_blocks);

@@ -74,6 +74,9 @@ __global__ void __launch_bounds__(256) k_bin_keys(int64_t n, const double *__res
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanThreads * kScanItems;
+// Tiles up to which each block adds the sums before its own itself (at most
+// four loads a thread: under a microsecond, where a launch takes 4.6).
+constexpr int64_t kScanTotals = 1024;
 
 // Block-wide exclusive scan of one value per thread; returns the block total.
 __device__ inline int block_exclusive_scan(int v, int *lds_waves, int *out_excl) {
@@ -125,10 +128,21 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_top(int32_t *__restrict__
   if (threadIdx.x == 0) *grand_total = carry;
 }
 
+// TOTALS: tile_off holds the tiles' sums, not yet their offsets: each block adds
+// those before its own (and the last one the total), a launch less.
+template <bool TOTALS>
 __global__ void __launch_bounds__(kScanThreads) k_scan_apply(const int32_t *__restrict__ cnt, int64_t n,
                                                               const int32_t *__restrict__ tile_off,
                                                               int32_t *__restrict__ start) {
   __shared__ int lds[kScanThreads / 64];
+  int off = 0;
+  if (TOTALS) {
+    int before = 0, excl;
+    for (int t = threadIdx.x; t < (int)blockIdx.x; t += kScanThreads) before += tile_off[t];
+    off = block_exclusive_scan(before, lds, &excl);
+  } else {
+    off = tile_off[blockIdx.x];
+  }
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
   int v[kScanItems];
   int s = 0;
@@ -138,8 +152,9 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_apply(const int32_t *__re
     s += v[k];
   }
   int excl;
-  block_exclusive_scan(s, lds, &excl);
-  int run = tile_off[blockIdx.x] + excl;
+  const int total = block_exclusive_scan(s, lds, &excl);
+  if (TOTALS && threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) start[n] = off + total;
+  int run = off + excl;
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     if (base + k < n) start[base + k] = run;
@@ -153,8 +168,12 @@ int64_t scan_tiles(int64_t n) { return (n + kScanTile - 1) / kScanTile; }
 void launch_exclusive_scan(const int32_t *cnt, int64_t n, int32_t *start, int32_t *tmp, hipStream_t st) {
   const int64_t nt = scan_tiles(n);
   k_scan_tiles<<<(unsigned)nt, kScanThreads, 0, st>>>(cnt, n, tmp);
-  k_scan_top<<<1, kScanThreads, 0, st>>>(tmp, nt, start + n);
-  k_scan_apply<<<(unsigned)nt, kScanThreads, 0, st>>>(cnt, n, tmp, start);
+  if (nt <= kScanTotals) {
+    k_scan_apply<true><<<(unsigned)nt, kScanThreads, 0, st>>>(cnt, n, tmp, start);
+  } else {
+    k_scan_top<<<1, kScanThreads, 0, st>>>(tmp, nt, start + n);
+    k_scan_apply<false><<<(unsigned)nt, kScanThreads, 0, st>>>(cnt, n, tmp, start);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -162,8 +181,10 @@ void launch_exclusive_scan(const int32_t *cnt, int64_t n, int32_t *start, int32_
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_scatter_prov(int64_t n, const int32_t *__restrict__ key,
                                                       const int32_t *__restrict__ slot,
-                                                      const int32_t *__restrict__ start, int32_t *__restrict__ tmp) {
+                                                      const int32_t *__restrict__ start, int32_t *__restrict__ tmp,
+                                                      int32_t *__restrict__ count, int64_t nkeys) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  for (int64_t k = i; k < nkeys; k += (int64_t)gridDim.x * blockDim.x) count[k] = 0;  // for a later keys pass
   if (i >= n) return;
   tmp[start[key[i]] + slot[i]] = (int32_t)i;
 }
@@ -175,29 +196,152 @@ __global__ void __launch_bounds__(256) k_place_buckets(int64_t nkeys, const int3
   place_bucket(start[k], start[k + 1], tmp, perm);
 }
 
-void launch_bin_clear(const BinBuffers &b, const Grid &g, hipStream_t st) {
-  launch_fill_i32(b.count, 2 * (int64_t)g.ncell, 0, st);
+// ---------------------------------------------------------------------------
+// small systems: one block
+// ---------------------------------------------------------------------------
+// The whole sort (POS: with its keys pass) in one block. What it replaces is
+// six launches of 4.6 us each for a few thousand particles; it is bound by the
+// latency of its own phases: a step's binning 28 -> 5.7 us at 2,000
+// particles. The histogram and the starts stay in memory (the L2): in LDS they
+// would limit the grid.
+constexpr int kBlockBinThreads = 1024, kBlockBinEach = 8;  // 8,192 particles
+constexpr int64_t kBlockBinKeys = 32768;
+// The block's accesses to the histogram, all of them atomics that the L2
+// executes, are done before any that follow (a fence of the device's scope
+// would write the L2 back: 3 us).
+__device__ inline void histogram_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+}
+template <bool POS>
+__global__ void __launch_bounds__(kBlockBinThreads) k_bin_block(int n, int nkeys, const double *__restrict__ x,
+                                                                const double *__restrict__ y,
+                                                                const double *__restrict__ z,
+                                                                const double *__restrict__ q, Grid g,
+                                                                const int32_t *__restrict__ key_in, int32_t *count,
+                                                                int32_t *start, int32_t *__restrict__ perm) {
+  constexpr int T = kBlockBinThreads, E = kBlockBinEach;
+  __shared__ int32_t tmp[T * E];
+  __shared__ int waves[T / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int k = tid; k < nkeys; k += T) __hip_atomic_store(&count[k], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  int key[E], slot[E];
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    const int i = u * T + tid;
+    key[u] = -1 - lane;  // lanes past the end: a key no other lane has
+    if (i < n) {
+      if (POS) {
+        const int cx = cell_coord(wrap_coord(x[i], g.L[0]), g.inv_h[0], g.nx);
+        const int cy = cell_coord(wrap_coord(y[i], g.L[1]), g.inv_h[1], g.ny);
+        const int cz = cell_coord(wrap_coord(z[i], g.L[2]), g.inv_h[2], g.nz);
+        key[u] = (q[i] == 0.0 ? g.ncell : 0) + (cz * g.ny + cy) * g.nx + cx;
+      } else {
+        key[u] = key_in[i];
+      }
+    }
+  }
+  histogram_sync();  // it is clear
+#pragma unroll
+  for (int u = 0; u < E; ++u)
+    if (u * T < n) slot[u] = run_slot(key[u], u * T + tid < n, count);
+  histogram_sync();  // and complete
+  int carry = 0;
+  for (int base = 0; base < nkeys; base += T * E) {
+    const int k0 = base + tid * E;
+    int v[E], s = 0;
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+      v[u] = k0 + u < nkeys ? __hip_atomic_load(&count[k0 + u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+      s += v[u];
+    }
+    int incl = s;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += t;
+    }
+    if (lane == 63) waves[wave] = incl;
+    __syncthreads();
+    int run = carry + incl - s;
+    for (int w = 0; w < T / 64; ++w) {
+      if (w < wave) run += waves[w];
+      carry += waves[w];
+    }
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+      if (k0 + u < nkeys) start[k0 + u] = run;
+      run += v[u];
+    }
+    __syncthreads();  // waves is read before the next round writes it
+  }
+  if (tid == 0) start[nkeys] = carry;
+  __syncthreads();
+  int lo[E], hi[E];
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    lo[u] = hi[u] = 0;
+    if (u * T + tid < n) {
+      lo[u] = start[key[u]];
+      hi[u] = start[key[u] + 1];
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < E; ++u)
+    if (u * T + tid < n) tmp[lo[u] + slot[u]] = u * T + tid;
+  __syncthreads();
+  // a particle's place: the members of its bucket with a smaller input index
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    const int i = u * T + tid;
+    if (i >= n) continue;
+    int r = lo[u];
+    for (int t = lo[u]; t < hi[u]; ++t) r += tmp[t] < i;
+    perm[r] = i;
+  }
 }
 
-void launch_bin_place(const BinBuffers &b, const Grid &g, int64_t n, int32_t *cell_start, int32_t *perm,
+bool bin_in_block(int64_t n, int64_t nkeys) {
+  return n <= kBlockBinThreads * kBlockBinEach && nkeys <= kBlockBinKeys;
+}
+
+void launch_bin_clear(const BinBuffers &b, int64_t nkeys, int64_t n, hipStream_t st) {
+  if (!bin_in_block(n, nkeys)) launch_fill_i32(b.count, nkeys, 0, st);
+}
+
+BinKeyOut bin_keys_out(const BinBuffers &b, int64_t nkeys, int64_t n, const double *q) {
+  return BinKeyOut{q, b.key, b.slot, bin_in_block(n, nkeys) ? nullptr : b.count};
+}
+
+void launch_bin_place(const BinBuffers &b, int64_t nkeys, int64_t n, int32_t *cell_start, int32_t *perm,
                       hipStream_t st) {
-  const int64_t nkeys = 2 * (int64_t)g.ncell;
-  launch_exclusive_scan(b.count, nkeys, cell_start, b.scan_tmp, st);
-  if (n > 0) {
-    const unsigned blocks = (unsigned)((n + 255) / 256);
-    k_scatter_prov<<<blocks, 256, 0, st>>>(n, b.key, b.slot, cell_start, b.tmp);
-    k_place_buckets<<<(unsigned)((nkeys + 255) / 256), 256, 0, st>>>(nkeys, cell_start, b.tmp, perm);
+  if (bin_in_block(n, nkeys)) {
+    k_bin_block<false><<<1, kBlockBinThreads, 0, st>>>((int)n, (int)nkeys, nullptr, nullptr, nullptr, nullptr, Grid{},
+                                                       b.key, b.count, cell_start, perm);
+    return;
   }
+  launch_exclusive_scan(b.count, nkeys, cell_start, b.scan_tmp, st);
+  if (n <= 0) return;
+  const unsigned blocks = (unsigned)((n + 255) / 256);
+  k_scatter_prov<<<blocks, 256, 0, st>>>(n, b.key, b.slot, cell_start, b.tmp, b.count, nkeys);
+  k_place_buckets<<<(unsigned)((nkeys + 255) / 256), 256, 0, st>>>(nkeys, cell_start, b.tmp, perm);
 }
 
 void launch_bin(const BinBuffers &b, const Grid &g, int64_t n, const double *x, const double *y, const double *z,
                 const double *q, int32_t *cell_start, int32_t *perm, hipStream_t st) {
-  launch_bin_clear(b, g, st);
+  const int64_t nkeys = 2 * (int64_t)g.ncell;
+  if (bin_in_block(n, nkeys)) {
+    k_bin_block<true><<<1, kBlockBinThreads, 0, st>>>((int)n, (int)nkeys, x, y, z, q, g, nullptr, b.count, cell_start,
+                                                      perm);
+    return;
+  }
+  launch_bin_clear(b, nkeys, n, st);
   if (n > 0) {
     const unsigned blocks = (unsigned)((n + 255) / 256);
     k_bin_keys<<<blocks, 256, 0, st>>>(n, x, y, z, q, g, b.key, b.slot, b.count);
   }
-  launch_bin_place(b, g, n, cell_start, perm, st);
+  launch_bin_place(b, nkeys, n, cell_start, perm, st);
 }
 
 }  // namespace rbe

@@ -199,6 +199,7 @@ __device__ inline void drift_key(const BinKeyOut &bk, const Grid &g, int64_t i, 
     k = (bk.q[i] == 0.0 ? g.ncell : 0) + (cz * g.ny + cy) * g.nx + cx;
     bk.key[i] = k;
   }
+  if (!bk.count) return;
   const int sl = run_slot(k, active, bk.count);
   if (active) bk.slot[i] = sl;
 }

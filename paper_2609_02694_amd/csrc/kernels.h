@@ -21,9 +21,18 @@ void launch_exclusive_scan(const int32_t *cnt, int64_t n, int32_t *start, int32_
 void launch_bin(const BinBuffers &b, const Grid &g, int64_t n, const double *x, const double *y, const double *z,
                 const double *q, int32_t *cell_start, int32_t *perm, hipStream_t st);
 // The passes of launch_bin around its keys pass, for a keys pass fused into
-// another kernel: clearing the histogram, then scan, scatter and placement.
-void launch_bin_clear(const BinBuffers &b, const Grid &g, hipStream_t st);
-void launch_bin_place(const BinBuffers &b, const Grid &g, int64_t n, int32_t *cell_start, int32_t *perm,
+// another kernel: clearing the histogram (needed before the first keys pass of
+// a call: the scatter leaves it clear), the keys pass' outputs, then scan,
+// scatter and placement. Small systems (bin_in_block) are sorted by one block
+// from the keys alone: no histogram, no clearing.
+struct BinKeyOut {
+  const double *q;
+  int32_t *key, *slot, *count;  // count == nullptr: keys only
+};
+bool bin_in_block(int64_t n, int64_t nkeys);
+void launch_bin_clear(const BinBuffers &b, int64_t nkeys, int64_t n, hipStream_t st);
+BinKeyOut bin_keys_out(const BinBuffers &b, int64_t nkeys, int64_t n, const double *q);
+void launch_bin_place(const BinBuffers &b, int64_t nkeys, int64_t n, int32_t *cell_start, int32_t *perm,
                       hipStream_t st);
 
 // ---------------------------------------------------------------------------
@@ -308,10 +317,6 @@ void launch_sub_mean(int64_t n, const double *mean, double *fx, double *fy, doub
 // Binning keys of the drifted positions, written by the drift kernels for the
 // step's counting sort (key, run slot and histogram as the keys pass of
 // launch_bin; the histogram must be cleared before). key == nullptr: none.
-struct BinKeyOut {
-  const double *q;
-  int32_t *key, *slot, *count;
-};
 void launch_kick_kick_drift(int64_t n, double h, double dt, const Grid &g, const double *mean, const double *fx,
                             const double *fy, const double *fz, double *vx, double *vy, double *vz, double *x,
                             double *y, double *z, int *err, BinKeyOut bk, hipStream_t st);
@@ -392,7 +397,8 @@ struct BatchArgs {
 };
 
 // One step (mode 0) or force evaluation (mode 1) of every replica.
-void launch_batch_step(int prec, const BatchArgs &a, uint64_t eval, hipStream_t st);
+// first: the call's first step (the histogram is not clear).
+void launch_batch_step(int prec, const BatchArgs &a, uint64_t eval, bool first, hipStream_t st);
 // Per-replica charge statistics: nq[r] charged count, qs[2r] = sum q, qs[2r+1] = sum |q|.
 void launch_qstats_rep(int nrep, const int64_t *off, const double *q, int32_t *nq, double *qs, hipStream_t st);
 // Checks of Eq. 1 per replica (device error flags) and the structure-factor
