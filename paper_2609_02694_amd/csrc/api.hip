@@ -856,11 +856,12 @@ static int eval_sorted(rbe_ctx *c, int64_t n, const int32_t *m, const double *w,
     } else {
       TScope ts(c, RBE_TK_SAMPLE, st);
       if (!m) {
-        launch_sample_modes(c->mt, c->cdf_dev, c->p.seed, eval, P, c->m_dev, c->w_dev, c->err, st);
+        launch_sample_modes(c->mt, c->cdf_dev, c->p.seed, eval, P, c->m_dev, c->w_dev, c->err, st, 1, fb.mkd);
         m = c->m_dev;
         w = c->w_dev;
+      } else {
+        launch_modes_to_double(P, m, fb.mkd, st);
       }
-      launch_modes_to_double(P, m, fb.mkd, st);
     }
     {
       TScope ts(c, RBE_TK_RHO_PARTIAL, st);
@@ -1200,15 +1201,17 @@ extern "C" int rbe_energy(rbe_ctx *c, const rbe_state *s, const int32_t *m, cons
   const int P = c->p.P;
   EnergyFinal fin{};
   if (fourier) {
+    bool drawn = false;
     if (!m && c->fixed_modes) {
       m = c->m_dev;
       w = c->w_dev;
     } else if (!m) {
-      launch_sample_modes(c->mt, c->cdf_dev, c->p.seed, eval, P, c->m_dev, c->w_dev, c->err, st);
+      launch_sample_modes(c->mt, c->cdf_dev, c->p.seed, eval, P, c->m_dev, c->w_dev, c->err, st, 1, c->fb.mkd);
       m = c->m_dev;
       w = c->w_dev;
+      drawn = true;
     }
-    launch_modes_to_double(P, m, c->fb.mkd, st);
+    if (!drawn) launch_modes_to_double(P, m, c->fb.mkd, st);
     // structure factors always in FP64 here, whatever the context's precision
     const int32_t *nq = c->cell_start + c->g.ncell;
     FourierBuffers fb = c->fb;

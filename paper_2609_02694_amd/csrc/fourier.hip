@@ -9,19 +9,22 @@
 // box size.
 //
 // Structure factor: thread = mode, particles walked in a wave-uniform loop
-// (scalar loads of the packed (s, q) records), one partial sum per particle
-// chunk and mode. A wave left with fewer than 64 modes (P not a multiple of
+// (the chunk's (s, q) records staged in LDS), one partial sum per particle
+// chunk and mode; up to 128 modes the waves of a block share them (FP64). A wave left with fewer than 64 modes (P not a multiple of
 // 64) spreads each mode over several lanes that split the chunk's particles
 // and adds their sums with a fixed butterfly. The chunk partials are summed
 // in FP64 in a fixed order by a second kernel.
 //
 // Gather: thread = particle, modes walked in a wave-uniform loop with the
-// per-mode coefficients (m, w Im rho, w Re rho) in scalar registers.
+// per-mode coefficients (m, w Im rho, w Re rho) in scalar registers; for few
+// particles the waves of a block share the modes.
 //
 // FP32C form: the turn reduction stays FP64; the hardware turn-argument
 // sine/cosine (v_sin_f32 / v_cos_f32 compute sin(2 pi x), cos(2 pi x)) run on
 // the FP32 fraction; sums are FP32: blocks of 8 terms summed plainly, the
 // block sums added with Kahan compensation.
+#include <type_traits>
+
 #include "fourier_device.h"
 
 namespace rbe {
@@ -73,13 +76,18 @@ __global__ void __launch_bounds__(kModesPerBlock) k_rho_partial_f64(const int32_
   static_assert(kModesPerBlock == kTurnTable, "one table entry per thread");
   __shared__ double2 tab[kTurnTable];
   __shared__ double4 rec[kModesPerBlock];  // the chunk's records, staged a round at a time
+  __shared__ double2 shares[kModesPerBlock];
   const int64_t nq = *nq_ptr;
   int nchunks;
   const int chunk = rho_layout(nq, P, nchunk_max, &nchunks);
   if ((int)blockIdx.x >= nchunks) return;  // uniform over the block
   tab[threadIdx.x] = turn_tab[threadIdx.x];
-  const int lane = threadIdx.x & 63;
-  const int l0 = blockIdx.y * kModesPerBlock + (threadIdx.x & ~63);  // first mode of this wave
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // waves that share a mode set (1, 2 or 4: what P leaves of the block's four),
+  // each taking a run of every round's records
+  const int sets = blockIdx.y == 0 && P <= 128 ? (P + 63) / 64 : 4, split = 4 / sets;
+  const int share = wave / sets;
+  const int l0 = blockIdx.y * kModesPerBlock + wave % sets * 64;  // first mode of this wave
   const int a = max(0, min(64, P - l0));  // modes of this wave (0: it only stages records)
   const int64_t j0 = (int64_t)blockIdx.x * chunk;
   const int64_t j1 = min(nq, j0 + chunk);
@@ -102,13 +110,23 @@ __global__ void __launch_bounds__(kModesPerBlock) k_rho_partial_f64(const int32_
     if ((int)threadIdx.x < cnt) rec[threadIdx.x] = sq[b + threadIdx.x];
     __syncthreads();
     if (a == 0) continue;
+    const int run = (cnt + split - 1) / split, end = min(cnt, (share + 1) * run);
 #pragma unroll 4
-    for (int u = ph; u < cnt; u += rep) {
+    for (int u = share * run + ph; u < end; u += rep) {
       const double4 r = rec[u];
       double sn, cs;
       sincos_phase_f64(phase_dot(mx, my, mz, r.x, r.y, r.z), tab, &sn, &cs);
       re = fma(r.w, cs, re);
       im = fma(r.w, sn, im);
+    }
+  }
+  if (split > 1) {
+    shares[threadIdx.x] = make_double2(re, im);
+    __syncthreads();
+    if (share) return;
+    for (int k = 1; k < split; ++k) {
+      re += shares[threadIdx.x + k * sets * 64].x;
+      im += shares[threadIdx.x + k * sets * 64].y;
     }
   }
   if (a == 0) return;
@@ -760,6 +778,88 @@ __global__ void __launch_bounds__(kGatherThreads) k_gather_f32c(const int32_t *_
   if (two) put(i2, s2, hx, dx, hy, dy, hz, dz);
 }
 
+// Few particles: the W waves of a block share 64 of them, each taking every
+// W-th block of kSumBlock modes, and the waves' sums are added in order (FP64)
+// or, of W such blocks at a time, each block's with Kahan compensation in the
+// order of the modes (FP32C: the same bits as a lane that sums them one after
+// another). A lane on its own waits for 100 modes' loads and chains one after
+// another: 2,000 to 10,000 particles, 100 modes, FP64 21 -> 6.5 us, FP32C 32 ->
+// 5.6; 4,000 and 92,000 modes, FP32C 490 -> 292.
+template <bool F32, int W>
+__global__ void __launch_bounds__(64 * W) k_gather_waves(const int32_t *__restrict__ nq_ptr, int P, int M,
+                                                         const double4 *__restrict__ sq,
+                                                         const GatherMode *__restrict__ modes,
+                                                         const double2 *__restrict__ turn_tab, double kx, double ky,
+                                                         double kz, double *__restrict__ fx, double *__restrict__ fy,
+                                                         double *__restrict__ fz, double4 *__restrict__ gpart,
+                                                         int64_t stride, const int32_t *__restrict__ run_count) {
+  if (run_count && *run_count > 0) return;
+  using T = std::conditional_t<F32, float, double>;
+  __shared__ double2 tab[F32 ? 1 : kTurnTable];
+  __shared__ T sums[W][3][64];
+  const int64_t nq = *nq_ptr, i0 = blockIdx.x * (int64_t)64;
+  if (i0 >= nq) return;  // uniform over the block
+  if (!F32) {
+    for (int k = threadIdx.x; k < kTurnTable; k += 64 * W) tab[k] = turn_tab[k];
+    __syncthreads();
+  }
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const double4 s = sq[min(i0 + lane, nq - 1)];
+  const double sx = kTurnTable * s.x, sy = kTurnTable * s.y, sz = kTurnTable * s.z;
+  const int first = blockIdx.y * M, end = min(P, first + M);
+  const int nb = (end - first) / kSumBlock + 1;  // blocks of modes; the last may be empty
+  T g[3] = {};
+  float sum = 0.f, comp = 0.f;  // FP32C: component wave of the lane's particle
+  for (int b0 = 0; b0 < nb; b0 += W) {
+    const int lb = first + (b0 + wave) * kSumBlock, le = min(end, lb + kSumBlock);
+    if (F32) g[0] = g[1] = g[2] = 0;
+#pragma unroll 4
+    for (int l = lb; l < le; ++l) {
+      const GatherMode gm = modes[l];
+      if constexpr (F32) {
+        const float t = turn_f32(gm.mx, gm.my, gm.mz, s.x, s.y, s.z);
+        const float h = fmaf(gm.af, __builtin_amdgcn_cosf(t), -gm.bf * __builtin_amdgcn_sinf(t));
+        g[0] = fmaf(h, gm.mxf, g[0]);
+        g[1] = fmaf(h, gm.myf, g[1]);
+        g[2] = fmaf(h, gm.mzf, g[2]);
+      } else {
+        double sn, cs;
+        sincos_phase_f64(phase_dot(gm.mx, gm.my, gm.mz, sx, sy, sz), tab, &sn, &cs);
+        const double h = gm.a * cs - gm.b * sn;
+        g[0] = fma(h, gm.mx, g[0]);
+        g[1] = fma(h, gm.my, g[1]);
+        g[2] = fma(h, gm.mz, g[2]);
+      }
+    }
+    if (F32) {
+      for (int d = 0; d < 3; ++d) sums[wave][d][lane] = g[d];
+      __syncthreads();
+      if (wave < 3)
+        for (int k = 0; k < W && b0 + k < nb; ++k) kahan_add(sum, comp, (float)sums[k][wave][lane]);
+      __syncthreads();
+    }
+  }
+  if (!F32) {
+    for (int d = 0; d < 3; ++d) sums[wave][d][lane] = g[d];
+    __syncthreads();
+  }
+  const int64_t i = i0 + lane;
+  if (wave >= 3 || i >= nq) return;
+  double v;
+  if (F32) {
+    v = (double)sum - (double)comp;
+  } else {
+    v = 0.0;
+    for (int k = 0; k < W; ++k) v += (double)sums[k][wave][lane];
+  }
+  if (gpart) {
+    ((double *)&gpart[blockIdx.y * stride + i])[wave] = v;
+    return;
+  }
+  double *f = wave == 0 ? fx : wave == 1 ? fy : fz;
+  f[i] -= s.w * (wave == 0 ? kx : wave == 1 ? ky : kz) * v;
+}
+
 // The groups' sums of each charged particle added in group order (FP64),
 // then applied like the single-group gather.
 __global__ void __launch_bounds__(256) k_gather_reduce(const int32_t *__restrict__ nq_ptr, int groups,
@@ -801,6 +901,12 @@ static int gather_split(int64_t nq_max, int P, const FourierBuffers &fb, int *M)
   return (int)((P + m - 1) / m);
 }
 
+// Particles up to which the waves of a block share them (k_gather_waves),
+// against the other form in us: 100 modes FP64 20,000: 7, 21; 130,000: 20, 23;
+// 200,000: 27, 26; 300,000: 38, 31; FP32C 20,000: 8, 32; 200,000: 28, 33;
+// 300,000: 40, 37; 500 modes FP64 200,000: 90, 108; FP32C 200,000: 101, 134;
+// 300,000: 148, 137.
+constexpr int64_t kGatherWavesMost64 = 196608, kGatherWavesMost32 = 262144;
 void launch_fourier_gather(int prec, const int32_t *nq, int64_t nq_max, int P, const double4 *sq,
                            const FourierBuffers &fb, const Grid &g, double *fx, double *fy, double *fz,
                            hipStream_t st) {
@@ -811,21 +917,28 @@ void launch_fourier_gather(int prec, const int32_t *nq, int64_t nq_max, int P, c
   const int G = gather_split(nq_max, P, fb, &M);
   double4 *gp = G > 1 ? fb.gpart : nullptr;
   const int64_t stride = (int64_t)blocks * 256;
-  const dim3 grid(blocks, (unsigned)G);
-  // segments: groups for about 1024 blocks, if the particles alone are fewer
+  // segments: groups for about 1024 blocks, if the particles alone are fewer,
+  // of at least eight segments a wave
   const ModeRuns &R = fb.runs;
   const int32_t *rc = R.cap ? R.count : nullptr;
   const int64_t rb = (nq_max + kRunGather - 1) / kRunGather;
-  const int64_t rg = gp ? std::max<int64_t>(1, std::min(1024 / rb, kGatherPartMax / stride)) : 1;
-  if (prec == RBE_FP32C)
+  const int64_t rg = gp ? std::max<int64_t>(1, std::min({1024 / rb, kGatherPartMax / stride,
+                                                         (int64_t)P / (32 * kRunLen)}))
+                        : 1;
+  if (R.cap)
+    k_gather_runs<<<dim3((unsigned)rb, (unsigned)rg), 256, 0, st>>>(nq, R.count, R.rec, sq, fb.turn_tab, kx, ky, kz,
+                                                                    fx, fy, fz, gp, stride);
+  const bool f32 = prec == RBE_FP32C;
+  if (nq_max <= (f32 ? kGatherWavesMost32 : kGatherWavesMost64)) {
+    const auto kernel = f32 ? k_gather_waves<true, 16> : k_gather_waves<false, 16>;
+    kernel<<<dim3((unsigned)((nq_max + 63) / 64), (unsigned)G), 1024, 0, st>>>(
+        nq, P, M, sq, fb.modes, fb.turn_tab, kx, ky, kz, fx, fy, fz, gp, stride, rc);
+  } else if (f32) {
     k_gather_f32c<<<dim3((unsigned)((nq_max + kGatherPerBlock - 1) / kGatherPerBlock), (unsigned)G), kGatherThreads,
                     0, st>>>(nq, P, M, sq, fb.modes, kx, ky, kz, fx, fy, fz, gp, stride);
-  else {
-    if (R.cap)
-      k_gather_runs<<<dim3((unsigned)rb, (unsigned)rg), 256, 0, st>>>(nq, R.count, R.rec, sq, fb.turn_tab, kx, ky, kz,
-                                                                      fx, fy, fz, gp, stride);
-    k_gather_f64<<<grid, kTurnTable, 0, st>>>(nq, P, M, sq, fb.modes, fb.turn_tab, kx, ky, kz, fx, fy, fz, gp,
-                                              stride, rc);
+  } else {
+    k_gather_f64<<<dim3(blocks, (unsigned)G), kTurnTable, 0, st>>>(nq, P, M, sq, fb.modes, fb.turn_tab, kx, ky, kz, fx,
+                                                                   fy, fz, gp, stride, rc);
   }
   if (G > 1) k_gather_reduce<<<blocks, 256, 0, st>>>(nq, G, (int)rg, rc, stride, gp, sq, kx, ky, kz, fx, fy, fz);
 }
