@@ -31,6 +31,7 @@ struct TileCtx {
   Sten s;                  // halo radius in cells
   int ntx, nty, ntz;       // tiles per axis
   int cap;                 // records the LDS staging holds
+  int parts;               // blocks per tile (LANES > 1)
   int iblk;                // species blocks supplying i (bit 0 charged, bit 1 neutral)
   const double4 *__restrict__ xq;
   const int32_t *__restrict__ cell_start;
@@ -150,15 +151,21 @@ __device__ inline void tile_kahan(float &s, float &c, float v) {
 
 // Five waves per SIMD (at most 96 VGPRs, two of them spilled outside the
 // candidate loop): 25.8 against 27.3 ms per 64M step at four.
-template <bool GHOST, bool COUNT>
+//
+// LANES, parts: systems of too few tiles to fill the chip (the tiles cannot be
+// smaller: their centres set the rounding of the frame) take LANES lanes per
+// particle, which walk LANES consecutive rows at a time and then add their
+// sums in the order of the rows, and `parts` blocks per tile, each with a
+// share of its particles: the same bits from any number of lanes and blocks.
+// 2,001 particles, 16 tiles: 43 -> 18 us.
+template <bool GHOST, bool COUNT, int LANES>
 __global__ void __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(5))) k_pair_tile(TileCtx c) {
   using T = float;
   using V = float4;
   extern __shared__ __align__(16) unsigned char tile_lds[];
   __shared__ int wsum[kTileThreads / 64];
-  __shared__ int seg_n[kTileMaxSegs];       // own row segments: i count, then prefix
-  __shared__ int seg_g0[kTileMaxSegs];      // first native index of each segment
-  __shared__ int seg_i0[kTileMaxSegs + 1];
+  __shared__ int seg_g0[kTileMaxSegs];      // own row segments: first native index
+  __shared__ int seg_i0[kTileMaxSegs + 1];  // and particles before
   __shared__ int chunk_r0[kTileMaxChunks], chunk_r1[kTileMaxChunks];  // row ranges staged together
   __shared__ int nchunk_s;
   __shared__ int ilist[kTileIMax];  // the tile's particles grouped by quadrant
@@ -167,7 +174,8 @@ __global__ void __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_
   const PairParams &pp = c.pp;
   const Grid &g = pp.g;
   const int tid = threadIdx.x;
-  const int tile = (int)xcd_block(blockIdx.x, gridDim.x);
+  const int item = (int)xcd_block(blockIdx.x, gridDim.x);
+  const int tile = LANES == 1 ? item : item / c.parts, part = LANES == 1 ? 0 : item % c.parts;
   const int tx = tile % c.ntx, ty = (tile / c.ntx) % c.nty, tz = tile / (c.ntx * c.nty);
   const int x0 = tx * c.TX, y0 = ty * c.TY, z0 = tz * c.TZ;
   const int HX = c.TX + 2 * c.s.x, HY = c.TY + 2 * c.s.y, HZ = c.TZ + 2 * c.s.z;
@@ -203,6 +211,7 @@ __global__ void __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_
 
   // ---- own row segments (one per own row and species block) ----------------
   const int nsegs = 2 * c.TY * c.TZ;
+  int own = 0;  // particles of this thread's segment
   if (tid < nsegs) {
     const int b = tid / (c.TY * c.TZ), rr = tid % (c.TY * c.TZ);
     const int yy = y0 + rr % c.TY, zz = z0 + rr / c.TY;
@@ -213,8 +222,19 @@ __global__ void __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_
       a = c.cell_start[key + x0];
       e = c.cell_start[key + xe];
     }
-    seg_n[tid] = e - a;
+    own = e - a;
     seg_g0[tid] = a;
+  }
+  static_assert(kTileMaxSegs == 64, "a wave scans the segments' counts");
+  if (tid < 64) {
+    int incl = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(incl, o, 64);
+      if (tid >= o) incl += t;
+    }
+    if (tid < nsegs) seg_i0[tid + 1] = incl;
+    if (tid == 0) seg_i0[0] = 0;
   }
   // ---- halo cell counts -----------------------------------------------------
   for (int h = tid; h < ncells; h += kTileThreads) {
@@ -227,14 +247,6 @@ __global__ void __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_
     cs[h] = cnt;
   }
   __syncthreads();
-  if (tid == 0) {
-    int tot = 0;
-    for (int k = 0; k < nsegs; ++k) {
-      seg_i0[k] = tot;
-      tot += seg_n[k];
-    }
-    seg_i0[nsegs] = tot;
-  }
   const int total = tile_scan(cs, ncells, wsum);
   const int ni = seg_i0[nsegs];
   if (ni == 0) return;  // uniform: no particle of these species in the tile
@@ -243,6 +255,11 @@ __global__ void __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_
   if (tid == 0) {
     cs[ncells] = total;
     int nch = 0, row0 = 0;
+    if (total <= c.cap) {
+      chunk_r0[0] = 0;
+      chunk_r1[0] = row0 = nrows;
+      nch = 1;
+    }
     while (row0 < nrows && nch < kTileMaxChunks) {
       int r1 = row0;
       while (r1 < nrows && cs[(r1 + 1) * HX] - cs[row0 * HX] <= c.cap) ++r1;
@@ -299,7 +316,7 @@ __global__ void __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_
     while (sgi + 1 < nsegs && seg_i0[sgi + 1] <= li) ++sgi;
     return seg_g0[sgi] + (li - seg_i0[sgi]);
   };
-  const bool grouped = ni <= kTileIMax;
+  const bool grouped = LANES == 1 && ni <= kTileIMax;
   if (grouped) {
     if (tid < 4) qcnt[tid] = 0;
     __syncthreads();
@@ -329,9 +346,11 @@ __global__ void __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_
   }
 
   unsigned long long n_pairs = 0, n_cand = 0;
-  const int rounds = (ni + kTileThreads - 1) / kTileThreads;
+  constexpr int kRound = kTileThreads / LANES;  // particles of a round of this block
+  const int parts = LANES == 1 ? 1 : c.parts, sub = tid % LANES;
+  const int rounds = (ni + kRound * parts - 1) / (kRound * parts);
   for (int round = 0; round < rounds; ++round) {
-    const int li = round * kTileThreads + tid;
+    const int li = (round * parts + part) * kRound + tid / LANES;
     const bool active = li < ni;
     int gi = 0;
     if (active) gi = grouped ? ilist[li] : nth_particle(li);
@@ -392,64 +411,90 @@ __global__ void __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_
         if (k.band) k.in = fp64_in(v);
         add(k, px, py, pz);
       };
-      // the rows the reach sphere touches, each trimmed to the x-cells it
-      // spans; a row's terms are summed in FP32 and its sum added to the
-      // total with Kahan compensation
-      for (int dz = -c.s.z; dz <= c.s.z; ++dz) {
-        const int rz = iz + dz;
-        const T gz = tile_gap(zi, Z0 + (T)rz * Hz, Hz, margin);
-        if (gz * gz > rc2) continue;
-        for (int dy = -c.s.y; dy <= c.s.y; ++dy) {
-          const int ry = iy + dy;
-          const int row = rz * HY + ry;
-          if (row < r0 || row >= r1) continue;
-          const T gy = tile_gap(yi, Y0 + (T)ry * Hy, Hy, margin);
-          const T rem = rc2 - (gy * gy + gz * gz);
-          if (rem < T(0)) continue;
-          // the hardware square root (within 1 ulp) suffices: the margin
-          // (1e-4 in FP32) covers its error many times over
-          const T ext = __builtin_amdgcn_sqrtf(rem) + margin;
-          int xa = (int)floor((xi - ext - X0) * invHx), xb = (int)floor((xi + ext - X0) * invHx);
-          xa = max(xa, max(ix - c.s.x, 0));
-          xb = min(xb, min(ix + c.s.x, HX - 1));
-          if (xa > xb) continue;
-          const int ka = cs[row * HX + xa] - base, kb = cs[row * HX + xb + 1] - base;
+      // a row the reach sphere touches (at slab distance gz along z), trimmed
+      // to the x-cells it spans: its terms' FP32 sum; false: out of reach
+      auto row_sum = [&](T gz, int rz, int dy, T &px, T &py, T &pz) {
+        const int ry = iy + dy;
+        const int row = rz * HY + ry;
+        if (row < r0 || row >= r1) return false;
+        const T gy = tile_gap(yi, Y0 + (T)ry * Hy, Hy, margin);
+        const T rem = rc2 - (gy * gy + gz * gz);
+        if (rem < T(0)) return false;
+        // the hardware square root (within 1 ulp) suffices: the margin
+        // (1e-4 in FP32) covers its error many times over
+        const T ext = __builtin_amdgcn_sqrtf(rem) + margin;
+        int xa = (int)floor((xi - ext - X0) * invHx), xb = (int)floor((xi + ext - X0) * invHx);
+        xa = max(xa, max(ix - c.s.x, 0));
+        xb = min(xb, min(ix + c.s.x, HX - 1));
+        if (xa > xb) return false;
+        const int ka = cs[row * HX + xa] - base, kb = cs[row * HX + xb + 1] - base;
+        // four candidates per trip, all records requested before use; the
+        // trip count runs on the record pointer alone
+        const V *q = rec + ka;
+        const V *const qe = rec + kb, *const qe4 = qe - 3;
+        for (; q < qe4; q += 4) {
+          const V v0 = q[0], v1 = q[1], v2 = q[2], v3 = q[3];
+          Cand k0 = prep(v0), k1 = prep(v1), k2 = prep(v2), k3 = prep(v3);
+          // one wave-uniform branch for the rare guard-band candidates of
+          // the trip (the lane masks are combined as scalars)
+          if (__builtin_amdgcn_ballot_w64(k0.band) | __builtin_amdgcn_ballot_w64(k1.band) |
+              __builtin_amdgcn_ballot_w64(k2.band) | __builtin_amdgcn_ballot_w64(k3.band)) {
+            if (k0.band) k0.in = fp64_in(v0);
+            if (k1.band) k1.in = fp64_in(v1);
+            if (k2.band) k2.in = fp64_in(v2);
+            if (k3.band) k3.in = fp64_in(v3);
+          }
+          add(k0, px, py, pz);
+          add(k1, px, py, pz);
+          add(k2, px, py, pz);
+          add(k3, px, py, pz);
+        }
+        if (q + 1 < qe) {
+          const V v0 = q[0], v1 = q[1];
+          cand(v0, px, py, pz);
+          cand(v1, px, py, pz);
+          q += 2;
+        }
+        if (q < qe) cand(q[0], px, py, pz);
+        return true;
+      };
+      // the rows' sums are added to the total with Kahan compensation, in order
+      if constexpr (LANES == 1) {
+        for (int dz = -c.s.z; dz <= c.s.z; ++dz) {
+          const int rz = iz + dz;
+          const T gz = tile_gap(zi, Z0 + (T)rz * Hz, Hz, margin);
+          if (gz * gz > rc2) continue;
+          for (int dy = -c.s.y; dy <= c.s.y; ++dy) {
+            T px = T(0), py = T(0), pz = T(0);
+            if (!row_sum(gz, rz, dy, px, py, pz)) continue;
+            tile_kahan(S[0], K[0], px);
+            tile_kahan(S[1], K[1], py);
+            tile_kahan(S[2], K[2], pz);
+          }
+        }
+      } else {
+        const int ny = 2 * c.s.y + 1, all = ny * (2 * c.s.z + 1);
+        for (int e0 = 0; e0 < all; e0 += LANES) {  // the lanes of a particle together
+          const int e = e0 + sub;
           T px = T(0), py = T(0), pz = T(0);
-          // four candidates per trip, all records requested before use; the
-          // trip count runs on the record pointer alone
-          const V *q = rec + ka;
-          const V *const qe = rec + kb, *const qe4 = qe - 3;
-          for (; q < qe4; q += 4) {
-            const V v0 = q[0], v1 = q[1], v2 = q[2], v3 = q[3];
-            Cand k0 = prep(v0), k1 = prep(v1), k2 = prep(v2), k3 = prep(v3);
-            // one wave-uniform branch for the rare guard-band candidates of
-            // the trip (the lane masks are combined as scalars)
-            if (__builtin_amdgcn_ballot_w64(k0.band) | __builtin_amdgcn_ballot_w64(k1.band) |
-                __builtin_amdgcn_ballot_w64(k2.band) | __builtin_amdgcn_ballot_w64(k3.band)) {
-              if (k0.band) k0.in = fp64_in(v0);
-              if (k1.band) k1.in = fp64_in(v1);
-              if (k2.band) k2.in = fp64_in(v2);
-              if (k3.band) k3.in = fp64_in(v3);
-            }
-            add(k0, px, py, pz);
-            add(k1, px, py, pz);
-            add(k2, px, py, pz);
-            add(k3, px, py, pz);
+          bool met = false;
+          if (e < all) {
+            const int rz = iz + e / ny - c.s.z;
+            const T gz = tile_gap(zi, Z0 + (T)rz * Hz, Hz, margin);
+            if (gz * gz <= rc2) met = row_sum(gz, rz, e % ny - c.s.y, px, py, pz);
           }
-          if (q + 1 < qe) {
-            const V v0 = q[0], v1 = q[1];
-            cand(v0, px, py, pz);
-            cand(v1, px, py, pz);
-            q += 2;
+#pragma unroll
+          for (int k = 0; k < LANES; ++k) {
+            const T ax = __shfl(px, k, LANES), ay = __shfl(py, k, LANES), az = __shfl(pz, k, LANES);
+            if (!__shfl((int)met, k, LANES)) continue;
+            tile_kahan(S[0], K[0], ax);
+            tile_kahan(S[1], K[1], ay);
+            tile_kahan(S[2], K[2], az);
           }
-          if (q < qe) cand(q[0], px, py, pz);
-          tile_kahan(S[0], K[0], px);
-          tile_kahan(S[1], K[1], py);
-          tile_kahan(S[2], K[2], pz);
         }
       }
     }
-    if (active) {
+    if (active && sub == 0) {
       c.fx[gi] = lj_scale * ((double)S[0] - (double)K[0]);
       c.fy[gi] = lj_scale * ((double)S[1] - (double)K[1]);
       c.fz[gi] = lj_scale * ((double)S[2] - (double)K[2]);
@@ -464,6 +509,10 @@ __global__ void __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_
 // ---------------------------------------------------------------------------
 // launch
 // ---------------------------------------------------------------------------
+// Tiles up to which a particle takes 8 or 2 lanes, and a tile as many blocks;
+// 1, 2 and 8 lanes in us: 16 tiles 47, 34, 22; 80: 32, 25, 25; 120: 31, 26, 36
+// (with ghosts, 100: 67, 50, 41); 160: 31, 26, 40; 400: 39, 48, 86.
+constexpr int64_t kTileLanes8 = 96, kTileLanes2 = 256;
 constexpr size_t kTileLdsBytes = 48 * 1024;
 
 // Tile of the LJ pass: y/z extent of about 4-5 sigma, x extent such that a
@@ -505,14 +554,22 @@ static void tile_geometry(const PairParams &pp, const Sten &s, int64_t n, TileCt
 }
 
 template <bool GHOST>
-static void launch_tile_t(const TileCtx &c, hipStream_t st) {
+static void launch_tile_t(TileCtx c, hipStream_t st) {
   const int ncells = (c.TY + 2 * c.s.y) * (c.TZ + 2 * c.s.z) * (c.TX + 2 * c.s.x);
   const size_t lds = ((size_t)(ncells + 1) * sizeof(int) + 15) / 16 * 16 + (size_t)c.cap * sizeof(float4);
-  const unsigned tiles = (unsigned)((int64_t)c.ntx * c.nty * c.ntz);
-  if (c.counters)
-    k_pair_tile<GHOST, true><<<tiles, kTileThreads, lds, st>>>(c);
-  else
-    k_pair_tile<GHOST, false><<<tiles, kTileThreads, lds, st>>>(c);
+  const int64_t tiles = (int64_t)c.ntx * c.nty * c.ntz;
+  const int lanes = tiles <= kTileLanes8 ? 8 : tiles <= kTileLanes2 ? 2 : 1;
+  c.parts = lanes;  // one round of a full tile's particles per block
+  if (lanes == 8) {
+    const auto kernel = c.counters ? k_pair_tile<GHOST, true, 8> : k_pair_tile<GHOST, false, 8>;
+    kernel<<<(unsigned)(tiles * c.parts), kTileThreads, lds, st>>>(c);
+  } else if (lanes == 2) {
+    const auto kernel = c.counters ? k_pair_tile<GHOST, true, 2> : k_pair_tile<GHOST, false, 2>;
+    kernel<<<(unsigned)(tiles * c.parts), kTileThreads, lds, st>>>(c);
+  } else {
+    const auto kernel = c.counters ? k_pair_tile<GHOST, true, 1> : k_pair_tile<GHOST, false, 1>;
+    kernel<<<(unsigned)tiles, kTileThreads, lds, st>>>(c);
+  }
 }
 
 bool lj_tile_applicable(int prec, const PairParams &pp, int64_t n) {

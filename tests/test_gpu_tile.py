@@ -1,0 +1,26 @@
+"""LJ cell tiles of the FP32C form with 8, 2 and 1 lanes per particle (few,
+some and many tiles): against the oracle to 1e-5 as for the other FP32C forms."""
+import pytest
+
+import oracle
+from gpu_common import ROW32, gpu_forces, max_row_err, oracle_forces, rel_err, system
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import paper_2609_02694_amd as rbe  # noqa: E402
+
+
+@pytest.mark.parametrize("name,n,over", [
+    ("replica", 868, {}), ("replica", 2_001, {}), ("replica", 24_000, {}), ("replica", 36_000, {}),
+    ("replica", 50_001, {}), ("replica", 90_000, {}),
+    ("subdomain64m", 9_001, {}), ("subdomain64m", 30_000, {}), ("subdomain64m", 45_000, {}),
+])
+def test_tile_lanes_match_oracle(name, n, over):
+    p, s = system(name, n=n - n % 4, **over)
+    m, w = oracle.sample_k(p["seed"], 0, p["L"], p["alpha"], p["P"])
+    ref = oracle_forces(p, s, m, w, terms=oracle.LJ, cells=True)["F"]
+    F = gpu_forces(p, s, prec=rbe.FP32C, terms=rbe.TERM_LJ, m=m, w=w)
+    e, r = rel_err(F, ref), max_row_err(F, ref)
+    print(f"tile lanes {name} n={n} rel err {e:.3e} max row {r:.3e}")
+    assert e < 1e-5 and r < ROW32
