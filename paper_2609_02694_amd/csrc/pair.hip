@@ -718,13 +718,14 @@ PairF32 make_pair_f32(const PairParams &pp) {
 
 // Random batch list of a part. FP32C: the cluster form, whose lanes add their
 // terms in its own order. FP64: the group form, 64 lanes per particle, or 32
-// where the mean shell would leave most of 64 without a candidate, up to the
-// size from which the cluster form's waves fill the chip (group / cluster):
-// wide shells 200,000 electrolyte 319 / 453 us, 1M 1.35 / 1.39 ms, 2M 2.62 /
-// 2.49; narrow ones 20,000 LJ electrolyte 32 / 43 us, 50,000 78 / 72, 200,000
-// 236 / 186.
+// and 16 where the mean shell would leave most of 64 without a candidate, up
+// to the size from which the cluster form's waves fill the chip (group /
+// cluster): wide shells 200,000 electrolyte 319 / 453 us, 1M 1.35 / 1.39 ms,
+// 2M 2.62 / 2.49; narrow ones (32 lanes, 16 lanes / cluster) 2,000 LJ
+// electrolyte 11, 15; 10,000 21, 20; 30,000 46, 39 / 51; 50,000 78, 57 / 71;
+// 100,000 134, 115 / 108.
 constexpr double kRblWide = 48.0;  // particles within r_coul of one, on average
-constexpr int64_t kRblGroupWide = 1 << 20, kRblGroupNarrow = 32768;
+constexpr int64_t kRblGroupWide = 1 << 20, kRblGroupNarrow = 65536, kRblNarrow32 = 8192;
 template <bool F32, bool COUNT, bool GHOST, bool QSHELL>
 static void launch_rbl(PairCtx c, hipStream_t st) {
   const Grid &g = c.pp.g;
@@ -733,7 +734,8 @@ static void launch_rbl(PairCtx c, hipStream_t st) {
   if (F32 || c.n > (wide ? kRblGroupWide : kRblGroupNarrow))
     k_pair_rbl<F32, COUNT, GHOST, QSHELL><<<(unsigned)((c.n + kCI - 1) / kCI), 64, 0, st>>>(c);
   else if (wide) k_pair_rbl_group<COUNT, GHOST, QSHELL, 64><<<group_blocks(c.n, 64), 256, 0, st>>>(c);
-  else k_pair_rbl_group<COUNT, GHOST, QSHELL, 32><<<group_blocks(c.n, 32), 256, 0, st>>>(c);
+  else if (c.n <= kRblNarrow32) k_pair_rbl_group<COUNT, GHOST, QSHELL, 32><<<group_blocks(c.n, 32), 256, 0, st>>>(c);
+  else k_pair_rbl_group<COUNT, GHOST, QSHELL, 16><<<group_blocks(c.n, 16), 256, 0, st>>>(c);
 }
 
 // Plain sums of a part (c.charged): one thread per particle, or a group of

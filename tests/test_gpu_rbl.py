@@ -1,7 +1,7 @@
 """Random batch list, FP64: the group form (64 lanes per particle for a wide
-shell, 32 for a narrow one) and the cluster form, at the sizes where one gives
-way to the other. Against the oracle with the bounds of the other FP64 forms:
-1e-12 over all particles, 1e-10 of the RMS force per row."""
+shell, 32 or 16 for a narrow one) and the cluster form, at the sizes where one
+gives way to the other. Against the oracle with the bounds of the other FP64
+forms: 1e-12 over all particles, 1e-10 of the RMS force per row."""
 import numpy as np
 import pytest
 
@@ -17,8 +17,11 @@ import paper_2609_02694_amd as rbe  # noqa: E402
 @pytest.mark.parametrize("name,n,over", [
     ("ljelectrolyte", 1_024, {}),                   # narrow shell, small grid
     ("ljelectrolyte", 2_000, {"r_core": 0.0001}),   # no core: all pairs in the shell
-    ("ljelectrolyte", 32_768, {}),                  # narrow shell, the last size of the group form
-    ("ljelectrolyte", 32_770, {}),                  # and the cluster form after it
+    ("ljelectrolyte", 8_192, {}),                   # narrow shell, the last size of 32 lanes
+    ("ljelectrolyte", 8_194, {}),                   # and 16
+    ("ljelectrolyte", 32_770, {}),
+    ("ljelectrolyte", 65_536, {}),                  # the last size of the group form
+    ("ljelectrolyte", 65_538, {}),                  # and the cluster form after it
     ("electrolyte1m", 9_001, {"ghost": 6.0}),       # wide shell, ghosts, a last group alone
     ("electrolyte1m", 9_001, {"p_shell": 32}),      # the longest batch
     ("electrolyte1m", (1 << 20) + 1, {}),           # wide shell, the cluster form
