@@ -17,7 +17,8 @@
 // in runs. A wave takes one atomic per run (its length) and hands out the
 // slots of the run in input order; a bucket is then usually already in order
 // and its placement a copy (checked per bucket; out-of-order buckets are
-// sorted by insertion).
+// sorted by insertion). Small systems run all steps in one block
+// (k_bin_block).
 #include "rbe_internal.h"
 #include "kernels.h"
 

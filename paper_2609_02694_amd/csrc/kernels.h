@@ -176,7 +176,7 @@ void launch_pair(int prec, int part, const PairParams &pp, int64_t n, const int3
 // particles (counters [4] or nullptr: [1] LJ pair terms, [2] candidates).
 // Used on grids whose mean cell occupancy suits the staging
 // (lj_tile_applicable, false for every other precision); the other cases
-// keep the thread-form walks.
+// take the walks of launch_pair.
 bool lj_tile_applicable(int prec, const PairParams &pp, int64_t n);
 void launch_lj_tile(const PairParams &pp, int64_t n, int iblk, const Sorted &s, const int32_t *cell_start,
                     const GhostBuffers *gb, double *fx, double *fy, double *fz, unsigned long long *counters,

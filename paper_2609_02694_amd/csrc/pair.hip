@@ -1,14 +1,24 @@
 // Near-field force (Sec. 2.1, Eq. 7-8, 10-11): erfc-screened Coulomb plus
 // 12-6 Lennard-Jones over a cell list, with the core-shell random batch list.
 //
-// Full neighbour sums per particle i (cell order), no atomics. Two forms:
-// plain sums run one thread per particle, each walking the stencil rows of
-// its own cell; the random batch list runs one wave per cluster of 8
-// consecutive particles: lane l takes i = cluster[l / 8] and every 8th record
-// of one candidate sequence shared by the wave (the union of the cluster's
-// stencils), so the candidate loads are contiguous and the loop is uniform
-// (pair_device.h, cluster traversal); the 8 partial sums of an i are added
-// in a fixed order at the end.
+// Full neighbour sums per particle i (cell order), no atomics, in one of
+// these forms (pair_device.h; the rules and what they measured stand at
+// group_lanes and launch_rbl):
+//   k_pair_group      plain sums of few particles: 64 or 32 lanes share one,
+//                     over its own trimmed stencil rows put end to end;
+//   k_pair_queue      plain sums of many, FP64: one lane per particle,
+//                     candidates filtered on packed 16-bit positions, the
+//                     pairs that pass evaluated from queues in LDS;
+//   k_pair_plain      plain sums of many, FP32C: one thread per particle
+//                     walking the stencil rows of its own cell;
+//   k_pair_rbl_group  random batch list, FP64: 64, 32 or 16 lanes per particle;
+//   k_pair_rbl        random batch list of large FP64 systems and in FP32C: one
+//                     wave per cluster of 8 consecutive particles. Lane l
+//                     takes i = cluster[l / 8] and every 8th record of one
+//                     candidate sequence shared by the wave (the union of the
+//                     cluster's stencils), so the candidate loads are
+//                     contiguous and the loop is uniform; the 8 partial sums
+//                     of an i are added in a fixed order at the end.
 //
 // Species blocks: charged particles occupy keys [0, C), neutral ones
 // [C, 2C). Coulomb terms only involve charged pairs, so without the random
@@ -21,7 +31,7 @@
 // members (r_core^2 < r^2 <= r_coul^2) are counted, #S_i, and ranked by the
 // 32-bit key of Eq. 11's batch: the batch B_i is the min(p, #S_i) members
 // with the smallest keys, summed with the weight #S_i/|B_i|. Selection in one
-// pass: keys below a threshold T are appended to the cluster's LDS buffer.
+// pass: keys below a threshold T are appended to a buffer in LDS.
 // T is chosen so that about 3p keys fall below it for the mean shell size; if
 // the buffer ends with fewer than min(p, #S_i) keys or overflows, a pass that
 // only collects keys is repeated with T moved by bisection (keys are distinct,

@@ -649,13 +649,6 @@ struct ForceAcc<false> {
   __device__ inline double total(int k) const {
     return group_sum<G>(v[k]);
   }
-  // the thread-form walks: same as add (FP64 sums need no row partials)
-  template <bool COUL, bool TABLE = false>
-  __device__ inline void add_row(const PairParams &pp, const PairF32 &pf, double r2, double qi, double qj, double dx,
-                                 double dy, double dz) {
-    add<COUL, TABLE>(pp, pf, r2, qi, qj, dx, dy, dz);
-  }
-  __device__ inline void flush_row() {}
 };
 template <>
 struct ForceAcc<true> {
