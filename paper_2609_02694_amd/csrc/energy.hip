@@ -95,10 +95,14 @@ struct EnergySums {
   }
 };
 
+// Bound by the issue of the library's erfc and exp, about 250 instructions a
+// pair: the pairs wait until all lanes have one (GroupHits). 130,000 ions 590
+// -> 500 us a call, 20,000 145 -> 130.
 template <int G>
 __global__ void __launch_bounds__(kEnergyThreads) k_energy_near(EnergyNear a) {
   __shared__ double lds[kEnergyThreads / 64];
   __shared__ GroupRows<G> rows[kEnergyThreads / G];
+  __shared__ GroupHits<G, double2> hits[kEnergyThreads / G];
   const int64_t per = (a.n + gridDim.x - 1) / gridDim.x;  // consecutive particles per block
   const int64_t end = min(a.n, (blockIdx.x + 1) * per);
   const PairParams &pp = a.pp;
@@ -106,13 +110,19 @@ __global__ void __launch_bounds__(kEnergyThreads) k_energy_near(EnergyNear a) {
   EnergySums sums;
   for (int64_t i = blockIdx.x * per + threadIdx.x / G; i < end; i += kEnergyThreads / G) {
     const double4 pi = a.xq[i];
+    const bool charged = pi.w != 0.0;
+    GroupHits<G, double2> &H = hits[threadIdx.x / G];
+    int pending = 0;
+    auto eval = [&](const double2 &h) { sums.add(a, pi.w, h.y, h.x); };  // r^2, q_j
     group_walk<G, false>(
-        pp.g, a.cell_start, a.xq, nullptr, nullptr, 0, pi, pi.w != 0.0 ? Block{pp.s_coul, pp.rq2} : near_lj, near_lj,
+        pp.g, a.cell_start, a.xq, nullptr, nullptr, 0, pi, charged ? Block{pp.s_coul, pp.rq2} : near_lj, near_lj,
         rows[threadIdx.x / G],
-        [&](bool ok, int, int, int j, const double4 &pj, double, double, double, double r2) {
-          if (ok && j != (int)i) sums.add(a, pi.w, pj.w, r2);
+        [&](bool ok, int, int blk, int j, const double4 &pj, double, double, double, double r2) {
+          const double reach2 = charged && blk == 0 ? pp.rq2 : pp.rlj2;
+          put_hits<G>(H, pending, ok & (j != (int)i) & (r2 <= reach2), make_double2(r2, pj.w), eval);
         },
         [](int, int) {}, [](uint64_t) {});
+    take_hits<G>(H, pending, eval);
   }
   sums.put(a, lds);
 }

@@ -618,6 +618,33 @@ __device__ inline void group_walk(const Grid &g, const int32_t *__restrict__ cel
       listed, rows_end);
 }
 
+// Pairs of a group walk that passed their test, kept in LDS until a lane of
+// the group has one each: about half of the lanes hold a pair in a trip, which
+// tells where a term costs many times its test (the energies' library error
+// function; the forces' terms gain less than the registers cost). The whole
+// group calls put_hits for every trip (in: this lane has the pair v) and
+// take_hits at the end; eval(v) then runs for G pairs at a time, together with
+// the other group of the wave, whose pairs are taken as they are.
+template <int G, class Pair>
+struct GroupHits {
+  Pair list[2 * G];  // `pending` of them, fewer than G between trips
+};
+template <int G, class Pair, class Eval>
+__device__ inline void take_hits(GroupHits<G, Pair> &H, int &pending, Eval &&eval) {
+  const int sub = threadIdx.x & (G - 1), k = min(pending, G);
+  wave_sync();
+  if (sub < k) eval(H.list[pending - k + sub]);
+  pending -= k;
+  wave_sync();
+}
+template <int G, class Pair, class Eval>
+__device__ inline void put_hits(GroupHits<G, Pair> &H, int &pending, bool in, const Pair &v, Eval &&eval) {
+  const uint64_t who = group_ballot<G>(in);
+  if (in) H.list[pending + bits_below<G>(who)] = v;
+  pending += __popcll(who);
+  if (__builtin_amdgcn_ballot_w64(pending >= G)) take_hits<G>(H, pending, eval);
+}
+
 // Ordered sums of the FP32C form in a group walk: the terms of a chunk are
 // left in LDS by the lanes that evaluated them, each row's are then added in
 // order by the lane of that row, and the rows' sums by every lane (flush_rows):
