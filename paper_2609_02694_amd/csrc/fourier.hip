@@ -10,14 +10,19 @@
 //
 // Structure factor: thread = mode, particles walked in a wave-uniform loop
 // (the chunk's (s, q) records staged in LDS), one partial sum per particle
-// chunk and mode; up to 128 modes the waves of a block share them (FP64). A wave left with fewer than 64 modes (P not a multiple of
-// 64) spreads each mode over several lanes that split the chunk's particles
-// and adds their sums with a fixed butterfly. The chunk partials are summed
-// in FP64 in a fixed order by a second kernel.
+// chunk and mode; up to 128 modes the waves of a block share the records
+// (FP64). A wave left with fewer than 64 modes (P not a multiple of 64)
+// spreads each mode over several lanes that split the chunk's particles and
+// adds their sums with a fixed butterfly. The chunk partials are summed in
+// FP64 in a fixed order by a second kernel.
 //
 // Gather: thread = particle, modes walked in a wave-uniform loop with the
 // per-mode coefficients (m, w Im rho, w Re rho) in scalar registers; for few
 // particles the waves of a block share the modes.
+//
+// Tables with columns (an Ewald lattice given by the caller, FP64): up to nine
+// modes consecutive in m_z share one sine and cosine (k_rho_runs,
+// k_gather_runs).
 //
 // FP32C form: the turn reduction stays FP64; the hardware turn-argument
 // sine/cosine (v_sin_f32 / v_cos_f32 compute sin(2 pi x), cos(2 pi x)) run on
