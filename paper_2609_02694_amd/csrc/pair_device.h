@@ -285,7 +285,27 @@ struct RowFrame {
     *b = min(s, (int)floorf((ux + ext) * inv_hx));
     return *a <= *b;
   }
+  // Whether the enlarged reach may be what a row at g2 owes its place to (the
+  // enlargements above, summed, are under half of this band).
+  __device__ inline bool doubtful(float g2) const { return r2 - g2 < 8.0f * margin * __builtin_amdgcn_sqrtf(r2); }
 };
+
+// Distance from p to the slab of unwrapped cell c, less 1e-9 (the rounding of
+// the binning), at least 0.
+__device__ inline double slab_gap(double p, int c, double h) {
+#pragma clang fp contract(off)
+  const double lo = (double)c * h, hi = lo + h;
+  const double d = lo - p > 0.0 ? lo - p : (p - hi > 0.0 ? p - hi : 0.0);
+  return d > 1e-9 ? d - 1e-9 : 0.0;
+}
+// The rows a walk closes are part of an FP32C result (closing an empty row can
+// move a Kahan sum's rounding), so a doubtful row is decided in FP64: whether
+// unwrapped row (cy, cz) is out of the squared reach of (y, z).
+__device__ inline bool row_beyond(const Grid &g, double y, double z, int cy, int cz, double reach2) {
+#pragma clang fp contract(off)
+  const double gy = slab_gap(y, cy, g.h[1]), gz = slab_gap(z, cz, g.h[2]);
+  return reach2 - (gy * gy + gz * gz) < 0.0;
+}
 
 // Cell in [0, n) of an unwrapped cell index a in [-n, 2 n), and the boxes it
 // lies off. (A cutoff is at most half the box, so a stencil radius is at most
@@ -321,7 +341,9 @@ __device__ inline void for_stencil(const Grid &g, const int32_t *__restrict__ ce
     for (int oy = -s.y; oy <= s.y; ++oy) {
       const float gy = F.gap(F.uy, oy, F.hy);
       int a, a_end;
-      if (!F.range(fmaf(gy, gy, gz * gz), s.x, &a, &a_end)) continue;
+      const float g2 = fmaf(gy, gy, gz * gz);
+      if (!F.range(g2, s.x, &a, &a_end)) continue;
+      if (F.doubtful(g2) && row_beyond(g, y, z, cy + oy, cz + oz, r2)) continue;
       a += cx;
       a_end += cx;
       int qy;
@@ -360,7 +382,9 @@ __device__ inline void for_stencil_ghost(const Grid &g, const int32_t *__restric
     for (int oy = -s.y; oy <= s.y; ++oy) {
       const float gy = F.gap(F.uy, oy, F.hy);
       int xa, xb;
-      if (!F.range(fmaf(gy, gy, gz * gz), s.x, &xa, &xb)) continue;
+      const float g2 = fmaf(gy, gy, gz * gz);
+      if (!F.range(g2, s.x, &xa, &xb)) continue;
+      if (F.doubtful(g2) && row_beyond(g, py, pz, cy + oy, cz + oz, r2)) continue;
       xa += cx;
       xb += cx;
       const int y = cy + oy;
@@ -478,7 +502,9 @@ __device__ inline void group_list(const Grid &g, const int32_t *__restrict__ cel
       const int oy = row - oz * ny - s.y;
       oz -= s.z;
       const float gz = F.gap(F.uz, oz, F.hz), gy = F.gap(F.uy, oy, F.hy);
-      if (F.range(fmaf(gy, gy, gz * gz), s.x, &a, &a_end)) {
+      const float g2 = fmaf(gy, gy, gz * gz);
+      if (F.range(g2, s.x, &a, &a_end) &&
+          !(F.doubtful(g2) && row_beyond(g, pi.y, pi.z, cy + oy, cz + oz, blk ? B.r2 : A.r2))) {
         a += cx;
         a_end += cx;
       } else {
