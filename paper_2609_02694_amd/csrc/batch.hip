@@ -230,7 +230,7 @@ __global__ void __launch_bounds__(kBatchThreads) k_batch_near_group(BatchArgs a)
     ForceAcc<F32> acc;
     group_sums<F32, false, G>(a.pp, a.pf, R.g, R.s_coul, R.s_lj, a.cell_start + R.c0, a.xq, nullptr, nullptr, 0,
                               (int)i, a.xq[i], false, rows[threadIdx.x / G], &terms[threadIdx.x / G].t[0], acc,
-                              [](bool, double) {});
+                              [](bool, bool, double) {});
     const double f0 = acc.template total<G>(0), f1 = acc.template total<G>(1), f2 = acc.template total<G>(2);
     if (threadIdx.x % G == 0) {
       a.ofx[i] = f0;

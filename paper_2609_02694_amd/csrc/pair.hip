@@ -326,11 +326,11 @@ __global__ void __launch_bounds__(256) k_pair_group(PairCtx c, int coulomb) {
     ForceAcc<F32> acc;
     group_sums<F32, GHOST, G>(
         pp, c.pf, pp.g, pp.s_coul, pp.s_lj, c.cell_start, c.xq, c.gcell_start, c.gxq, (int)c.n, (int)i, pi4,
-        coulomb != 0, rows[threadIdx.x / G], &terms[threadIdx.x / G].t[0], acc, [&](bool coul, double r2) {
+        coulomb != 0, rows[threadIdx.x / G], &terms[threadIdx.x / G].t[0], acc, [&](bool coul, bool other, double r2) {
           if (COUNT) {
             ++n_tested;
-            n_coul += (coul && pp.do_coul && r2 <= pp.rc2);
-            n_lj += (!coulomb && pp.do_lj && r2 <= pp.rlj2);
+            n_coul += (other && coul && pp.do_coul && r2 <= pp.rc2);
+            n_lj += (other && !coulomb && pp.do_lj && r2 <= pp.rlj2);
           }
         });
     const double f0 = acc.template total<G>(0), f1 = acc.template total<G>(1), f2 = acc.template total<G>(2);

@@ -963,7 +963,7 @@ inline unsigned group_blocks(int64_t most, int lanes) {
 // Plain sums of particle i by its group: charged i against the charged block
 // out to max(r_coul, r_lj) and the neutral block out to r_lj, neutral i
 // against both out to r_lj; coulomb: the screened Coulomb terms alone.
-// tested(coul, r^2) is called for every candidate but i.
+// tested(coul, other, r^2) is called for every candidate (other: it is not i).
 template <bool F32, bool GHOST, int G, class Tested>
 __device__ inline void group_sums(const PairParams &pp, const PairF32 &pf, const Grid &g, const Sten &s_coul,
                                   const Sten &s_lj, const int32_t *__restrict__ cell_start,
@@ -983,7 +983,7 @@ __device__ inline void group_sums(const PairParams &pp, const PairF32 &pf, const
       [&](bool ok, int k, int blk, int j, const double4 &pj, double dx, double dy, double dz, double r2) {
         const bool coul = charged && blk == 0;  // every other pairing: LJ only
         const bool in = ok & (j != i) & (r2 <= (coul ? A.r2 : pp.rlj2));
-        if (ok & (j != i)) tested(coul, r2);
+        if (ok) tested(coul, j != i, r2);
         if constexpr (F32) {
           float sc = 0.f;
           if (in) sc = coul ? pair_scalar_f32(pp, pf, r2, (float)(qi * pj.w)) : pair_scalar_lj_f32(pp, pf, r2);
