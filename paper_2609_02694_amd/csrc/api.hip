@@ -1037,7 +1037,7 @@ static int batch_forces(rbe_ctx *c, const rbe_state *s, const int32_t *m, const 
   a.cfz = s->fz;
   {
     TScope ts(c, RBE_TK_BATCH, st);
-    launch_batch_step(c->p.prec, a, eval, true, st);
+    launch_batch_step(c->p.prec, a, eval, true, true, st);
   }
   HIP_TRY(c, hipGetLastError());
   return RBE_OK;
@@ -1074,7 +1074,7 @@ static int batch_step(rbe_ctx *c, rbe_state *s, int32_t nsteps, uint64_t first_e
     const WorkSet *out = k == nsteps - 1 ? &S : &c->ws[k % 2];
     const BatchArgs a = batch_step_args(c, *in, *out);
     TScope ts(c, RBE_TK_BATCH, st);
-    launch_batch_step(c->p.prec, a, first_eval + (uint64_t)k, k == 0, st);
+    launch_batch_step(c->p.prec, a, first_eval + (uint64_t)k, k == 0, k == nsteps - 1, st);
     in = out;
   }
   HIP_TRY(c, hipGetLastError());
@@ -1328,7 +1328,7 @@ extern "C" int rbe_step(rbe_ctx *c, rbe_state *s, int32_t nsteps, uint64_t first
     }
     {
       TScope ts(c, RBE_TK_BIN, st);
-      launch_bin_place(c->bb, 2 * (int64_t)c->g.ncell, n, c->cell_start, c->perm, st);
+      launch_bin_place(c->bb, 2 * (int64_t)c->g.ncell, n, c->cell_start, c->perm, k < nsteps - 1, st);
     }
     {
       TScope ts(c, RBE_TK_REORDER, st);

@@ -445,7 +445,7 @@ __global__ void __launch_bounds__(kBatchThreads) k_batch_gather(BatchArgs a, con
   }
 }
 
-void launch_batch_step(int prec, const BatchArgs &a, uint64_t eval, bool first, hipStream_t st) {
+void launch_batch_step(int prec, const BatchArgs &a, uint64_t eval, bool first, bool last, hipStream_t st) {
   const unsigned nb = (unsigned)((a.ntot + kBatchThreads - 1) / kBatchThreads);
   const int64_t nm = (int64_t)a.nrep * a.P;
   const unsigned mb = a.do_far ? (unsigned)((nm + kBatchThreads - 1) / kBatchThreads) : 0u;
@@ -453,7 +453,7 @@ void launch_batch_step(int prec, const BatchArgs &a, uint64_t eval, bool first, 
   if (first) launch_bin_clear(a.bin, a.nkeys, a.ntot, st);
   k_batch_drift<<<nb + mb, kBatchThreads, 0, st>>>(a, eval, nb,
                                                    bin_keys_out(a.bin, a.nkeys, a.ntot, nullptr).count);
-  launch_bin_place(a.bin, a.nkeys, a.ntot, a.cell_start, a.perm, st);
+  launch_bin_place(a.bin, a.nkeys, a.ntot, a.cell_start, a.perm, !last, st);
   k_batch_reorder<<<nb, kBatchThreads, 0, st>>>(a);
   unsigned near_blocks;
   const BatchKernel near = batch_near_kernel(prec, a.ntot, &near_blocks);

@@ -22,8 +22,9 @@ void launch_bin(const BinBuffers &b, const Grid &g, int64_t n, const double *x, 
                 const double *q, int32_t *cell_start, int32_t *perm, hipStream_t st);
 // The passes of launch_bin around its keys pass, for a keys pass fused into
 // another kernel: clearing the histogram (needed before the first keys pass of
-// a call: the scatter leaves it clear), the keys pass' outputs, then scan,
-// scatter and placement. Small systems (bin_in_block) are sorted by one block
+// a call), the keys pass' outputs, then scan, scatter and placement (more: a
+// keys pass of the same call follows, and the scatter clears the histogram for
+// it). Small systems (bin_in_block) are sorted by one block
 // from the keys alone: no histogram, no clearing.
 struct BinKeyOut {
   const double *q;
@@ -32,7 +33,7 @@ struct BinKeyOut {
 bool bin_in_block(int64_t n, int64_t nkeys);
 void launch_bin_clear(const BinBuffers &b, int64_t nkeys, int64_t n, hipStream_t st);
 BinKeyOut bin_keys_out(const BinBuffers &b, int64_t nkeys, int64_t n, const double *q);
-void launch_bin_place(const BinBuffers &b, int64_t nkeys, int64_t n, int32_t *cell_start, int32_t *perm,
+void launch_bin_place(const BinBuffers &b, int64_t nkeys, int64_t n, int32_t *cell_start, int32_t *perm, bool more,
                       hipStream_t st);
 
 // ---------------------------------------------------------------------------
@@ -402,8 +403,8 @@ struct BatchArgs {
 };
 
 // One step (mode 0) or force evaluation (mode 1) of every replica.
-// first: the call's first step (the histogram is not clear).
-void launch_batch_step(int prec, const BatchArgs &a, uint64_t eval, bool first, hipStream_t st);
+// first: the call's first step (the histogram is not clear); last: its last.
+void launch_batch_step(int prec, const BatchArgs &a, uint64_t eval, bool first, bool last, hipStream_t st);
 // Per-replica charge statistics: nq[r] charged count, qs[2r] = sum q, qs[2r+1] = sum |q|.
 void launch_qstats_rep(int nrep, const int64_t *off, const double *q, int32_t *nq, double *qs, hipStream_t st);
 // Checks of Eq. 1 per replica (device error flags) and the structure-factor

@@ -1,0 +1,49 @@
+"""Where one form of a kernel gives way to another, a call costs no more than
+its neighbours on the other side of the line. Times are the best of several
+runs and are compared with each other only, with room for their scatter."""
+import time
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import paper_2609_02694_amd as rbe  # noqa: E402
+
+
+def best_us(fn, reps=20, rounds=9):
+    """Best time of fn in microseconds over rounds of reps calls."""
+    best = float("inf")
+    for _ in range(rounds + 1):  # the first one warms up
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        for _ in range(reps):
+            fn()
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t) / reps)
+    return 1e6 * best
+
+
+def random_state(n, L, charged=1.0, seed=5):
+    """Particles on randomly occupied lattice sites, displaced by up to 0.15 of the lattice constant, in random order."""
+    g = np.random.default_rng(seed)
+    side = int(np.ceil(n ** (1 / 3) - 1e-9))
+    site = g.permutation(side ** 3)[:n]
+    r = [(np.asarray(k) + 0.5 + g.uniform(-0.15, 0.15, n)) * (L / side)
+         for k in (site % side, site // side % side, site // side ** 2)]
+    half = int(n * charged) // 2
+    q = np.zeros(n)
+    q[:half], q[half:2 * half] = 1.0, -1.0
+    return rbe.Particles.from_numpy(dict(x=r[0], y=r[1], z=r[2], q=g.permutation(q), id=np.arange(n, dtype=np.int32)))
+
+
+def test_binning_on_a_grid_of_many_more_cells_than_particles():
+    """16 million keys: binning 300 particles takes no longer than 50,000."""
+    t, params = {}, rbe.make_params(400.0, 0.3, 2.0, 1.0, 4, ncell=(200, 200, 200))
+    for n in (300, 50_000):
+        ctx, st = rbe.Context(params, n), random_state(n, 400.0)
+        t[n] = best_us(lambda: ctx.build_cells(st.x, st.y, st.z, st.q))
+        ctx.close()
+    print(f"binning, 16M keys: {t}")
+    assert t[300] < 1.3 * t[50_000]
