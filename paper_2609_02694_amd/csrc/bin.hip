@@ -211,7 +211,6 @@ __global__ void __launch_bounds__(256) k_place_buckets(int64_t nkeys, const int3
 // particles. The histogram and the starts stay in memory (the L2): in LDS they
 // would limit the grid.
 constexpr int kBlockBinThreads = 1024, kBlockBinEach = 8;  // 8,192 particles
-constexpr int64_t kBlockBinKeys = 32768;
 // The block's accesses to the histogram, all of them atomics that the L2
 // executes, are done before any that follow (a fence of the device's scope
 // would write the L2 back: 3 us).
@@ -308,16 +307,25 @@ __global__ void __launch_bounds__(kBlockBinThreads) k_bin_block(int n, int nkeys
   }
 }
 
-bool bin_in_block(int64_t n, int64_t nkeys) {
-  return n <= kBlockBinThreads * kBlockBinEach && nkeys <= kBlockBinKeys;
+// One block's time grows with the keys (its clearing and scan) and with the
+// particles, at random places most (an atomic each, where a step's cell order
+// makes runs); the launches' does not. Block against launches in us, a binning
+// of particles in random order: 2,000 and 16,000 keys 23.2, 27.6; and 27,648:
+// 32.9, 27.5; 4,000 and 8,192: 22.1, 27.1; and 16,000: 29.1, 27.3; 6,000 and
+// 3,456: 23.5, 27.2; and 8,192: 28.3, 27.2; 8,000 and 27,648: 51.5, 27.2. Two
+// steps from given keys: 300 and 4,096 keys 52, 61; and 13,824: 62, 61; 4,000
+// and 4,096: 64, 73; and 13,824: 75, 66; 8,000 and 4,096: 93, 95; and 13,824:
+// 95, 81.
+static bool bin_in_block(int64_t n, int64_t nkeys, bool keys_given) {
+  return n <= kBlockBinThreads * kBlockBinEach && (keys_given ? nkeys + n <= 13000 : nkeys + 4 * n <= 26000);
 }
 
 void launch_bin_clear(const BinBuffers &b, int64_t nkeys, int64_t n, hipStream_t st) {
-  if (!bin_in_block(n, nkeys)) launch_fill_i32(b.count, nkeys, 0, st);
+  if (!bin_in_block(n, nkeys, true)) launch_fill_i32(b.count, nkeys, 0, st);
 }
 
 BinKeyOut bin_keys_out(const BinBuffers &b, int64_t nkeys, int64_t n, const double *q) {
-  return BinKeyOut{q, b.key, b.slot, bin_in_block(n, nkeys) ? nullptr : b.count};
+  return BinKeyOut{q, b.key, b.slot, bin_in_block(n, nkeys, true) ? nullptr : b.count};
 }
 
 // Keys that a thread of the scatter clears at most: on a grid of many more
@@ -326,13 +334,8 @@ BinKeyOut bin_keys_out(const BinBuffers &b, int64_t nkeys, int64_t n, const doub
 // without the clearing 145).
 constexpr int64_t kClearEach = 16;
 
-void launch_bin_place(const BinBuffers &b, int64_t nkeys, int64_t n, int32_t *cell_start, int32_t *perm, bool more,
-                      hipStream_t st) {
-  if (bin_in_block(n, nkeys)) {
-    k_bin_block<false><<<1, kBlockBinThreads, 0, st>>>((int)n, (int)nkeys, nullptr, nullptr, nullptr, nullptr, Grid{},
-                                                       b.key, b.count, cell_start, perm);
-    return;
-  }
+static void launch_bin_passes(const BinBuffers &b, int64_t nkeys, int64_t n, int32_t *cell_start, int32_t *perm,
+                              bool more, hipStream_t st) {
   launch_exclusive_scan(b.count, nkeys, cell_start, b.scan_tmp, st);
   if (n <= 0) return;
   int64_t blocks = (n + 255) / 256;
@@ -342,20 +345,29 @@ void launch_bin_place(const BinBuffers &b, int64_t nkeys, int64_t n, int32_t *ce
   k_place_buckets<<<(unsigned)((nkeys + 255) / 256), 256, 0, st>>>(nkeys, cell_start, b.tmp, perm);
 }
 
+void launch_bin_place(const BinBuffers &b, int64_t nkeys, int64_t n, int32_t *cell_start, int32_t *perm, bool more,
+                      hipStream_t st) {
+  if (bin_in_block(n, nkeys, true))
+    k_bin_block<false><<<1, kBlockBinThreads, 0, st>>>((int)n, (int)nkeys, nullptr, nullptr, nullptr, nullptr, Grid{},
+                                                       b.key, b.count, cell_start, perm);
+  else
+    launch_bin_passes(b, nkeys, n, cell_start, perm, more, st);
+}
+
 void launch_bin(const BinBuffers &b, const Grid &g, int64_t n, const double *x, const double *y, const double *z,
                 const double *q, int32_t *cell_start, int32_t *perm, hipStream_t st) {
   const int64_t nkeys = 2 * (int64_t)g.ncell;
-  if (bin_in_block(n, nkeys)) {
+  if (bin_in_block(n, nkeys, false)) {
     k_bin_block<true><<<1, kBlockBinThreads, 0, st>>>((int)n, (int)nkeys, x, y, z, q, g, nullptr, b.count, cell_start,
                                                       perm);
     return;
   }
-  launch_bin_clear(b, nkeys, n, st);
+  launch_fill_i32(b.count, nkeys, 0, st);
   if (n > 0) {
     const unsigned blocks = (unsigned)((n + 255) / 256);
     k_bin_keys<<<blocks, 256, 0, st>>>(n, x, y, z, q, g, b.key, b.slot, b.count);
   }
-  launch_bin_place(b, nkeys, n, cell_start, perm, false, st);
+  launch_bin_passes(b, nkeys, n, cell_start, perm, false, st);
 }
 
 }  // namespace rbe

@@ -24,13 +24,12 @@ void launch_bin(const BinBuffers &b, const Grid &g, int64_t n, const double *x, 
 // another kernel: clearing the histogram (needed before the first keys pass of
 // a call), the keys pass' outputs, then scan, scatter and placement (more: a
 // keys pass of the same call follows, and the scatter clears the histogram for
-// it). Small systems (bin_in_block) are sorted by one block
-// from the keys alone: no histogram, no clearing.
+// it). Small systems are sorted by one block from the
+// keys alone: no histogram, no clearing.
 struct BinKeyOut {
   const double *q;
   int32_t *key, *slot, *count;  // count == nullptr: keys only
 };
-bool bin_in_block(int64_t n, int64_t nkeys);
 void launch_bin_clear(const BinBuffers &b, int64_t nkeys, int64_t n, hipStream_t st);
 BinKeyOut bin_keys_out(const BinBuffers &b, int64_t nkeys, int64_t n, const double *q);
 void launch_bin_place(const BinBuffers &b, int64_t nkeys, int64_t n, int32_t *cell_start, int32_t *perm, bool more,

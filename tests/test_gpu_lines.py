@@ -47,3 +47,30 @@ def test_binning_on_a_grid_of_many_more_cells_than_particles():
         ctx.close()
     print(f"binning, 16M keys: {t}")
     assert t[300] < 1.3 * t[50_000]
+
+
+@pytest.mark.parametrize("n,ncell", [(300, (32, 32, 15)), (4_000, (32, 32, 15)), (8_000, (16, 16, 16)),
+                                     (8_000, (32, 32, 15))])
+def test_binning_in_one_block(n, ncell):
+    """A grid just small enough for the sort in one block so far, against one too large for it in any case."""
+    t = {}
+    for nc in (ncell, (32, 32, 40)):
+        ctx, st = rbe.Context(rbe.make_params(96.0, 0.3, 2.0, 1.0, 4, ncell=nc), n), random_state(n, 96.0)
+        t[nc] = best_us(lambda: ctx.build_cells(st.x, st.y, st.z, st.q))
+        ctx.close()
+    print(f"binning of {n}: {t}")
+    assert t[ncell] < 1.15 * t[32, 32, 40]
+
+
+@pytest.mark.parametrize("n,ncell", [(900, (32, 32, 15)), (8_000, (32, 32, 15))])
+def test_steps_binned_in_one_block(n, ncell):
+    """The same for the binning of a step, from keys (Fourier part alone: the grid matters to nothing else)."""
+    t = {}
+    for nc in (ncell, (32, 32, 40)):
+        params = rbe.make_params(96.0, 0.3, 2.0, 1.0, 4, ncell=nc, terms=rbe.TERM_FOURIER, dt=1e-6)
+        ctx, st = rbe.Context(params, n), random_state(n, 96.0)
+        ctx.forces(st)
+        t[nc] = best_us(lambda: ctx.step(st, 10, 1), reps=4)
+        ctx.close()
+    print(f"10 steps of {n}: {t}")
+    assert t[ncell] < 1.1 * t[32, 32, 40]
