@@ -79,6 +79,7 @@ struct rbe_ctx {
   bool fixed_modes = false;  // rbe_set_modes: slot 0 of m_dev/w_dev/mkd_dev is the caller's table
   double *mean_part = nullptr, *mean = nullptr;
   double *epart = nullptr;   // energy partial sums
+  uint2 *epk = nullptr;      // packed positions of an energy call (FP32C: the forces need none)
   double *nh_part = nullptr, *nh_scale = nullptr;  // thermostat: |v|^2 partials, pending velocity scaling
   int *err = nullptr;
   double *qstats = nullptr;  // [2 kQBlocks] per-block (sum q, sum |q|)
@@ -403,7 +404,7 @@ extern "C" int rbe_create(rbe_ctx **out, const rbe_params *p, int64_t n_max, int
   c->srt.xq = b.alloc<double4>(n_max + kScanPad);
   c->srt.sq = b.alloc<double4>(n_max);
   c->srt.id = b.alloc<int32_t>(n_max + kScanPad);
-  if (p->prec == RBE_FP64) c->srt.pk = b.alloc<uint2>(n_max + kScanPad);
+  (p->prec == RBE_FP64 ? c->srt.pk : c->epk) = b.alloc<uint2>(n_max + kScanPad);
   c->srt.pk_scale = pack_scale(std::fmax(p->r_coul, p->r_lj), std::fmax(g.h[0], std::fmax(g.h[1], g.h[2])));
   for (int s = 0; s < 2; ++s) {
     WorkSet &w = c->ws[s];
@@ -1194,10 +1195,12 @@ extern "C" int rbe_energy(rbe_ctx *c, const rbe_state *s, const int32_t *m, cons
   hipStream_t st = (hipStream_t)stream;
   const int64_t n = s->n;
   launch_charge_check(c, n, s->q, st);
+  Sorted srt = c->srt;
+  if (c->epk) srt.pk = c->epk;
   const bool near = (c->p.terms & (RBE_TERM_LJ | RBE_TERM_COUL_REAL)) != 0;
   const bool fourier = (c->p.terms & RBE_TERM_FOURIER) != 0;
   launch_bin(c->bb, c->g, n, s->x, s->y, s->z, s->q, c->cell_start, c->perm, st);
-  launch_gather_sorted(n, c->perm, s->x, s->y, s->z, s->q, s->id, c->g, c->srt, st);
+  launch_gather_sorted(n, c->perm, s->x, s->y, s->z, s->q, s->id, c->g, srt, st);
   const int P = c->p.P;
   EnergyFinal fin{};
   if (fourier) {
@@ -1221,7 +1224,7 @@ extern "C" int rbe_energy(rbe_ctx *c, const rbe_state *s, const int32_t *m, cons
     } else if (c->fixed_modes) {
       fb.runs = c->runs;
     }
-    launch_rho_partial(RBE_FP64, nq, n, P, c->srt.sq, fb, st);
+    launch_rho_partial(RBE_FP64, nq, n, P, srt.sq, fb, st);
     launch_rho_final(nq, n, P, fb, w, c->p.coulomb_k, rho_out, st);
     fin.w = w;
     fin.rho = c->fb.rho;
@@ -1234,7 +1237,7 @@ extern "C" int rbe_energy(rbe_ctx *c, const rbe_state *s, const int32_t *m, cons
   fin.self_coef = c->p.coulomb_k * std::sqrt(c->p.alpha / kPi);
   fin.half_mass = 0.5 * c->p.mass;
   fin.out = u_out;
-  launch_energy(c->pp, 4.0 * c->p.lj_eps, n, c->srt, c->cell_start, near, s->q, s->vx, s->vy, s->vz, c->epart, fin,
+  launch_energy(c->pp, 4.0 * c->p.lj_eps, n, srt, c->cell_start, near, s->q, s->vx, s->vy, s->vz, c->epart, fin,
                 st);
   HIP_TRY(c, hipGetLastError());
   return RBE_OK;

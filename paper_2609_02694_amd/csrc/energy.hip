@@ -18,17 +18,16 @@ namespace rbe {
 
 constexpr int kEnergyThreads = 256;
 // Lanes per particle of the near field: 64 or 32 (group walk), or one (queue
-// walk), which needs the packed positions of an FP64 context and is the faster
-// form from the size at which its waves fill the chip, sooner where the cutoff
-// sphere is nearly empty. A whole call in us with 64, 32 and one: electrolyte
-// 4,000 particles 82, 87, 455; 20,000: 131, 119, 459; 130,000: 386, 351, 446;
-// 260,000: 653, 575, 508; LJ electrolyte (21 particles in the sphere) 20,000:
-// 107, 90, 123; 65,000: 220, 164, 134.
+// walk), the faster form from the size at which its waves fill the chip, sooner
+// where the cutoff sphere is nearly empty. A whole call in us with 64, 32 and
+// one: electrolyte 4,000 particles 82, 87, 455; 20,000: 131, 119, 459; 130,000:
+// 386, 351, 446; 260,000: 653, 575, 508; LJ electrolyte (21 particles in the
+// sphere) 20,000: 107, 90, 123; 65,000: 220, 164, 134.
 constexpr int64_t kEnergyWide = 196608, kEnergyNarrow = 40960;
-static int energy_lanes(const PairParams &pp, int64_t n, bool packed) {
+static int energy_lanes(const PairParams &pp, int64_t n) {
   const double r = std::sqrt(pp.rq2);
   const double mean = (double)n / (pp.g.L[0] * pp.g.L[1] * pp.g.L[2]) * (4.0 / 3.0) * kPi * r * r * r;
-  return n <= 4096 ? 64 : !packed || n <= (mean < 48.0 ? kEnergyNarrow : kEnergyWide) ? 32 : 1;
+  return n <= 4096 ? 64 : n <= (mean < 48.0 ? kEnergyNarrow : kEnergyWide) ? 32 : 1;
 }
 constexpr int64_t kEnergyNearBlocks = 16384;  // most blocks of the near field (each leaves one partial sum)
 constexpr int kEnergySqBlocks = 1024;  // grid of the q^2 / v^2 sums
@@ -259,7 +258,7 @@ void launch_energy(const PairParams &pp, double lj4, int64_t n, const Sorted &s,
                    const double *vz, double *part, EnergyFinal fin, hipStream_t st) {
   int64_t nb_near = 0;
   if (near && n > 0) {
-    const int lanes = energy_lanes(pp, n, s.pk != nullptr);
+    const int lanes = energy_lanes(pp, n);
     nb_near = energy_near_blocks(n, lanes);
     EnergyNear a{};
     a.pp = pp;

@@ -43,7 +43,8 @@ void launch_bin_place(const BinBuffers &b, int64_t nkeys, int64_t n, int32_t *ce
 //   sq[i] = (x/L_x, y/L_y, z/L_z, q) fractional coordinates (Fourier part,
 //           only the charged range [0, nq) is used)
 //   pk[i] = packed 16-bit positions (pack_position), the candidates of the
-//           FP64 queue walks and batch lists; nullptr in FP32C.
+//           FP64 queue walks and batch lists; nullptr in FP32C but for the
+//           energies.
 struct Sorted {
   double4 *xq;
   double4 *sq;

@@ -74,3 +74,17 @@ def test_steps_binned_in_one_block(n, ncell):
         ctx.close()
     print(f"10 steps of {n}: {t}")
     assert t[ncell] < 1.1 * t[32, 32, 40]
+
+
+@pytest.mark.parametrize("n,m", [(120_000, 3), (600_000, 3), (600_000, 60)])
+def test_energy_of_a_single_precision_context(n, m):
+    """Energies are summed in FP64 whatever the context's precision: the call costs the same."""
+    t, r = {}, (m / (4.0 / 3.0 * np.pi * 0.1)) ** (1 / 3)
+    L = (n / 0.1) ** (1 / 3)
+    for prec in (rbe.FP64, rbe.FP32C):
+        params = rbe.make_params(L, (3.0 / r) ** 2, r, r, 20, prec=prec, terms=rbe.TERM_LJ | rbe.TERM_COUL_REAL)
+        ctx, st = rbe.Context(params, n), random_state(n, L, charged=0.1)
+        t[prec] = best_us(lambda: ctx.energy(st))
+        ctx.close()
+    print(f"energy of {n}, {m} in the cutoff: {t}")
+    assert t[rbe.FP32C] < 1.1 * t[rbe.FP64]
