@@ -24,10 +24,12 @@ constexpr int kEnergyThreads = 256;
 // 386, 351, 446; 260,000: 653, 575, 508; LJ electrolyte (21 particles in the
 // sphere) 20,000: 107, 90, 123; 65,000: 220, 164, 134.
 constexpr int64_t kEnergyWide = 196608, kEnergyNarrow = 40960;
-static int energy_lanes(const PairParams &pp, int64_t n) {
+static bool energy_narrow(const PairParams &pp, int64_t n) {
   const double r = std::sqrt(pp.rq2);
-  const double mean = (double)n / (pp.g.L[0] * pp.g.L[1] * pp.g.L[2]) * (4.0 / 3.0) * kPi * r * r * r;
-  return n <= 4096 ? 64 : n <= (mean < 48.0 ? kEnergyNarrow : kEnergyWide) ? 32 : 1;
+  return (double)n / (pp.g.L[0] * pp.g.L[1] * pp.g.L[2]) * (4.0 / 3.0) * kPi * r * r * r < 48.0;
+}
+static int energy_lanes(bool narrow, int64_t n) {
+  return n <= 4096 ? 64 : n <= (narrow ? kEnergyNarrow : kEnergyWide) ? 32 : 1;
 }
 constexpr int64_t kEnergyNearBlocks = 16384;  // most blocks of the near field (each leaves one partial sum)
 constexpr int kEnergySqBlocks = 1024;  // grid of the q^2 / v^2 sums
@@ -66,6 +68,7 @@ struct EnergyNear {
   const uint2 *__restrict__ pk;
   double pk_scale;
   uint32_t t2_q, t2_lj;  // squared reaches in packed units
+  bool queue_lj;         // queue walk: LJ pairs too (k_energy_near_queue)
   const int32_t *__restrict__ cell_start;
   double *__restrict__ part;
 };
@@ -81,11 +84,12 @@ struct EnergySums {
       uc += qq * er;
       wc += qq * (er + a.two_sqrt_a_pi * exp(-pp.alpha * r2));
     }
-    if (pp.do_lj && r2 <= pp.rlj2) {
-      const double s2 = pp.sig2 / r2, s6 = s2 * s2 * s2;
-      ul += s6 * s6 - s6;
-      wl += 2.0 * s6 * s6 - s6;
-    }
+    if (pp.do_lj && r2 <= pp.rlj2) add_lj(pp, r2);
+  }
+  __device__ inline void add_lj(const PairParams &pp, double r2) {
+    const double s2 = pp.sig2 / r2, s6 = s2 * s2 * s2;
+    ul += s6 * s6 - s6;
+    wl += 2.0 * s6 * s6 - s6;
   }
   __device__ inline void put(const EnergyNear &a, double *lds) {
     const double sc = block_sum(0.5 * uc, lds), sl = block_sum(0.5 * a.lj4 * ul, lds);
@@ -132,6 +136,12 @@ __global__ void __launch_bounds__(kEnergyThreads) k_energy_near(EnergyNear a) {
 // the lanes or more instead of the half whose candidate is inside the cutoff,
 // and the walk's set-up is a lane's, not a wave's. 1M ions 3.78 -> 3.00 ms a
 // call, 1M LJ electrolyte 1.26 -> 0.72.
+// A pair without a Coulomb term costs less than a queue entry's fetch: such
+// blocks are summed as they are met, but for nearly empty spheres, whose rows
+// leave most lanes idle. A whole call in us, queued and as met: neutral
+// particles, 400,000, 1,000 in the sphere 5851, 4370; 120: 622, 562; a tenth
+// charged, 200,000, 300 in the sphere 1020, 767; 30: 202, 203; 60,000, 30: 114,
+// 139.
 __global__ void __launch_bounds__(kEnergyThreads) __attribute__((amdgpu_waves_per_eu(3)))
 k_energy_near_queue(EnergyNear a) {
   static_assert(kEnergyThreads == kQueueThreads, "queue layout");
@@ -160,13 +170,24 @@ k_energy_near_queue(EnergyNear a) {
       if (j != (int)i) sums.add(a, pi.w, pj.w, sq_dist(dx, dy, dz));
     };
     auto drain = [&](bool all) { drain_queue(Q, all, one); };
-    const bool charged = pi.w != 0.0;
-    const bool some = charged ? pp.do_coul || pp.do_lj : pp.do_lj;
+    const bool charged = pi.w != 0.0, coul = charged && pp.do_coul;
+    const bool some = coul || (a.queue_lj && pp.do_lj);
     queue_walk<false>(g, a.cell_start, a.pk, nullptr, nullptr, 0, active && some, pi, charged ? pp.s_coul : pp.s_lj,
                       charged ? pp.rq2 : pp.rlj2, charged ? a.t2_q : a.t2_lj, a.pk_scale, coded, Q, [](int) {}, drain);
-    queue_walk<false>(g, a.cell_start + g.ncell, a.pk, nullptr, nullptr, 0, active && pp.do_lj, pi, pp.s_lj, pp.rlj2,
-                      a.t2_lj, a.pk_scale, coded, Q, [](int) {}, drain);
+    if (a.queue_lj)
+      queue_walk<false>(g, a.cell_start + g.ncell, a.pk, nullptr, nullptr, 0, active && pp.do_lj, pi, pp.s_lj,
+                        pp.rlj2, a.t2_lj, a.pk_scale, coded, Q, [](int) {}, drain);
     drain(true);
+    if (a.queue_lj || !pp.do_lj || !active) continue;
+    const int cx = cell_coord(pi.x, g.inv_h[0], g.nx), cy = cell_coord(pi.y, g.inv_h[1], g.ny),
+              cz = cell_coord(pi.z, g.inv_h[2], g.nz);
+    for (int blk = coul; blk < 2; ++blk)
+      for_stencil(g, a.cell_start, a.xq, blk, cx, cy, cz, pp.s_lj, pi.x, pi.y, pi.z, pp.rlj2,
+                  [&](int j, const double4 &pj, double shx, double shy, double shz) {
+                    const double dx = (pi.x - pj.x) - shx, dy = (pi.y - pj.y) - shy, dz = (pi.z - pj.z) - shz;
+                    const double r2 = sq_dist(dx, dy, dz);
+                    if (j != (int)i && r2 <= pp.rlj2) sums.add_lj(pp, r2);
+                  });
   }
   sums.put(a, lds);
 }
@@ -258,7 +279,8 @@ void launch_energy(const PairParams &pp, double lj4, int64_t n, const Sorted &s,
                    const double *vz, double *part, EnergyFinal fin, hipStream_t st) {
   int64_t nb_near = 0;
   if (near && n > 0) {
-    const int lanes = energy_lanes(pp, n);
+    const bool narrow = energy_narrow(pp, n);
+    const int lanes = energy_lanes(narrow, n);
     nb_near = energy_near_blocks(n, lanes);
     EnergyNear a{};
     a.pp = pp;
@@ -270,6 +292,7 @@ void launch_energy(const PairParams &pp, double lj4, int64_t n, const Sorted &s,
     a.pk_scale = s.pk_scale;
     a.t2_q = pack_reach2(std::sqrt(pp.rq2), s.pk_scale);
     a.t2_lj = pack_reach2(std::sqrt(pp.rlj2), s.pk_scale);
+    a.queue_lj = narrow;
     a.cell_start = cell_start;
     a.part = part;
     const auto kernel = lanes == 64 ? k_energy_near<64> : lanes == 32 ? k_energy_near<32> : k_energy_near_queue;

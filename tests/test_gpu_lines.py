@@ -88,3 +88,16 @@ def test_energy_of_a_single_precision_context(n, m):
         ctx.close()
     print(f"energy of {n}, {m} in the cutoff: {t}")
     assert t[rbe.FP32C] < 1.1 * t[rbe.FP64]
+
+
+def test_energy_of_neutral_particles():
+    """LJ pairs alone, 1,000 to a particle: their energies cost no more than their forces (1.18 of it from queues,
+    0.90 summed as they are met)."""
+    n, m = 300_000, 1_000
+    r, L = (m / (4.0 / 3.0 * np.pi * 0.1)) ** (1 / 3), (n / 0.1) ** (1 / 3)
+    ctx = rbe.Context(rbe.make_params(L, (3.0 / r) ** 2, r, r, 20, terms=rbe.TERM_LJ), n)
+    st = random_state(n, L, charged=0.0)
+    t = [best_us(lambda: f(st), reps=5) for f in (ctx.energy, ctx.forces)]
+    ctx.close()
+    print(f"LJ of {n}, {m} in the cutoff: energy, forces {t}")
+    assert t[0] < 1.04 * t[1]
