@@ -62,6 +62,7 @@ struct PairCtx {
   const int32_t *__restrict__ nq_ptr;         // charged count (device): [0, nq) charged, [nq, n) neutral
   int charged;                                // this launch: 1 the charged range, 0 the neutral range
   int64_t n;                                  // all particles
+  int64_t group_rbl;                          // random batch list: largest part of the group form
   // ghost shell (GHOST kernels only)
   const double4 *__restrict__ gxq;
   const int32_t *__restrict__ gid;
@@ -354,12 +355,14 @@ __global__ void __launch_bounds__(256) k_pair_group(PairCtx c, int coulomb) {
 // r_coul.
 // QSHELL: the shell holds charged particles only (variant of Eq. 10; the
 // neutral j beyond the core then carry no force, since r_lj <= r_core).
-template <bool F32, bool COUNT, bool GHOST, bool QSHELL>
+// EITHER: the group form was launched as well, for parts of up to group_rbl.
+template <bool F32, bool COUNT, bool GHOST, bool QSHELL, bool EITHER>
 __global__ void __launch_bounds__(64, 5) k_pair_rbl(PairCtx c) {
   __shared__ uint32_t kbuf[kCI * kShellCap];
   __shared__ uint32_t ksel[kCI * RBE_MAX_SHELL_BATCH];
   __shared__ int kcnt[kCI];
   int64_t first, end;
+  if (EITHER && (c.charged ? *c.nq_ptr : c.n - *c.nq_ptr) <= c.group_rbl) return;
   if (!part_block(c, kCI, &first, &end)) return;
   const ClusterI I = load_cluster_i(c, first, end);
   const PairParams &pp = c.pp;
@@ -514,6 +517,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
   __shared__ RblLists<G> lists[256 / G];
   const int64_t nq = *c.nq_ptr;
   const int64_t a = c.charged ? 0 : nq, end = c.charged ? nq : c.n;
+  if (end - a > c.group_rbl) return;  // k_pair_rbl
   const int64_t per = (end - a + gridDim.x - 1) / gridDim.x;  // consecutive particles per block
   const int64_t first = a + xcd_block(blockIdx.x, gridDim.x) * per, last = min(end, first + per);
   const int sub = threadIdx.x & (G - 1);
@@ -728,24 +732,46 @@ PairF32 make_pair_f32(const PairParams &pp) {
 
 // Random batch list of a part. FP32C: the cluster form, whose lanes add their
 // terms in its own order. FP64: the group form, 64 lanes per particle, or 32
-// and 16 where the mean shell would leave most of 64 without a candidate, up
-// to the size from which the cluster form's waves fill the chip (group /
-// cluster): wide shells 200,000 electrolyte 319 / 453 us, 1M 1.35 / 1.39 ms,
-// 2M 2.62 / 2.49; narrow ones (32 lanes, 16 lanes / cluster) 2,000 LJ
-// electrolyte 11, 15; 10,000 21, 20; 30,000 46, 39 / 51; 50,000 78, 57 / 71;
-// 100,000 134, 115 / 108.
+// and 16 where the mean shell would leave most of 64 without a candidate or
+// there are waves enough with fewer, up to the size from which the cluster
+// form's waves fill the chip. A whole force call in us with 64, 32 and 16 lanes
+// and clusters, all charged unless said (m: particles within r_coul):
+//   wide shells    50,000, m = 60 195, 164, 146, 200; 300: 264, 251, 239, 295;
+//                  200,000, 60: 561, 442, 425, 471; 300: 781, 714, 780, 713;
+//                  1M, 60: 2679, 2011, 1848, 1991; 300: 3697, 3212, 3372, 3000;
+//                  a quarter charged, m = 724 50,000: 217, 245, 320, 376;
+//                  500,000: 1107, 1082, 1158, 1203; 1M, 300: 1408, 1315, 1318, 1498
+//   narrow shells  3,000, m = 25 74, 76, 82, 145; 8,000: 68, 62, 66, 104;
+//                  50,000, 45: 192, 161, 140, 190; 100,000, 25: 291, 240, 233, 242
+// What counts for wide shells is the part, whose size is known on the device
+// only: above the group form's most both kernels are launched, and one of them
+// exits at once; beyond kRblEither that costs as much as it gains.
 constexpr double kRblWide = 48.0;  // particles within r_coul of one, on average
-constexpr int64_t kRblGroupWide = 1 << 20, kRblGroupNarrow = 65536, kRblNarrow32 = 8192;
+constexpr int64_t kRblWide64 = 65536, kRblWide32 = 262144, kRblEither = 1 << 20;
+constexpr int64_t kRblNarrow32 = 8192, kRblNarrow16 = 65536;
 template <bool F32, bool COUNT, bool GHOST, bool QSHELL>
 static void launch_rbl(PairCtx c, hipStream_t st) {
   const Grid &g = c.pp.g;
   const double r = std::sqrt(c.pp.rc2);
   const bool wide = (double)c.n / (g.L[0] * g.L[1] * g.L[2]) * (4.0 / 3.0) * kPi * r * r * r >= kRblWide;
-  if (F32 || c.n > (wide ? kRblGroupWide : kRblGroupNarrow))
-    k_pair_rbl<F32, COUNT, GHOST, QSHELL><<<(unsigned)((c.n + kCI - 1) / kCI), 64, 0, st>>>(c);
-  else if (wide) k_pair_rbl_group<COUNT, GHOST, QSHELL, 64><<<group_blocks(c.n, 64), 256, 0, st>>>(c);
-  else if (c.n <= kRblNarrow32) k_pair_rbl_group<COUNT, GHOST, QSHELL, 32><<<group_blocks(c.n, 32), 256, 0, st>>>(c);
-  else k_pair_rbl_group<COUNT, GHOST, QSHELL, 16><<<group_blocks(c.n, 16), 256, 0, st>>>(c);
+  const unsigned clusters = (unsigned)((c.n + kCI - 1) / kCI);
+  if constexpr (!F32) {
+    c.group_rbl = wide ? kRblWide32 : kRblNarrow16;
+    const int64_t most = std::min(c.n, c.group_rbl);
+    if (c.n > (wide ? kRblEither : kRblNarrow16)) {
+      k_pair_rbl<F32, COUNT, GHOST, QSHELL, false><<<clusters, 64, 0, st>>>(c);
+      return;
+    }
+    if (wide && c.n <= kRblWide64)
+      k_pair_rbl_group<COUNT, GHOST, QSHELL, 64><<<group_blocks(most, 64), 256, 0, st>>>(c);
+    else if (wide || c.n <= kRblNarrow32)
+      k_pair_rbl_group<COUNT, GHOST, QSHELL, 32><<<group_blocks(most, 32), 256, 0, st>>>(c);
+    else
+      k_pair_rbl_group<COUNT, GHOST, QSHELL, 16><<<group_blocks(most, 16), 256, 0, st>>>(c);
+    if (c.n > c.group_rbl) k_pair_rbl<F32, COUNT, GHOST, QSHELL, true><<<clusters, 64, 0, st>>>(c);
+  } else {
+    k_pair_rbl<F32, COUNT, GHOST, QSHELL, false><<<clusters, 64, 0, st>>>(c);
+  }
 }
 
 // Plain sums of a part (c.charged): one thread per particle, or a group of

@@ -101,3 +101,18 @@ def test_energy_of_neutral_particles():
     ctx.close()
     print(f"LJ of {n}, {m} in the cutoff: energy, forces {t}")
     assert t[0] < 1.04 * t[1]
+
+
+@pytest.mark.parametrize("n", [200_000, 700_000])
+def test_random_batch_list_of_neighbouring_densities(n):
+    """52 particles within r_coul on average against 45, on either side of the line between wide and narrow shells."""
+    t, L = {}, (n / 0.1) ** (1 / 3)
+    for m in (45, 52):
+        r = (m / (4.0 / 3.0 * np.pi * 0.1)) ** (1 / 3)
+        params = rbe.make_params(L, (3.0 / r) ** 2, r, 0.5 * r, 20, r_core=0.5 * r, p_shell=20,
+                                 terms=rbe.TERM_LJ | rbe.TERM_COUL_REAL)
+        ctx, st = rbe.Context(params, n), random_state(n, L)
+        t[m] = best_us(lambda: ctx.forces(st), reps=10)
+        ctx.close()
+    print(f"batch list of {n}: {t}")
+    assert t[52] < 1.16 * t[45]
