@@ -809,7 +809,7 @@ static int eval_sorted(rbe_ctx *c, int64_t n, const int32_t *m, const double *w,
         launch_pair(c->p.prec, PAIR_PART_COULOMB, pp, n, nq, c->srt, c->cell_start, c->inv_id, gb, fx, fy, fz,
                     part_cnt(PAIR_PART_CHARGED), st);
       }
-    } else if (!pp.rbl && pair_grouped(c->p.prec, n) && !c->counting && !c->tm.on) {
+    } else if (!pp.rbl && pair_grouped(c->p.prec, pp, n) && !c->counting && !c->tm.on) {
       // one launch for both ranges (the counters and timings tell them apart)
       launch_pair(c->p.prec, PAIR_PART_BOTH, pp, n, nq, c->srt, c->cell_start, c->inv_id, gb, fx, fy, fz,
                   PairCounters{nullptr}, st);

@@ -25,8 +25,7 @@ constexpr int kEnergyThreads = 256;
 // sphere) 20,000: 107, 90, 123; 65,000: 220, 164, 134.
 constexpr int64_t kEnergyWide = 196608, kEnergyNarrow = 40960;
 static bool energy_narrow(const PairParams &pp, int64_t n) {
-  const double r = std::sqrt(pp.rq2);
-  return (double)n / (pp.g.L[0] * pp.g.L[1] * pp.g.L[2]) * (4.0 / 3.0) * kPi * r * r * r < 48.0;
+  return mean_within(pp.g, n, std::sqrt(pp.rq2)) < 48.0;
 }
 static int energy_lanes(bool narrow, int64_t n) {
   return n <= 4096 ? 64 : n <= (narrow ? kEnergyNarrow : kEnergyWide) ? 32 : 1;

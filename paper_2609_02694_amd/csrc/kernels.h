@@ -171,7 +171,7 @@ struct PairCounters {
 // PAIR_PART_BOTH: the plain sums of both ranges in one launch, for systems of
 // so few particles that a group of lanes shares one (pair_grouped).
 enum { PAIR_PART_CHARGED = 0, PAIR_PART_SHELL = 1, PAIR_PART_NEUTRAL = 2, PAIR_PART_COULOMB = 3, PAIR_PART_BOTH = 4 };
-bool pair_grouped(int prec, int64_t n);
+bool pair_grouped(int prec, const PairParams &pp, int64_t n);
 // gb: ghost shell of the natives (nullptr for the periodic traversal).
 void launch_pair(int prec, int part, const PairParams &pp, int64_t n, const int32_t *nq, const Sorted &s,
                  const int32_t *cell_start, const int32_t *inv_id, const GhostBuffers *gb, double *fx, double *fy,

@@ -3,7 +3,7 @@
 //
 // Full neighbour sums per particle i (cell order), no atomics, in one of
 // these forms (pair_device.h; the rules and what they measured stand at
-// group_lanes and launch_rbl):
+// group_most and launch_rbl):
 //   k_pair_group      plain sums of few particles: 64 or 32 lanes share one,
 //                     over its own trimmed stencil rows put end to end;
 //   k_pair_queue      plain sums of many, FP64: one lane per particle,
@@ -62,6 +62,7 @@ struct PairCtx {
   const int32_t *__restrict__ nq_ptr;         // charged count (device): [0, nq) charged, [nq, n) neutral
   int charged;                                // this launch: 1 the charged range, 0 the neutral range
   int64_t n;                                  // all particles
+  int64_t group_plain;                        // plain sums: largest part of the group walk
   int64_t group_rbl;                          // random batch list: largest part of the group form
   // ghost shell (GHOST kernels only)
   const double4 *__restrict__ gxq;
@@ -174,7 +175,7 @@ k_pair_plain(PairCtx c) {
   constexpr bool F32 = true;
   static_assert(MODE >= 0 && MODE <= 2, "mode");
   const int64_t nq = *c.nq_ptr;
-  if (group_lanes(F32, MODE, MODE ? nq : c.n - nq) > 1) return;  // too few particles: k_pair_group
+  if ((MODE ? nq : c.n - nq) <= c.group_plain) return;  // too few particles: k_pair_group
   int64_t first, end;
   if (!part_block(c, blockDim.x, &first, &end)) return;
   const int64_t i = first + threadIdx.x;
@@ -247,7 +248,7 @@ __global__ void __launch_bounds__(kQueueThreads) __attribute__((amdgpu_waves_per
   static_assert(MODE == 0 || MODE == 1, "mode");
   __shared__ uint32_t queue[kQueueCap * kQueueThreads];
   const int64_t nq = *c.nq_ptr;
-  if (group_lanes(F32, MODE, MODE ? nq : c.n - nq) > 1) return;  // too few particles: k_pair_group
+  if ((MODE ? nq : c.n - nq) <= c.group_plain) return;  // too few particles: k_pair_group
   int64_t first, end;
   if (!part_block(c, blockDim.x, &first, &end)) return;
   const int64_t i = first + threadIdx.x;
@@ -317,7 +318,7 @@ __global__ void __launch_bounds__(256) k_pair_group(PairCtx c, int coulomb) {
   __shared__ GroupTerms<F32 ? G : 1> terms[256 / G];
   const int64_t nq = *c.nq_ptr;
   const int64_t a = c.charged ? 0 : nq, end = c.charged == 1 ? nq : c.n;
-  if (group_lanes(F32, c.charged, end - a) == 1) return;  // enough particles: k_pair_plain or k_pair_queue
+  if (end - a > c.group_plain) return;  // enough particles: k_pair_plain or k_pair_queue
   const int64_t per = (end - a + gridDim.x - 1) / gridDim.x;  // consecutive particles per block
   const int64_t first = a + blockIdx.x * per, last = min(end, first + per);
   const PairParams &pp = c.pp;
@@ -751,9 +752,7 @@ constexpr int64_t kRblWide64 = 65536, kRblWide32 = 262144, kRblEither = 1 << 20;
 constexpr int64_t kRblNarrow32 = 8192, kRblNarrow16 = 65536;
 template <bool F32, bool COUNT, bool GHOST, bool QSHELL>
 static void launch_rbl(PairCtx c, hipStream_t st) {
-  const Grid &g = c.pp.g;
-  const double r = std::sqrt(c.pp.rc2);
-  const bool wide = (double)c.n / (g.L[0] * g.L[1] * g.L[2]) * (4.0 / 3.0) * kPi * r * r * r >= kRblWide;
+  const bool wide = mean_within(c.pp.g, c.n, std::sqrt(c.pp.rc2)) >= kRblWide;
   const unsigned clusters = (unsigned)((c.n + kCI - 1) / kCI);
   if constexpr (!F32) {
     c.group_rbl = wide ? kRblWide32 : kRblNarrow16;
@@ -775,18 +774,23 @@ static void launch_rbl(PairCtx c, hipStream_t st) {
 }
 
 // Plain sums of a part (c.charged): one thread per particle, or a group of
-// lanes when the part is small. Whether a part of a large system is small is
-// known on the device only, so both kernels are launched then and one of them
-// exits at once (about 3 us beside a walk of hundreds).
+// lanes when the part is small (group_most). Whether a part of a large system
+// is small is known on the device only, so both kernels are launched then and
+// one of them exits at once (about 3 us beside a walk of hundreds). A group has
+// 64 lanes in systems of up to 8,192 particles, whatever their parts (25,000
+// charged: 64 lanes 86 us, 32 88), and 32 in larger ones.
+static int64_t plain_group_most(bool f32, bool charged, const PairParams &pp, int64_t n) {
+  return group_most(f32, charged, mean_within(pp.g, n, std::sqrt(charged ? pp.rq2 : pp.rlj2)));
+}
 template <bool F32, bool COUNT, int MODE, bool GHOST>
 static void launch_plain(PairCtx c, hipStream_t st) {
-  const int lanes = group_lanes(F32, MODE, c.n);
-  const int64_t most = std::min(c.n, group_most(F32, MODE));
-  if (lanes == 64)
+  c.group_plain = c.charged == 2 ? c.n : plain_group_most(F32, MODE, c.pp, c.n);
+  const int64_t most = std::min(c.n, c.group_plain);
+  if (c.n <= 8192)
     k_pair_group<F32, COUNT, GHOST, 64><<<group_blocks(most, 64), 256, 0, st>>>(c, MODE == 2);
   else
     k_pair_group<F32, COUNT, GHOST, 32><<<group_blocks(most, 32), 256, 0, st>>>(c, MODE == 2);
-  if (lanes > 1) return;
+  if (c.n <= c.group_plain) return;
   const unsigned blocks = (unsigned)((c.n + 255) / 256);
   if constexpr (F32) k_pair_plain<COUNT, MODE, GHOST><<<blocks, 256, 0, st>>>(c);
   else k_pair_queue<COUNT, MODE, GHOST><<<blocks, kQueueThreads, 0, st>>>(c);
@@ -821,7 +825,9 @@ static void launch_part(PairCtx c, int part, hipStream_t st) {
   }
 }
 
-bool pair_grouped(int prec, int64_t n) { return group_lanes(prec == RBE_FP32C, false, n) > 1; }
+bool pair_grouped(int prec, const PairParams &pp, int64_t n) {
+  return n <= std::min<int64_t>(65536, plain_group_most(prec == RBE_FP32C, true, pp, n));
+}
 
 template <bool GHOST>
 static void launch_prec(int prec, PairCtx c, int part, hipStream_t st) {

