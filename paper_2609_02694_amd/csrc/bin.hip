@@ -17,7 +17,7 @@
 // in runs. A wave takes one atomic per run (its length) and hands out the
 // slots of the run in input order; a bucket is then usually already in order
 // and its placement a copy (checked per bucket; out-of-order buckets are
-// sorted by insertion). Small systems run all steps in one block
+// sorted by insertion, on grids of few cells by counting). Small systems run all steps in one block
 // (k_bin_block).
 #include <algorithm>
 
@@ -195,11 +195,37 @@ __global__ void __launch_bounds__(256) k_scatter_prov(int64_t n, const int32_t *
   tmp[start[key[i]] + slot[i]] = (int32_t)i;
 }
 
-__global__ void __launch_bounds__(256) k_place_buckets(int64_t nkeys, const int32_t *__restrict__ start,
+// Blocks [0, nb): one thread per bucket. Blocks from nb on (grids of few cells):
+// one thread per particle of a bucket longer than kPlaceAlone, whose place is
+// the count of the members with a smaller input index. A lone thread sorting hundreds of entries by insertion is bound by the latency of
+// its moves, as many as the disorder that the atomics happened to leave:
+// binning 12,000 particles in random order into 64 cells took 19.0 ms, now 50
+// us, 332,000 into 17,576 570 us, now 105.
+constexpr int kPlaceAlone = 8;
+// Particles a key from which on the second kind of block is launched: buckets
+// are twice as long where one species fills the grid, longer where the density
+// varies.
+constexpr int kPlaceMean = 4;
+__global__ void __launch_bounds__(256) k_place_buckets(int64_t nkeys, int64_t n, unsigned nb,
+                                                       const int32_t *__restrict__ key,
+                                                       const int32_t *__restrict__ start,
                                                        const int32_t *__restrict__ tmp, int32_t *__restrict__ perm) {
-  const int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (k >= nkeys) return;
-  place_bucket(start[k], start[k + 1], tmp, perm);
+  if (blockIdx.x < nb) {
+    const int64_t k = blockIdx.x * (int64_t)256 + threadIdx.x;
+    if (k >= nkeys) return;
+    const int lo = start[k], hi = start[k + 1];
+    if (gridDim.x == nb || hi - lo <= kPlaceAlone) place_bucket(lo, hi, tmp, perm);
+    return;
+  }
+  const int64_t t = (blockIdx.x - nb) * (int64_t)256 + threadIdx.x;
+  if (t >= n) return;
+  const int32_t i = tmp[t];
+  const int k = key[i], lo = start[k], hi = start[k + 1];
+  if (hi - lo <= kPlaceAlone) return;
+  int r = lo;
+#pragma unroll 8
+  for (int u = lo; u < hi; ++u) r += tmp[u] < i;
+  perm[r] = i;
 }
 
 // ---------------------------------------------------------------------------
@@ -308,16 +334,21 @@ __global__ void __launch_bounds__(kBlockBinThreads) k_bin_block(int n, int nkeys
 }
 
 // One block's time grows with the keys (its clearing and scan) and with the
-// particles, at random places most (an atomic each, where a step's cell order
-// makes runs); the launches' does not. Block against launches in us, a binning
-// of particles in random order: 2,000 and 16,000 keys 23.2, 27.6; and 27,648:
-// 32.9, 27.5; 4,000 and 8,192: 22.1, 27.1; and 16,000: 29.1, 27.3; 6,000 and
-// 3,456: 23.5, 27.2; and 8,192: 28.3, 27.2; 8,000 and 27,648: 51.5, 27.2. Two
-// steps from given keys: 300 and 4,096 keys 52, 61; and 13,824: 62, 61; 4,000
-// and 4,096: 64, 73; and 13,824: 75, 66; 8,000 and 4,096: 93, 95; and 13,824:
-// 95, 81.
+// particles, of random order most (an atomic each, where cell order makes
+// runs); the launches' hardly does, but each costs the caller its submission.
+// Block against launches in us, kernels alone and (a whole call): a step's
+// passes from given keys 500 particles and 8,192 keys 11.4, 12.6; and 14,400:
+// 17.4, 13.0; 4,000 and 8,192: 14.3, 12.4; 8,000 and 3,456: 15.1, 15.6 (two
+// steps 1,000 and 13,824: 81, 99; and 32,768: 112, 100; 8,000 and 4,096: 83,
+// 95; and 13,824: 96, 94). All passes, particles in random order 2,000 and
+// 8,192: 17.1, 19.0; 4,000 and 3,456: 18.5, 20.9; 8,000 and 8,192: 35.6, 22.1
+// (a force call 2,000 and 13,824: 36, 40; and 32,768: 51, 40; 4,000 and 4,096:
+// 39, 42; and 13,824: 45, 41; 6,000 and 4,096: 47, 46).
+// A particle's place is a count over its bucket in both, of long buckets faster
+// by the launches (8,000 and 128 keys: 184, 36; 2,000: 19, 23).
 static bool bin_in_block(int64_t n, int64_t nkeys, bool keys_given) {
-  return n <= kBlockBinThreads * kBlockBinEach && (keys_given ? nkeys + n <= 13000 : nkeys + 4 * n <= 26000);
+  return n <= kBlockBinThreads * kBlockBinEach && nkeys + (keys_given ? n : 4 * n) <= (keys_given ? 13000 : 26000) &&
+         n * n <= 180000 * nkeys;
 }
 
 void launch_bin_clear(const BinBuffers &b, int64_t nkeys, int64_t n, hipStream_t st) {
@@ -342,7 +373,9 @@ static void launch_bin_passes(const BinBuffers &b, int64_t nkeys, int64_t n, int
   if (more) blocks = std::max(blocks, std::min<int64_t>(8192, nkeys / (256 * kClearEach)));
   k_scatter_prov<<<(unsigned)blocks, 256, 0, st>>>(n, b.key, b.slot, cell_start, b.tmp, more ? b.count : nullptr,
                                                    nkeys);
-  k_place_buckets<<<(unsigned)((nkeys + 255) / 256), 256, 0, st>>>(nkeys, cell_start, b.tmp, perm);
+  const unsigned nb = (unsigned)((nkeys + 255) / 256);
+  const unsigned pb = n > kPlaceMean * nkeys ? (unsigned)((n + 255) / 256) : 0u;
+  k_place_buckets<<<nb + pb, 256, 0, st>>>(nkeys, n, nb, b.key, cell_start, b.tmp, perm);
 }
 
 void launch_bin_place(const BinBuffers &b, int64_t nkeys, int64_t n, int32_t *cell_start, int32_t *perm, bool more,

@@ -1,6 +1,8 @@
 """Binning at the edges of its one-block forms: from positions (keys + 4 n up to
-26,000) bit-exact against the oracle, and in a step from keys (keys + n up to
-13,000, n up to 8,192), which returns the particles in cell order."""
+26,000, n^2 up to 180,000 keys) bit-exact against the oracle, and in a step from
+keys (keys + n up to 13,000, n up to 8,192), which returns the particles in cell
+order; and the buckets that are placed by counting (more than 8 entries, on
+grids of fewer keys than a quarter of the particles)."""
 import numpy as np
 import pytest
 
@@ -24,7 +26,8 @@ def particles(n, seed):
     return dict(x=x, y=y, z=z, vx=vx, vy=vy, vz=vz, q=rng.permutation(q), id=np.arange(n, dtype=np.int32))
 
 
-@pytest.mark.parametrize("n,ncell", [(6_400, (10, 5, 4)), (6_401, (10, 5, 4)), (500, (12, 40, 25)), (501, (12, 40, 25))])
+@pytest.mark.parametrize("n,ncell", [(6_250, (10, 10, 5)), (6_251, (10, 10, 5)), (500, (20, 20, 30)),
+                                     (501, (20, 20, 30)), (848, (2, 1, 1)), (849, (2, 1, 1)), (1, (1, 1, 1))])
 def test_from_positions(n, ncell):
     s = particles(n, n)
     ctx = rbe.Context(rbe.make_params(L, 0.3, 1.0, 0.5, 4, ncell=ncell), n)
@@ -35,7 +38,7 @@ def test_from_positions(n, ncell):
     ctx.close()
 
 
-@pytest.mark.parametrize("n,ncell", [(8_192, (12, 20, 10)), (8_193, (12, 20, 10)), (4_000, (20, 15, 15)),
+@pytest.mark.parametrize("n,ncell", [(8_192, (8, 25, 12)), (8_193, (8, 25, 12)), (4_000, (20, 15, 15)),
                                      (4_001, (20, 15, 15)), (3, (50, 13, 10))])
 def test_in_steps(n, ncell):
     ctx = rbe.Context(rbe.make_params(L, 0.3, 1.0, 0.5, 4, ncell=ncell, terms=rbe.TERM_FOURIER, dt=0.01), n)
@@ -47,3 +50,19 @@ def test_in_steps(n, ncell):
     got = {k: getattr(st, k).cpu().numpy() for k in ("x", "y", "z", "q", "id")}
     _, perm = oracle.bin_cells(got["x"], got["y"], got["z"], got["q"], L, ncell)
     assert np.array_equal(perm, np.arange(n)) and np.array_equal(np.sort(got["id"]), np.arange(n))
+
+
+@pytest.mark.parametrize("n,ncell", [(20_000, (16, 16, 9)), (20_000, (16, 16, 10)),  # 4.3 and 3.9 particles a key
+                                     (9_000, (16, 8, 8)),                           # buckets of about 8
+                                     (70_000, (1, 1, 1)), (9_001, (2, 1, 1))])
+@pytest.mark.parametrize("ordered", [False, True])
+def test_long_buckets(n, ncell, ordered):
+    s = particles(n, n)
+    if ordered:
+        _, o = oracle.bin_cells(s["x"], s["y"], s["z"], s["q"], L, ncell)
+        s = {k: np.ascontiguousarray(v[o]) for k, v in s.items()}
+    ctx = rbe.Context(rbe.make_params(L, 0.3, 1.0, 0.5, 4, ncell=ncell), n)
+    cs, perm = ctx.build_cells(*(torch.as_tensor(s[k]).cuda() for k in ("x", "y", "z", "q")))
+    cs_o, perm_o = oracle.bin_cells(s["x"], s["y"], s["z"], s["q"], L, ncell)
+    ctx.close()
+    assert np.array_equal(cs.cpu().numpy(), cs_o) and np.array_equal(perm.cpu().numpy(), perm_o)

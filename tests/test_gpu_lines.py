@@ -121,3 +121,10 @@ def test_plain_sums_of_sparse_systems(prec, small, large):
     """Two particles in the reach: a system costs less than a larger one, which takes one thread per particle."""
     f = [forces(n, r_coul=reach(2), prec=prec, terms=rbe.TERM_COUL_REAL) for n in (small, large)]
     assert_no_slower(*f, 0.98)
+
+
+@pytest.mark.parametrize("n,ncell", [(12_000, (4, 4, 4)), (300_000, (20, 20, 20)), (8_192, (7, 7, 7))])
+def test_binning_on_a_grid_of_few_cells(n, ncell):
+    """Particles in random order: long buckets cost no more than a few times what short ones do."""
+    f = [build(rbe.make_params(96.0, 0.3, 2.0, 1.0, 4, ncell=nc), n, 96.0) for nc in (ncell, (48, 48, 48))]
+    assert_no_slower(*f, 4.0, reps=3)
