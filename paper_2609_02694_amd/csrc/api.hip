@@ -1265,7 +1265,7 @@ __global__ void __launch_bounds__(256) k_reorder_pack(int64_t n, const int32_t *
   s.xq[k] = make_double4(x, y, z, q);
   if (q != 0.0) s.sq[k] = make_double4(x / g.L[0], y / g.L[1], z / g.L[2], q);
   s.id[k] = id;
-  if (s.pk) s.pk[k] = pack_position(x, y, z, s.pk_scale);
+  if (s.pk) s.pk[k] = pack_record(x, y, z, s.pk_scale);
 }
 
 extern "C" int rbe_step(rbe_ctx *c, rbe_state *s, int32_t nsteps, uint64_t first_eval, void *stream) {

@@ -119,7 +119,7 @@ __global__ void __launch_bounds__(kBatchThreads) k_batch_reorder(BatchArgs a) {
   }
   a.xq[k] = make_double4(x, y, z, q);
   if (q != 0.0) a.sq[k] = make_double4(x / R.g.L[0], y / R.g.L[1], z / R.g.L[2], q);
-  if (a.pk) a.pk[k] = pack_position(x, y, z, a.pk_scale);
+  if (a.pk) a.pk[k] = pack_record(x, y, z, a.pk_scale);
 }
 
 // ---------------------------------------------------------------------------

@@ -76,7 +76,7 @@ __global__ void __launch_bounds__(256) k_ghost_fill(Grid g, int64_t cap, const i
       const double4 r = xq[j];
       gxq[d] = make_double4(r.x + sx, r.y + sy, r.z + sz, r.w);
       gid[d] = ids[j];
-      if (gpk) gpk[d] = pack_position(r.x + sx, r.y + sy, r.z + sz, pk_scale);
+      if (gpk) gpk[d] = pack_record(r.x + sx, r.y + sy, r.z + sz, pk_scale);
     }
   }
   gstart[key] = (int32_t)(d0 < cap ? d0 : cap);

@@ -60,18 +60,21 @@ struct Sorted {
 // ones alias. The period is four times the largest reach, and at least so long
 // that a candidate of a trimmed row (at most the reach and one cell edge away
 // along an axis) never aliases to within the reach.
-// A non-finite position, which is within no reach of anything, has bit 31 of z
-// set and the rest clear: its squared distance in grid units (packed_dist2) is
-// 2^30 or more from a finite one, above every reach, and 0 from another of its
-// kind, so that the pair is left to the exact test that rejects it.
 __host__ __device__ inline double pack_scale(double reach, double edge) {
   const double period = 2.02 * (reach + edge);
   return 1.0 / (period > 4.0 * reach ? period : 4.0 * reach);
 }
 __device__ inline uint2 pack_position(double x, double y, double z, double scale) {
   auto one = [&](double v) { return (uint32_t)(__builtin_amdgcn_fract(v * scale) * 65536.0) & 0xFFFFu; };
-  if (!__builtin_isfinite(x + y + z)) return make_uint2(0u, 0x80000000u);
   return make_uint2(one(x) | (one(y) << 16), one(z));
+}
+// A particle's record. A non-finite position, which is within no reach of
+// anything, has bit 31 of z set: its squared distance in grid units from any
+// other (packed_dist2) is 2^30 or more, above every reach.
+__device__ inline uint2 pack_record(double x, double y, double z, double scale) {
+  uint2 r = pack_position(x, y, z, scale);
+  if (!__builtin_isfinite(x + y + z)) r.y |= 0x80000000u;
+  return r;
 }
 // Squared reach in grid units that no pair inside r exceeds: each coordinate
 // difference is off by less than one unit, the distance by less than sqrt 3.

@@ -62,8 +62,6 @@ struct PairCtx {
   const int32_t *__restrict__ nq_ptr;         // charged count (device): [0, nq) charged, [nq, n) neutral
   int charged;                                // this launch: 1 the charged range, 0 the neutral range
   int64_t n;                                  // all particles
-  int64_t group_plain;                        // plain sums: largest part of the group walk
-  int64_t group_rbl;                          // random batch list: largest part of the group form
   // ghost shell (GHOST kernels only)
   const double4 *__restrict__ gxq;
   const int32_t *__restrict__ gid;
@@ -76,6 +74,8 @@ struct PairCtx {
   // random batch list: no pair outside r_coul up to t2_out, every one inside
   // it below t2_in; no pair inside r_core above t2_core
   uint32_t t2_out, t2_in, t2_core;
+  // largest parts of the group forms: plain sums, random batch list
+  int64_t group_plain, group_rbl;
 };
 
 // Cluster walk of one species block for a row group.
@@ -512,13 +512,13 @@ struct RblLists {
   uint32_t key[kShellCap];        // shell keys below the threshold
   uint32_t sel[RBE_MAX_SHELL_BATCH];
 };
-template <bool COUNT, bool GHOST, bool QSHELL, int G>
+template <bool COUNT, bool GHOST, bool QSHELL, int G, bool EITHER>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_pair_rbl_group(PairCtx c) {
   __shared__ GroupRows<G> rows_lds[256 / G];
   __shared__ RblLists<G> lists[256 / G];
   const int64_t nq = *c.nq_ptr;
   const int64_t a = c.charged ? 0 : nq, end = c.charged ? nq : c.n;
-  if (end - a > c.group_rbl) return;  // k_pair_rbl
+  if (EITHER && end - a > c.group_rbl) return;  // k_pair_rbl
   const int64_t per = (end - a + gridDim.x - 1) / gridDim.x;  // consecutive particles per block
   const int64_t first = a + xcd_block(blockIdx.x, gridDim.x) * per, last = min(end, first + per);
   const int sub = threadIdx.x & (G - 1);
@@ -711,9 +711,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
                  f1 = group_sum<G>(fma(scale, sh.get(1), acc.get(1))),
                  f2 = group_sum<G>(fma(scale, sh.get(2), acc.get(2)));
     if (sub == 0) {
-      c.fx[i] = f0;
-      c.fy[i] = f1;
-      c.fz[i] = f2;
+      // (a non-finite position is within no reach of anything)
+      const bool here = __builtin_isfinite(pi.x + pi.y + pi.z);
+      c.fx[i] = here ? f0 : 0.0;
+      c.fy[i] = here ? f1 : 0.0;
+      c.fz[i] = here ? f2 : 0.0;
     }
     if (sub == 0) n_shell += (unsigned long long)m;
   }
@@ -741,35 +743,37 @@ PairF32 make_pair_f32(const PairParams &pp) {
 //                  200,000, 60: 561, 442, 425, 471; 300: 781, 714, 780, 713;
 //                  1M, 60: 2679, 2011, 1848, 1991; 300: 3697, 3212, 3372, 3000;
 //                  a quarter charged, m = 724 50,000: 217, 245, 320, 376;
-//                  500,000: 1107, 1082, 1158, 1203; 1M, 300: 1408, 1315, 1318, 1498
+//                  200,000: 542, 551, 610, 682; 500,000: 1107, 1082, 1158, 1203;
+//                  1M, 300: 1408, 1315, 1318, 1498
 //   narrow shells  3,000, m = 25 74, 76, 82, 145; 8,000: 68, 62, 66, 104;
 //                  50,000, 45: 192, 161, 140, 190; 100,000, 25: 291, 240, 233, 242
 // What counts for wide shells is the part, whose size is known on the device
-// only: above the group form's most both kernels are launched, and one of them
-// exits at once; beyond kRblEither that costs as much as it gains.
-constexpr double kRblWide = 48.0;  // particles within r_coul of one, on average
-constexpr int64_t kRblWide64 = 65536, kRblWide32 = 262144, kRblEither = 1 << 20;
+// only: between kRblWide32 and kRblEither particles both kernels are launched,
+// and one of them exits (the clusters' blocks in 9 us at 280,000, 26 at 1M;
+// beyond, that costs as much as it gains). Shells so full that 64 lanes are
+// busy keep them longer.
+constexpr double kRblWide = 48.0, kRblFull = 500.0;  // particles within r_coul of one, on average
+constexpr int64_t kRblWide64 = 65536, kRblFull64 = 393216, kRblWide32 = 262144, kRblEither = 1 << 20;
 constexpr int64_t kRblNarrow32 = 8192, kRblNarrow16 = 65536;
 template <bool F32, bool COUNT, bool GHOST, bool QSHELL>
 static void launch_rbl(PairCtx c, hipStream_t st) {
-  const bool wide = mean_within(c.pp.g, c.n, std::sqrt(c.pp.rc2)) >= kRblWide;
+  const double mean = mean_within(c.pp.g, c.n, std::sqrt(c.pp.rc2));
+  const bool wide = mean >= kRblWide;
   const unsigned clusters = (unsigned)((c.n + kCI - 1) / kCI);
-  if constexpr (!F32) {
-    c.group_rbl = wide ? kRblWide32 : kRblNarrow16;
-    const int64_t most = std::min(c.n, c.group_rbl);
-    if (c.n > (wide ? kRblEither : kRblNarrow16)) {
-      k_pair_rbl<F32, COUNT, GHOST, QSHELL, false><<<clusters, 64, 0, st>>>(c);
-      return;
-    }
-    if (wide && c.n <= kRblWide64)
-      k_pair_rbl_group<COUNT, GHOST, QSHELL, 64><<<group_blocks(most, 64), 256, 0, st>>>(c);
-    else if (wide || c.n <= kRblNarrow32)
-      k_pair_rbl_group<COUNT, GHOST, QSHELL, 32><<<group_blocks(most, 32), 256, 0, st>>>(c);
-    else
-      k_pair_rbl_group<COUNT, GHOST, QSHELL, 16><<<group_blocks(most, 16), 256, 0, st>>>(c);
-    if (c.n > c.group_rbl) k_pair_rbl<F32, COUNT, GHOST, QSHELL, true><<<clusters, 64, 0, st>>>(c);
-  } else {
+  if constexpr (F32) {
     k_pair_rbl<F32, COUNT, GHOST, QSHELL, false><<<clusters, 64, 0, st>>>(c);
+  } else if (c.n > (wide ? kRblEither : kRblNarrow16)) {
+    k_pair_rbl<F32, COUNT, GHOST, QSHELL, false><<<clusters, 64, 0, st>>>(c);
+  } else if (wide && c.n <= (mean >= kRblFull ? kRblFull64 : kRblWide64)) {
+    k_pair_rbl_group<COUNT, GHOST, QSHELL, 64, false><<<group_blocks(c.n, 64), 256, 0, st>>>(c);
+  } else if (c.n <= (wide ? kRblWide32 : kRblNarrow32)) {
+    k_pair_rbl_group<COUNT, GHOST, QSHELL, 32, false><<<group_blocks(c.n, 32), 256, 0, st>>>(c);
+  } else if (wide) {
+    c.group_rbl = kRblWide32;
+    k_pair_rbl_group<COUNT, GHOST, QSHELL, 32, true><<<group_blocks(kRblWide32, 32), 256, 0, st>>>(c);
+    k_pair_rbl<F32, COUNT, GHOST, QSHELL, true><<<clusters, 64, 0, st>>>(c);
+  } else {
+    k_pair_rbl_group<COUNT, GHOST, QSHELL, 16, false><<<group_blocks(c.n, 16), 256, 0, st>>>(c);
   }
 }
 

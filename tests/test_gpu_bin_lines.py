@@ -1,8 +1,8 @@
 """Binning at the edges of its one-block forms: from positions (keys + 4 n up to
-26,000, n^2 up to 180,000 keys) bit-exact against the oracle, and in a step from
+28,000, n^2 up to 180,000 keys) bit-exact against the oracle, and in a step from
 keys (keys + n up to 13,000, n up to 8,192), which returns the particles in cell
 order; and the buckets that are placed by counting (more than 8 entries, on
-grids of fewer keys than a quarter of the particles)."""
+grids of fewer keys than half the particles)."""
 import numpy as np
 import pytest
 
@@ -26,8 +26,8 @@ def particles(n, seed):
     return dict(x=x, y=y, z=z, vx=vx, vy=vy, vz=vz, q=rng.permutation(q), id=np.arange(n, dtype=np.int32))
 
 
-@pytest.mark.parametrize("n,ncell", [(6_250, (10, 10, 5)), (6_251, (10, 10, 5)), (500, (20, 20, 30)),
-                                     (501, (20, 20, 30)), (848, (2, 1, 1)), (849, (2, 1, 1)), (1, (1, 1, 1))])
+@pytest.mark.parametrize("n,ncell", [(6_750, (10, 10, 5)), (6_751, (10, 10, 5)), (500, (20, 20, 32)),
+                                     (600, (20, 20, 32)), (601, (20, 20, 32)), (848, (2, 1, 1)), (849, (2, 1, 1)), (1, (1, 1, 1))])
 def test_from_positions(n, ncell):
     s = particles(n, n)
     ctx = rbe.Context(rbe.make_params(L, 0.3, 1.0, 0.5, 4, ncell=ncell), n)
@@ -52,7 +52,7 @@ def test_in_steps(n, ncell):
     assert np.array_equal(perm, np.arange(n)) and np.array_equal(np.sort(got["id"]), np.arange(n))
 
 
-@pytest.mark.parametrize("n,ncell", [(20_000, (16, 16, 9)), (20_000, (16, 16, 10)),  # 4.3 and 3.9 particles a key
+@pytest.mark.parametrize("n,ncell", [(20_000, (16, 16, 19)), (20_000, (16, 16, 20)),  # 2.06 and 1.95 particles a key
                                      (9_000, (16, 8, 8)),                           # buckets of about 8
                                      (70_000, (1, 1, 1)), (9_001, (2, 1, 1))])
 @pytest.mark.parametrize("ordered", [False, True])

@@ -23,7 +23,7 @@ def reference(p, s, rows, ev):
 @pytest.mark.parametrize("name,n,over", [
     ("ljelectrolyte", 2_000, {}), ("ljelectrolyte", 9_000, {}), ("ljelectrolyte", 66_000, {}),
     ("electrolyte1m", 9_001, {}), ("electrolyte1m", 9_001, {"ghost": 6.0}),
-    ("electrolyte1m", 65_538, {}),                             # wide shell, the first size of 32 lanes
+    ("electrolyte1m", 65_538, {"r_coul": 5.0}),                # wide shell, the first size of 32 lanes
 ])
 def test_forces_and_mean(name, n, over):
     p, s = system(name, n=n, **over)
@@ -35,14 +35,16 @@ def test_forces_and_mean(name, n, over):
         assert e < 1e-12 and r < ROW64
 
 
-@pytest.mark.parametrize("over", [
-    {},                                       # 32 lanes
-    {"frac_charged": 1.0},                    # clusters
-    {"frac_charged": 0.02, "r_lj": 4.0},      # the neutral part takes the list too, as clusters
-    {"ghost": 6.0},
+@pytest.mark.parametrize("n,over", [
+    (270_002, {}),                                       # a full shell: 64 lanes
+    (270_002, {"r_coul": 5.0}),                          # 32 lanes, launched beside the clusters
+    (270_002, {"r_coul": 5.0, "frac_charged": 1.0}),     # clusters
+    (270_002, {"r_coul": 5.0, "frac_charged": 0.02, "r_lj": 4.0}),  # the neutral part takes the list too
+    (270_002, {"r_coul": 5.0, "ghost": 5.0}),
+    (393_218, {}),                                       # a full shell, 32 lanes
 ])
-def test_parts_of_a_large_system(over):
-    p, s = system("electrolyte1m", n=270_002, **over)
+def test_parts_of_a_large_system(n, over):
+    p, s = system("electrolyte1m", n=n, **over)
     rows = np.arange(0, p["n"], 61)
     F = gpu_forces(p, s, terms=rbe.TERM_LJ | rbe.TERM_COUL_REAL, ev=3)
     frms = np.sqrt((F ** 2).sum() / len(F))
