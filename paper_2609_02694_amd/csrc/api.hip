@@ -79,7 +79,6 @@ struct rbe_ctx {
   bool fixed_modes = false;  // rbe_set_modes: slot 0 of m_dev/w_dev/mkd_dev is the caller's table
   double *mean_part = nullptr, *mean = nullptr;
   double *epart = nullptr;   // energy partial sums
-  uint2 *epk = nullptr;      // packed positions of an energy call (FP32C: the forces need none)
   double *nh_part = nullptr, *nh_scale = nullptr;  // thermostat: |v|^2 partials, pending velocity scaling
   int *err = nullptr;
   double *qstats = nullptr;  // [2 kQBlocks] per-block (sum q, sum |q|)
@@ -404,11 +403,11 @@ extern "C" int rbe_create(rbe_ctx **out, const rbe_params *p, int64_t n_max, int
   c->srt.xq = b.alloc<double4>(n_max + kScanPad);
   c->srt.sq = b.alloc<double4>(n_max);
   c->srt.id = b.alloc<int32_t>(n_max + kScanPad);
-  (p->prec == RBE_FP64 ? c->srt.pk : c->epk) = b.alloc<uint2>(n_max + kScanPad);
+  if (p->prec == RBE_FP64) c->srt.pk = b.alloc<uint2>(n_max + kScanPad);
   c->srt.pk_scale = pack_scale(std::fmax(p->r_coul, p->r_lj), std::fmax(g.h[0], std::fmax(g.h[1], g.h[2])));
   for (int s = 0; s < 2; ++s) {
     WorkSet &w = c->ws[s];
-    w.x = b.alloc<double>(n_max);
+    w.x = b.alloc<double>(n_max + kScanPad);  // (padding: the energies)
     w.y = b.alloc<double>(n_max);
     w.z = b.alloc<double>(n_max);
     w.vx = b.alloc<double>(n_max);
@@ -1195,8 +1194,11 @@ extern "C" int rbe_energy(rbe_ctx *c, const rbe_state *s, const int32_t *m, cons
   hipStream_t st = (hipStream_t)stream;
   const int64_t n = s->n;
   launch_charge_check(c, n, s->q, st);
+  // FP32C contexts keep no packed positions: those of the queue walk go to a
+  // working array of rbe_step
+  static_assert(sizeof(uint2) == sizeof(double), "packed positions in an array of doubles");
   Sorted srt = c->srt;
-  if (c->epk) srt.pk = c->epk;
+  if (!srt.pk && energy_packed(c->pp, n)) srt.pk = (uint2 *)c->ws[0].x;
   const bool near = (c->p.terms & (RBE_TERM_LJ | RBE_TERM_COUL_REAL)) != 0;
   const bool fourier = (c->p.terms & RBE_TERM_FOURIER) != 0;
   launch_bin(c->bb, c->g, n, s->x, s->y, s->z, s->q, c->cell_start, c->perm, st);

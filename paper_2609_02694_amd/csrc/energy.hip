@@ -30,6 +30,7 @@ static bool energy_narrow(const PairParams &pp, int64_t n) {
 static int energy_lanes(bool narrow, int64_t n) {
   return n <= 4096 ? 64 : n <= (narrow ? kEnergyNarrow : kEnergyWide) ? 32 : 1;
 }
+bool energy_packed(const PairParams &pp, int64_t n) { return energy_lanes(energy_narrow(pp, n), n) == 1; }
 constexpr int64_t kEnergyNearBlocks = 16384;  // most blocks of the near field (each leaves one partial sum)
 constexpr int kEnergySqBlocks = 1024;  // grid of the q^2 / v^2 sums
 

@@ -301,6 +301,8 @@ struct EnergyFinal {
   double kc, self_coef, half_mass;  // kc, kc sqrt(alpha/pi), mass/2
   double *out;              // [8] device
 };
+// Whether the near field of n particles reads their packed positions.
+bool energy_packed(const PairParams &pp, int64_t n);
 // Length of the partial-sum scratch launch_energy needs for n_max particles.
 int energy_part_len(int64_t n_max);
 // Near-field energies of the sorted particles (when near), the q^2 and v^2
