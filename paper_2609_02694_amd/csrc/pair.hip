@@ -61,6 +61,7 @@ struct PairCtx {
   unsigned long long *__restrict__ counters;  // [4] when counting
   const int32_t *__restrict__ nq_ptr;         // charged count (device): [0, nq) charged, [nq, n) neutral
   int charged;                                // this launch: 1 the charged range, 0 the neutral range
+  int group_plain;                            // plain sums: largest part of the group walk
   int64_t n;                                  // all particles
   // ghost shell (GHOST kernels only)
   const double4 *__restrict__ gxq;
@@ -74,8 +75,7 @@ struct PairCtx {
   // random batch list: no pair outside r_coul up to t2_out, every one inside
   // it below t2_in; no pair inside r_core above t2_core
   uint32_t t2_out, t2_in, t2_core;
-  // largest parts of the group forms: plain sums, random batch list
-  int64_t group_plain, group_rbl;
+  int group_rbl;  // random batch list: largest part of the group form
 };
 
 // Cluster walk of one species block for a row group.
@@ -788,8 +788,8 @@ static int64_t plain_group_most(bool f32, bool charged, const PairParams &pp, in
 }
 template <bool F32, bool COUNT, int MODE, bool GHOST>
 static void launch_plain(PairCtx c, hipStream_t st) {
-  c.group_plain = c.charged == 2 ? c.n : plain_group_most(F32, MODE, c.pp, c.n);
-  const int64_t most = std::min(c.n, c.group_plain);
+  c.group_plain = (int)(c.charged == 2 ? c.n : plain_group_most(F32, MODE, c.pp, c.n));
+  const int64_t most = std::min<int64_t>(c.n, c.group_plain);
   if (c.n <= 8192)
     k_pair_group<F32, COUNT, GHOST, 64><<<group_blocks(most, 64), 256, 0, st>>>(c, MODE == 2);
   else
