@@ -366,12 +366,12 @@ __device__ inline void for_stencil(const Grid &g, const int32_t *__restrict__ ce
 // rows that lie inside the native grid, then the ghosts of the same rows of
 // the padded grid, each row trimmed to the reach. (cx, cy, cz) is a native
 // cell. Ghosts reach fn with indices offset by nnat.
-template <class Fn, class RowEnd = NoRowEnd>
+template <class Fn, class RowEnd>
 __device__ inline void for_stencil_ghost(const Grid &g, const int32_t *__restrict__ cell_start,
                                          const double4 *__restrict__ xq,
                                          const int32_t *__restrict__ gcell_start, const double4 *__restrict__ gxq,
                                          int nnat, int blk, int cx, int cy, int cz, const Sten &s, double px,
-                                         double py, double pz, double r2, Fn &&fn, RowEnd row_end = RowEnd()) {
+                                         double py, double pz, double r2, Fn &&fn, RowEnd row_end) {
   const int32_t *cs = cell_start + (int64_t)blk * g.ncell;
   const int32_t *gs = gcell_start + (int64_t)blk * g.pncell;
   const RowFrame F(g, px, py, pz, cx, cy, cz, r2);
