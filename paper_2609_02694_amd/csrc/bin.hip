@@ -347,7 +347,7 @@ __global__ void __launch_bounds__(kBlockBinThreads) k_bin_block(int n, int nkeys
 // A particle's place is a count over its bucket in both, of long buckets faster
 // by the launches (8,000 and 128 keys: 184, 36; 2,000: 19, 23).
 static bool bin_in_block(int64_t n, int64_t nkeys, bool keys_given) {
-  return n <= kBlockBinThreads * kBlockBinEach && nkeys + (keys_given ? n : 4 * n) <= (keys_given ? 13000 : 28000) &&
+  return n <= kBlockBinThreads * kBlockBinEach && nkeys + (keys_given ? n : 3 * n) <= (keys_given ? 13000 : 21000) &&
          n * n <= 180000 * nkeys;
 }
 

@@ -1,5 +1,5 @@
-"""Binning at the edges of its one-block forms: from positions (keys + 4 n up to
-28,000, n^2 up to 180,000 keys) bit-exact against the oracle, and in a step from
+"""Binning at the edges of its one-block forms: from positions (keys + 3 n up to
+21,000, n^2 up to 180,000 keys) bit-exact against the oracle, and in a step from
 keys (keys + n up to 13,000, n up to 8,192), which returns the particles in cell
 order; and the buckets that are placed by counting (more than 8 entries, on
 grids of fewer keys than half the particles)."""
@@ -26,8 +26,8 @@ def particles(n, seed):
     return dict(x=x, y=y, z=z, vx=vx, vy=vy, vz=vz, q=rng.permutation(q), id=np.arange(n, dtype=np.int32))
 
 
-@pytest.mark.parametrize("n,ncell", [(6_750, (10, 10, 5)), (6_751, (10, 10, 5)), (500, (20, 20, 32)),
-                                     (600, (20, 20, 32)), (601, (20, 20, 32)), (848, (2, 1, 1)), (849, (2, 1, 1)), (1, (1, 1, 1))])
+@pytest.mark.parametrize("n,ncell", [(6_600, (10, 10, 6)), (6_601, (10, 10, 6)), (500, (20, 20, 24)),
+                                     (600, (20, 20, 24)), (601, (20, 20, 24)), (848, (2, 1, 1)), (849, (2, 1, 1)), (1, (1, 1, 1))])
 def test_from_positions(n, ncell):
     s = particles(n, n)
     ctx = rbe.Context(rbe.make_params(L, 0.3, 1.0, 0.5, 4, ncell=ncell), n)
