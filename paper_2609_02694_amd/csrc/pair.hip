@@ -830,7 +830,8 @@ static void launch_part(PairCtx c, int part, hipStream_t st) {
 }
 
 bool pair_grouped(int prec, const PairParams &pp, int64_t n) {
-  return n <= std::min<int64_t>(65536, plain_group_most(prec == RBE_FP32C, true, pp, n));
+  const bool f32 = prec == RBE_FP32C;
+  return n <= std::min(plain_group_most(f32, true, pp, n), pp.do_lj ? plain_group_most(f32, false, pp, n) : 65536);
 }
 
 template <bool GHOST>

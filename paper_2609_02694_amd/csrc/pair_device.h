@@ -947,16 +947,16 @@ __device__ inline void drain_queue(HitQueue &Q, bool all, One &&one) {
 // charged, 80,000: 294, 224, 187 and ten times that many 1280, -, 1850). Neutral
 // FP64 (LJ only) 45,000: 77, 77, 54; 100,000: 82, 151, 98. FP32C 25,000: 283, 91,
 // 81; 100,000: 318, 322, 265; 80,000 of a sparse kind: 150, 239, 160.
-// With few particles in the reach a wave has little to share, and the line
-// lies lower (mean: particles within the reach of one). A whole force call,
-// one thread against 32 lanes: FP64 charged, mean 2 60,000: 129, 129; 120,000:
-// 187, 219; 260,000: 309, 409; mean 20 60,000: 109, 98; 120,000: 131, 160;
-// 260,000: 203, 299; mean 100 120,000: 237, 229; 200,000: 325, 362. FP32C, mean
-// 2 20,000: 98, 85; 40,000: 122, 135; 60,000: 151, 169; mean 10 40,000: 90, 95;
-// mean 40 60,000: 114, 109.
+// With few particles in the reach a wave has little to share, and the lines
+// lie lower (mean: particles within the reach of one). The kernel alone, one
+// thread against 32 lanes: FP64 charged, mean 1 20,000: 22, 19; 48,000: 23, 42;
+// mean 4 48,000: 30, 45; mean 16 100,000: 54, 99; neutral, mean 2 48,000: 33,
+// 43; FP32C mean 1 20,000: 18, 18; mean 4: 24, 20. A whole force call FP64
+// charged, mean 20 60,000: 109, 98; 120,000: 131, 160; mean 100 120,000: 237,
+// 229; 200,000: 325, 362; FP32C mean 10 40,000: 90, 95; mean 40 60,000: 114, 109.
 inline int64_t group_most(bool f32, bool charged, double mean) {
-  if (f32) return mean < 24.0 ? 32768 : 65536;
-  return charged && mean >= 48.0 ? 262144 : 65536;
+  if (mean < (charged && !f32 ? 12.0 : 24.0)) return 32768;
+  return charged && !f32 && mean >= 48.0 ? 262144 : 65536;
 }
 // Mean number of particles within r of one of the n in the grid's box.
 inline double mean_within(const Grid &g, int64_t n, double r) {
