@@ -16,9 +16,9 @@
 // The input of a step is the previous step's cell order, so equal keys come
 // in runs. A wave takes one atomic per run (its length) and hands out the
 // slots of the run in input order; a bucket is then usually already in order
-// and its placement a copy (checked per bucket; out-of-order buckets are
-// sorted by insertion, on grids of few cells by counting). Small systems run all steps in one block
-// (k_bin_block).
+// and its placement a copy (checked per bucket; short buckets out of order are
+// sorted by insertion, long ones by counting). Small systems run all steps in
+// one block (k_bin_block).
 #include <algorithm>
 
 #include "rbe_internal.h"
@@ -197,10 +197,11 @@ __global__ void __launch_bounds__(256) k_scatter_prov(int64_t n, const int32_t *
 
 // Blocks [0, nb): one thread per bucket. Blocks from nb on (grids of few cells):
 // one thread per particle of a bucket longer than kPlaceAlone, whose place is
-// the count of the members with a smaller input index. A lone thread sorting hundreds of entries by insertion is bound by the latency of
-// its moves, as many as the disorder that the atomics happened to leave:
-// binning 12,000 particles in random order into 64 cells took 19.0 ms, now 50
-// us, 332,000 into 17,576 570 us, now 105.
+// the count of the members with a smaller input index. A lone thread sorting
+// hundreds of entries by insertion is bound by the latency of its moves, as many
+// as the disorder that the atomics happened to leave: binning 12,000 particles in
+// random order into 64 cells took 19.0 ms, now 50 us, 332,000 into 17,576 570 us,
+// now 105.
 constexpr int kPlaceAlone = 8;
 // Particles a key from which on the second kind of block is launched: buckets
 // are twice as long where one species fills the grid, longer where the density
