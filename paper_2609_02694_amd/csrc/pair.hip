@@ -752,25 +752,39 @@ PairF32 make_pair_f32(const PairParams &pp) {
 // and one of them exits (the clusters' blocks in 9 us at 280,000, 26 at 1M;
 // beyond, that costs as much as it gains). Shells so full that 64 lanes are
 // busy keep them longer.
+// The clusters' candidates come in few long rows where the cells are hardly
+// wider than the reach (9 rows of them; the default grid with r_lj = r_coul),
+// and they win sooner there, by most where the density varies. 32 lanes and
+// clusters, parts of 70,000, m = 60: 208, 199; 200: 300, 312; 100,000: 264, 237
+// and 392, 411, half charged 454, 438 and 715, 672; 200,000: 443, 388 and 671,
+// 642; 138,000 in a box that they fill to an eighth, half charged: 3796, 3100
+// and 11906, 10077. Cells from 1.3 times the reach on are as the narrow ones:
+// parts of 140,000, m = 300, half charged, 1.05: 1243, 1113; 1.3: 1444, 1584;
+// 1.6: 1853, 2349; 0.85 (m = 200): 965, 1380.
 constexpr double kRblWide = 48.0, kRblFull = 500.0;  // particles within r_coul of one, on average
 constexpr int64_t kRblWide64 = 65536, kRblFull64 = 393216, kRblWide32 = 262144, kRblEither = 1 << 20;
+constexpr int64_t kRblTight32 = 65536;
+static bool rbl_tight(const PairParams &pp) {
+  return pp.s_coul.y == 1 && pp.s_coul.z == 1 && 1.44 * pp.rq2 * pp.g.inv_h[1] * pp.g.inv_h[2] >= 1.0;
+}
 constexpr int64_t kRblNarrow32 = 8192, kRblNarrow16 = 65536;
 template <bool F32, bool COUNT, bool GHOST, bool QSHELL>
 static void launch_rbl(PairCtx c, hipStream_t st) {
   const double mean = mean_within(c.pp.g, c.n, std::sqrt(c.pp.rc2));
-  const bool wide = mean >= kRblWide;
+  const bool wide = mean >= kRblWide, tight = rbl_tight(c.pp);
+  const int64_t wide32 = tight ? kRblTight32 : kRblWide32;
   const unsigned clusters = (unsigned)((c.n + kCI - 1) / kCI);
   if constexpr (F32) {
     k_pair_rbl<F32, COUNT, GHOST, QSHELL, false><<<clusters, 64, 0, st>>>(c);
   } else if (c.n > (wide ? kRblEither : kRblNarrow16)) {
     k_pair_rbl<F32, COUNT, GHOST, QSHELL, false><<<clusters, 64, 0, st>>>(c);
-  } else if (wide && c.n <= (mean >= kRblFull ? kRblFull64 : kRblWide64)) {
+  } else if (wide && c.n <= (mean >= kRblFull && !tight ? kRblFull64 : kRblWide64)) {
     k_pair_rbl_group<COUNT, GHOST, QSHELL, 64, false><<<group_blocks(c.n, 64), 256, 0, st>>>(c);
-  } else if (c.n <= (wide ? kRblWide32 : kRblNarrow32)) {
+  } else if (c.n <= (wide ? wide32 : kRblNarrow32)) {
     k_pair_rbl_group<COUNT, GHOST, QSHELL, 32, false><<<group_blocks(c.n, 32), 256, 0, st>>>(c);
   } else if (wide) {
-    c.group_rbl = kRblWide32;
-    k_pair_rbl_group<COUNT, GHOST, QSHELL, 32, true><<<group_blocks(kRblWide32, 32), 256, 0, st>>>(c);
+    c.group_rbl = (int)wide32;
+    k_pair_rbl_group<COUNT, GHOST, QSHELL, 32, true><<<group_blocks(wide32, 32), 256, 0, st>>>(c);
     k_pair_rbl<F32, COUNT, GHOST, QSHELL, true><<<clusters, 64, 0, st>>>(c);
   } else {
     k_pair_rbl_group<COUNT, GHOST, QSHELL, 16, false><<<group_blocks(c.n, 16), 256, 0, st>>>(c);

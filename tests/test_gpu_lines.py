@@ -116,6 +116,19 @@ def test_random_batch_list_of_neighbouring_densities(n):
     assert_no_slower(*f, 1.16, reps=10)
 
 
+def test_random_batch_list_of_a_droplet():
+    """Particles in an eighth of the box, cells as wide as the reach: 280,000 cost little more each than a
+    million (1.15 in clusters, as both are now: the call's launches and the last blocks weigh more; 1.42 shared by
+    lanes)."""
+    def droplet(n):
+        L, r = (n / 0.1) ** (1 / 3), reach(60)
+        params = rbe.make_params(L, (3.0 / r) ** 2, r, r, 20, r_core=0.5 * r, p_shell=20,
+                                 terms=rbe.TERM_LJ | rbe.TERM_COUL_REAL)
+        ctx, st = rbe.Context(params, n), random_state(n, L / 2, charged=0.5)
+        return lambda: ctx.forces(st)
+    assert_no_slower(droplet(280_000), droplet(1_060_000), 1.25 * 280 / 1060, reps=4, rounds=5)
+
+
 @pytest.mark.parametrize("prec,small,large", [(rbe.FP64, 250_000, 300_000), (rbe.FP32C, 60_000, 70_000)])
 def test_plain_sums_of_sparse_systems(prec, small, large):
     """Two particles in the reach: a system costs less than a larger one, which takes one thread per particle."""

@@ -42,6 +42,11 @@ def test_forces_and_mean(name, n, over):
     (270_002, {"r_coul": 5.0, "frac_charged": 0.02, "r_lj": 4.0}),  # the neutral part takes the list too
     (270_002, {"r_coul": 5.0, "ghost": 5.0}),
     (393_218, {}),                                       # a full shell, 32 lanes
+    # cells as wide as the reach: clusters from parts of 65,537 on
+    (83_002, {"r_coul": 4.0, "r_lj": 4.0, "frac_charged": 0.5}),
+    (83_002, {"r_coul": 4.0, "r_lj": 4.0, "frac_charged": 1.0}),
+    (90_002, {"r_coul": 4.0, "r_lj": 4.0, "frac_charged": 0.05}),
+    (100_002, {"r_coul": 4.0, "r_lj": 4.0, "frac_charged": 1.0, "ghost": 4.0}),
 ])
 def test_parts_of_a_large_system(n, over):
     p, s = system("electrolyte1m", n=n, **over)
