@@ -760,10 +760,13 @@ PairF32 make_pair_f32(const PairParams &pp) {
 // 642; 138,000 in a box that they fill to an eighth, half charged: 3796, 3100
 // and 11906, 10077. Cells from 1.3 times the reach on are as the narrow ones:
 // parts of 140,000, m = 300, half charged, 1.05: 1243, 1113; 1.3: 1444, 1584;
-// 1.6: 1853, 2349; 0.85 (m = 200): 965, 1380.
+// 1.6: 1853, 2349; 0.85 (m = 200): 965, 1380. 64 lanes, 32 and clusters there,
+// half charged, 30,000, m = 200: 185, 190, 282; 500: 270, 321, 470; 60,000,
+// 60: 230, 177, 221; 200: 303, 262, 351; LJ alone with ghosts, 57,000, 110:
+// 261, 221, 198.
 constexpr double kRblWide = 48.0, kRblFull = 500.0;  // particles within r_coul of one, on average
 constexpr int64_t kRblWide64 = 65536, kRblFull64 = 393216, kRblWide32 = 262144, kRblEither = 1 << 20;
-constexpr int64_t kRblTight32 = 65536;
+constexpr int64_t kRblTight64 = 32768, kRblTight32 = 65536;
 static bool rbl_tight(const PairParams &pp) {
   return pp.s_coul.y == 1 && pp.s_coul.z == 1 && 1.44 * pp.rq2 * pp.g.inv_h[1] * pp.g.inv_h[2] >= 1.0;
 }
@@ -778,7 +781,7 @@ static void launch_rbl(PairCtx c, hipStream_t st) {
     k_pair_rbl<F32, COUNT, GHOST, QSHELL, false><<<clusters, 64, 0, st>>>(c);
   } else if (c.n > (wide ? kRblEither : kRblNarrow16)) {
     k_pair_rbl<F32, COUNT, GHOST, QSHELL, false><<<clusters, 64, 0, st>>>(c);
-  } else if (wide && c.n <= (mean >= kRblFull && !tight ? kRblFull64 : kRblWide64)) {
+  } else if (wide && c.n <= (tight ? kRblTight64 : mean >= kRblFull ? kRblFull64 : kRblWide64)) {
     k_pair_rbl_group<COUNT, GHOST, QSHELL, 64, false><<<group_blocks(c.n, 64), 256, 0, st>>>(c);
   } else if (c.n <= (wide ? wide32 : kRblNarrow32)) {
     k_pair_rbl_group<COUNT, GHOST, QSHELL, 32, false><<<group_blocks(c.n, 32), 256, 0, st>>>(c);
